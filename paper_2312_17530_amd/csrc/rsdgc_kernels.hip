@@ -2786,17 +2786,39 @@ __global__ __launch_bounds__(256) void k_scatter_blocks(const LayerDev *__restri
 // ---------------------------------------------------------------- apply --
 // Eq. 12, third line: w <- w - eta * (sum over the nodes' messages).  No dense accumulator: the
 // messages are index-sorted per layer (rsdgc_compress writes them so), so the pairs that fall into
-// one 8192-element chunk of a layer are one contiguous stretch of every message.  A first
-// kernel finds those stretches (two binary searches per message and chunk, all in parallel); the
-// second takes one chunk per workgroup, sums the messages' values in an LDS array in the order
-// given -- message after message, a barrier between them, plain float32 adds starting from +0 --
-// and updates the weights at the positions that were named.  One message needs none of this:
-// every pair is applied on its own.
+// one stretch of kApplySpan elements of a layer are one contiguous stretch of every message.  A first
+// kernel finds where those begin (one search per message and stretch, all in parallel); the second
+// takes one stretch per workgroup, sums the messages' values in an LDS array in the order given --
+// message after message, a barrier between them, plain float32 adds starting from +0 -- and updates
+// the weights whose sum is not +0.  One message needs none of this: every pair is applied on its own.
 struct ApplyMsgs {
     const uint32_t *idx[RSDGC_MAX_MSGS];
     const float *val[RSDGC_MAX_MSGS];
     const int32_t *counts[RSDGC_MAX_MSGS];
 };
+// Half a chunk: 16 KB of LDS, so that a CU holds eight workgroups (a whole chunk left it four, and
+// what a workgroup waits for is latency).
+constexpr int kApplySpan = kChunk / 2;
+constexpr int kApplyAhead = 2;            // pairs of a message that a lane requests before any is added: 128 a message
+
+// First position in a[0, n) whose value is not below x (a ascending).  Seven probes a round instead
+// of one: the rounds are dependent loads, about 1 us each, and there are a third as many of them.
+// Any content of a gives a position in [0, n] and reads inside it.
+__device__ __forceinline__ uint32_t lower_bound_wide(const uint32_t *__restrict__ a, uint32_t n, uint32_t x) {
+    uint32_t lo = 0, len = n;             // the answer lies in [lo, lo + len]
+    while (len >= 8u) {
+        const uint32_t step = len >> 3;
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t i = 1; i < 8u; ++i) c += a[lo + i * step - 1u] < x ? 1u : 0u;
+        lo += c * step;
+        len = c == 7u ? len - 7u * step : step - 1u;
+    }
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 7u; ++i) c += i < len && a[lo + min(i, len - 1u)] < x ? 1u : 0u;
+    return lo + c;
+}
 
 // First position in a[0, n) whose value is not below x (a ascending).
 __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t *__restrict__ a, uint32_t n, uint32_t x) {
@@ -2808,68 +2830,123 @@ __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t *__restrict__
     return lo;
 }
 
-// ranges[(k * n_chunks + c) * 2 + {0, 1}]: first and one-past-last pair of message k (positions
-// in the message's arrays) that fall into chunk c.
-__global__ __launch_bounds__(256) void k_apply_ranges(const LayerDev *__restrict__ layers,
-                                                      const ChunkInfo *__restrict__ chunk_info,
-                                                      uint32_t n_chunks, int n_msgs, const ApplyMsgs msgs,
-                                                      uint32_t *__restrict__ ranges) {
-    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-    if (t >= n_chunks * static_cast<uint32_t>(n_msgs)) return;
-    const uint32_t k = t / n_chunks, c = t - k * n_chunks;
-    const ChunkInfo ci = chunk_info[c];
-    const int32_t raw = msgs.counts[k][ci.layer];
-    const uint32_t n = static_cast<uint32_t>(min(max(raw, 0), static_cast<int32_t>(min(ci.cap, 0x7fffffffu))));
-    const uint32_t *__restrict__ seg = msgs.idx[k] + ci.out_off;
-    const uint32_t a = lower_bound_u32(seg, n, ci.start);
-    const uint32_t b = ci.last ? n : lower_bound_u32(seg, n, ci.start + ci.len);
-    ranges[2 * t] = a;
-    ranges[2 * t + 1] = max(a, b);
+// Pairs of a layer in one message, whatever the message says.
+__device__ __forceinline__ uint32_t pairs_in_segment(int32_t count, uint32_t cap) {
+    return static_cast<uint32_t>(min(max(count, 0), static_cast<int32_t>(min(cap, 0x7fffffffu))));
 }
 
+// starts[k * 2 n_chunks + 2 c + s]: first pair of message k in its layer's segment that falls into
+// half s of chunk c, or later (a short last chunk's second half: the number of pairs).
+// VGG-19, eight messages: 22 us with two binary searches per chunk, 20 us for twice the stretches; filling the
+// table on one pass over the indices took 30 us.
+__global__ __launch_bounds__(256) void k_apply_ranges(const ChunkInfo *__restrict__ chunk_info,
+                                                      uint32_t n_chunks, int n_msgs, const ApplyMsgs msgs,
+                                                      uint32_t *__restrict__ starts) {
+    const uint64_t t = static_cast<uint64_t>(blockIdx.x) * 256u + threadIdx.x;
+    const uint64_t per = 2ull * n_chunks;
+    if (t >= per * static_cast<uint32_t>(n_msgs)) return;
+    const uint32_t k = static_cast<uint32_t>(t / per), cs = static_cast<uint32_t>(t - k * per);
+    const ChunkInfo ci = chunk_info[cs >> 1];
+    const uint32_t n = pairs_in_segment(msgs.counts[k][ci.layer], ci.cap);
+    // (no index of the layer reaches start + len in its last chunk: the search would end at n)
+    starts[t] = lower_bound_wide(msgs.idx[k] + ci.out_off, n, ci.start + (cs & 1u) * kApplySpan);
+}
+
+// One workgroup per half chunk; every wave requests the pairs of its messages before any is added (one load
+// latency for all eight instead of one each), and the weights are updated by all threads side by side, 16 bytes
+// each, where any of the four sums is not +0 (a thread that walked the bits of a touched-map word had ten
+// dependent updates in a row).  Moved on VGG-19 with eight messages: 560 MB for 340 MB of pairs and weights -- windows
+// of p elements reach 60 % of the weights' 64-byte lines.  275 us -> 169 us there.  Measured and not taken: every
+// thread requesting a pair of every message (178 us: the waves issue four times the instructions); one stretch
+// of 1024 elements per wave without barriers (175 us, and eight times the ranges to find); of 2048 (240 us: half
+// the waves); persistent waves with a cursor into every message (296 us), or software-pipelined (213 us: 153 registers).
 __global__ __launch_bounds__(256) void k_apply_chunks(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
                                                       int n_msgs, const ApplyMsgs msgs,
-                                                      const uint32_t *__restrict__ ranges,
+                                                      const uint32_t *__restrict__ starts,
                                                       float *__restrict__ weights, float eta) {
-    __shared__ float acc[kChunk];
-    __shared__ uint32_t touched[kChunk / 32];
+    __shared__ __attribute__((aligned(16))) float acc[kApplySpan];
     __shared__ uint32_t s_rng[RSDGC_MAX_MSGS][2];
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = blockIdx.x >> 1, s = blockIdx.x & 1u;
     const ChunkInfo ci = chunk_info[c];
-    uint32_t mine = 0;
+    const uint32_t first = s * kApplySpan;             // the stretch inside the chunk: [first, end)
+    if (first >= ci.len) return;
+    const uint32_t end = min(ci.len, first + kApplySpan), len = end - first;
+    bool mine = false;
     if (tid < n_msgs) {
-        const uint32_t a = ranges[2 * (static_cast<uint32_t>(tid) * n_chunks + c)];
-        const uint32_t b = ranges[2 * (static_cast<uint32_t>(tid) * n_chunks + c) + 1];
+        const uint32_t *__restrict__ st = starts + static_cast<size_t>(tid) * 2u * n_chunks + 2u * c + s;
+        const uint32_t a = st[0], b = ci.last && end == ci.len ? pairs_in_segment(msgs.counts[tid][ci.layer], ci.cap) : st[1];
         s_rng[tid][0] = a;
         s_rng[tid][1] = b;
-        mine = b - a;
+        mine = a < b;
     }
-    if (!__syncthreads_or(mine != 0u)) return;         // no message names an element of this chunk
+    if (!__syncthreads_or(mine)) return;               // no message names an element of this stretch
 #pragma unroll
-    for (int j = 0; j < kChunk / 256; ++j) acc[tid + 256 * j] = 0.f;
-    touched[tid] = 0u;
+    for (int j = 0; j < kApplySpan / 1024; ++j) *reinterpret_cast<float4 *>(&acc[j * 1024 + 4 * tid]) = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    for (int k = 0; k < n_msgs; ++k) {                 // the sum, message by message, in the order given
-        const uint32_t a = s_rng[k][0], b = s_rng[k][1];
-        const uint32_t *__restrict__ idx = msgs.idx[k] + ci.out_off;
-        const float *__restrict__ val = msgs.val[k] + ci.out_off;
-        for (uint32_t j = a + tid; j < b; j += 256) {
-            const uint32_t rel = idx[j] - ci.start;
-            if (rel < ci.len) {                        // (always, for a sorted message)
-                acc[rel] = acc[rel] + val[j];
-                atomicOr(&touched[rel >> 5], 1u << (rel & 31));
+    const uint32_t base = ci.start + first;
+    const int lane = tid & 63, wave = tid >> 6;
+    for (int k0 = 0; k0 < n_msgs; k0 += 8) {           // wave w takes messages k0 + w and k0 + 4 + w of a batch of eight
+        uint32_t rel[2][kApplyAhead];
+        float val[2][kApplyAhead];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int k = k0 + 4 * m + wave;
+            const uint32_t a = k < n_msgs ? s_rng[k][0] : 0u, b = k < n_msgs ? s_rng[k][1] : 0u;
+            const int kc = min(k, n_msgs - 1);
+#pragma unroll
+            for (int q = 0; q < kApplyAhead; ++q) {
+                rel[m][q] = 0xffffffffu;
+                val[m][q] = 0.f;
+                const uint32_t j = a + 64u * q + lane;
+                if (j < b) {
+                    rel[m][q] = msgs.idx[kc][ci.out_off + j] - base;
+                    val[m][q] = msgs.val[kc][ci.out_off + j];
+                }
             }
         }
-        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {               // the sum, message by message, in the order given
+            const int k = k0 + kk;
+            if (k >= n_msgs) break;                    // uniform
+            if (wave == (kk & 3)) {
+#pragma unroll
+                for (int q = 0; q < kApplyAhead; ++q)
+                    if (rel[kk >> 2][q] < len) acc[rel[kk >> 2][q]] = acc[rel[kk >> 2][q]] + val[kk >> 2][q];   // (always, for a sorted message)
+                const uint32_t b = s_rng[k][1];
+                for (uint32_t j = s_rng[k][0] + 64u * kApplyAhead + lane; j < b; j += 64u) {
+                    const uint32_t rj = msgs.idx[k][ci.out_off + j] - base;
+                    if (rj < len) acc[rj] = acc[rj] + msgs.val[k][ci.out_off + j];
+                }
+            }
+            __syncthreads();
+        }
     }
-    uint32_t word = touched[tid];
-    float *__restrict__ w = weights + ci.arena_off;
-    while (word) {
-        const uint32_t rel = 32u * static_cast<uint32_t>(tid) + static_cast<uint32_t>(__ffs(word)) - 1u;
-        word &= word - 1u;
-        const float sum = acc[rel];
-        if (__float_as_uint(sum) != 0u) w[rel] = w[rel] - __fmul_rn(eta, sum);
+    float *__restrict__ w = weights + ci.arena_off + first;
+    float4 sum[kApplySpan / 1024], old[kApplySpan / 1024];
+    bool any[kApplySpan / 1024];
+#pragma unroll
+    for (int j = 0; j < kApplySpan / 1024; ++j) {
+        const uint32_t e = j * 1024 + 4 * tid;
+        sum[j] = *reinterpret_cast<const float4 *>(&acc[e]);
+        any[j] = (__float_as_uint(sum[j].x) | __float_as_uint(sum[j].y) | __float_as_uint(sum[j].z) | __float_as_uint(sum[j].w)) != 0u;
+        if (any[j] && e + 3 < len) old[j] = *reinterpret_cast<const float4 *>(w + e);
+    }
+#pragma unroll
+    for (int j = 0; j < kApplySpan / 1024; ++j) {
+        const uint32_t e = j * 1024 + 4 * tid;
+        if (!any[j]) continue;
+        const float t[4] = {sum[j].x, sum[j].y, sum[j].z, sum[j].w};
+        if (e + 3 < len) {
+            float v[4] = {old[j].x, old[j].y, old[j].z, old[j].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (__float_as_uint(t[q]) != 0u) v[q] = v[q] - __fmul_rn(eta, t[q]);
+            *reinterpret_cast<float4 *>(w + e) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+            for (uint32_t q = 0; q < 4 && e + q < len; ++q)
+                if (__float_as_uint(t[q]) != 0u) w[e + q] = w[e + q] - __fmul_rn(eta, t[q]);
+        }
     }
 }
 
@@ -3734,13 +3811,12 @@ int rsdgc_apply(rsdgc_plan_t *plan, int32_t n_msgs, const uint32_t *const *idx,
         m.counts[k] = counts[k];
     }
     const ChunkInfo *chunk_info = reinterpret_cast<const ChunkInfo *>(ws + plan->ws.chunk_info);
-    uint32_t *ranges = reinterpret_cast<uint32_t *>(ws + plan->ws.apply_ranges);
+    uint32_t *starts = reinterpret_cast<uint32_t *>(ws + plan->ws.apply_starts);
     const uint32_t n_chunks = plan->n_chunks;
-    const unsigned range_blocks = static_cast<unsigned>((static_cast<uint64_t>(n_chunks) * n_msgs + 255) / 256);
-    hipLaunchKernelGGL(k_apply_ranges, dim3(range_blocks), dim3(256), 0, stream, layers, chunk_info, n_chunks,
-                       n_msgs, m, ranges);
-    hipLaunchKernelGGL(k_apply_chunks, dim3(n_chunks), dim3(256), 0, stream, chunk_info, n_chunks, n_msgs, m,
-                       ranges, weights, eta);
+    const unsigned range_blocks = static_cast<unsigned>((2ull * n_chunks * static_cast<unsigned>(n_msgs) + 255) / 256);
+    hipLaunchKernelGGL(k_apply_ranges, dim3(range_blocks), dim3(256), 0, stream, chunk_info, n_chunks, n_msgs, m, starts);
+    hipLaunchKernelGGL(k_apply_chunks, dim3(2 * n_chunks), dim3(256), 0, stream, chunk_info, n_chunks, n_msgs, m,
+                       starts, weights, eta);
     HIP_TRY(hipGetLastError());
     return RSDGC_OK;
 }

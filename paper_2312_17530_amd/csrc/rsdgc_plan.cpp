@@ -250,7 +250,7 @@ int build_tables(rsdgc_plan_s *plan) {
     // any call, several of them in the same one
     w.nsi = off;          off = align_up(off + sizeof(float) * static_cast<size_t>(plan->total_elems), A);
     w.dyn = off;          off = align_up(off + 256 + sizeof(uint64_t) * kHistBins + sizeof(uint32_t) * 2 * size_t(L), A);
-    w.apply_ranges = off; off = align_up(off + sizeof(uint32_t) * 2 * RSDGC_MAX_MSGS * static_cast<size_t>(plan->n_chunks), A);
+    w.apply_starts = off; off = align_up(off + sizeof(uint32_t) * 2 * RSDGC_MAX_MSGS * static_cast<size_t>(plan->n_chunks), A);
     w.total = off;
 
     plan->table.assign(w.table_bytes, 0);

@@ -1,0 +1,56 @@
+"""GPU kernels at the sizes where their tilings can go wrong: edges of tiles and stretches, remainders,
+the smallest and largest of their ranges.  Against the CPU oracle or plain numpy.  Needs a real MI355X."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2312_17530_amd import binding
+
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _bits(a):
+    return np.ascontiguousarray(a).view(np.uint32)
+
+
+def _message(plan, rng, G, share):
+    """A sorted message as rsdgc_compress lays it out: in every layer a random share of the elements."""
+    idx = np.zeros(max(1, plan.out_capacity), np.uint32)
+    val = np.zeros(max(1, plan.out_capacity), np.float32)
+    counts, host = np.zeros(len(G), np.int32), []
+    for l, g in enumerate(G):
+        i = np.flatnonzero(rng.random(g) < share).astype(np.uint32)
+        v = rng.standard_normal(i.size).astype(np.float32)
+        o = plan.out_offset(l)
+        idx[o:o + i.size], val[o:o + i.size], counts[l] = i, v, i.size
+        host.append((i, v))
+    return (_dev(idx.view(np.int32)), _dev(val), _dev(counts)), host
+
+
+@pytest.mark.parametrize("n_msgs, share", [(2, 1.0), (7, 0.02), (8, 0.3), (9, 0.02), (64, 0.001)])
+def test_apply_sums_messages_at_the_edges_of_its_stretches(n_msgs, share):
+    """Layers that end on, just before and just after a stretch of 4096 elements; stretches without a pair, with
+    fewer than one pair per thread and with sixteen; messages beyond one batch.  Sums and steps have their
+    order laid down, so every bit has to agree; the padding between layers keeps its values."""
+    import torch
+    shapes = [(1, 1), (1, 4095), (64, 64), (1, 4097), (1, 8191), (2, 4096), (1, 8193), (3, 4099), (50, 333)]
+    G = [r * c for r, c in shapes]
+    plan = binding.rsdgc_plan(shapes, 1, 0.5, [1.0] * len(shapes))
+    ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    rng = np.random.default_rng(n_msgs)
+    w = rng.standard_normal(plan.total_elems).astype(np.float32)
+    msgs = [_message(plan, rng, G, share) for _ in range(n_msgs)]
+    w_dev = _dev(w)
+    binding.rsdgc_apply(plan, [m[0] for m in msgs], w_dev, 0.05, ws)
+    want = w.copy()
+    for l, g in enumerate(G):
+        o = plan.layer_offset(l)
+        want[o:o + g] = oracle.apply_messages(w[o:o + g].reshape(1, g), [m[1][l] for m in msgs], 0.05).reshape(-1)
+    assert np.array_equal(_bits(w_dev.cpu().numpy()), _bits(want))
+
