@@ -3048,9 +3048,300 @@ __global__ __launch_bounds__(256) void k_apply_blocks(const LayerDev *__restrict
 
 // ------------------------------------------------------- dynamic ratios --
 // Section III-B, Eqs. 3-5: one ranking of mu = |w| over all layers; the K top-ranked weights
-// survive and a layer's keep ratio is its share of survivors.  The K-th largest 31-bit key
-// (the bit pattern of |w|) is found by a radix select over three streaming passes
-// (12 + 10 + 9 bits), a fourth pass counts per layer the keys above and at the threshold.
+// survive and a layer's keep ratio is its share of survivors.  Keys are the 31-bit patterns of |w|.
+// Large networks: a sample of the weights brackets the K-th largest key, and ONE pass over the
+// weights counts per layer what lies above the bracket and lists what lies inside it (a per cent
+// or less); the rest is decided on the list.  When the sample misled (the K-th key lies outside the
+// bracket, or far more weights in it than expected) the call goes on with the general path: the
+// K-th largest key by a radix select over three streaming passes (12 + 10 + 9 bits), a
+// fourth pass counting per layer the keys above and at the threshold.
+
+// f(key) for the len keys at src (16-byte aligned), by a workgroup: a whole chunk's loads go out together.
+template <typename F>
+__device__ __forceinline__ void dyn_for_each_key(const uint32_t *__restrict__ src, uint32_t len, F f) {
+    typedef uint32_t vu4 __attribute__((ext_vector_type(4)));       // (read once per pass: streamed)
+    constexpr int N = kChunk / 1024;
+    const int tid = threadIdx.x;
+    if (len == static_cast<uint32_t>(kChunk)) {
+        vu4 q[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) q[j] = __builtin_nontemporal_load(reinterpret_cast<const vu4 *>(src + j * 1024 + 4 * tid));
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            f(q[j].x & 0x7fffffffu);
+            f(q[j].y & 0x7fffffffu);
+            f(q[j].z & 0x7fffffffu);
+            f(q[j].w & 0x7fffffffu);
+        }
+    } else {
+        for (uint32_t e = tid; e < len; e += 256) f(src[e] & 0x7fffffffu);
+    }
+}
+
+constexpr int kDynSampleBits = 13;                       // the sample's histogram: top 13 of the 31 key bits (3 % steps)
+constexpr int kDynSampleBins = 1 << kDynSampleBits;
+constexpr int kDynSubBins = 2048;                        // bins of the bracket
+constexpr uint32_t kDynFinalCap = 4096;                  // keys of one such bin that the last kernel can hold
+constexpr int kDynMaxLayers = 4096;                      // layers that the list's counters cover (LDS)
+constexpr uint32_t kDynStage = 1024;                     // listed keys a workgroup of the main pass holds back
+constexpr uint32_t kDynSamplePieces = 4;                 // 64-byte pieces sampled per chunk: one weight in 128
+constexpr int64_t kDynSplitMin = 1 << 20;                // weights from which the one-pass form is taken
+
+// State of the one-pass form (cleared by k_dyn_clear).
+struct DynSplit {
+    unsigned long long above;  // keys above the bracket, all layers
+    uint32_t lo, hi;           // the bracket: lo <= key < hi
+    uint32_t sub_shift;        // its bins are 2^sub_shift keys wide
+    uint32_t bad;              // the sample's bracket is not used
+    uint32_t n_list, n_final;  // keys listed; of those, keys in the bin that holds the K-th
+};
+struct DynSplitArgs {
+    DynSplit *state;
+    uint32_t *sample_hist;     // [kDynSampleBins]
+    uint32_t *sub_hist;        // [kDynSubBins]
+    uint32_t *cnt;             // [n_layers][2]
+    uint2 *final_list;         // [kDynFinalCap]  (key, layer)
+    uint2 *list;               // [list_cap]
+    uint32_t list_cap, n_layers;
+    unsigned long long K, n_weights;
+};
+
+__global__ __launch_bounds__(256) void k_dyn_clear(const DynSplitArgs a) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, stride = gridDim.x * 256u;
+    if (i == 0) *a.state = DynSplit{0ull, 0u, 0u, 0u, 0u, 0u, 0u};
+    for (uint32_t b = i; b < kDynSampleBins; b += stride) a.sample_hist[b] = 0u;
+    for (uint32_t b = i; b < kDynSubBins; b += stride) a.sub_hist[b] = 0u;
+    for (uint32_t b = i; b < 2u * a.n_layers; b += stride) a.cnt[b] = 0u;
+}
+
+// Histogram of a sample: kDynSamplePieces pieces of 16 weights per chunk, at places given by a hash; a short chunk
+// gives each of its pieces with the probability of its share of a whole one.
+__global__ __launch_bounds__(256) void k_dyn_sample(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
+                                                    const uint32_t *__restrict__ w, const DynSplitArgs a) {
+    __shared__ uint32_t lhist[kDynSampleBins];
+    const int tid = threadIdx.x;
+    for (int b = tid; b < kDynSampleBins; b += 256) lhist[b] = 0u;
+    __syncthreads();
+    const uint32_t n_pieces = n_chunks * kDynSamplePieces;
+    for (uint32_t i0 = blockIdx.x * 16u; i0 < n_pieces; i0 += gridDim.x * 16u) {
+        const uint32_t i = i0 + (tid >> 4);
+        if (i < n_pieces) {
+            const ChunkInfo ci = chunk_info[i / kDynSamplePieces];
+            const uint32_t h = (i + 1u) * 2654435761u;
+            const bool take = (h >> 19) < ci.len;                       // 13 bits: 0 .. kChunk - 1
+            const uint32_t groups = (ci.len + 15u) / 16u;
+            const uint32_t e = (((h * 40503u) >> 8) % groups) * 16u + (tid & 15u);
+            if (take && e < ci.len) atomicAdd(&lhist[(w[ci.arena_off + e] & 0x7fffffffu) >> (31 - kDynSampleBits)], 1u);
+        }
+    }
+    __syncthreads();
+    for (int b = tid; b < kDynSampleBins; b += 256) {
+        const uint32_t c = lhist[b];
+        if (c) atomicAdd(&a.sample_hist[b], c);
+    }
+}
+
+// The main pass.  Every workgroup reads the bracket off the sample's histogram (the same one in each): the K-th key's
+// rank in the sample, give or take eight standard deviations of it, on the safe side of the bin edges.  Then it strides over
+// the chunks; reading 4 bytes per weight is what bounds it.
+// VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding before; now this one of 132 us and
+// 38 us around it (a call, with its wait and read-back, 706 -> 202 us).
+__global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
+                                                   const uint32_t *__restrict__ w, const DynSplitArgs a) {
+    __shared__ uint32_t sub[kDynSubBins];
+    __shared__ uint2 stage[kDynStage];
+    __shared__ uint32_t wave_tot[4];
+    __shared__ uint32_t s_above, s_n, s_base, s_hi_bin, s_lo_bin, s_cum_hi, s_cum_lo;
+    const int tid = threadIdx.x;
+    for (int b = tid; b < kDynSubBins; b += 256) sub[b] = 0u;
+    if (tid == 0) {
+        s_above = s_n = 0u;
+        s_hi_bin = kDynSampleBins;         // (nothing is certainly above)
+        s_lo_bin = 0u;
+        s_cum_hi = 0u;
+    }
+    {
+        constexpr int per = kDynSampleBins / 256;
+        const int top = kDynSampleBins - tid * per;          // thread 0 holds the top bins
+        uint32_t v[per], own = 0;
+#pragma unroll
+        for (int j = 0; j < per / 4; ++j) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(a.sample_hist + top - 4 * (j + 1));
+            v[4 * j] = q.w; v[4 * j + 1] = q.z; v[4 * j + 2] = q.y; v[4 * j + 3] = q.x;
+            own += q.x + q.y + q.z + q.w;
+        }
+        const uint32_t incl = block_scan_incl(own, wave_tot);
+        if (tid == 255) { s_base = incl; s_cum_lo = incl; }
+        __syncthreads();
+        const uint32_t S = s_base;
+        const float q = static_cast<float>(static_cast<double>(a.K) / static_cast<double>(a.n_weights));
+        const float r = q * static_cast<float>(S), slack = 8.f * sqrtf(r * (1.f - q)) + 16.f;
+        // bins are certainly above while the sample holds at most r - slack keys from their lower edge on; the bracket
+        // ends with the bin at which it holds r + slack
+        const float upper = r - slack, lower = r + slack;
+        uint32_t acc = incl - own;
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            const uint32_t before = acc;
+            acc += v[j];
+            if (static_cast<float>(acc) > upper && static_cast<float>(before) <= upper) { s_hi_bin = top - j; s_cum_hi = before; }
+            if (static_cast<float>(acc) >= lower && static_cast<float>(before) < lower) { s_lo_bin = top - 1 - j; s_cum_lo = acc; }
+        }
+        __syncthreads();
+        // far more keys in the bracket than a continuous distribution has there: the general path
+        if (S == 0u || s_cum_lo - s_cum_hi > S / 16u) {      // uniform, and the same in every workgroup
+            if (blockIdx.x == 0 && tid == 0) a.state->bad = 1u;
+            return;
+        }
+    }
+    const uint32_t lo = s_lo_bin << (31 - kDynSampleBits);
+    const uint32_t hi = min(s_hi_bin << (31 - kDynSampleBits), 0x80000000u);
+    const uint32_t width = hi - lo;
+    uint32_t sub_shift = 0;
+    while (((width - 1u) >> sub_shift) >= static_cast<uint32_t>(kDynSubBins)) ++sub_shift;
+    if (blockIdx.x == 0 && tid == 0) {
+        a.state->lo = lo;
+        a.state->hi = hi;
+        a.state->sub_shift = sub_shift;
+    }
+    uint32_t cur_l = 0xffffffffu, above = 0;               // this thread's count for cur_l
+    unsigned long long above_all = 0;                        // thread 0: the workgroup's, all layers
+    auto flush_layer = [&]() {
+        if (above) atomicAdd(&s_above, above);
+        above = 0;
+        __syncthreads();
+        if (tid == 0 && s_above) {
+            atomicAdd(&a.cnt[2 * cur_l], s_above);
+            above_all += s_above;
+            s_above = 0u;
+        }
+        __syncthreads();
+    };
+    auto flush_stage = [&]() {
+        __syncthreads();
+        const uint32_t n = min(s_n, kDynStage);
+        if (tid == 0 && n) s_base = atomicAdd(&a.state->n_list, n);
+        __syncthreads();
+        for (uint32_t i = tid; i < n; i += 256)
+            if (s_base + i < a.list_cap) a.list[s_base + i] = stage[i];
+        __syncthreads();
+        if (tid == 0) s_n = 0u;
+        __syncthreads();
+    };
+    for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
+        const ChunkInfo ci = chunk_info[c];
+        if (ci.layer != cur_l) {                             // uniform
+            if (cur_l != 0xffffffffu) flush_layer();
+            cur_l = ci.layer;
+        }
+        dyn_for_each_key(w + ci.arena_off, ci.len, [&](uint32_t key) {
+            above += key >= hi ? 1u : 0u;
+            const uint32_t rel = key - lo;
+            if (rel < width) {                               // rare
+                atomicAdd(&sub[rel >> sub_shift], 1u);
+                const uint32_t pos = atomicAdd(&s_n, 1u);
+                if (pos < kDynStage) {
+                    stage[pos] = make_uint2(key, cur_l);
+                } else {                                     // (a chunk full of such keys)
+                    const uint32_t g = atomicAdd(&a.state->n_list, 1u);
+                    if (g < a.list_cap) a.list[g] = make_uint2(key, cur_l);
+                }
+            }
+        });
+        __syncthreads();
+        if (s_n > kDynStage / 2) flush_stage();              // uniform
+    }
+    if (cur_l != 0xffffffffu) flush_layer();
+    flush_stage();
+    if (tid == 0 && above_all) atomicAdd(&a.state->above, above_all);
+    for (int b = tid; b < kDynSubBins; b += 256) {
+        const uint32_t c = sub[b];
+        if (c) atomicAdd(&a.sub_hist[b], c);
+    }
+}
+
+// The bracket's bin that holds the K-th key, and the keys still to take inside it; all 256 or more
+// threads of the workgroup return the same (found = 0: the K-th key is not in the bracket).
+template <int NW>
+__device__ __forceinline__ DigitResult dyn_sub_bin(const DynSplitArgs &a, uint32_t *lh /*[kDynSubBins]*/,
+                                                   uint32_t *wave_tot, DigitResult *res) {
+    for (int b = threadIdx.x; b < kDynSubBins; b += NW * 64) lh[b] = a.sub_hist[b];
+    __syncthreads();
+    const DynSplit st = *a.state;
+    DigitResult none = {0u, 0u, 0u, 0u};
+    if (st.bad || st.above >= a.K || st.n_list > a.list_cap || a.K - st.above > st.n_list) return none;      // uniform
+    return block_find_digit<NW>(lh, kDynSubBins, static_cast<uint32_t>(a.K - st.above), wave_tot, res);
+}
+
+// The listed keys of the bins above that one, per layer; those inside it go to the final list.
+__global__ __launch_bounds__(256) void k_dyn_list(const DynSplitArgs a) {
+    __shared__ uint32_t lh[kDynSubBins];
+    __shared__ uint32_t cnt[kDynMaxLayers];
+    __shared__ uint32_t wave_tot[4];
+    __shared__ DigitResult res;
+    const DigitResult r = dyn_sub_bin<4>(a, lh, wave_tot, &res);
+    if (!r.found) return;                                    // uniform
+    for (uint32_t i = threadIdx.x; i < a.n_layers; i += 256) cnt[i] = 0u;
+    __syncthreads();
+    const DynSplit st = *a.state;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < st.n_list; i += gridDim.x * 256u) {
+        const uint2 k = a.list[i];
+        const uint32_t bin = (k.x - st.lo) >> st.sub_shift;
+        if (bin > r.digit) {
+            atomicAdd(&cnt[k.y], 1u);
+        } else if (bin == r.digit) {
+            const uint32_t pos = atomicAdd(&a.state->n_final, 1u);
+            if (pos < kDynFinalCap) a.final_list[pos] = k;
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < a.n_layers; i += 256)
+        if (cnt[i]) atomicAdd(&a.cnt[2 * i], cnt[i]);
+}
+
+// One workgroup: the K-th key itself, then the final list's keys above and at it per layer.  cnt[0] = ~0 tells the host that the
+// sample's bracket did not serve.
+__global__ __launch_bounds__(1024) void k_dyn_last(const DynSplitArgs a) {
+    __shared__ uint32_t lh[kDynSubBins];
+    __shared__ uint2 keys[kDynFinalCap];
+    __shared__ uint32_t wave_tot[16];
+    __shared__ DigitResult res;
+    const uint32_t tid = threadIdx.x;
+    const DigitResult r = dyn_sub_bin<16>(a, lh, wave_tot, &res);
+    const DynSplit st = *a.state;
+    if (!r.found || st.n_final > kDynFinalCap) {             // uniform
+        if (tid == 0) a.cnt[0] = 0xffffffffu;
+        return;
+    }
+    const uint32_t n = st.n_final;
+    for (uint32_t i = tid; i < n; i += 1024) keys[i] = a.final_list[i];
+    const uint32_t base = st.lo + (r.digit << st.sub_shift);
+    uint32_t k_rem = static_cast<uint32_t>(a.K - st.above) - r.above;        // >= 1, <= n
+    uint32_t T = 0;                                          // key - base, digit by digit: at most 11 bits each
+    for (int left = static_cast<int>(st.sub_shift); left > 0;) {
+        const int bits = min(left, 11), shift = left - bits, nb = 1 << bits;
+        __syncthreads();
+        for (int b = tid; b < nb; b += 1024) lh[b] = 0u;
+        __syncthreads();
+        for (uint32_t i = tid; i < n; i += 1024) {
+            const uint32_t rel = keys[i].x - base;
+            if ((rel >> left) == (T >> left)) atomicAdd(&lh[(rel >> shift) & (nb - 1)], 1u);
+        }
+        __syncthreads();
+        const DigitResult d = block_find_digit<16>(lh, nb, k_rem, wave_tot, &res);
+        T |= d.digit << shift;
+        k_rem -= d.above;
+        left = shift;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += 1024) {
+        const uint32_t rel = keys[i].x - base;
+        if (rel > T) atomicAdd(&a.cnt[2 * keys[i].y], 1u);
+        else if (rel == T) atomicAdd(&a.cnt[2 * keys[i].y + 1], 1u);
+    }
+}
+
+// ---- the general path
 __global__ __launch_bounds__(256) void k_dyn_init(DynState *__restrict__ state,
                                                   unsigned long long *__restrict__ hist,
                                                   uint32_t *__restrict__ cnt, uint32_t n_cnt,
@@ -3173,12 +3464,10 @@ __global__ __launch_bounds__(256) void k_dyn_count(const ChunkInfo *__restrict__
             }
             cur_l = ci.layer;
         }
-        const uint32_t *__restrict__ src = w + ci.arena_off;
-        for (uint32_t e = tid; e < ci.len; e += 256) {
-            const uint32_t key = src[e] & 0x7fffffffu;
+        dyn_for_each_key(w + ci.arena_off, ci.len, [&](uint32_t key) {
             gt += key > T ? 1u : 0u;
             eq += key == T ? 1u : 0u;
-        }
+        });
     }
     if (cur_l != 0xffffffffu) {
         if (gt) atomicAdd(&s_gt, gt);
@@ -3875,27 +4164,61 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
     const ChunkInfo *chunk_info = reinterpret_cast<const ChunkInfo *>(ws + w.chunk_info);
     const uint32_t *keys = reinterpret_cast<const uint32_t *>(weights);
     const uint32_t n_chunks = plan->n_chunks;
-    const uint32_t grid = std::min<uint32_t>(n_chunks, kNumCUs * 4u);
-    hipLaunchKernelGGL(k_dyn_init, dim3(1), dim3(256), 0, stream, state, hist, cnt,
-                       static_cast<uint32_t>(2 * L), K);
-    int prev_shift = 31;
-    for (int lv = 0; lv < 3; ++lv) {                    // 12 + 10 + 9 bits of the 31-bit key
-        const int bits = lv == 0 ? 12 : lv == 1 ? 10 : 9, shift = lv == 0 ? 19 : lv == 1 ? 9 : 0;
-        hipLaunchKernelGGL(k_dyn_hist, dim3(grid), dim3(256), 0, stream, chunk_info, n_chunks, keys,
-                           state, shift, bits, prev_shift, hist);
-        hipLaunchKernelGGL(k_dyn_find, dim3(1), dim3(256), 0, stream, state, hist, bits);
-        prev_shift = shift;
-    }
-    hipLaunchKernelGGL(k_dyn_count, dim3(grid), dim3(256), 0, stream, chunk_info, n_chunks, keys, state, cnt);
-    HIP_TRY(hipGetLastError());
     std::vector<uint32_t> host;
     try {
         host.resize(2 * static_cast<size_t>(L));
     } catch (const std::bad_alloc &) {
         return RSDGC_ENOMEM;
     }
-    HIP_TRY(hipMemcpyAsync(host.data(), cnt, sizeof(uint32_t) * host.size(), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
+    auto read_counts = [&]() -> int {
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpyAsync(host.data(), cnt, sizeof(uint32_t) * host.size(), hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipStreamSynchronize(stream));
+        return RSDGC_OK;
+    };
+    const uint32_t grid = std::min<uint32_t>(n_chunks, kNumCUs * 4u);
+    // One pass, where it is the better one: from a million weights on (below, both forms are a chain of launches), and with a
+    // counter per layer in LDS.  Its lists lie where a compress call keeps its score map.
+    bool counted = false;
+    if (n_real >= static_cast<double>(kDynSplitMin) && L <= kDynMaxLayers) {
+        DynSplitArgs a;
+        char *area = ws + w.nsi;
+        a.state = reinterpret_cast<DynSplit *>(ws + w.dyn);
+        a.sample_hist = reinterpret_cast<uint32_t *>(hist);
+        a.cnt = cnt;
+        a.sub_hist = reinterpret_cast<uint32_t *>(area);
+        a.final_list = reinterpret_cast<uint2 *>(area + sizeof(uint32_t) * kDynSubBins);
+        a.list = a.final_list + kDynFinalCap;
+        const size_t bytes = sizeof(float) * static_cast<size_t>(plan->total_elems) - sizeof(uint32_t) * kDynSubBins - sizeof(uint2) * kDynFinalCap;
+        a.list_cap = static_cast<uint32_t>(std::min<size_t>(bytes / sizeof(uint2), 0x7fffffffu));
+        a.n_layers = static_cast<uint32_t>(L);
+        a.K = K;
+        a.n_weights = static_cast<unsigned long long>(n_real);
+        hipLaunchKernelGGL(k_dyn_clear, dim3(16), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(k_dyn_sample, dim3(std::min<uint32_t>((n_chunks * kDynSamplePieces + 15u) / 16u, kNumCUs)), dim3(256), 0, stream,
+                           chunk_info, n_chunks, keys, a);
+        hipLaunchKernelGGL(k_dyn_split, dim3(std::min<uint32_t>(n_chunks, kNumCUs * 8u)), dim3(256), 0, stream, chunk_info, n_chunks, keys, a);
+        hipLaunchKernelGGL(k_dyn_list, dim3(kNumCUs / 2u), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(k_dyn_last, dim3(1), dim3(1024), 0, stream, a);
+        rc = read_counts();
+        if (rc != RSDGC_OK) return rc;
+        counted = host[0] != 0xffffffffu;                 // (no layer has that many weights: rows * cols < 2^32)
+    }
+    if (!counted) {
+        hipLaunchKernelGGL(k_dyn_init, dim3(1), dim3(256), 0, stream, state, hist, cnt,
+                           static_cast<uint32_t>(2 * L), K);
+        int prev_shift = 31;
+        for (int lv = 0; lv < 3; ++lv) {                    // 12 + 10 + 9 bits of the 31-bit key
+            const int bits = lv == 0 ? 12 : lv == 1 ? 10 : 9, shift = lv == 0 ? 19 : lv == 1 ? 9 : 0;
+            hipLaunchKernelGGL(k_dyn_hist, dim3(grid), dim3(256), 0, stream, chunk_info, n_chunks, keys,
+                               state, shift, bits, prev_shift, hist);
+            hipLaunchKernelGGL(k_dyn_find, dim3(1), dim3(256), 0, stream, state, hist, bits);
+            prev_shift = shift;
+        }
+        hipLaunchKernelGGL(k_dyn_count, dim3(grid), dim3(256), 0, stream, chunk_info, n_chunks, keys, state, cnt);
+        rc = read_counts();
+        if (rc != RSDGC_OK) return rc;
+    }
     // survivors per layer: everything above the threshold, then the keys equal to it in layer order
     unsigned long long above = 0, equal = 0;
     for (int l = 0; l < L; ++l) { above += host[2 * l]; equal += host[2 * l + 1]; }

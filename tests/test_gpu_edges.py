@@ -6,7 +6,6 @@ import pytest
 import oracle
 from paper_2312_17530_amd import binding
 
-
 pytestmark = pytest.mark.gpu
 
 
@@ -54,3 +53,47 @@ def test_apply_sums_messages_at_the_edges_of_its_stretches(n_msgs, share):
         want[o:o + g] = oracle.apply_messages(w[o:o + g].reshape(1, g), [m[1][l] for m in msgs], 0.05).reshape(-1)
     assert np.array_equal(_bits(w_dev.cpu().numpy()), _bits(want))
 
+
+def _ratio_weights(kind, G, rng):
+    n = sum(G)
+    if kind == "normal":
+        w = rng.standard_normal(n) * np.repeat(10.0 ** rng.uniform(-3, 0, len(G)), G)
+    elif kind == "rows":              # runs of 16 on one scale: what one sampled piece sees is all alike
+        w = rng.standard_normal(n) * np.repeat(10.0 ** rng.uniform(-2, 0, n // 16 + 1), 16)[:n]
+    elif kind == "pruned":            # nine in ten exactly zero
+        w = rng.standard_normal(n) * (rng.random(n) < 0.1)
+    elif kind == "few":               # seven different magnitudes
+        w = rng.integers(-7, 8, n) / 8.0
+    elif kind == "steps":             # sixteen thousand different magnitudes: ties inside the bracket's bins
+        w = np.round(rng.standard_normal(n) * 4096.0) / 4096.0
+    else:                             # one layer far above all others
+        w = rng.standard_normal(n) * 1e-3
+        w[:G[0]] *= 1e6
+    w = w.astype(np.float32)
+    edges = np.cumsum([0] + list(G))
+    return [w[edges[l]:edges[l + 1]] for l in range(len(G))]
+
+
+@pytest.mark.parametrize("kind", ["normal", "rows", "pruned", "few", "steps", "outlier"])
+def test_dynamic_ratios_on_a_million_weights(kind):
+    """From 2^20 weights on, one pass with a bracket from a sample.  Layers of one element up to most of the
+    network; ranks from the first to the last but one; distributions for which the sample's bracket serves and
+    ones for which the call has to go on with the general path.  Counts are whole numbers: all have to agree."""
+    import torch
+    shapes = [(7, 13), (1, 1), (1000, 1021), (1, 16383), (64, 147), (130, 257), (1, 8192)]
+    G = [r * c for r, c in shapes]
+    n = sum(G)
+    assert n >= 1 << 20
+    plan = binding.rsdgc_plan(shapes, 3, 0.5, [0.02] * len(shapes))
+    ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    ws2 = torch.full_like(ws, 0xff)                        # scratch that holds something else
+    weights = _ratio_weights(kind, G, np.random.default_rng(11))
+    host = np.full(plan.total_elems, np.nan, np.float32)    # (padding is never looked at)
+    for l, g in enumerate(G):
+        host[plan.layer_offset(l):plan.layer_offset(l) + g] = weights[l]
+    arena = _dev(host)
+    for rho in (1.0 / n, 0.0005, 0.02, 0.3, 0.97, (n - 1.0) / n):
+        want = oracle.dynamic_ratios([w.reshape(s) for w, s in zip(weights, shapes)], rho)
+        for w in (ws, ws2, ws):
+            binding.rsdgc_plan_forget_workspace(plan)
+            assert binding.rsdgc_dynamic_ratios(plan, arena, rho, w) == want, (kind, rho)
