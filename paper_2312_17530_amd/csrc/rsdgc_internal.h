@@ -99,7 +99,7 @@ struct LayerDev {
 };
 static_assert(sizeof(LayerDev) == 128, "LayerDev layout");
 
-// Per-layer selection state (40 bytes), lives in the workspace, rewritten by every call.
+// Per-layer selection state (40 bytes), lives in the workspace; every call leaves it as the next one needs it.
 struct SelState {
     unsigned long long T;   // threshold on the composite key (score bits << 32 | ~index)
     uint32_t k_rem;         // centres still to take inside the current bucket
@@ -109,9 +109,11 @@ struct SelState {
     uint32_t overflow;      // candidate path: a tile slot overflowed
     uint32_t lo;            // first ranking digit resolved: the k-th score lies in [lo, lo + 2^span)
     uint32_t span;
-    uint32_t predicted;     // 1: the candidate bound was predicted from earlier calls, not sampled
+    uint32_t predicted;     // bit 0: the candidate bound was predicted from earlier calls, not sampled; from kLastPathShift on:
+                            // the path of the last finished call (rsdgc_last_paths)
 };
 static_assert(sizeof(SelState) == 40, "SelState layout");
+constexpr int kLastPathShift = 8;
 
 // What a large layer remembers from one call to the next (uploaded as zeros with the tables).
 struct PredState {
@@ -143,13 +145,17 @@ struct SampleEntry {
     uint32_t local_tile;
 };
 
-// Work item of the candidate passes: kSlotGroup (or fewer) consecutive tile slots of a large layer.
+// Work item of the candidate passes: kSlotGroup (or fewer) consecutive tile slots of a large layer.  It says all
+// that is needed to request the slots' contents, beside the layer's own constants instead of after them.
 struct GroupEntry {
     uint32_t layer;
     uint32_t slot0;      // first tile slot (index over the tiles of all layers)
-    uint32_t ntile;      // slots in the group
-    uint32_t pad_;
+    uint8_t ntile;       // slots in the group
+    uint8_t ent0_high;   // position of the first slot's first entry, halved (slots have an even number of entries): bits 32 and up,
+    uint16_t slot_cap;   // LayerDev::slot_cap
+    uint32_t ent0_low;   // ... and the lower 32
 };
+static_assert(sizeof(GroupEntry) == 16, "GroupEntry layout");
 
 // Work item of the score-map passes: one 8192-element chunk of a layer ranked on the full map.
 struct ChunkEntry {
@@ -204,14 +210,15 @@ struct WsLayout {
     size_t chunk_info = 0;   // ChunkInfo[n_chunks]
     size_t cand_groups = 0;  // GroupEntry[]: slot groups of the large layers (work list of the candidate passes)
     size_t map_chunks = 0;   // ChunkEntry[]: chunks of the other layers that select something
-    size_t map_tiles = 0;    // SampleEntry[]: tiles of those layers
+    size_t map_tiles = 0;    // SampleEntry[]: tiles of those layers, then the large layers' tiles per p-group
     size_t count_groups = 0; // CountGroup[n_count_groups]
     size_t pred = 0;         // PredState[n_layers]  uploaded as zeros, then kept by the kernels from call to call
     size_t table_bytes = 0;  // bytes uploaded from the host
-    size_t state = 0;        // SelState[n_layers], rewritten at the start of every compress
-    size_t flags = 0;        // uint32[64]  [0]: some large layer is ranked on the full map in this call (set at the
-                             //             start of every compress, raised by the kernels that send a layer there)
-    // cleared at the start of every compress
+    size_t state = 0;        // SelState[n_layers]
+    size_t flags = 0;        // uint32[64]  [0]: some large layer is ranked on the full map in this call (set with the state,
+                             //             raised by the kernels that send a layer there)
+    // zero when a compress call starts: cleared by the first with a workspace, then every call leaves them so
+    // (hist .. hist1, list_cnt .. cmask by its last kernels; chunk_cnt .. group_ccnt before it counts)
     size_t zero_begin = 0;
     size_t hist = 0;         // uint32[n_layers][kHistBins]  first ranking digit
     size_t hist_s = 0;       // uint32[n_layers][kHistBins]  sampled scores of the large layers (coarse digit)
@@ -250,6 +257,7 @@ struct PGroup {           // layers sharing one neighbourhood side: one launch p
     uint32_t large_dir_begin = 0;   // index of the first DirEntry in large_dir
     uint32_t large_dir_count = 0;   // entries excluding the sentinel
     uint32_t n_large_tiles = 0;
+    uint32_t large_list_begin = 0;  // index of their first SampleEntry in map_tiles (behind the map layers' tiles)
 };
 
 }  // namespace rsdgc
@@ -270,6 +278,7 @@ struct rsdgc_plan_s {
     std::vector<rsdgc::GroupEntry> cand_groups;
     std::vector<rsdgc::ChunkEntry> map_chunks;
     std::vector<rsdgc::SampleEntry> map_tiles;
+    uint32_t n_map_tiles = 0;           // entries of map_tiles that belong to layers ranked on the full map (the first ones)
     uint32_t n_tiles_all = 0;
     uint64_t slot_entries = 0;          // composite keys in all tile slots together
     uint32_t n_slot_groups = 0;
@@ -290,6 +299,7 @@ struct rsdgc_plan_s {
     const void *uploaded_ws = nullptr;
     int calls_since_upload = 0;         // compress calls since the tables went to uploaded_ws (counted up to kSamplingCalls)
     uint64_t uploaded_version = 0;
+    bool ws_ready = false;              // uploaded_ws is as a compress call needs it: counters zero, layer states set
     // block reading (non-overlapping p x p neighbourhoods): this plan describes the element
     // matrices; `inner` describes the block grids as layers with p = 1 and the same k_l, and
     // the selection machinery runs on it.  The workspace is this plan's tables followed by

@@ -154,8 +154,9 @@ __device__ __forceinline__ float margin_init_log2(uint32_t k) {
 }
 
 // ---------------------------------------------------------------- begin --
-// Start of a compress call: all workgroups but the last clear the histograms, counters and
-// bitmasks; the last one writes every layer's initial selection state.  A large layer gets its
+// The first call with a workspace (k_begin): all workgroups but the last clear the histograms, counters and
+// bitmasks; the last one writes every layer's initial selection state.  After that every call leaves both as
+// the next one needs them (prepare_next_call).  A large layer gets its
 // candidate bound here when the thresholds of its last two calls (kept in `pred`) lie close
 // together.  While a residual builds up, the threshold keeps moving in one direction by steps
 // that, on a logarithmic scale, shrink smoothly from call to call; so after a step d of
@@ -168,71 +169,121 @@ __device__ __forceinline__ float margin_init_log2(uint32_t k) {
 // calls with a workspace (`sampling`); later such a layer is ranked on the full map until its
 // threshold has settled, and the call needs neither the sampled tiles nor k_hint.
 // flags[0] tells the fallback kernels whether any large layer is on the full map.
+// One layer's state; true: the layer starts on the full map for want of a bound.
+__device__ __forceinline__ bool init_layer_state(const LayerDev *__restrict__ layers, SelState *__restrict__ state, int l,
+                                                 PredState *__restrict__ pred /* nullable */, int sampling,
+                                                 uint32_t last_path) {
+    SelState s;
+    const LayerDev L = layers[l];
+    bool fallback_work = false;
+    s.T = L.k == 0 ? ~0ull : 0ull;   // no key reaches ~0: nothing is selected when k = 0
+    s.k_rem = L.k;
+    s.done = L.k == 0 ? 1u : 0u;
+    s.mode = L.k == 0 ? kModeSkip : (L.large ? kModeCandidates : kModeFullMap);
+    s.hint_key = 0;
+    s.overflow = 0;
+    s.lo = 0;
+    s.span = 0;
+    s.predicted = last_path << kLastPathShift;
+    if (pred && s.mode == kModeCandidates) {
+        PredState ps = pred[l];
+        // after a failed bound the layer goes back to sampled bounds for a few calls -- where there
+        // are any: past the calls that sample, the alternative would be the full map, and the
+        // widened margin is tried at once
+        const bool paused = ps.cooldown > 0 && sampling;
+        // the call before failed: its threshold was a jump, not part of a trend -- the forecast
+        // is that threshold itself
+        const bool just_failed = ps.cooldown == kCooldownCalls;
+        if (ps.cooldown > 0) ps.cooldown -= 1;
+        ps.has_forecast = 0;
+        bool predicted = false;
+        if (ps.tau1 >= (1u << 23) && ps.tau2 >= (1u << 23)) {   // (both in the normal float32 range)
+            const float l1 = __log2f(__uint_as_float(ps.tau1)), l2 = __log2f(__uint_as_float(ps.tau2));
+            const float d = l1 - l2;
+            const float dd = just_failed ? 0.f : fminf(fmaxf(d, -2.f * kTrendMaxLog2), kTrendMaxLog2);
+            // the forecast is made in every call, used or not: how far the threshold then ends
+            // below it is what sizes the margin (publish_threshold)
+            ps.forecast = l1 + (dd > 0.f ? 0.6f * dd : 1.15f * dd);
+            ps.has_forecast = 1;
+            // (a threshold that jumps: sampled bounds while there are any; later the trend is
+            // taken as far as it is trusted -- a bound that fails costs less than the full map)
+            if (!paused && (fabsf(d) <= kTrendMaxLog2 || !sampling)) {   // (d, not dd: a jump is sampled)
+                const float margin = ps.margin > 0.f ? ps.margin : margin_init_log2(L.k);
+                const float bound = exp2f(ps.forecast - margin);
+                const uint32_t key = __float_as_uint(bound);
+                if (key >= kPreF32MinKey && key <= kPreF32MaxKey) {   // (else: no bound, the full map)
+                    s.hint_key = key;
+                    predicted = true;
+                }
+            }
+        }
+        pred[l] = ps;
+        if (predicted) {
+            s.predicted |= 1u;
+        } else if (!sampling) {
+            s.mode = kModeFullMap;
+            fallback_work = true;
+        }
+    }
+    state[l] = s;
+    return fallback_work;
+}
+
+// Every layer's state for the next call, by one workgroup of 256 threads.
+__device__ __forceinline__ void init_states(const LayerDev *__restrict__ layers, SelState *__restrict__ state, int n_layers,
+                                            PredState *__restrict__ pred, uint32_t *__restrict__ flags, int sampling,
+                                            bool finished_call) {
+    bool fallback_work = false;
+    for (int l = threadIdx.x; l < n_layers; l += 256) {
+        uint32_t last_path = 0;
+        if (finished_call) {
+            const SelState s = state[l];
+            last_path = s.mode == kModeCandidates && (s.predicted & 1u) ? 3u : s.mode;
+        }
+        fallback_work |= init_layer_state(layers, state, l, pred, sampling, last_path);
+    }
+    const int any = __syncthreads_or(fallback_work ? 1 : 0);
+    if (threadIdx.x == 0) flags[0] = any ? 1u : 0u;
+}
+
 __global__ __launch_bounds__(256) void k_begin(uint4 *__restrict__ p, size_t n16,
                                                const LayerDev *__restrict__ layers,
                                                SelState *__restrict__ state, int n_layers,
                                                PredState *__restrict__ pred /* nullable */,
                                                uint32_t *__restrict__ flags, int sampling) {
     if (blockIdx.x + 1 == gridDim.x) {
-        bool fallback_work = false;
-        for (int l = threadIdx.x; l < n_layers; l += 256) {
-            SelState s;
-            const LayerDev L = layers[l];
-            s.T = L.k == 0 ? ~0ull : 0ull;   // no key reaches ~0: nothing is selected when k = 0
-            s.k_rem = L.k;
-            s.done = L.k == 0 ? 1u : 0u;
-            s.mode = L.k == 0 ? kModeSkip : (L.large ? kModeCandidates : kModeFullMap);
-            s.hint_key = 0;
-            s.overflow = 0;
-            s.lo = 0;
-            s.span = 0;
-            s.predicted = 0;
-            if (pred && s.mode == kModeCandidates) {
-                PredState ps = pred[l];
-                // after a failed bound the layer goes back to sampled bounds for a few calls -- where there
-                // are any: past the calls that sample, the alternative would be the full map, and the
-                // widened margin is tried at once
-                const bool paused = ps.cooldown > 0 && sampling;
-                // the call before failed: its threshold was a jump, not part of a trend -- the forecast
-                // is that threshold itself
-                const bool just_failed = ps.cooldown == kCooldownCalls;
-                if (ps.cooldown > 0) ps.cooldown -= 1;
-                ps.has_forecast = 0;
-                if (ps.tau1 >= (1u << 23) && ps.tau2 >= (1u << 23)) {   // (both in the normal float32 range)
-                    const float l1 = __log2f(__uint_as_float(ps.tau1)), l2 = __log2f(__uint_as_float(ps.tau2));
-                    const float d = l1 - l2;
-                    const float dd = just_failed ? 0.f : fminf(fmaxf(d, -2.f * kTrendMaxLog2), kTrendMaxLog2);
-                    // the forecast is made in every call, used or not: how far the threshold then ends
-                    // below it is what sizes the margin (publish_threshold)
-                    ps.forecast = l1 + (dd > 0.f ? 0.6f * dd : 1.15f * dd);
-                    ps.has_forecast = 1;
-                    // (a threshold that jumps: sampled bounds while there are any; later the trend is
-                    // taken as far as it is trusted -- a bound that fails costs less than the full map)
-                    if (!paused && (fabsf(d) <= kTrendMaxLog2 || !sampling)) {   // (d, not dd: a jump is sampled)
-                        const float margin = ps.margin > 0.f ? ps.margin : margin_init_log2(L.k);
-                        const float bound = exp2f(ps.forecast - margin);
-                        const uint32_t key = __float_as_uint(bound);
-                        if (key >= kPreF32MinKey && key <= kPreF32MaxKey) {   // (else: no bound, the full map)
-                            s.hint_key = key;
-                            s.predicted = 1;
-                        }
-                    }
-                }
-                pred[l] = ps;
-                if (!s.predicted && !sampling) {
-                    s.mode = kModeFullMap;
-                    fallback_work = true;
-                }
-            }
-            state[l] = s;
-        }
-        const int any = __syncthreads_or(fallback_work ? 1 : 0);
-        if (threadIdx.x == 0) flags[0] = any ? 1u : 0u;
+        init_states(layers, state, n_layers, pred, flags, sampling, false);
         return;
     }
     const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
     const size_t stride = static_cast<size_t>(gridDim.x - 1) * 256;
     for (size_t j = i; j < n16; j += stride) p[j] = make_uint4(0, 0, 0, 0);
+}
+
+// What the last kernel of a call does for the next one, beside its own work: a launch of k_begin in front of every
+// call cost 5 us on a small plan (of 76 on resnet18) and 8 us on VGG-19.  Every workgroup clears a share of the
+// counters that no kernel of this call reads any more; one more workgroup (the grid's first: its chain of loads is
+// longer than a chunk's) sets the layers' states.
+struct NextCall {
+    uint4 *zero[2];            // two runs of counters
+    uint32_t n16[2];           // their lengths in 16-byte units
+    const LayerDev *layers;
+    SelState *state;
+    PredState *pred;
+    uint32_t *flags;
+    int n_layers, sampling;    // sampling: whether the next call still samples bounds
+};
+// True: this workgroup was the extra one and is done.  (The others' chunk is blockIdx.x - 1.)
+__device__ __forceinline__ bool prepare_next_call(const NextCall &nc) {
+    if (blockIdx.x == 0) {
+        init_states(nc.layers, nc.state, nc.n_layers, nc.pred, nc.flags, nc.sampling, true);
+        return true;
+    }
+    const uint32_t stride = (gridDim.x - 1) * 256u;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        for (uint32_t j = (blockIdx.x - 1) * 256u + threadIdx.x; j < nc.n16[r]; j += stride) nc.zero[r][j] = make_uint4(0, 0, 0, 0);
+    return false;
 }
 
 // 16-byte store of data this call does not read again (the new residual / momentum arena):
@@ -416,10 +467,10 @@ enum NsiPass : int {
 
 struct NsiArgs {
     const LayerDev *layers;
-    const DirEntry *dir;          // tile directory of the launch (all but kPassSample)
+    const DirEntry *dir;          // tile directory of the launch (kPassMapOnly, and with the work feed)
     uint32_t n_dir;
     uint32_t n_tiles;
-    const SampleEntry *samples;   // kPassSample
+    const SampleEntry *samples;   // the launch's tiles (kPassSample; the large layers' passes without the work feed)
     const float *grad;
     const float *resid;           // nullable: all-zero residual
     float *nsi_out;               // score map (kPassMapOnly, kPassFullMap)
@@ -549,8 +600,14 @@ void k_nsi(const NsiArgs a) {
     if (CAPTURE && tid == 0) { ncand = 0; nqueue = 0; }
     __syncthreads();
 
+    // Where the next tile is known beforehand its list entry is requested a tile ahead: a first tile costs one load where
+    // the directory takes a bisection (161 layers: 34.2 -> 32.2 us; 21 layers: no difference).  With the work
+    // feed the directory's neighbouring entry, usually cached, is the shorter way.
+    constexpr bool LISTED = !FEED && PASS != kPassMapOnly;
     uint32_t e = 0;                       // directory entry of the current layer
-    if (PASS != kPassSample) e = dir_lookup(a.dir, a.n_dir, first);
+    SampleEntry ahead = {0u, 0u};
+    if (LISTED) ahead = a.samples[first];
+    else e = dir_lookup(a.dir, a.n_dir, first);
     uint32_t cur_l = 0xffffffffu;         // layer whose counts sit in lhist
     uint32_t hint_key = 0;
     uint32_t *hist_base = a.hist;         // first pass: a.hist_s for the sampled tiles of a large layer
@@ -570,10 +627,10 @@ void k_nsi(const NsiArgs a) {
 
     for (uint32_t t = first; FEED ? t != kNoItem : t < n_items; t = FEED ? feed.next(feed_slot) : t + stride) {
         uint32_t l, local;
-        if (PASS == kPassSample) {
-            const SampleEntry se = a.samples[t];
-            l = se.layer;
-            local = se.local_tile;
+        if (LISTED) {
+            l = ahead.layer;
+            local = ahead.local_tile;
+            if (t + stride < n_items) ahead = a.samples[t + stride];
         } else {
             e = dir_advance(a.dir, a.n_dir, e, t);
             l = a.dir[e].layer;
@@ -612,7 +669,7 @@ void k_nsi(const NsiArgs a) {
             if (PASS == kPassSample) hist_base = whole ? a.hist : a.hist_s;
         }
         if (!active) {                    // skip the rest of this layer
-            if (!FEED && PASS != kPassSample) {
+            if (!FEED && !LISTED) {
                 const uint32_t nb = a.dir[e + 1].begin;          // first tile of the next layer
                 t += (nb - t + stride - 1) / stride * stride - stride;   // loop increment adds the last stride
             }
@@ -1122,10 +1179,13 @@ __global__ __launch_bounds__(256) void k_find0(const LayerDev *__restrict__ laye
                                                SelState *__restrict__ state,
                                                uint32_t *__restrict__ hist,
                                                uint32_t *__restrict__ flags,
-                                               PredState *__restrict__ pred /* nullable */) {
+                                               PredState *__restrict__ pred /* nullable */,
+                                               uint4 *__restrict__ counts, uint32_t n16) {
     __shared__ uint32_t wave_tot[4];
     __shared__ DigitResult res;
     const int l = blockIdx.x, tid = threadIdx.x;
+    // the chunk counters, which the last kernel of the call before still read
+    for (uint32_t j = blockIdx.x * 256u + tid; j < n16; j += gridDim.x * 256u) counts[j] = make_uint4(0, 0, 0, 0);
     // state, layer constants and counts are requested together: one round trip to memory
     // instead of three (each costs this one-workgroup-per-layer kernel about 2 us)
     const SelState st = state[l];
@@ -1176,7 +1236,7 @@ __global__ __launch_bounds__(256) void k_find0(const LayerDev *__restrict__ laye
             flags[0] = 1u;                 // the fallback pass has work
             PredState ps = pred[l];
             ps.cooldown = kCooldownCalls;
-            if (st.predicted) {
+            if (st.predicted & 1u) {
                 // the margin of the predicted bounds follows the way this one failed: too few centres above
                 // it -- twice the margin; a tile with too many, or a threshold beyond the bins -- the bound
                 // lay too low, and a wider margin would only repeat that: half of it, down to its start value
@@ -1231,6 +1291,10 @@ __global__ __launch_bounds__(256) void k_find0(const LayerDev *__restrict__ laye
 // than the launch they save.)
 constexpr int kStage = 2048;            // staged keys per workgroup (a round adds at most 1024)
 constexpr int kSlotsPerWave = kSlotGroup / 4;   // tile slots of a group that one wave of a gather workgroup takes
+// Small plans: a workgroup takes a quarter of a group.  Their gather is one short chain per workgroup -- entry, slots, marks,
+// words -- on a chip that is mostly idle, and four workgroups get through it in less time than one (12.3 -> 8.2 us for a
+// 512 x 512 layer, 13.0 -> 10.4 us on resnet18); on a large plan the words that neighbouring groups share, and their atomics, weigh more.
+constexpr int kSlotParts = 4;
 
 constexpr int kTileMaskWords = kTileRows * kTileCols / 32;    // mask words of one tile (rows of 8 words)
 constexpr int kGatherCountSlots = 64;                          // chunks a group of tiles counts for in LDS (the rest: directly)
@@ -1322,7 +1386,9 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
                                                               : blockIdx.x - gl.n_map_wgs - gl.n_slot_wgs;
     const uint32_t stride = role == 0 ? gl.n_map_wgs : role == 1 ? gl.n_slot_wgs
                                                                  : gridDim.x - gl.n_map_wgs - gl.n_slot_wgs;
-    const uint32_t n_items = role == 0 ? gl.n_map_chunks : role == 1 ? gl.n_cand_groups : gl.n_chunks;
+    constexpr uint32_t PARTS = COUNT ? kSlotParts : 1;           // workgroups per group of slots
+    constexpr uint32_t SLOTS = kSlotGroup / PARTS;
+    const uint32_t n_items = role == 0 ? gl.n_map_chunks : role == 1 ? gl.n_cand_groups * PARTS : gl.n_chunks;
     const DirEntry *__restrict__ dir = gl.chunk_dir;
     if (first >= n_items) return;
     if (role == 2 && a.flags[0] == 0u) return;
@@ -1342,12 +1408,18 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
         uint32_t l;
         ChunkEntry ce = {};
         GroupEntry ge = {};
+        const unsigned long long *__restrict__ ent0 = nullptr;     // role 1: the group's first slot entry
         if (role == 0) {
             ce = gl.map_chunks[it];
             l = ce.layer;
         } else if (role == 1) {
-            ge = gl.cand_groups[it];
+            ge = gl.cand_groups[it / PARTS];
             l = ge.layer;
+            const uint32_t s0 = (it % PARTS) * SLOTS;
+            if (s0 >= ge.ntile) continue;
+            ge.slot0 += s0;
+            ge.ntile = static_cast<uint8_t>(min(static_cast<uint32_t>(ge.ntile) - s0, SLOTS));
+            ent0 = a.slot_ent + (((static_cast<uint64_t>(ge.ent0_high) << 32) | ge.ent0_low) << 1) + s0 * ge.slot_cap;
         } else {
             e = dir_advance(dir, gl.n_layers, e, it);
             l = dir[e].layer;
@@ -1444,9 +1516,7 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
                 }
             }
         } else {
-            const uint32_t slot_cap = L.slot_cap;
-            const unsigned long long *__restrict__ ent0 =
-                a.slot_ent + L.slot_off + static_cast<size_t>(ge.slot0 - L.tile_begin_all) * slot_cap;
+            const uint32_t slot_cap = ge.slot_cap;
             const WindowGeom geom = {static_cast<size_t>(L.elem_off), static_cast<int>(L.R), static_cast<int>(L.C),
                                      (static_cast<int>(L.p) - 1) / 2};
             const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
@@ -1468,15 +1538,25 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
                     (static_cast<size_t>(max(0, (g0 / tiles_x) * kTileRows - h)) * C +
                      static_cast<size_t>(max(0, (g0 % tiles_x) * kTileCols - h))) / kChunk);
                 __syncthreads();                                 // (the previous group's words are written)
-                for (int i = tid; i < kSlotGroup * kTileMaskWords; i += 256) sh.bits[i] = 0u;
+                for (int i = tid; i < static_cast<int>(SLOTS) * kTileMaskWords; i += 256) sh.bits[i] = 0u;
                 if (COUNT && tid < kGatherCountSlots) sh.ccnt[tid] = 0u;
                 __syncthreads();
                 {
-                    // sixteen lanes per tile slot; a round covers 16 entries of each
-                    const int sidx0 = tid >> 4;
-                    const uint32_t cnt = sidx0 < gn ? min(a.slot_cnt[ge.slot0 + static_cast<uint32_t>(sidx0)], slot_cap) : 0u;
-                    for (uint32_t j = static_cast<uint32_t>(tid) & 15u; j < cnt; j += 16u) {
-                        const unsigned long long K = ent0[static_cast<size_t>(sidx0) * slot_cap + j];
+                    // LPS lanes per tile slot; a round covers as many entries of each.  The first entries are requested
+                    // beside the slot's count (a slot always has them; past the count they hold anything)
+                    constexpr uint32_t LPS = 256 / SLOTS;
+                    const int sidx0 = tid / static_cast<int>(LPS);
+                    const uint32_t j0 = static_cast<uint32_t>(tid) % LPS;
+                    const unsigned long long *__restrict__ slot = ent0 + static_cast<size_t>(sidx0) * slot_cap;
+                    unsigned long long K0 = 0;
+                    uint32_t cnt = 0;
+                    if (sidx0 < gn) {
+                        cnt = a.slot_cnt[ge.slot0 + static_cast<uint32_t>(sidx0)];
+                        if (j0 < slot_cap) K0 = slot[j0];
+                        cnt = min(cnt, slot_cap);
+                    }
+                    for (uint32_t j = j0; j < cnt; j += LPS) {
+                        const unsigned long long K = j == j0 ? K0 : slot[j];
                         const uint32_t score = static_cast<uint32_t>(K >> 32);
                         if (score >= above) {                    // selected for certain: its window, tile by tile
                             const uint32_t i = ~static_cast<uint32_t>(K);
@@ -2234,18 +2314,19 @@ __device__ __forceinline__ void chunk_prefix_wave0(const ChunkInfo &ci, uint32_t
 __global__ __launch_bounds__(256) void k_emit(const LayerDev *__restrict__ layers,
                                               const ChunkInfo *__restrict__ chunk_info, const float *__restrict__ grad,
                                               float *__restrict__ resid,
-                                              const uint32_t *__restrict__ mask,
+                                              uint32_t *__restrict__ mask,
                                               const uint32_t *__restrict__ chunk_cnt,
                                               const uint32_t *__restrict__ group_cnt,
                                               uint32_t *__restrict__ out_idx,
                                               float *__restrict__ out_val,
-                                              int32_t *__restrict__ out_counts) {
+                                              int32_t *__restrict__ out_counts, const NextCall nc) {
+    if (prepare_next_call(nc)) return;
     __shared__ uint32_t wave_tot[4];
     __shared__ uint32_t s_word[256];
     __shared__ uint32_t s_pref[256];
     __shared__ uint32_t s_cbase;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = blockIdx.x - 1;
     const ChunkInfo ci = chunk_info[c];
     const LayerDev L = layers[ci.layer];
     const uint32_t start = ci.start, len = ci.len;
@@ -2266,6 +2347,7 @@ __global__ __launch_bounds__(256) void k_emit(const LayerDev *__restrict__ layer
         }
     }
     chunk_prefix_wave0(ci, c, chunk_cnt, group_cnt, &s_cbase);
+    if (word) mask[(base >> 5) + tid] = 0u;            // (every word is read by one thread: clear for the next call)
     const uint32_t cnt = __popc(word);
     s_word[tid] = word;
     const uint32_t incl = block_scan_incl(cnt, wave_tot);
@@ -2357,17 +2439,18 @@ __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict
                                                      float *__restrict__ v_arena,
                                                      const float *__restrict__ mom_in,
                                                      float *__restrict__ mom_arena, float m,
-                                                     const uint32_t *__restrict__ mask,
+                                                     uint32_t *__restrict__ mask,
                                                      const uint32_t *__restrict__ chunk_cnt,
                                                      const uint32_t *__restrict__ group_cnt,
                                                      uint32_t *__restrict__ out_idx,
                                                      float *__restrict__ out_val,
-                                                     int32_t *__restrict__ out_counts) {
+                                                     int32_t *__restrict__ out_counts, const NextCall nc) {
+    if (prepare_next_call(nc)) return;
     __shared__ uint32_t wave_tot[4];
     __shared__ uint16_t s_list[kChunk];
     __shared__ uint32_t s_total, s_cbase;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = blockIdx.x - 1;
     const ChunkInfo ci = chunk_info[c];
     const uint32_t start = ci.start, len = ci.len;
     const size_t base = ci.arena_off;
@@ -2375,8 +2458,10 @@ __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict
     // the three loads that depend only on the chunk's entry go out together
     const uint32_t nwords = (len + 31) >> 5;
     uint32_t word = static_cast<uint32_t>(tid) < nwords ? mask[(base >> 5) + tid] : 0;
+    // (k_l = 0: kModeSkip in this call's state and in the next call's, which the first workgroup is writing)
     const uint32_t mode = state[ci.layer].mode;
     chunk_prefix_wave0(ci, c, chunk_cnt, group_cnt, &s_cbase);
+    if (word) mask[(base >> 5) + tid] = 0u;            // (every word is read by one thread: clear for the next call)
     if (mode == kModeSkip) {
         if (ci.last && tid == 0) out_counts[ci.layer] = 0;
         const float *__restrict__ g = grad + base;
@@ -2429,7 +2514,7 @@ __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict
 // Ascending list of the selected centres of every layer.
 __global__ __launch_bounds__(256) void k_emit_centres(const LayerDev *__restrict__ layers,
                                                       const ChunkInfo *__restrict__ chunk_info,
-                                                      const uint32_t *__restrict__ cmask,
+                                                      uint32_t *__restrict__ cmask,
                                                       const uint32_t *__restrict__ chunk_ccnt,
                                                       const uint32_t *__restrict__ group_ccnt,
                                                       uint32_t *__restrict__ out_centre_idx,
@@ -2445,6 +2530,7 @@ __global__ __launch_bounds__(256) void k_emit_centres(const LayerDev *__restrict
     const uint32_t nwords = (ci.len + 31) >> 5;
     uint32_t word = static_cast<uint32_t>(tid) < nwords ? cmask[(base >> 5) + tid] : 0;
     chunk_prefix_wave0(ci, c, chunk_ccnt, group_ccnt, &s_cbase);
+    if (word) cmask[(base >> 5) + tid] = 0u;           // (every word is read by one thread: clear for the next call)
     const uint32_t cnt = __popc(word);
     const uint32_t incl = block_scan_incl(cnt, wave_tot);
     const uint32_t cbase = s_cbase;
@@ -3486,6 +3572,7 @@ int upload_tables(rsdgc_plan_s *plan, void *workspace, hipStream_t stream) {
     HIP_TRY(hipMemcpyAsync(workspace, plan->table.data(), plan->ws.table_bytes,
                            hipMemcpyHostToDevice, stream));
     plan->calls_since_upload = 0;
+    plan->ws_ready = false;
     plan->uploaded_ws = workspace;
     plan->uploaded_version = plan->version;
     return RSDGC_OK;
@@ -3536,6 +3623,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     // the main pass and its fallback concern the large layers only: they walk those layers' tiles
     constexpr bool kLargeOnly = PASS == kPassCapture || PASS == kPassFullMap;
     const SampleEntry *samples = reinterpret_cast<const SampleEntry *>(ws + plan->ws.samples);
+    const SampleEntry *large_tiles = reinterpret_cast<const SampleEntry *>(ws + plan->ws.map_tiles);
     uint32_t *feed = reinterpret_cast<uint32_t *>(ws + plan->ws.feed);
     int group_index = 0;
     for (const PGroup &g : plan->groups) {
@@ -3547,7 +3635,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         a.dir = kLargeOnly ? large_dir + g.large_dir_begin : tile_dir + g.dir_begin;
         a.n_dir = kLargeOnly ? g.large_dir_count : g.dir_count;
         a.n_tiles = g.n_tiles;
-        a.samples = samples + g.sample_begin;
+        a.samples = kLargeOnly ? large_tiles + g.large_list_begin : samples + g.sample_begin;
         // work items of this launch and the number of workgroups that share them
         // (the first pass without the sampled tiles: only the layers that are always ranked on the full map)
         const uint32_t items = PASS == kPassSample ? (with_sampled_tiles ? g.n_samples : g.n_map_samples)
@@ -3673,7 +3761,7 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         gl.n_map_chunks = static_cast<uint32_t>(plan->map_chunks.size());
         gl.n_cand_groups = n_cand_groups;
         gl.n_map_wgs = std::min<uint32_t>(gl.n_map_chunks, kNumCUs * 4u);
-        gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups, kNumCUs * 8u);
+        gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (inline_count ? kSlotParts : 1u), kNumCUs * 8u);
         const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u;
         if (gl.n_map_wgs + gl.n_slot_wgs + n_fb_wgs > 0)
         {
@@ -3700,7 +3788,7 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         m.n_layers = static_cast<uint32_t>(L);
         m.n_tiles = plan->n_tiles_all;
         m.map_tiles = reinterpret_cast<const SampleEntry *>(ws + w.map_tiles);
-        m.n_map_tiles = static_cast<uint32_t>(plan->map_tiles.size());
+        m.n_map_tiles = plan->n_map_tiles;
         m.n_list_wgs = std::min<uint32_t>(m.n_map_tiles, kNumCUs * 8u);
         m.flags = flags;
         m.keys = reinterpret_cast<const uint32_t *>(nsi);
@@ -3776,16 +3864,27 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
 
     StageMarks marks(plan, stream);
-    // clear: state .. mask (and the centre mask only when it is used)
-    {
-        const size_t end = want_centres ? w.zero_end : w.cmask;
-        const size_t n16 = (end - w.zero_begin) / 16;
+    // the first call with a workspace (or after one that failed): everything a call expects
+    if (!plan->ws_ready) {
+        const size_t n16 = (w.zero_end - w.zero_begin) / 16;
         const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n16 + 255) / 256, 4096));
         hipLaunchKernelGGL(k_begin, dim3(blocks + 1), dim3(256), 0, stream,
                            reinterpret_cast<uint4 *>(ws + w.zero_begin), n16, layers, state, L, pred, flags,
                            sampling ? 1 : 0);
         HIP_TRY(hipGetLastError());
     }
+    plan->ws_ready = false;                // (until all of this call is enqueued)
+    NextCall nc;
+    nc.zero[0] = reinterpret_cast<uint4 *>(ws + w.hist);
+    nc.n16[0] = static_cast<uint32_t>((w.chunk_cnt - w.hist) / 16);
+    nc.zero[1] = reinterpret_cast<uint4 *>(ws + w.list_cnt);
+    nc.n16[1] = static_cast<uint32_t>((w.mask - w.list_cnt) / 16);
+    nc.layers = layers;
+    nc.state = state;
+    nc.pred = pred;
+    nc.flags = flags;
+    nc.n_layers = L;
+    nc.sampling = plan->any_large && plan->calls_since_upload < kSamplingCalls ? 1 : 0;
     marks.close(0);
 
     // first pass: every tile of the layers ranked on the full map (scores, histogram, v) and, where a
@@ -3804,7 +3903,8 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     }
     marks.close(2);
     // first ranking digit of every layer, and whether the candidate bounds held
-    hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, layers, state, hist, flags, pred);
+    hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, layers, state, hist, flags, pred,
+                       reinterpret_cast<uint4 *>(ws + w.chunk_cnt), static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16));
     if (plan->any_large) {
         // large layers whose candidate bound failed (rare): the workgroups find nothing to do otherwise
         rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream);
@@ -3816,12 +3916,12 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     if (rc != RSDGC_OK) return rc;
     const ChunkInfo *chunk_info = reinterpret_cast<const ChunkInfo *>(ws + w.chunk_info);
     if (in_place)
-        hipLaunchKernelGGL(k_emit, dim3(n_chunks), dim3(256), 0, stream, layers, chunk_info, grad,
-                           residual_out, mask, chunk_cnt, group_cnt, out_idx, out_val, out_counts);
+        hipLaunchKernelGGL(k_emit, dim3(n_chunks + 1), dim3(256), 0, stream, layers, chunk_info, grad,
+                           residual_out, mask, chunk_cnt, group_cnt, out_idx, out_val, out_counts, nc);
     else
-        hipLaunchKernelGGL(k_emit_sparse, dim3(n_chunks), dim3(256), 0, stream, chunk_info, state, grad,
+        hipLaunchKernelGGL(k_emit_sparse, dim3(n_chunks + 1), dim3(256), 0, stream, chunk_info, state, grad,
                            residual, residual_out, mom.in, mom.out, mom.m, mask, chunk_cnt, group_cnt, out_idx,
-                           out_val, out_counts);
+                           out_val, out_counts, nc);
     marks.close(7);
     if (want_centres)                      // the list, the counts, or both
         hipLaunchKernelGGL(k_emit_centres, dim3(n_chunks), dim3(256), 0, stream, layers, chunk_info,
@@ -3829,6 +3929,7 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
                            out_centre_counts);
     marks.close(8);
     HIP_TRY(hipGetLastError());
+    plan->ws_ready = true;
     return RSDGC_OK;
 }
 
@@ -4019,7 +4120,8 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     }
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, inner, state, hist,
-                       reinterpret_cast<uint32_t *>(ws + w.flags), static_cast<PredState *>(nullptr));
+                       reinterpret_cast<uint32_t *>(ws + w.flags), static_cast<PredState *>(nullptr),
+                       static_cast<uint4 *>(nullptr), 0u);
     rc = select_mark_count(in, ws, false, marks, nullptr, stream);
     if (rc != RSDGC_OK) return rc;
     hipLaunchKernelGGL(k_emit_blocks, dim3(in->n_chunks), dim3(256), 0, stream, outer, inner_chunks, mask,
@@ -4248,7 +4350,7 @@ int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, 
     HIP_TRY(hipMemcpy(host.data(), static_cast<const char *>(workspace) + plan->ws.state,
                       sizeof(SelState) * plan->n_layers, hipMemcpyDeviceToHost));
     for (int l = 0; l < plan->n_layers; ++l)
-        paths[l] = host[l].mode == kModeCandidates && host[l].predicted ? 3 : static_cast<int32_t>(host[l].mode);
+        paths[l] = static_cast<int32_t>(host[l].predicted >> kLastPathShift);
     return RSDGC_OK;
 }
 

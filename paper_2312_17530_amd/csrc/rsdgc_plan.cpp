@@ -147,8 +147,11 @@ int build_tables(rsdgc_plan_s *plan) {
         if (d.large) {
             for (uint32_t g = 0; g < d.n_groups; ++g) {
                 const uint32_t t0 = g * kSlotGroup;
+                const uint64_t ent0 = d.slot_off + static_cast<uint64_t>(t0) * d.slot_cap;
                 plan->cand_groups.push_back(GroupEntry{static_cast<uint32_t>(l), d.tile_begin_all + t0,
-                                                       std::min<uint32_t>(kSlotGroup, d.n_tiles - t0), 0u});
+                                                       static_cast<uint8_t>(std::min<uint32_t>(kSlotGroup, d.n_tiles - t0)),
+                                                       static_cast<uint8_t>(ent0 >> 33),
+                                                       static_cast<uint16_t>(d.slot_cap), static_cast<uint32_t>(ent0 >> 1)});
             }
         } else if (d.k > 0) {
             for (uint32_t c = 0; c < d.n_chunks; ++c) {
@@ -162,12 +165,15 @@ int build_tables(rsdgc_plan_s *plan) {
         }
     }
 
+    plan->n_map_tiles = static_cast<uint32_t>(plan->map_tiles.size());
+
     // one launch of each NSI pass per distinct neighbourhood side
     for (int p = 1; p <= RSDGC_MAX_P; p += 2) {
         PGroup g;
         g.p = p;
         g.dir_begin = static_cast<uint32_t>(plan->tile_dir.size());
         g.large_dir_begin = static_cast<uint32_t>(plan->large_dir.size());
+        g.large_list_begin = static_cast<uint32_t>(plan->map_tiles.size());
         g.sample_begin = static_cast<uint32_t>(plan->samples.size());
         for (int l = 0; l < L; ++l) {
             if (plan->p[l] != p) continue;
@@ -180,6 +186,7 @@ int build_tables(rsdgc_plan_s *plan) {
                 plan->large_dir.push_back(DirEntry{g.n_large_tiles, static_cast<uint32_t>(l)});
                 g.n_large_tiles += d.n_tiles;
                 ++g.large_dir_count;
+                for (uint32_t t = 0; t < d.n_tiles; ++t) plan->map_tiles.push_back(SampleEntry{static_cast<uint32_t>(l), t});
             }
         }
         // tile list of the first NSI pass: every tile of the layers that select something and are not

@@ -97,3 +97,43 @@ def test_dynamic_ratios_on_a_million_weights(kind):
         for w in (ws, ws2, ws):
             binding.rsdgc_plan_forget_workspace(plan)
             assert binding.rsdgc_dynamic_ratios(plan, arena, rho, w) == want, (kind, rho)
+
+
+@pytest.mark.parametrize("p", [1, 3, 5, 7])
+def test_every_call_leaves_the_workspace_ready_for_the_next(p):
+    """Counters, masks and layer states are cleared and set by the last kernels of a call for the one that follows.  Layers
+    that end on, before and after a tile's 16 rows and 256 columns, rows of odd length, one layer without anything to keep and one
+    ranked on the full map; enough calls for predicted bounds, then gradients a thousand times larger and smaller, so that bounds
+    fail.  Both residual forms of every call against each other, the first and the last ones against the oracle; a call of another
+    entry point with the same workspace in between."""
+    import torch
+    from paper_2312_17530_amd.session import Session
+    shapes = [(16, 256), (17, 257), (33, 512), (15, 1028), (48, 260), (31, 1001), (1, 700), (64, 64), (35, 516), (40, 40),
+              (130, 1030), (34, 300)]
+    ratios = [0.02] * len(shapes)
+    ratios[-1], ratios[9], ratios[2] = 0.0, 0.9, 0.002
+    rng = np.random.default_rng(p)
+    a = Session(shapes, p, 0.5, ratios)
+    b = Session(shapes, p, 0.5, ratios, in_place=True)
+    paths = set()
+    for t in range(16):
+        scale = 1e-2 * (1000.0 if t == 13 else 0.001 if t == 14 else 1.0)
+        grads = [(rng.standard_normal(sh) * scale).astype(np.float32) for sh in shapes]
+        before = b.unpack(b.residual)
+        for s in (a, b):
+            s.set_grad(grads)
+            s.compress()
+        paths |= {(t >= 13, x) for x in binding.rsdgc_last_paths(b.plan, b.workspace)}
+        for x, y in zip(a.results(), b.results()):
+            assert all(np.array_equal(u, v) for u, v in zip(x, y)), t
+        after = b.unpack(b.residual)
+        for x, y in zip(a.unpack(a.residual), after):
+            assert np.array_equal(_bits(x), _bits(y)), t
+        if t == 11:
+            binding.rsdgc_dynamic_ratios(b.plan, b.grad, 0.1, b.workspace)
+        if t < 2 or t >= 12:
+            for l, (idx, val, centres, _) in enumerate(b.results()):
+                o = oracle.compress_layer(grads[l], before[l], p, 0.5, ratios[l])
+                assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+                assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+    assert (False, 3) in paths and (True, 1) in paths and (False, 2) in paths
