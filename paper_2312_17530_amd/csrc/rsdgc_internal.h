@@ -220,14 +220,16 @@ struct WsLayout {
     // zero when a compress call starts: cleared by the first with a workspace, then every call leaves them so
     // (hist .. hist1, list_cnt .. cmask by its last kernels; chunk_cnt .. group_ccnt before it counts)
     size_t zero_begin = 0;
-    size_t hist = 0;         // uint32[n_layers][kHistBins]  first ranking digit
-    size_t hist_s = 0;       // uint32[n_layers][kHistBins]  sampled scores of the large layers (coarse digit)
+    size_t hist = 0;         // uint32[n_layers][kHistBins]  first ranking digit of the layers ranked on the full map
+    size_t hist_s = 0;       // uint32[n_layers][kHistBins]  large layers: sampled scores (coarse digit; k_hint clears them), then the
+                             //             candidates' first digit (kFineBins of them)
     size_t hist1 = 0;        // uint32[n_layers][kLevel1Bins]  second ranking digit
     size_t chunk_cnt = 0;    // uint32[n_chunks]  kept elements per chunk
     size_t chunk_ccnt = 0;   // uint32[n_chunks]  selected centres per chunk
     size_t group_cnt = 0;    // uint32[n_chunk_groups * kGroupCntStride]  kept elements per chunk group, each counter on its own cache line
     size_t group_ccnt = 0;   // the same for the selected centres
-    size_t list_cnt = 0;     // uint32[n_layers][kListShards][kListCntStride]  keys gathered per list shard
+    size_t list_cnt = 0;     // uint32[n_layers][kListShards][kListCntStride]  [0] of a shard: keys gathered into it, [1]: a part of the
+                             //             layer's candidates recorded by the main pass (any share of the workgroups')
     size_t list2_cnt = 0;    // uint32[n_layers]  of those, keys that k_filter picked for k_finish
     size_t feed = 0;         // uint32[16][8][32]  work-feed counters of the NSI launches
     size_t mask = 0;         // uint32[total_elems / 32]  kept-element bitmask

@@ -480,7 +480,9 @@ struct NsiArgs {
     float m;                      // momentum factor
     const uint32_t *flags;        // [0] != 0: some large layer fell back to the full map
     uint32_t *hist;               // [n_layers][kHistBins]
-    uint32_t *hist_s;             // [n_layers][kHistBins]  scores of the sampled tiles of the large layers
+    uint32_t *hist_s;             // [n_layers][kHistBins]  scores of the sampled tiles of the large layers; main pass: fine bins
+    uint32_t *list_cnt;           // main pass: adds up a layer's candidates in word 1 of its shards' lines
+    int n_layers;
     const SelState *state;
     SelState *state_rw;           // same array; the main pass sets the overflow flag
     uint32_t *slot_cnt;           // [n_tiles_all]
@@ -556,9 +558,44 @@ __device__ __forceinline__ WaveBucket wave_find_bucket(const uint32_t *__restric
 // a launch issues few same-address global atomics.
 // MOM: with Eq. 12's momentum term (a.mom, a.mom_out, a.m).  FEED: the workgroups take their
 // tiles from the launch's work feed instead of a fixed strided share.
-template <int P, int PASS, bool MOM, bool FEED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PASS == kPassCapture && !MOM ? (P <= 3 ? 5 : 4) : 1, 8)))
-void k_nsi(const NsiArgs a) {
+// Where a workgroup adds the candidates it recorded of a layer: word 1 of one of the first kRecordedParts list shards' lines
+// (several, as all workgroups of a launch end at about the same time).
+constexpr uint32_t kRecordedParts = 4;
+__device__ __forceinline__ uint32_t *recorded_slot(uint32_t *list_cnt, uint32_t layer, uint32_t wg) {
+    return list_cnt + (static_cast<size_t>(layer) * kListShards + (wg % kRecordedParts)) * kListCntStride + 1;
+}
+
+// Whether a large layer is ranked on the full map in this call: it started so, or its bound failed -- fewer than k_l
+// centres reach it, k_l or more lie in the open-ended top bin, or a tile slot overflowed.  k_find0's test, from what the
+// main pass has left, for workgroups of its own launch (which may see the mode before or after k_find0 has changed it).
+__device__ __forceinline__ bool layer_falls_back(const NsiArgs &a, uint32_t l) {
+    const SelState *st = a.state + l;
+    const uint32_t mode = st->mode, hint_key = st->hint_key, overflow = st->overflow;
+    const uint32_t large = a.layers[l].large, k = a.layers[l].k;
+    const uint32_t top = a.hist_s[static_cast<size_t>(l) * kHistBins + kFineBins - 1];
+    uint32_t recorded = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kRecordedParts; ++q) recorded += *recorded_slot(a.list_cnt, l, q);
+    if (large == 0u || mode == kModeSkip) return false;
+    return mode == kModeFullMap || hint_key == 0u || overflow != 0u || recorded < k || top >= k;
+}
+
+template <int P, int PASS>
+struct NsiShared {
+    static constexpr bool kCapture = PASS == kPassCapture;
+    static constexpr int kBins = PASS == kPassFullMap || PASS == kPassSample ? kHistBins : (kCapture ? kFineBins : 1);
+    __attribute__((aligned(16))) float tile[(kTileRows + P - 1) * (kTileCols + 8)];
+    unsigned long long cand[kCapture ? kSlotCapMax : 1];
+    uint32_t lhist[kBins];
+    uint16_t queue[kCapture ? kQueueCap : 1];
+    uint32_t ncand, nqueue;
+    uint32_t feed_slot[2];
+};
+
+// wg, n_wgs: the workgroup's number among those of this pass, and how many they are.  WITH_FIND0: the fallback pass
+// in one launch with k_find0 -- it cannot wait for the flag and looks at the layers itself (at most 256 of them).
+template <int P, int PASS, bool MOM, bool FEED, bool WITH_FIND0 = false>
+__device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &sh, uint32_t wg, uint32_t n_wgs) {
     constexpr int H = (P - 1) / 2;
     constexpr int ROWS = kTileRows + 2 * H;
     constexpr int PADL = 4;
@@ -570,28 +607,34 @@ void k_nsi(const NsiArgs a) {
     constexpr bool CAPTURE = PASS == kPassCapture;
     constexpr bool FULLHIST = PASS == kPassFullMap || PASS == kPassSample;
     constexpr bool STORE_V = PASS != kPassMapOnly;
-    constexpr int NBINS = FULLHIST ? kHistBins : (CAPTURE ? kFineBins : 1);
-    __shared__ __attribute__((aligned(16))) float tile[ROWS * PITCH];
-    __shared__ uint32_t lhist[NBINS];
-    __shared__ unsigned long long cand[CAPTURE ? kSlotCapMax : 1];
-    __shared__ uint16_t queue[CAPTURE ? kQueueCap : 1];
-    __shared__ uint32_t ncand, nqueue;
-    __shared__ uint32_t feed_slot[2];
+    constexpr int NBINS = NsiShared<P, PASS>::kBins;
+    float *const tile = sh.tile;
+    uint32_t *const lhist = sh.lhist;
+    unsigned long long *const cand = sh.cand;
+    uint16_t *const queue = sh.queue;
+    uint32_t &ncand = sh.ncand, &nqueue = sh.nqueue;
+    uint32_t *const feed_slot = sh.feed_slot;
 
     const int tid = threadIdx.x;
     // the launch's work items (tiles, or sampled tiles): at any moment the resident workgroups
     // work on one compact stretch of tiles, so neighbouring tiles' halo rows are still in
     // cache; inside a stretch each XCD takes one contiguous part
     const uint32_t n_items = a.n_tiles;
-    const uint32_t stride = gridDim.x;
-    if (PASS == kPassFullMap && a.flags[0] == 0u) return;   // no layer fell back: nothing to do
+    const uint32_t stride = n_wgs;
+    if (PASS == kPassFullMap) {            // no layer fell back: nothing to do
+        if (WITH_FIND0) {
+            if (!__syncthreads_or(tid < a.n_layers && layer_falls_back(a, tid))) return;
+        } else if (a.flags[0] == 0u) {
+            return;
+        }
+    }
     WorkFeed feed;
     uint32_t first;
     if (FEED) {
         first = feed.first(a.feed, n_items, a.feed_shift, feed_slot);
         if (first == kNoItem) return;      // uniform
     } else {
-        first = xcd_contiguous(blockIdx.x, gridDim.x);
+        first = xcd_contiguous(wg, n_wgs);
         if (first >= n_items) return;
     }
 
@@ -610,7 +653,8 @@ void k_nsi(const NsiArgs a) {
     else e = dir_lookup(a.dir, a.n_dir, first);
     uint32_t cur_l = 0xffffffffu;         // layer whose counts sit in lhist
     uint32_t hint_key = 0;
-    uint32_t *hist_base = a.hist;         // first pass: a.hist_s for the sampled tiles of a large layer
+    uint32_t *hist_base = CAPTURE ? a.hist_s : a.hist;         // first pass: a.hist_s for the sampled tiles of a large layer
+    uint32_t recorded = 0;                // main pass: the workgroup's candidates of layer cur_l
     bool active = true;
     bool whole = true;                    // every tile of the layer is visited: v and the scores go out
     LayerDev L;
@@ -643,6 +687,8 @@ void k_nsi(const NsiArgs a) {
                     const uint32_t c = lhist[b];
                     if (c) { atomicAdd(&gh[b], c); lhist[b] = 0; }
                 }
+                if (CAPTURE && tid == 0 && recorded) atomicAdd(recorded_slot(a.list_cnt, cur_l, wg), recorded);
+                recorded = 0;
                 __syncthreads();
             }
             cur_l = l;
@@ -652,7 +698,7 @@ void k_nsi(const NsiArgs a) {
             whole = PASS != kPassSample || L.large == 0u;
             if (PASS == kPassFullMap || PASS == kPassCapture || (PASS == kPassSample && !whole)) {
                 const SelState st = a.state[l];
-                if (PASS == kPassFullMap) active = st.mode == kModeFullMap && L.large != 0u;
+                if (PASS == kPassFullMap) active = WITH_FIND0 ? layer_falls_back(a, l) : st.mode == kModeFullMap && L.large != 0u;
                 else if (PASS == kPassSample) active = st.mode == kModeCandidates && st.hint_key == 0u;   // no predicted bound
                 else active = st.mode == kModeCandidates;
                 if (CAPTURE) {
@@ -930,6 +976,7 @@ void k_nsi(const NsiArgs a) {
 
         if (CAPTURE) {
             const uint32_t nc = ncand, cap = L.slot_cap;
+            recorded += nc;
             unsigned long long *__restrict__ dst = a.slot_ent + L.slot_off + static_cast<size_t>(local) * cap;
             for (uint32_t i = tid; i < min(nc, cap); i += 256) dst[i] = cand[i];
             if (tid == 0) {
@@ -948,8 +995,23 @@ void k_nsi(const NsiArgs a) {
             const uint32_t c = lhist[b];
             if (c) atomicAdd(&gh[b], c);
         }
+        if (CAPTURE && tid == 0 && recorded) atomicAdd(recorded_slot(a.list_cnt, cur_l, wg), recorded);
     }
 }
+
+template <int P, int PASS, bool MOM, bool FEED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PASS == kPassCapture && !MOM ? (P <= 3 ? 5 : 4) : 1, 8)))
+void k_nsi(const NsiArgs a) {
+    __shared__ NsiShared<P, PASS> sh;
+    nsi_pass<P, PASS, MOM, FEED>(a, sh, blockIdx.x, gridDim.x);
+}
+
+// All sides' launches in one (the fallback pass of small plans): a range of workgroups each.
+constexpr int kSides = (RSDGC_MAX_P + 1) / 2;
+struct NsiAllArgs {
+    NsiArgs side[kSides];                 // p = 1, 3, 5, 7
+    uint32_t first_wg[kSides + 1];
+};
 
 // ------------------------------------------------------- ranking digits --
 // The k_l-th largest composite key of a layer (Algorithm 1's ranking, Eq. 11's k_l) is found
@@ -1124,7 +1186,7 @@ __device__ __forceinline__ void mark_window(const WindowGeom &g, const CountCtx 
 // none (too few scores, or the target only in bucket 0) goes to the full map.
 __global__ __launch_bounds__(256) void k_hint(const LayerDev *__restrict__ layers,
                                               SelState *__restrict__ state,
-                                              const uint32_t *__restrict__ hist_s,
+                                              uint32_t *__restrict__ hist_s,
                                               uint32_t *__restrict__ flags) {
     __shared__ uint32_t wave_tot[4];
     __shared__ DigitResult res;
@@ -1132,7 +1194,7 @@ __global__ __launch_bounds__(256) void k_hint(const LayerDev *__restrict__ layer
     const SelState st = state[l];
     const uint32_t target = layers[l].hint_target;
     constexpr int per = kHistBins / 256;
-    const uint32_t *__restrict__ hs = hist_s + static_cast<size_t>(l) * kHistBins;
+    uint32_t *__restrict__ hs = hist_s + static_cast<size_t>(l) * kHistBins;
     const int hi = kHistBins - tid * per;          // thread 0 holds the top buckets
     uint32_t v[per];
     uint32_t own = 0;
@@ -1142,6 +1204,9 @@ __global__ __launch_bounds__(256) void k_hint(const LayerDev *__restrict__ layer
         own += v[j];
     }
     if (st.mode != kModeCandidates || st.hint_key != 0u) return;    // uniform
+#pragma unroll
+    for (int j = 0; j < per; ++j)                  // (the main pass counts its candidates here)
+        if (v[j]) hs[hi - 1 - j] = 0u;
     if (tid == 0) res.found = 0;
     const uint32_t incl = block_scan_incl(own, wave_tot);
     const uint32_t excl = incl - own;
@@ -1175,23 +1240,28 @@ __global__ __launch_bounds__(256) void k_hint(const LayerDev *__restrict__ layer
 // among them) and the k_l-th does not lie in the open-ended top bin.  Otherwise the layer falls
 // back to the full map in this call (a flag tells the fallback kernels that there is work), goes
 // back to sampled bounds for the next few calls and widens the margin of its predictions.
-__global__ __launch_bounds__(256) void k_find0(const LayerDev *__restrict__ layers,
-                                               SelState *__restrict__ state,
-                                               uint32_t *__restrict__ hist,
-                                               uint32_t *__restrict__ flags,
-                                               PredState *__restrict__ pred /* nullable */,
-                                               uint4 *__restrict__ counts, uint32_t n16) {
+struct Find0Args {
+    const LayerDev *layers;
+    SelState *state;
+    const uint32_t *hist, *hist_s;
+    uint32_t *flags;
+    PredState *pred;           // nullable
+    uint4 *counts;             // the chunk counters: cleared here for the kernels to come
+    uint32_t n16;
+    int n_layers;
+};
+__device__ __forceinline__ void find0(const Find0Args &f, int l) {
     __shared__ uint32_t wave_tot[4];
     __shared__ DigitResult res;
-    const int l = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     // the chunk counters, which the last kernel of the call before still read
-    for (uint32_t j = blockIdx.x * 256u + tid; j < n16; j += gridDim.x * 256u) counts[j] = make_uint4(0, 0, 0, 0);
+    for (uint32_t j = static_cast<uint32_t>(l) * 256u + tid; j < f.n16; j += static_cast<uint32_t>(f.n_layers) * 256u) f.counts[j] = make_uint4(0, 0, 0, 0);
     // state, layer constants and counts are requested together: one round trip to memory
     // instead of three (each costs this one-workgroup-per-layer kernel about 2 us)
-    const SelState st = state[l];
-    const uint32_t large = layers[l].large;
-    uint32_t *__restrict__ h = hist + static_cast<size_t>(l) * kHistBins;
+    const SelState st = f.state[l];
+    const uint32_t large = f.layers[l].large;
     const bool cand = st.mode == kModeCandidates;                  // uniform
+    const uint32_t *__restrict__ h = (cand ? f.hist_s : f.hist) + static_cast<size_t>(l) * kHistBins;
     const int nb = cand ? kFineBins : kHistBins, per = nb >> 8;
     const int hi = nb - tid * per;              // thread t owns bins [hi - per, hi): t = 0 holds the top bins
     constexpr int kMaxPer = kHistBins / 256;
@@ -1228,24 +1298,23 @@ __global__ __launch_bounds__(256) void k_find0(const LayerDev *__restrict__ laye
     const DigitResult r = res;
     if (cand && (!r.found || st.overflow != 0u || r.digit == static_cast<uint32_t>(kFineBins - 1) ||
                  st.hint_key == 0u)) {
-        for (int b = tid; b < kFineBins; b += 256) h[b] = 0;       // the fallback pass counts afresh
         if (tid == 0) {
             SelState ns = st;
             ns.mode = kModeFullMap;
-            state[l] = ns;
-            flags[0] = 1u;                 // the fallback pass has work
-            PredState ps = pred[l];
+            f.state[l] = ns;
+            f.flags[0] = 1u;                 // the fallback pass has work
+            PredState ps = f.pred[l];
             ps.cooldown = kCooldownCalls;
             if (st.predicted & 1u) {
                 // the margin of the predicted bounds follows the way this one failed: too few centres above
                 // it -- twice the margin; a tile with too many, or a threshold beyond the bins -- the bound
                 // lay too low, and a wider margin would only repeat that: half of it, down to its start value
-                const float init = margin_init_log2(layers[l].k);
+                const float init = margin_init_log2(f.layers[l].k);
                 const float m = ps.margin > 0.f ? ps.margin : init;
                 const bool too_low = st.overflow != 0u || (r.found && r.digit == static_cast<uint32_t>(kFineBins - 1));
                 ps.margin = too_low ? fmaxf(0.5f * m, init) : fminf(2.f * m, kMarginMaxLog2);
             }
-            pred[l] = ps;
+            f.pred[l] = ps;
         }
         return;
     }
@@ -1261,11 +1330,41 @@ __global__ __launch_bounds__(256) void k_find0(const LayerDev *__restrict__ laye
             ns.T = static_cast<unsigned long long>(ns.lo) << 32;
             if (r.count == ns.k_rem) {     // whole bucket taken: the threshold is its lower edge
                 ns.done = 1;
-                publish_threshold(pred, l, large, layers[l].k, ns.T);
+                publish_threshold(f.pred, l, large, f.layers[l].k, ns.T);
             }
         }
-        state[l] = ns;
+        f.state[l] = ns;
     }
+}
+
+__global__ __launch_bounds__(256) void k_find0(const Find0Args f) { find0(f, blockIdx.x); }
+
+// k_find0 and the fallback pass in one launch (up to 256 layers): in nearly every call the pass finds nothing to do, and
+// a launch that does nothing costs as much as k_find0's -- 4.7 us each.
+template <int P, bool MOM>
+__global__ __launch_bounds__(256) void k_find0_fallback(const Find0Args f, const NsiArgs a) {
+    __shared__ NsiShared<P, kPassFullMap> sh;
+    if (blockIdx.x < static_cast<uint32_t>(f.n_layers)) find0(f, blockIdx.x);
+    else nsi_pass<P, kPassFullMap, MOM, false, true>(a, sh, blockIdx.x - f.n_layers, gridDim.x - f.n_layers);
+}
+template <bool MOM>
+__global__ __launch_bounds__(256) void k_find0_fallback_all(const Find0Args f, const NsiAllArgs a) {
+    __shared__ union Shared {
+        NsiShared<1, kPassFullMap> s1;
+        NsiShared<3, kPassFullMap> s3;
+        NsiShared<5, kPassFullMap> s5;
+        NsiShared<7, kPassFullMap> s7;
+        __device__ Shared() {}
+    } sh;
+    if (blockIdx.x < static_cast<uint32_t>(f.n_layers)) {
+        find0(f, blockIdx.x);
+        return;
+    }
+    const uint32_t b = blockIdx.x - f.n_layers;
+    if (b < a.first_wg[1]) nsi_pass<1, kPassFullMap, MOM, false, true>(a.side[0], sh.s1, b, a.first_wg[1]);
+    else if (b < a.first_wg[2]) nsi_pass<3, kPassFullMap, MOM, false, true>(a.side[1], sh.s3, b - a.first_wg[1], a.first_wg[2] - a.first_wg[1]);
+    else if (b < a.first_wg[3]) nsi_pass<5, kPassFullMap, MOM, false, true>(a.side[2], sh.s5, b - a.first_wg[2], a.first_wg[3] - a.first_wg[2]);
+    else nsi_pass<7, kPassFullMap, MOM, false, true>(a.side[3], sh.s7, b - a.first_wg[3], a.first_wg[4] - a.first_wg[3]);
 }
 
 // --------------------------------------------------------------- gather --
@@ -3588,6 +3687,8 @@ uint32_t resident_workgroups(K kernel) {
     return kNumCUs * static_cast<uint32_t>(per_cu);
 }
 
+constexpr uint32_t kFeedTiles = 16u * kNumCUs * 4u;       // tiles from which a launch hands them out by the work feed
+
 // One launch of the NSI kernel per neighbourhood side.  kPassSample runs over the sampled
 // tiles of the large layers, every other pass over all tiles (workgroups of layers that
 // are in another mode leave at once).
@@ -3600,8 +3701,10 @@ struct Momentum {                 // Eq. 12's momentum term; all null / 0 withou
 template <int PASS>
 int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const float *resid,
                float *nsi_out, float *v_out, const Momentum &mom, hipStream_t stream,
-               bool with_sampled_tiles = true) {
+               bool with_sampled_tiles = true, const Find0Args *find0_args = nullptr) {
     NsiArgs a;
+    a.list_cnt = reinterpret_cast<uint32_t *>(ws + plan->ws.list_cnt);
+    a.n_layers = plan->n_layers;
     a.v_out = v_out;
     a.mom = mom.in;
     a.mom_out = mom.out;
@@ -3626,6 +3729,11 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     const SampleEntry *large_tiles = reinterpret_cast<const SampleEntry *>(ws + plan->ws.map_tiles);
     uint32_t *feed = reinterpret_cast<uint32_t *>(ws + plan->ws.feed);
     int group_index = 0;
+    // several sides in a small plan: one launch, where each of them would find nothing to do in nearly every call (all sides get
+    // the registers of the largest, which the main pass would feel)
+    const bool together = PASS == kPassFullMap && find0_args && plan->groups.size() > 1 && plan->n_tiles_all < kFeedTiles;
+    NsiAllArgs all = {};
+    uint32_t all_items = 0;
     for (const PGroup &g : plan->groups) {
         // this launch's work-feed counters (cleared at the start of the call)
         const int pass_index = PASS == kPassSample ? 0 : PASS == kPassCapture ? 1 : 2;
@@ -3642,6 +3750,11 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
                                                    : kLargeOnly ? g.n_large_tiles : g.n_tiles;
         if (items == 0) continue;
         a.n_tiles = items;
+        if (together) {
+            all.side[g.p / 2] = a;
+            all_items += items;
+            continue;
+        }
         a.feed_shift = 7;                  // 128 items per domain and stretch: one per resident workgroup of an XCD
         while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > items) --a.feed_shift;
         const dim3 block(256);
@@ -3654,7 +3767,11 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
            workgroups of three tiles each leave the CUs less crowded in all three) */      \
         const uint32_t rounds = (items + resident - 1) / resident;                          \
         const dim3 grid(FF ? std::min<uint32_t>(items, resident) : (items + rounds - 1) / rounds); \
-        hipLaunchKernelGGL((k_nsi<PP, PASS, MM, FF>), grid, block, 0, stream, a);           \
+        if (PASS == kPassFullMap && find0_args) {                                           \
+            hipLaunchKernelGGL((k_find0_fallback<PP, MM>), dim3(grid.x + find0_args->n_layers), block, 0, stream, *find0_args, a); \
+            find0_args = nullptr;          /* (the other sides' launches, if any, go by the flag) */ \
+        } else                                                                              \
+            hipLaunchKernelGGL((k_nsi<PP, PASS, MM, FF>), grid, block, 0, stream, a);       \
     }
 #define RSDGC_NSI_CASE(PP)                                                                  \
     case PP: {                                                                              \
@@ -3662,7 +3779,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
            a few round trips to the counters); built for the main pass */                   \
         constexpr bool kFeedBuilt = PASS == kPassCapture;                                   \
         const bool fed = kFeedBuilt && plan->work_feed != RSDGC_FEED_OFF &&                 \
-                         (plan->work_feed == RSDGC_FEED_ON || items >= 16u * kNumCUs * 4u); \
+                         (plan->work_feed == RSDGC_FEED_ON || items >= kFeedTiles);         \
         if (mom.in) {                                                                       \
             if (fed) RSDGC_NSI_LAUNCH(PP, true, kFeedBuilt)                                 \
             else RSDGC_NSI_LAUNCH(PP, true, false)                                          \
@@ -3680,6 +3797,16 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
 #undef RSDGC_NSI_LAUNCH
             default: return RSDGC_EINVAL;
         }
+        HIP_TRY(hipGetLastError());
+    }
+    if (together) {
+        const uint32_t resident = kNumCUs * 2u;
+        const uint32_t rounds = std::max<uint32_t>(1u, (all_items + resident - 1) / resident);
+        for (int i = 0; i < kSides; ++i)
+            all.first_wg[i + 1] = all.first_wg[i] + (all.side[i].n_tiles + rounds - 1) / rounds;
+        const dim3 grid(all.first_wg[kSides] + find0_args->n_layers);
+        if (mom.in) hipLaunchKernelGGL(k_find0_fallback_all<true>, grid, dim3(256), 0, stream, *find0_args, all);
+        else hipLaunchKernelGGL(k_find0_fallback_all<false>, grid, dim3(256), 0, stream, *find0_args, all);
         HIP_TRY(hipGetLastError());
     }
     return RSDGC_OK;
@@ -3895,19 +4022,29 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     if (rc != RSDGC_OK) return rc;
     if (sampling)
         hipLaunchKernelGGL(k_hint, dim3(L), dim3(256), 0, stream, layers, state,
-                           reinterpret_cast<const uint32_t *>(ws + w.hist_s), flags);
+                           reinterpret_cast<uint32_t *>(ws + w.hist_s), flags);
     marks.close(1);
     if (plan->any_large) {
         rc = launch_nsi<kPassCapture>(plan, ws, grad, residual, nsi, v_out, mom, stream);
         if (rc != RSDGC_OK) return rc;
     }
     marks.close(2);
-    // first ranking digit of every layer, and whether the candidate bounds held
-    hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, layers, state, hist, flags, pred,
-                       reinterpret_cast<uint4 *>(ws + w.chunk_cnt), static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16));
+    Find0Args f;
+    f.layers = layers;
+    f.state = state;
+    f.hist = hist;
+    f.hist_s = reinterpret_cast<const uint32_t *>(ws + w.hist_s);
+    f.flags = flags;
+    f.pred = pred;
+    f.counts = reinterpret_cast<uint4 *>(ws + w.chunk_cnt);
+    f.n16 = static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16);
+    f.n_layers = L;
+    // large layers whose candidate bound failed (rare): the workgroups find nothing to do otherwise.  Up to 256 layers they look
+    // for such layers themselves, in one launch with k_find0.
+    const bool one_launch = plan->any_large && L <= 256;
+    if (!one_launch) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
     if (plan->any_large) {
-        // large layers whose candidate bound failed (rare): the workgroups find nothing to do otherwise
-        rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream);
+        rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, one_launch ? &f : nullptr);
         if (rc != RSDGC_OK) return rc;
     }
     marks.close(3);
@@ -4119,9 +4256,8 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
         }
     }
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, inner, state, hist,
-                       reinterpret_cast<uint32_t *>(ws + w.flags), static_cast<PredState *>(nullptr),
-                       static_cast<uint4 *>(nullptr), 0u);
+    const Find0Args f = {inner, state, hist, hist, reinterpret_cast<uint32_t *>(ws + w.flags), nullptr, nullptr, 0u, L};
+    hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
     rc = select_mark_count(in, ws, false, marks, nullptr, stream);
     if (rc != RSDGC_OK) return rc;
     hipLaunchKernelGGL(k_emit_blocks, dim3(in->n_chunks), dim3(256), 0, stream, outer, inner_chunks, mask,
