@@ -285,7 +285,7 @@ struct rsdgc_plan_s {
     uint64_t slot_entries = 0;          // composite keys in all tile slots together
     uint32_t n_slot_groups = 0;
     bool any_large = false;
-    bool big_map_layers = false;        // some layer of a million elements or more is ranked on the full map
+    std::vector<uint16_t> big_map_layers;   // layers of a million elements or more that are ranked on the full map
     int64_t total_elems = 0;
     int64_t out_capacity = 0;
     int64_t centre_capacity = 0;

@@ -815,22 +815,42 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             if (halo_thread) tile[hrow * PITCH + (hc < H ? PADL - 1 - hc : PADL + kTileCols + (hc - H))] = rh + gh;
         } else {
             if (FEED) feed.stash(feed_slot);
-            for (int s = tid; s < ROWS * PITCH; s += 256) {
-                const int rr = s / PITCH, j = s - rr * PITCH;
-                const int x = x0 - H + rr, y = y0 - PADL + j;
-                float v = 0.f;
-                if (x >= 0 && x < R && y >= 0 && y < C) {
-                    const size_t off = static_cast<size_t>(x) * C + y;
-                    const bool own = rr >= H && rr < H + kTileRows && j >= PADL && j < PADL + kTileCols;
-                    float gu = g[off];
-                    if (MOM) {
-                        gu = __fmul_rn(a.m, a.mom[L.elem_off + off]) + gu;
-                        if (STORE_V && a.mom_out && whole && own) a.mom_out[L.elem_off + off] = gu;
+            // rows that are no multiple of 16 bytes long: a wave takes whole rows, all of a row's floats requested before any is used
+            // (split flat over the threads, every float waited for the one before and cost a division: 16 us for a tile of 22 rows)
+            constexpr int N = (PITCH + 63) / 64;
+            const int wave = tid >> 6, lane = tid & 63;
+#pragma unroll 1
+            for (int rr = wave; rr < ROWS; rr += 4) {
+                const int x = x0 - H + rr;
+                const size_t row = static_cast<size_t>(max(x, 0)) * C;
+                float gq[N], rq[N], uq[MOM ? N : 1];
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    const int j = lane + 64 * q, y = y0 - PADL + j;
+                    gq[q] = rq[q] = 0.f;
+                    if (MOM) uq[q] = 0.f;
+                    if (x >= 0 && x < R && j < PITCH && y >= 0 && y < C) {
+                        gq[q] = (g + row)[y];
+                        if (r) rq[q] = (r + row)[y];
+                        if (MOM) uq[q] = (a.mom + L.elem_off + row)[y];
                     }
-                    v = (r ? r[off] : 0.f) + gu;
-                    if (STORE_V && a.v_out && whole && own) a.v_out[L.elem_off + off] = v;
                 }
-                tile[s] = v;
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    const int j = lane + 64 * q, y = y0 - PADL + j;
+                    float v = 0.f;
+                    if (x >= 0 && x < R && j < PITCH && y >= 0 && y < C) {
+                        const bool own = rr >= H && rr < H + kTileRows && j >= PADL && j < PADL + kTileCols;
+                        float gu = gq[q];
+                        if (MOM) {
+                            gu = __fmul_rn(a.m, uq[q]) + gu;
+                            if (STORE_V && a.mom_out && whole && own) (a.mom_out + L.elem_off + row)[y] = gu;
+                        }
+                        v = rq[q] + gu;
+                        if (STORE_V && a.v_out && whole && own) (a.v_out + L.elem_off + row)[y] = v;
+                    }
+                    if (j < PITCH) tile[rr * PITCH + j] = v;
+                }
             }
         }
         __syncthreads();
@@ -1803,7 +1823,15 @@ constexpr int kFilterSplit = 32;
 constexpr int kFilterThreads = 1024;
 constexpr int kList2Cap = 2048;          // == kStage: what k_finish can hold in LDS
 
-__global__ __launch_bounds__(kFilterThreads) void k_filter(const LayerDev *__restrict__ layers,
+// The layers come as a list (161 layers of which nine are meant: 5152 workgroups of 1024 threads that nearly all leave at once
+// took 16 us); beyond kFilterLayers of them every layer gets its workgroups.
+constexpr int kFilterLayers = 256;
+struct FilterLayers {
+    uint32_t listed;
+    uint16_t id[kFilterLayers];
+};
+
+__global__ __launch_bounds__(kFilterThreads) void k_filter(const FilterLayers fl, const LayerDev *__restrict__ layers,
                                                            const SelState *__restrict__ state,
                                                            const uint32_t *__restrict__ hist1,
                                                            const uint32_t *__restrict__ list_cnt,
@@ -1815,7 +1843,8 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter(const LayerDev *__res
     __shared__ uint32_t wave_tot[kFilterThreads / 64];
     __shared__ DigitResult res;
     __shared__ uint32_t nstage, base_pos;
-    const int l = blockIdx.x / kFilterSplit, part = blockIdx.x % kFilterSplit, tid = threadIdx.x;
+    const int part = blockIdx.x % kFilterSplit, tid = threadIdx.x;
+    const int l = fl.listed ? fl.id[blockIdx.x / kFilterSplit] : blockIdx.x / kFilterSplit;
     // lane s of every wave reads shard s's counter (unused shards stay 0); issued with the other loads
     const uint32_t *__restrict__ cnt = list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
     const uint32_t c = (tid & 63) < kListShards ? cnt[(tid & 63) * kListCntStride] : 0u;
@@ -2814,21 +2843,40 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
                 }
             }
         } else {
-            for (int s = tid; s < TR * TC; s += 256) {
-                const int rr = s / TC, j = s - rr * TC;
-                const int x = x0 + rr, y = y0 + j;
-                float v = 0.f;
-                if (x < R && y < C) {
-                    const size_t off = static_cast<size_t>(x) * C + y;
-                    float gu = g[off];
-                    if (MOM) {
-                        gu = __fmul_rn(m, ui[off]) + gu;
-                        uo[off] = gu;
+            // (whole rows per wave, all of a row's floats requested together, as in the NSI passes)
+            constexpr int N = (TC + 63) / 64;
+            const int wave = tid >> 6, lane = tid & 63;
+#pragma unroll 1
+            for (int rr = wave; rr < TR; rr += 4) {
+                const int x = x0 + rr;
+                const size_t row = static_cast<size_t>(x) * C;
+                float gq[N], rq[N], uq[MOM ? N : 1];
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    const int j = lane + 64 * q, y = y0 + j;
+                    gq[q] = rq[q] = 0.f;
+                    if (MOM) uq[q] = 0.f;
+                    if (x < R && j < TC && y < C) {
+                        gq[q] = (g + row)[y];
+                        rq[q] = (r + row)[y];
+                        if (MOM) uq[q] = (ui + row)[y];
                     }
-                    v = r[off] + gu;
-                    vo[off] = v;
                 }
-                tile[s] = v;
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    const int j = lane + 64 * q, y = y0 + j;
+                    float v = 0.f;
+                    if (x < R && j < TC && y < C) {
+                        float gu = gq[q];
+                        if (MOM) {
+                            gu = __fmul_rn(m, uq[q]) + gu;
+                            (uo + row)[y] = gu;
+                        }
+                        v = rq[q] + gu;
+                        (vo + row)[y] = v;
+                    }
+                    if (j < TC) tile[rr * TC + j] = v;
+                }
             }
         }
         __syncthreads();
@@ -3918,9 +3966,14 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         }
         uint32_t *list2_cnt = reinterpret_cast<uint32_t *>(ws + w.list2_cnt);
         unsigned long long *list2_ent = reinterpret_cast<unsigned long long *>(ws + w.list2_ent);
-        if (plan->big_map_layers)          // long threshold-bucket lists: many workgroups pick the keys k_finish needs
-            hipLaunchKernelGGL(k_filter, dim3(L * kFilterSplit), dim3(kFilterThreads), 0, stream, layers, state,
-                               a.hist1, a.list_cnt, a.list_ent, list2_cnt, list2_ent);
+        if (!plan->big_map_layers.empty()) {   // long threshold-bucket lists: many workgroups pick the keys k_finish needs
+            FilterLayers fl = {};
+            const size_t n_big = plan->big_map_layers.size();
+            fl.listed = n_big <= static_cast<size_t>(kFilterLayers);
+            if (fl.listed) std::copy(plan->big_map_layers.begin(), plan->big_map_layers.end(), fl.id);
+            hipLaunchKernelGGL(k_filter, dim3((fl.listed ? static_cast<uint32_t>(n_big) : static_cast<uint32_t>(L)) * kFilterSplit),
+                               dim3(kFilterThreads), 0, stream, fl, layers, state, a.hist1, a.list_cnt, a.list_ent, list2_cnt, list2_ent);
+        }
         hipLaunchKernelGGL(k_finish, dim3(L), dim3(kFinishThreads), 0, stream, layers, state, hist, a.hist1,
                            a.list_cnt, a.list_ent, a.keys, slot_cnt, slot_ent, list2_cnt, list2_ent, pred);
     }

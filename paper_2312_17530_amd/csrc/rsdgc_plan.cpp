@@ -36,7 +36,7 @@ int build_tables(rsdgc_plan_s *plan) {
     plan->map_chunks.clear();
     plan->map_tiles.clear();
     plan->any_large = false;
-    plan->big_map_layers = false;
+    plan->big_map_layers.clear();
 
     int64_t elem_off = 0, out_off = 0, centre_off = 0;
     uint32_t chunk_begin = 0, tile_begin_all = 0, group_begin = 0, cgroup_begin = 0;
@@ -112,7 +112,7 @@ int build_tables(rsdgc_plan_s *plan) {
         slot_off += static_cast<uint64_t>(d.n_tiles) * d.slot_cap;
         d.hint_target = d.large ? static_cast<uint32_t>(std::ceil(want + 4.0 * std::sqrt(want) + 8.0)) : 0u;
         plan->any_large = plan->any_large || d.large;
-        plan->big_map_layers = plan->big_map_layers || (!d.large && k > 0 && G >= kBigMapLayer);
+        if (!d.large && k > 0 && G >= kBigMapLayer) plan->big_map_layers.push_back(static_cast<uint16_t>(l));   // (l < 65536)
 
         plan->chunk_dir.push_back(DirEntry{chunk_begin, static_cast<uint32_t>(l)});
         plan->all_tile_dir.push_back(DirEntry{tile_begin_all, static_cast<uint32_t>(l)});

@@ -137,3 +137,40 @@ def test_every_call_leaves_the_workspace_ready_for_the_next(p):
                 assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
                 assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
     assert (False, 3) in paths and (True, 1) in paths and (False, 2) in paths
+
+
+@pytest.mark.parametrize("p", [1, 3, 5, 7])
+def test_rows_of_odd_length_in_every_pass(p):
+    """Layers whose rows are no multiple of 16 bytes, around the 256 columns and the neighbouring columns of a tile: the main pass, the
+    score-map pass (a ratio beyond the candidate path's), with momentum, and the block reading, against the oracle."""
+    from paper_2312_17530_amd.session import BlockSession, Session
+    shapes = [(20, 255), (17, 257), (33, 259), (5, 513), (64, 27), (40, 147), (2, 1021)]
+    rng = np.random.default_rng(100 + p)
+    grads = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+    resid = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+    mom = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+    for m in (None, 0.9):
+        u = mom if m is not None else [np.zeros(sh, np.float32) for sh in shapes]
+        for rho in (0.02, 0.9):
+            s = Session(shapes, p, 0.5, [rho] * len(shapes), momentum=m)
+            s.set_grad(grads)
+            s.set_residual(resid)
+            if m is not None:
+                s.set_momentum(u)
+            s.compress()
+            after = s.unpack(s.residual)
+            for l, (idx, val, _, _) in enumerate(s.results()):
+                o = oracle.compress_layer_momentum(grads[l], u[l], resid[l], m or 0.0, p, 0.5, rho).layer
+                assert np.array_equal(idx, o.idx) and np.array_equal(_bits(val), _bits(o.val)), (m, rho, l)
+                assert np.array_equal(_bits(after[l]), _bits(o.r_new)), (m, rho, l)
+        b = BlockSession(shapes, p, 0.5, [0.05] * len(shapes), momentum=m)
+        b.set_grad(grads)
+        b.set_residual(resid)
+        if m is not None:
+            b.set_momentum(u)
+        b.compress()
+        after = b.unpack(b.residual)
+        for l, (blocks, val) in enumerate(b.results()):
+            o = oracle.compress_layer_blocks_momentum(grads[l], u[l], resid[l], m or 0.0, p, 0.5, 0.05).layer
+            assert np.array_equal(blocks, o.blocks) and np.array_equal(_bits(val), _bits(np.asarray(o.val).reshape(-1))), (m, l)
+            assert np.array_equal(_bits(after[l]), _bits(o.r_new)), (m, l)
