@@ -1952,7 +1952,9 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
     __shared__ uint32_t wave_tot[kFinishWaves];
     __shared__ DigitResult res;
     __shared__ uint32_t nstage;
+    __shared__ unsigned long long rank_key;
     const int l = blockIdx.x, tid = threadIdx.x;
+    if (tid == 0) rank_key = 0ull;
     // lane s of every wave reads shard s's counter (unused shards stay 0); issued with the other loads
     const uint32_t *__restrict__ cnt = list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
     const uint32_t c = (tid & 63) < kListShards ? cnt[(tid & 63) * kListCntStride] : 0u;
@@ -2024,6 +2026,24 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
         const bool staged = nsel <= static_cast<uint32_t>(kStage);
         unsigned long long Trel = 0;
         int shift_prev = top;
+        if (nsel <= 64u) {
+            // The usual case: a lane per key counts the larger ones (all keys differ); the one with k_rem - 1 of them is the
+            // threshold.  (Digit by digit that took up to twenty barriers of sixteen waves: 11.4 us on VGG-19, now 9.7.)
+            if (tid < 64) {
+                const unsigned long long own = static_cast<uint32_t>(tid) < nsel ? sel[tid] : 0ull;
+                uint32_t larger = 0;
+                for (uint32_t j = 0; j < nsel; ++j) {
+                    const unsigned long long o = static_cast<unsigned long long>(__builtin_amdgcn_readlane(static_cast<uint32_t>(own >> 32), j)) << 32 |
+                                                 static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(own), j));
+                    larger += o > own ? 1u : 0u;
+                }
+                if (static_cast<uint32_t>(tid) < nsel && larger == k_rem - 1u) rank_key = own;
+            }
+            __syncthreads();
+            Trel = rank_key;               // (1 <= k_rem <= nsel: the digit's count, as histogram and list agree)
+            k_rem = 1;
+            done = true;
+        }
 #pragma unroll 1
         for (int lv = 0; lv < 4 && !done; ++lv) {
             const int shift = lv == 0 ? 32 : lv == 1 ? 21 : lv == 2 ? 10 : 0;
