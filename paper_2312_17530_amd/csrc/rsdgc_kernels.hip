@@ -2714,26 +2714,73 @@ __global__ __launch_bounds__(256) void k_zero_layers(const ChunkInfo *__restrict
     }
 }
 
+// Pairs of a layer in one message, whatever the message says.
+__device__ __forceinline__ uint32_t pairs_in_segment(int32_t count, uint32_t cap) {
+    return static_cast<uint32_t>(min(max(count, 0), static_cast<int32_t>(min(cap, 0x7fffffffu))));
+}
+
+// f(arena position, value) for the pairs of a message that are to be taken: kScatterPairs consecutive positions per workgroup.  Nearly
+// always they lie in one layer's segment: its constants are looked up once, by the whole workgroup, and every thread's pairs are
+// requested together.  (A search per thread, then the pair: 20.0 us for VGG-19's 2.3 M pairs, now 17.5 us.)
+constexpr int kScatterPairs = 1024;
+template <typename F>
+__device__ __forceinline__ void for_each_pair(const LayerDev *__restrict__ layers, int n_layers, long long capacity,
+                                              const uint32_t *__restrict__ idx, const float *__restrict__ val,
+                                              const int32_t *__restrict__ counts, F f) {
+    constexpr int N = kScatterPairs / 256;
+    const long long j0 = static_cast<long long>(blockIdx.x) * kScatterPairs;
+    auto layer_of = [&](long long j) {    // last layer whose segment starts at or before j
+        int lo = 0, hi = n_layers;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (layers[mid].out_off <= j) lo = mid; else hi = mid;
+        }
+        return lo;
+    };
+    const int lo = layer_of(j0);
+    const LayerDev &L = layers[lo];
+    const long long end = lo + 1 < n_layers ? layers[lo + 1].out_off : capacity;
+    if (j0 + kScatterPairs <= end) {       // uniform
+        const uint32_t n = pairs_in_segment(counts[lo], L.cap), G = L.G;
+        const size_t elem_off = static_cast<size_t>(L.elem_off);
+        const uint32_t q0 = static_cast<uint32_t>(j0 - L.out_off) + threadIdx.x;
+        uint32_t i[N];
+        float v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            i[u] = 0xffffffffu;
+            v[u] = 0.f;
+            if (q0 + 256u * u < n) {
+                i[u] = idx[j0 + threadIdx.x + 256 * u];
+                v[u] = val[j0 + threadIdx.x + 256 * u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (i[u] < G) f(elem_off + i[u], v[u]);          // (malformed message: the pair is ignored; G < 2^32)
+    } else {
+#pragma unroll 1
+        for (int u = 0; u < N; ++u) {
+            const long long j = j0 + threadIdx.x + 256 * u;
+            if (j >= capacity) return;
+            const int l = layer_of(j);
+            const long long q = j - layers[l].out_off;
+            if (q >= counts[l] || q >= static_cast<long long>(layers[l].cap)) continue;
+            const uint32_t i = idx[j];
+            if (i < layers[l].G) f(static_cast<size_t>(layers[l].elem_off) + i, val[j]);
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_scatter(const LayerDev *__restrict__ layers, int n_layers,
                                                  long long capacity,
                                                  const uint32_t *__restrict__ idx,
                                                  const float *__restrict__ val,
                                                  const int32_t *__restrict__ counts,
                                                  float *__restrict__ dense, int accumulate) {
-    const long long j = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
-    if (j >= capacity) return;
-    int lo = 0, hi = n_layers;            // last layer whose segment starts at or before j
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (layers[mid].out_off <= j) lo = mid; else hi = mid;
-    }
-    const LayerDev L = layers[lo];
-    const long long q = j - L.out_off;
-    if (q >= counts[lo] || q >= static_cast<long long>(L.cap)) return;
-    const uint32_t i = idx[j];
-    if (i >= L.G) return;                 // malformed message: ignore the pair
-    float *d = dense + L.elem_off + i;
-    if (accumulate) *d = *d + val[j]; else *d = val[j];
+    for_each_pair(layers, n_layers, capacity, idx, val, counts, [&](size_t pos, float v) {
+        if (accumulate) dense[pos] = dense[pos] + v; else dense[pos] = v;
+    });
 }
 
 // --------------------------------------------------------- block reading --
@@ -3085,11 +3132,6 @@ __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t *__restrict__
     return lo;
 }
 
-// Pairs of a layer in one message, whatever the message says.
-__device__ __forceinline__ uint32_t pairs_in_segment(int32_t count, uint32_t cap) {
-    return static_cast<uint32_t>(min(max(count, 0), static_cast<int32_t>(min(cap, 0x7fffffffu))));
-}
-
 // starts[k * 2 n_chunks + 2 c + s]: first pair of message k in its layer's segment that falls into
 // half s of chunk c, or later (a short last chunk's second half: the number of pairs).
 // VGG-19, eight messages: 22 us with two binary searches per chunk, 20 us for twice the stretches; filling the
@@ -3211,21 +3253,10 @@ __global__ __launch_bounds__(256) void k_apply_single(const LayerDev *__restrict
                                                       const float *__restrict__ val,
                                                       const int32_t *__restrict__ counts,
                                                       float *__restrict__ weights, float eta) {
-    const long long j = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
-    if (j >= capacity) return;
-    int lo = 0, hi = n_layers;            // last layer whose segment starts at or before j
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (layers[mid].out_off <= j) lo = mid; else hi = mid;
-    }
-    const LayerDev L = layers[lo];
-    const long long q = j - L.out_off;
-    if (q >= counts[lo] || q >= static_cast<long long>(L.cap)) return;
-    const uint32_t i = idx[j];
-    if (i >= L.G) return;                 // malformed message: ignore the pair
-    const float sum = 0.f + val[j];       // (the sum of one message, formed like any other: +0 + val)
-    const size_t pos = static_cast<size_t>(L.elem_off) + i;
-    if (__float_as_uint(sum) != 0u) weights[pos] = weights[pos] - __fmul_rn(eta, sum);
+    for_each_pair(layers, n_layers, capacity, idx, val, counts, [&](size_t pos, float v) {
+        const float sum = 0.f + v;        // (the sum of one message, formed like any other: +0 + val)
+        if (__float_as_uint(sum) != 0u) weights[pos] = weights[pos] - __fmul_rn(eta, sum);
+    });
 }
 
 // Block messages (the block reading): one thread per kept block of every message.  The block
@@ -4417,7 +4448,7 @@ int rsdgc_apply(rsdgc_plan_t *plan, int32_t n_msgs, const uint32_t *const *idx,
     const LayerDev *layers = reinterpret_cast<const LayerDev *>(ws + plan->ws.layers);
     if (plan->out_capacity == 0) return RSDGC_OK;      // no message can hold a pair
     if (n_msgs == 1) {
-        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + 255) / 256);
+        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + kScatterPairs - 1) / kScatterPairs);
         hipLaunchKernelGGL(k_apply_single, dim3(blocks), dim3(256), 0, stream, layers, plan->n_layers,
                            static_cast<long long>(plan->out_capacity), idx[0], val[0], counts[0], weights, eta);
         HIP_TRY(hipGetLastError());
@@ -4668,7 +4699,7 @@ int rsdgc_decompress(rsdgc_plan_t *plan, const uint32_t *idx, const float *val,
         hipLaunchKernelGGL(k_zero_layers, dim3(plan->n_chunks), dim3(256), 0, stream,
                            reinterpret_cast<const ChunkInfo *>(ws + plan->ws.chunk_info), dense);
     if (plan->out_capacity > 0) {
-        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + 255) / 256);
+        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + kScatterPairs - 1) / kScatterPairs);
         hipLaunchKernelGGL(k_scatter, dim3(blocks), dim3(256), 0, stream, layers, plan->n_layers,
                            static_cast<long long>(plan->out_capacity), idx, val, counts, dense,
                            accumulate);

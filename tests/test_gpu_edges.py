@@ -139,6 +139,42 @@ def test_every_call_leaves_the_workspace_ready_for_the_next(p):
     assert (False, 3) in paths and (True, 1) in paths and (False, 2) in paths
 
 
+@pytest.mark.parametrize("share", [0.001, 0.4, 1.0])
+def test_one_message_at_the_edges_of_a_workgroups_pairs(share):
+    """Segments shorter than, exactly as long as and longer than the 1024 positions a workgroup takes, empty layers between
+    them, pairs in any order: decompressed (overwriting and adding) and applied; the padding keeps its values."""
+    import torch
+    shapes = [(1, 5), (1, 1023), (1, 1024), (4, 4), (1, 1025), (32, 64), (3, 4099), (1, 1), (64, 100), (50, 333)]
+    G = [r * c for r, c in shapes]
+    plan = binding.rsdgc_plan(shapes, 1, 0.5, [0.0 if l in (3, 7) else 1.0 for l in range(len(G))])
+    ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    rng = np.random.default_rng(int(share * 1000))
+    idx = np.zeros(plan.out_capacity, np.uint32)
+    val = np.zeros(plan.out_capacity, np.float32)
+    counts, host = np.zeros(len(G), np.int32), []
+    for l, g in enumerate(G):
+        cap = plan.layer_k(l)
+        i = rng.permutation(g)[:int(np.ceil(share * cap))].astype(np.uint32)
+        v = rng.standard_normal(i.size).astype(np.float32)
+        o = plan.out_offset(l)
+        idx[o:o + i.size], val[o:o + i.size], counts[l] = i, v, i.size
+        host.append((i, v))
+    msg = (_dev(idx.view(np.int32)), _dev(val), _dev(counts))
+    base = rng.standard_normal(plan.total_elems).astype(np.float32)
+    dense, added, w = _dev(base), _dev(base), _dev(base)
+    binding.rsdgc_decompress(plan, *msg, dense, False, ws)
+    binding.rsdgc_decompress(plan, *msg, added, True, ws)
+    binding.rsdgc_apply(plan, [msg], w, 0.05, ws)
+    want = [base.copy(), base.copy(), base.copy()]
+    for l, g in enumerate(G):
+        o, (i, v) = plan.layer_offset(l), host[l]
+        want[0][o:o + g] = oracle.decompress(i, v, g)
+        want[1][o + i] += v
+        want[2][o:o + g] = oracle.apply_messages(base[o:o + g].reshape(1, g), [(i, v)], 0.05).reshape(-1)
+    for got, x in zip((dense, added, w), want):
+        assert np.array_equal(_bits(got.cpu().numpy()), _bits(x))
+
+
 @pytest.mark.parametrize("p", [1, 3, 5, 7])
 def test_rows_of_odd_length_in_every_pass(p):
     """Layers whose rows are no multiple of 16 bytes, around the 256 columns and the neighbouring columns of a tile: the main pass, the
