@@ -2694,12 +2694,14 @@ __global__ __launch_bounds__(256) void k_emit_centres(const LayerDev *__restrict
 
 // ----------------------------------------------------------- decompress --
 // +0 into every element of every layer (the padding between layers is left alone): one chunk
-// per workgroup, streaming 16-byte stores.  Each XCD writes one contiguous part: 103 -> 93 us for VGG-19's 559 MB (a fill
-// of 16 bytes per thread that need not look up its chunk takes 83 us; without streaming stores 130 us here, and the
-// scatter that follows 30 instead of 20 us).
+// per workgroup, streaming 16-byte stores.  In a large arena each XCD writes one contiguous part: 103 -> 93 us for VGG-19's
+// 559 MB (a fill of 16 bytes per thread that need not look up its chunk takes 83 us; without streaming stores 130 us here, and
+// the scatter that follows 30 instead of 20 us).  Whole calls by parts / without, one layer of so many MB: 33: 11.0 / 10.5 us,
+// 67: 17.1 / 15.8, 100: 22.9 / 22.9, 150: 32.9 / 33.4, 218: 45.8 / 47.8, 268: 54.4 / 56.9, 470: 91.2 / 98.8.
+constexpr uint32_t kZeroByParts = 4096;   // chunks of an arena (134 MB) from which the XCDs take parts
 __global__ __launch_bounds__(256) void k_zero_layers(const ChunkInfo *__restrict__ chunk_info, float *__restrict__ dense) {
     const int tid = threadIdx.x;
-    const ChunkInfo ci = chunk_info[xcd_contiguous(blockIdx.x, gridDim.x)];
+    const ChunkInfo ci = chunk_info[gridDim.x >= kZeroByParts ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x];
     const uint32_t len = ci.len;
     float *__restrict__ d = dense + ci.arena_off;
 #pragma unroll
@@ -2719,56 +2721,50 @@ __device__ __forceinline__ uint32_t pairs_in_segment(int32_t count, uint32_t cap
     return static_cast<uint32_t>(min(max(count, 0), static_cast<int32_t>(min(cap, 0x7fffffffu))));
 }
 
-// f(arena position, value) for the pairs of a message that are to be taken: kScatterPairs consecutive positions per workgroup.  Nearly
-// always they lie in one layer's segment: its constants are looked up once, by the whole workgroup, and every thread's pairs are
-// requested together.  (A search per thread, then the pair: 20.0 us for VGG-19's 2.3 M pairs, now 17.5 us.)
-constexpr int kScatterPairs = 1024;
+// f(arena position, value) for the pairs of a message that are to be taken: one position per thread.  Nearly always a wave's 64
+// positions lie in one layer's segment: the wave looks that up once, 64 layers at a time, and its constants stay in scalar
+// registers.  (A binary search by every thread: 20.0 us for VGG-19's 2.3 M pairs, now 15.8; ResNet-18 with few pairs 3.2, now
+// 3.4.  Four pairs per thread: 16.7 and 4.8, two: 15.1 and 3.6.)
 template <typename F>
 __device__ __forceinline__ void for_each_pair(const LayerDev *__restrict__ layers, int n_layers, long long capacity,
                                               const uint32_t *__restrict__ idx, const float *__restrict__ val,
                                               const int32_t *__restrict__ counts, F f) {
-    constexpr int N = kScatterPairs / 256;
-    const long long j0 = static_cast<long long>(blockIdx.x) * kScatterPairs;
-    auto layer_of = [&](long long j) {    // last layer whose segment starts at or before j
-        int lo = 0, hi = n_layers;
+    const int lane = threadIdx.x & 63;
+    const long long j0 = static_cast<long long>(blockIdx.x) * 256 + 64 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (j0 >= capacity) return;            // (the whole wave)
+    const long long j = j0 + lane;
+    // last layer of [lo, hi) whose segment starts at or before `at`, by the whole wave
+    auto layer_of = [&](long long at, int lo, int hi) {
         while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (layers[mid].out_off <= j) lo = mid; else hi = mid;
+            const int step = (hi - lo + 63) >> 6, l = lo + lane * step;
+            const bool starts = l < hi && layers[l].out_off <= at;          // (true in lane 0)
+            lo += (__popcll(__ballot(starts)) - 1) * step;
+            hi = min(hi, lo + step);
         }
         return lo;
     };
-    const int lo = layer_of(j0);
+    const int lo = layer_of(j0, 0, n_layers);
     const LayerDev &L = layers[lo];
     const long long end = lo + 1 < n_layers ? layers[lo + 1].out_off : capacity;
-    if (j0 + kScatterPairs <= end) {       // uniform
+    if (j0 + 64 <= end) {
         const uint32_t n = pairs_in_segment(counts[lo], L.cap), G = L.G;
-        const size_t elem_off = static_cast<size_t>(L.elem_off);
-        const uint32_t q0 = static_cast<uint32_t>(j0 - L.out_off) + threadIdx.x;
-        uint32_t i[N];
-        float v[N];
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            i[u] = 0xffffffffu;
-            v[u] = 0.f;
-            if (q0 + 256u * u < n) {
-                i[u] = idx[j0 + threadIdx.x + 256 * u];
-                v[u] = val[j0 + threadIdx.x + 256 * u];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-            if (i[u] < G) f(elem_off + i[u], v[u]);          // (malformed message: the pair is ignored; G < 2^32)
-    } else {
-#pragma unroll 1
-        for (int u = 0; u < N; ++u) {
-            const long long j = j0 + threadIdx.x + 256 * u;
-            if (j >= capacity) return;
-            const int l = layer_of(j);
-            const long long q = j - layers[l].out_off;
-            if (q >= counts[l] || q >= static_cast<long long>(layers[l].cap)) continue;
+        if (static_cast<uint32_t>(j - L.out_off) < n) {
             const uint32_t i = idx[j];
-            if (i < layers[l].G) f(static_cast<size_t>(layers[l].elem_off) + i, val[j]);
+            const float v = val[j];
+            if (i < G) f(static_cast<size_t>(L.elem_off) + i, v);           // (malformed message: the pair is ignored; G < 2^32)
         }
+    } else {
+        const int last = layer_of(min(j0 + 64, capacity) - 1, lo, n_layers);
+        if (j >= capacity) return;
+        int l = lo, hi = last + 1;
+        while (hi - l > 1) {
+            const int mid = (l + hi) >> 1;
+            if (layers[mid].out_off <= j) l = mid; else hi = mid;
+        }
+        const long long q = j - layers[l].out_off;
+        if (q >= counts[l] || q >= static_cast<long long>(layers[l].cap)) return;
+        const uint32_t i = idx[j];
+        if (i < layers[l].G) f(static_cast<size_t>(layers[l].elem_off) + i, val[j]);
     }
 }
 
@@ -4448,7 +4444,7 @@ int rsdgc_apply(rsdgc_plan_t *plan, int32_t n_msgs, const uint32_t *const *idx,
     const LayerDev *layers = reinterpret_cast<const LayerDev *>(ws + plan->ws.layers);
     if (plan->out_capacity == 0) return RSDGC_OK;      // no message can hold a pair
     if (n_msgs == 1) {
-        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + kScatterPairs - 1) / kScatterPairs);
+        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + 255) / 256);
         hipLaunchKernelGGL(k_apply_single, dim3(blocks), dim3(256), 0, stream, layers, plan->n_layers,
                            static_cast<long long>(plan->out_capacity), idx[0], val[0], counts[0], weights, eta);
         HIP_TRY(hipGetLastError());
@@ -4699,7 +4695,7 @@ int rsdgc_decompress(rsdgc_plan_t *plan, const uint32_t *idx, const float *val,
         hipLaunchKernelGGL(k_zero_layers, dim3(plan->n_chunks), dim3(256), 0, stream,
                            reinterpret_cast<const ChunkInfo *>(ws + plan->ws.chunk_info), dense);
     if (plan->out_capacity > 0) {
-        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + kScatterPairs - 1) / kScatterPairs);
+        const unsigned blocks = static_cast<unsigned>((plan->out_capacity + 255) / 256);
         hipLaunchKernelGGL(k_scatter, dim3(blocks), dim3(256), 0, stream, layers, plan->n_layers,
                            static_cast<long long>(plan->out_capacity), idx, val, counts, dense,
                            accumulate);

@@ -139,12 +139,14 @@ def test_every_call_leaves_the_workspace_ready_for_the_next(p):
     assert (False, 3) in paths and (True, 1) in paths and (False, 2) in paths
 
 
-@pytest.mark.parametrize("share", [0.001, 0.4, 1.0])
-def test_one_message_at_the_edges_of_a_workgroups_pairs(share):
-    """Segments shorter than, exactly as long as and longer than the 1024 positions a workgroup takes, empty layers between
-    them, pairs in any order: decompressed (overwriting and adding) and applied; the padding keeps its values."""
+@pytest.mark.parametrize("share,more", [(0.001, 0), (0.4, 0), (1.0, 0), (1.0, 55), (0.4, 4200)])
+def test_one_message_at_the_edges_of_a_waves_pairs(share, more):
+    """Segments shorter than, exactly as long as and longer than the 64 positions a wave takes, empty layers between them, 64
+    layers and fewer and more than 64 * 64, pairs in any order: decompressed (overwriting and adding) and applied; the padding
+    keeps its values."""
     import torch
-    shapes = [(1, 5), (1, 1023), (1, 1024), (4, 4), (1, 1025), (32, 64), (3, 4099), (1, 1), (64, 100), (50, 333)]
+    shapes = [(1, 5), (1, 1023), (1, 64), (4, 4), (1, 65), (32, 64), (3, 4099), (1, 1), (64, 100), (50, 333)]
+    shapes += [(1, 1 + 7 * l % 130) for l in range(more)]
     G = [r * c for r, c in shapes]
     plan = binding.rsdgc_plan(shapes, 1, 0.5, [0.0 if l in (3, 7) else 1.0 for l in range(len(G))])
     ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
