@@ -818,9 +818,13 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             // rows that are no multiple of 16 bytes long: a wave takes whole rows, all of a row's floats requested before any is used
             // (split flat over the threads, every float waited for the one before and cost a division: 16 us for a tile of 22 rows)
             constexpr int N = (PITCH + 63) / 64;
-            const int wave = tid >> 6, lane = tid & 63;
+            const int wave = tid >> 6;
 #pragma unroll 1
             for (int rr = wave; rr < ROWS; rr += 4) {
+                // (the columns' masks are worked out row by row: held over the rows they cost the pass its scalar registers, and
+                // 4 of 234 us with p = 5 on 103 M elements whose rows never come here)
+                int lane = tid & 63;
+                asm("" : "+v"(lane));
                 const int x = x0 - H + rr;
                 const size_t row = static_cast<size_t>(max(x, 0)) * C;
                 float gq[N], rq[N], uq[MOM ? N : 1];
