@@ -1415,9 +1415,11 @@ __global__ __launch_bounds__(256) void k_find0_fallback_all(const Find0Args f, c
 constexpr int kStage = 2048;            // staged keys per workgroup (a round adds at most 1024)
 constexpr int kSlotsPerWave = kSlotGroup / 4;   // tile slots of a group that one wave of a gather workgroup takes
 // Small plans: a workgroup takes a quarter of a group.  Their gather is one short chain per workgroup -- entry, slots, marks,
-// words -- on a chip that is mostly idle, and four workgroups get through it in less time than one (12.3 -> 8.2 us for a
-// 512 x 512 layer, 13.0 -> 10.4 us on resnet18); on a large plan the words that neighbouring groups share, and their atomics, weigh more.
+// words -- on a chip that is mostly idle, and four workgroups get through it in less time than one.  Where all of them no longer
+// are resident at once, the words that neighbours share, and their atomics, weigh more.  By groups, whole / quarters:
+// resnet18 13.7 / 10.1 us, 256 groups 16.8 / 12.4, resnet50 (377) 19.6 / 18.3, 512 groups 18.4 / 20.7 and with p = 1 12.4 / 17.5.
 constexpr int kSlotParts = 4;
+constexpr uint32_t kSplitGroups = 512;  // groups from which a workgroup takes a whole one
 
 constexpr int kTileMaskWords = kTileRows * kTileCols / 32;    // mask words of one tile (rows of 8 words)
 constexpr int kGatherCountSlots = 64;                          // chunks a group of tiles counts for in LDS (the rest: directly)
@@ -1499,7 +1501,7 @@ __device__ __forceinline__ void gather_stage_key(GatherShared &sh, bool hit, uns
     }
 }
 
-template <bool COUNT>
+template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1509,7 +1511,6 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
                                                               : blockIdx.x - gl.n_map_wgs - gl.n_slot_wgs;
     const uint32_t stride = role == 0 ? gl.n_map_wgs : role == 1 ? gl.n_slot_wgs
                                                                  : gridDim.x - gl.n_map_wgs - gl.n_slot_wgs;
-    constexpr uint32_t PARTS = COUNT ? kSlotParts : 1;           // workgroups per group of slots
     constexpr uint32_t SLOTS = kSlotGroup / PARTS;
     const uint32_t n_items = role == 0 ? gl.n_map_chunks : role == 1 ? gl.n_cand_groups * PARTS : gl.n_chunks;
     const DirEntry *__restrict__ dir = gl.chunk_dir;
@@ -4007,13 +4008,15 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         gl.n_map_chunks = static_cast<uint32_t>(plan->map_chunks.size());
         gl.n_cand_groups = n_cand_groups;
         gl.n_map_wgs = std::min<uint32_t>(gl.n_map_chunks, kNumCUs * 4u);
-        gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (inline_count ? kSlotParts : 1u), kNumCUs * 8u);
+        const bool split = inline_count && n_cand_groups < kSplitGroups;
+        gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (split ? kSlotParts : 1u), kNumCUs * 8u);
         const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u;
         if (gl.n_map_wgs + gl.n_slot_wgs + n_fb_wgs > 0)
         {
             const dim3 grid(gl.n_map_wgs + gl.n_slot_wgs + n_fb_wgs);
-            if (inline_count) hipLaunchKernelGGL(k_gather<true>, grid, dim3(256), 0, stream, a, gl);
-            else hipLaunchKernelGGL(k_gather<false>, grid, dim3(256), 0, stream, a, gl);
+            if (split) hipLaunchKernelGGL((k_gather<true, kSlotParts>), grid, dim3(256), 0, stream, a, gl);
+            else if (inline_count) hipLaunchKernelGGL((k_gather<true, 1>), grid, dim3(256), 0, stream, a, gl);
+            else hipLaunchKernelGGL((k_gather<false, 1>), grid, dim3(256), 0, stream, a, gl);
         }
         uint32_t *list2_cnt = reinterpret_cast<uint32_t *>(ws + w.list2_cnt);
         unsigned long long *list2_ent = reinterpret_cast<unsigned long long *>(ws + w.list2_ent);

@@ -212,3 +212,30 @@ def test_rows_of_odd_length_in_every_pass(p):
             o = oracle.compress_layer_blocks_momentum(grads[l], u[l], resid[l], m or 0.0, p, 0.5, 0.05).layer
             assert np.array_equal(blocks, o.blocks) and np.array_equal(_bits(val), _bits(np.asarray(o.val).reshape(-1))), (m, l)
             assert np.array_equal(_bits(after[l]), _bits(o.r_new)), (m, l)
+
+
+@pytest.mark.parametrize("n, p, m", [(900, 1, None), (900, 3, None)])
+def test_plans_of_many_layers(n, p, m):
+    """More than 512 groups of tiles in a small plan: a workgroup gathers a whole group.  Layers shorter than a mask word
+    or two, layers that end on, before and after a chunk, chunks kept whole (more than a wave lists at a time), nearly
+    empty and empty ones, layers without anything to keep.  Three calls, every one against the oracle."""
+    from paper_2312_17530_amd.session import Session
+    shapes = [(1, 1 + l % 70) for l in range(n)] + [(64, 128), (100, 300), (1, 8191), (1, 8193), (130, 127), (3, 8192), (50, 333)]
+    ratios = [(0.0, 1.0, 0.3)[l % 3] for l in range(n)] + [1.0, 0.9, 0.0, 0.02, 0.1, 0.5, 0.001]
+    rng = np.random.default_rng(7)
+    s = Session(shapes, p, 0.5, ratios, momentum=m)
+    resid = [np.zeros(sh, np.float32) for sh in shapes]
+    mom = [np.zeros(sh, np.float32) for sh in shapes]
+    for t in range(3):
+        grads = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+        s.set_grad(grads)
+        s.compress()
+        after = s.unpack(s.residual)
+        u_after = s.unpack(s.momentum_buf) if m is not None else mom
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o, u_new = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, p, 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+            if m is not None:
+                assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)
+        resid, mom = after, u_after
