@@ -1502,7 +1502,7 @@ __device__ __forceinline__ void gather_stage_key(GatherShared &sh, bool hit, uns
 }
 
 template <bool COUNT, int PARTS>
-__global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const GatherLists gl) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // role 0: listed score-map chunks, 1: listed slot groups, 2: fallback walk over all chunks
@@ -1516,9 +1516,13 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
     const DirEntry *__restrict__ dir = gl.chunk_dir;
     if (first >= n_items) return;
     if (role == 2 && a.flags[0] == 0u) return;
-    if (tid == 0) sh.n = 0;
-    for (int b = tid; b < kLevel1Bins; b += 256) sh.hist[b] = 0;
-    __syncthreads();
+    // (role 1 counts its few bucket keys in the layer's histogram itself: clearing and flushing 2048 bins in LDS costs a
+    // workgroup more than the two or three atomics)
+    if (role != 1) {
+        if (tid == 0) sh.n = 0;
+        for (int b = tid; b < kLevel1Bins; b += 256) sh.hist[b] = 0;
+        __syncthreads();
+    }
 
     uint32_t e = role == 2 ? dir_lookup(dir, gl.n_layers, first) : 0u;
     uint32_t cur_l = 0xffffffffu;
@@ -1549,7 +1553,7 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
             l = dir[e].layer;
         }
         if (l != cur_l) {
-            if (active) {                  // uniform: the finished layer's keys and counts go out
+            if (active && role != 1) {     // uniform: the finished layer's keys and counts go out
                 gather_flush_keys(sh, list);
                 uint32_t *__restrict__ gh = a.hist1 + static_cast<size_t>(cur_l) * kLevel1Bins;
                 for (int b = tid; b < kLevel1Bins; b += 256) {
@@ -1731,7 +1735,7 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
                         } else if (score - lo < width) {         // in the threshold bucket (never when the layer is done):
                             const uint32_t pos = atomicAdd(list.cnt, 1u);       // few of them, one atomic each
                             if (pos < list.cap) list.ent[pos] = K;
-                            atomicAdd(&sh.hist[(score - lo) >> shift1], 1u);
+                            atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
                         }
                     }
                 }
@@ -1799,7 +1803,7 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
                         if (hit) {
                             const uint32_t pos = base + static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
                             if (pos < list.cap) list.ent[pos] = K[c];
-                            atomicAdd(&sh.hist[(score - lo) >> shift1], 1u);
+                            atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
                         }
                     }
                 }
@@ -1807,7 +1811,7 @@ __global__ __launch_bounds__(256) void k_gather(const GatherArgs a, const Gather
             }
         }
     }
-    if (active) {
+    if (active && role != 1) {
         gather_flush_keys(sh, list);
         uint32_t *__restrict__ gh = a.hist1 + static_cast<size_t>(cur_l) * kLevel1Bins;
         for (int b = tid; b < kLevel1Bins; b += 256) {
