@@ -2586,9 +2586,6 @@ __global__ __launch_bounds__(256) void k_emit(const LayerDev *__restrict__ layer
 // residual arena, so only the kept elements are touched -- their value goes out and the
 // arena gets +0 there.  A chunk without kept elements costs one read of its mask words.  A
 // layer with k_l = 0 went through no NSI pass; its v is formed here.
-// (Four chunks per workgroup -- a quarter of the dependent chains of mask word, prefix and kept
-// values, four value requests per thread in flight -- was built and measured: no faster.  The
-// kernel is bound by the rate of its scattered 4-byte reads and writes, not by their latency.)
 __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict__ chunk_info,
                                                      const SelState *__restrict__ state,
                                                      const float *__restrict__ grad,
@@ -2665,6 +2662,153 @@ __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict
         }
         v[e] = 0.f;
         if (mom_arena) mom_arena[base + e] = 0.f;     // the momentum restarts where v was sent
+    }
+}
+
+// The same for plans of many chunks: one wave per chunk, four chunks per workgroup, no barrier.  What bounds the emit there is
+// the chain entry -> mask words and prefix -> values, so as many chunks as possible have to be on their way at once: 40.8 -> 30.7 us
+// on VGG-19 (17 k chunks; of the 40.8 us, 12 were the scattered reads and writes of v), 16.1 -> 10.1 us on the 25088 x 4096 layer at
+// 0.1 %.  On a plan of few chunks a workgroup each has the shorter chain (ResNet-18's 1.4 k chunks: 6.3 against 7.6 us; 3.1 k
+// chunks with dense ones among them: 14.5 against 16.9 us).
+constexpr int kEmitList = 1024;            // kept elements of a chunk that a wave lists at a time
+
+// What one wave has written to LDS and reads back (its DS operations are carried out in order): keeps the compiler from
+// moving the accesses of different lanes past each other.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The 128 mask bits that a lane of the wave holds of its chunk, and the kept elements before them.
+struct ChunkBits {
+    uint32_t w[4];
+    uint32_t before, total;                // kept elements of the chunk before this lane's / in all
+};
+__device__ __forceinline__ ChunkBits chunk_bits(const uint2 lo, const uint2 hi) {
+    const int lane = threadIdx.x & 63;
+    ChunkBits b;
+    b.w[0] = lo.x; b.w[1] = lo.y; b.w[2] = hi.x; b.w[3] = hi.y;
+    const uint32_t own = __popc(lo.x) + __popc(lo.y) + __popc(hi.x) + __popc(hi.y);
+    uint32_t incl = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += o;
+    }
+    b.before = incl - own;
+    b.total = __builtin_amdgcn_readlane(incl, 63);
+    return b;
+}
+
+// Offsets inside the chunk of its kept elements number b0 .. b0 + n - 1 (n <= kEmitList), in ascending order, to list.
+__device__ __forceinline__ void list_chunk_bits(const ChunkBits &b, uint32_t b0, uint32_t n, uint16_t *list) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t pos = b.before - b0;          // (may wrap below zero: not below n then)
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+        uint32_t word = b.w[j];
+        while (word) {
+            const uint32_t bit = static_cast<uint32_t>(__ffs(word)) - 1u;
+            word &= word - 1u;
+            if (pos < n) list[pos] = static_cast<uint16_t>(128u * lane + 32u * j + bit);
+            ++pos;
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_emit_waves(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
+                                                    const SelState *__restrict__ state,
+                                                    const float *__restrict__ grad,
+                                                    const float *__restrict__ resid_in,
+                                                    float *__restrict__ v_arena,
+                                                    const float *__restrict__ mom_in,
+                                                    float *__restrict__ mom_arena, float m,
+                                                    uint32_t *__restrict__ mask,
+                                                    const uint32_t *__restrict__ chunk_cnt,
+                                                    const uint32_t *__restrict__ group_cnt,
+                                                    uint32_t *__restrict__ out_idx,
+                                                    float *__restrict__ out_val,
+                                                    int32_t *__restrict__ out_counts, const NextCall nc) {
+    if (prepare_next_call(nc)) return;
+    __shared__ uint16_t s_list[4][kEmitList];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint16_t *list = s_list[wave];
+    const uint32_t c = __builtin_amdgcn_readfirstlane((blockIdx.x - 1) * 4u + wave);
+    if (c >= n_chunks) return;
+    const ChunkInfo ci = chunk_info[c];
+    const uint32_t start = ci.start, len = ci.len;
+    const size_t base = ci.arena_off;
+    float *__restrict__ v = v_arena + base;
+    // the loads that depend only on the chunk's entry go out together.  (A layer starts at a multiple of two words and is
+    // padded to one: a pair whose first word exists may be read whole.)
+    const uint32_t nwords = (len + 31) >> 5;
+    uint2 *__restrict__ words = reinterpret_cast<uint2 *>(mask + (base >> 5)) + 2 * lane;
+    uint2 lo = make_uint2(0u, 0u), hi = make_uint2(0u, 0u);
+    if (4 * lane < nwords) lo = words[0];
+    if (4 * lane + 2 < nwords) hi = words[1];
+    // (k_l = 0: kModeSkip in this call's state and in the next call's, which the first workgroup is writing)
+    const uint32_t mode = state[ci.layer].mode;
+    const uint32_t cbase = chunk_prefix_by_wave(ci, c, chunk_cnt, group_cnt);
+    // (every word is read by one lane: clear for the next call)
+    if (lo.x | lo.y) words[0] = make_uint2(0u, 0u);
+    if (hi.x | hi.y) words[1] = make_uint2(0u, 0u);
+    if (mode == kModeSkip) {
+        if (ci.last && lane == 0) out_counts[ci.layer] = 0;
+        const float *__restrict__ g = grad + base;
+        const float *__restrict__ r = resid_in + base;
+        for (uint32_t e = 4 * lane; e < len; e += 256) {
+            if (e + 3 < len) {
+                float4 gu = load_streaming(g + e);
+                const float4 rv = load_streaming(r + e);
+                if (mom_in) {
+                    const float4 u = load_streaming(mom_in + base + e);
+                    gu = make_float4(__fmul_rn(m, u.x) + gu.x, __fmul_rn(m, u.y) + gu.y, __fmul_rn(m, u.z) + gu.z, __fmul_rn(m, u.w) + gu.w);
+                    store_streaming(mom_arena + base + e, gu);
+                }
+                store_streaming(v + e, make_float4(rv.x + gu.x, rv.y + gu.y, rv.z + gu.z, rv.w + gu.w));
+                continue;
+            }
+            for (uint32_t q = 0; q < 4 && e + q < len; ++q) {
+                float gu = g[e + q];
+                if (mom_in) {
+                    gu = __fmul_rn(m, mom_in[base + e + q]) + gu;
+                    mom_arena[base + e + q] = gu;
+                }
+                v[e + q] = r[e + q] + gu;
+            }
+        }
+        return;
+    }
+    const ChunkBits bits = chunk_bits(lo, hi);
+    if (ci.last && lane == 0) out_counts[ci.layer] = static_cast<int32_t>(cbase + bits.total);
+    const size_t obase = static_cast<size_t>(ci.out_off) + cbase;
+    const uint32_t room = ci.cap > cbase ? ci.cap - cbase : 0u;   // never write past the segment
+    for (uint32_t b0 = 0; b0 < bits.total; b0 += kEmitList) {
+        const uint32_t n = min(bits.total - b0, static_cast<uint32_t>(kEmitList));
+        wave_lds_order();
+        list_chunk_bits(bits, b0, n, list);
+        wave_lds_order();
+        constexpr int U = 4;               // kept elements of a lane on their way at once; coalesced pair stores
+        for (uint32_t i0 = lane; i0 < n; i0 += 64 * U) {
+            uint32_t e[U];
+            float val[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                e[u] = i0 + 64 * u < n ? list[i0 + 64 * u] : 0xffffffffu;
+                if (e[u] < len) val[u] = v[e[u]];            // (mask bits exist only for elements of the layer)
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (e[u] >= len) continue;
+                const uint32_t i = b0 + i0 + 64 * u;
+                if (i < room) {
+                    out_idx[obase + i] = start + e[u];
+                    out_val[obase + i] = val[u];
+                }
+                v[e[u]] = 0.f;
+                if (mom_arena) mom_arena[base + e[u]] = 0.f;     // the momentum restarts where v was sent
+            }
+        }
     }
 }
 
@@ -4186,6 +4330,10 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     if (in_place)
         hipLaunchKernelGGL(k_emit, dim3(n_chunks + 1), dim3(256), 0, stream, layers, chunk_info, grad,
                            residual_out, mask, chunk_cnt, group_cnt, out_idx, out_val, out_counts, nc);
+    else if (n_chunks > kInlineCountChunks)
+        hipLaunchKernelGGL(k_emit_waves, dim3((n_chunks + 3) / 4 + 1), dim3(256), 0, stream, chunk_info, n_chunks, state, grad,
+                           residual, residual_out, mom.in, mom.out, mom.m, mask, chunk_cnt, group_cnt, out_idx,
+                           out_val, out_counts, nc);
     else
         hipLaunchKernelGGL(k_emit_sparse, dim3(n_chunks + 1), dim3(256), 0, stream, chunk_info, state, grad,
                            residual, residual_out, mom.in, mom.out, mom.m, mask, chunk_cnt, group_cnt, out_idx,

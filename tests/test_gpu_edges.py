@@ -214,9 +214,10 @@ def test_rows_of_odd_length_in_every_pass(p):
             assert np.array_equal(_bits(after[l]), _bits(o.r_new)), (m, l)
 
 
-@pytest.mark.parametrize("n, p, m", [(900, 1, None), (900, 3, None)])
+@pytest.mark.parametrize("n, p, m", [(900, 1, None), (900, 3, None), (4100, 1, None), (4100, 3, None), (4100, 3, 0.9)])
 def test_plans_of_many_layers(n, p, m):
-    """More than 512 groups of tiles in a small plan: a workgroup gathers a whole group.  Layers shorter than a mask word
+    """More than 512 groups of tiles in a small plan: a workgroup gathers a whole group; more than 4096 chunks: the
+    emit of a wave per chunk and the counting launch.  Layers shorter than a mask word
     or two, layers that end on, before and after a chunk, chunks kept whole (more than a wave lists at a time), nearly
     empty and empty ones, layers without anything to keep.  Three calls, every one against the oracle."""
     from paper_2312_17530_amd.session import Session
