@@ -3138,7 +3138,7 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
 // list, +0 into the new residual (and into the new momentum, when the call carries one).
 __global__ __launch_bounds__(256) void k_emit_blocks(const LayerDev *__restrict__ outer,
                                                      const ChunkInfo *__restrict__ inner_chunks,
-                                                     const uint32_t *__restrict__ mask,
+                                                     uint32_t *__restrict__ mask,
                                                      const uint32_t *__restrict__ chunk_cnt,
                                                      const uint32_t *__restrict__ group_cnt,
                                                      const LayerDev *__restrict__ inner,
@@ -3146,16 +3146,18 @@ __global__ __launch_bounds__(256) void k_emit_blocks(const LayerDev *__restrict_
                                                      float *__restrict__ u_arena /* nullable */,
                                                      uint32_t *__restrict__ out_blocks,
                                                      float *__restrict__ out_val,
-                                                     int32_t *__restrict__ out_counts) {
+                                                     int32_t *__restrict__ out_counts, const NextCall nc) {
+    if (prepare_next_call(nc)) return;
     __shared__ uint32_t wave_tot[4];
     __shared__ uint16_t s_list[kChunk];
     __shared__ uint32_t s_total, s_cbase;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = blockIdx.x - 1;
     const ChunkInfo ci = inner_chunks[c];
     const uint32_t nwords = (ci.len + 31) >> 5;
     uint32_t word = static_cast<uint32_t>(tid) < nwords ? mask[(ci.arena_off >> 5) + tid] : 0;
     chunk_prefix_wave0(ci, c, chunk_cnt, group_cnt, &s_cbase);
+    if (word) mask[(ci.arena_off >> 5) + tid] = 0u;   // (every word is read by one thread: clear for the next call)
     if (!__syncthreads_or(word != 0u) && !ci.last) return;      // uniform
     const uint32_t cbase = s_cbase;
     const uint32_t cnt = __popc(word);
@@ -4223,6 +4225,24 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
     return RSDGC_OK;
 }
 
+// What the last kernel of a call with this plan clears and sets for the next (sampling: whether that one samples bounds).
+static NextCall next_call(const rsdgc_plan_s *plan, char *ws, const LayerDev *layers, SelState *state, PredState *pred,
+                          bool sampling) {
+    const WsLayout &w = plan->ws;
+    NextCall nc;
+    nc.zero[0] = reinterpret_cast<uint4 *>(ws + w.hist);
+    nc.n16[0] = static_cast<uint32_t>((w.chunk_cnt - w.hist) / 16);
+    nc.zero[1] = reinterpret_cast<uint4 *>(ws + w.list_cnt);
+    nc.n16[1] = static_cast<uint32_t>((w.mask - w.list_cnt) / 16);
+    nc.layers = layers;
+    nc.state = state;
+    nc.pred = pred;
+    nc.flags = reinterpret_cast<uint32_t *>(ws + w.flags);
+    nc.n_layers = plan->n_layers;
+    nc.sampling = sampling ? 1 : 0;
+    return nc;
+}
+
 static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &mom,
                          const float *residual, float *residual_out, uint32_t *out_idx,
                          float *out_val, int32_t *out_counts, uint32_t *out_centre_idx,
@@ -4276,17 +4296,7 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
         HIP_TRY(hipGetLastError());
     }
     plan->ws_ready = false;                // (until all of this call is enqueued)
-    NextCall nc;
-    nc.zero[0] = reinterpret_cast<uint4 *>(ws + w.hist);
-    nc.n16[0] = static_cast<uint32_t>((w.chunk_cnt - w.hist) / 16);
-    nc.zero[1] = reinterpret_cast<uint4 *>(ws + w.list_cnt);
-    nc.n16[1] = static_cast<uint32_t>((w.mask - w.list_cnt) / 16);
-    nc.layers = layers;
-    nc.state = state;
-    nc.pred = pred;
-    nc.flags = flags;
-    nc.n_layers = L;
-    nc.sampling = plan->any_large && plan->calls_since_upload < kSamplingCalls ? 1 : 0;
+    const NextCall nc = next_call(plan, ws, layers, state, pred, plan->any_large && plan->calls_since_upload < kSamplingCalls);
     marks.close(0);
 
     // first pass: every tile of the layers ranked on the full map (scores, histogram, v) and, where a
@@ -4484,14 +4494,17 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     const uint32_t *group_cnt = reinterpret_cast<const uint32_t *>(ws + w.group_cnt);
     float *score_map = reinterpret_cast<float *>(ws + w.nsi);
     StageMarks marks(in, stream);                      // (the inner plan never records events)
-    {
+    // (as for the element reading: the first call with a workspace sets it up, every call leaves it so.  A block grid is
+    // always ranked on its full map: no bounds, nothing to predict)
+    if (!in->ws_ready) {
         const size_t n16 = (w.cmask - w.zero_begin) / 16;
         const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n16 + 255) / 256, 4096));
         hipLaunchKernelGGL(k_begin, dim3(blocks + 1), dim3(256), 0, stream,
                            reinterpret_cast<uint4 *>(ws + w.zero_begin), n16, inner, state, L,
-                           static_cast<PredState *>(nullptr),    // a block grid is always ranked on its full map
-                           reinterpret_cast<uint32_t *>(ws + w.flags), 0);
+                           static_cast<PredState *>(nullptr), reinterpret_cast<uint32_t *>(ws + w.flags), 0);
     }
+    in->ws_ready = false;                  // (until all of this call is enqueued)
+    const NextCall nc = next_call(in, ws, inner, state, nullptr, false);
     bool have[RSDGC_MAX_P + 1] = {};
     for (int l = 0; l < L; ++l) have[plan->p[l]] = true;
     // the work feed (counters in the inner plan's workspace, cleared above) pays when a
@@ -4535,13 +4548,15 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
         }
     }
     HIP_TRY(hipGetLastError());
-    const Find0Args f = {inner, state, hist, hist, reinterpret_cast<uint32_t *>(ws + w.flags), nullptr, nullptr, 0u, L};
+    const Find0Args f = {inner, state, hist, hist, reinterpret_cast<uint32_t *>(ws + w.flags), nullptr,
+                         reinterpret_cast<uint4 *>(ws + w.chunk_cnt), static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16), L};
     hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
     rc = select_mark_count(in, ws, false, marks, nullptr, stream);
     if (rc != RSDGC_OK) return rc;
-    hipLaunchKernelGGL(k_emit_blocks, dim3(in->n_chunks), dim3(256), 0, stream, outer, inner_chunks, mask,
-                       chunk_cnt, group_cnt, inner, residual_out, mom.out, out_block_idx, out_val, out_counts);
+    hipLaunchKernelGGL(k_emit_blocks, dim3(in->n_chunks + 1), dim3(256), 0, stream, outer, inner_chunks, mask,
+                       chunk_cnt, group_cnt, inner, residual_out, mom.out, out_block_idx, out_val, out_counts, nc);
     HIP_TRY(hipGetLastError());
+    in->ws_ready = true;
     return RSDGC_OK;
 }
 
