@@ -4,7 +4,9 @@
 // keep ratio leaves room for it records only the centres whose score reaches a bound and ranks
 // those; the other layers are ranked on a full score map.  The result is the same on both.
 //   begin      zero histograms, bitmasks, counters, flags; per-layer state; for every layer on
-//              the candidate path the bound predicted from the thresholds of the two calls before
+//              the candidate path the bound predicted from the thresholds of the two calls before.
+//              A launch of its own (k_begin) in the first call with a workspace only: every call
+//              clears what it has used and its emit sets the next call's states (NextCall)
 //   first pass every tile of the layers that are always ranked on the full score map: v = r + g
 //              (Eq. 12), NSI (Eqs. 6-10), score map, exact 12-bit histogram; during the first calls
 //              with a workspace, in the same launch, one tile in 16 .. 64 of the candidate-path
@@ -17,7 +19,8 @@
 //   find0      first ranking digit of every layer; a layer whose bound caught fewer than k_l
 //              centres, or overfilled a tile, falls back to the full map (a flag tells the
 //              fallback kernels there is work)
-//   fallback   score map + histogram of such layers (rare)
+//   fallback   score map + histogram of such layers (rare); the same launch as find0 where its
+//              workgroups can look at every layer (k_find0_fallback)
 //   select     gather: the candidates above each layer's threshold bucket are selected for certain
 //              and mark their windows; the bucket's keys are copied to a list and their next digit
 //              counted; finish: one workgroup per layer resolves the remaining digits
@@ -25,21 +28,22 @@
 //   mark       the bucket's keys that reach the threshold set the bits of their p x p window
 //              (Section III-C: whole neighbourhoods are kept); full-map layers: every centre
 //   count      kept elements per chunk and per group of chunks (no scan kernel: each consumer
-//              adds up its own prefix from those)
+//              adds up its own prefix from those); small plans count as they mark
 //   emit       ordered (index, value) pairs and the residual update (Eq. 12): either only the
-//              kept elements are touched (second arena), or g and r are streamed again
-//              (update in place)
+//              kept elements are touched (second arena; by workgroups or, on large plans, by
+//              waves), or g and r are streamed again (update in place)
 //
 // Sections of this file, in order (each starts with a "// ---- name --" line):
 //   begin            k_begin
 //   work feed        WorkFeed: tiles handed to persistent workgroups through per-XCD counters
 //   nsi              k_nsi<P, PASS, MOM, FEED>: the four NSI passes, with or without Eq. 12's momentum
 //   ranking digits   block_find_digit, publish_threshold
-//   hint .. finish   k_hint, k_find0, k_gather, k_filter, k_finish: bounds and the radix select
-//   mark             k_mark: p x p windows into the bitmask
+//   hint .. finish   k_hint, k_find0, k_find0_fallback(_all), k_gather, k_filter, k_finish: bounds and
+//                    the radix select
+//   mark             k_mark: p x p windows into the bitmask; k_mark_flat: block grids
 //   count            k_count, chunk_prefix_wave0
-//   emit             k_emit, k_emit_sparse, k_emit_centres
-//   decompress       k_zero_layers, k_scatter
+//   emit             k_emit, k_emit_sparse, k_emit_waves, k_emit_centres
+//   decompress       k_zero_layers, k_scatter (for_each_pair)
 //   block reading    k_block_nsi, k_emit_blocks, k_scatter_blocks
 //   apply            k_apply_ranges, k_apply_chunks, k_apply_single, k_apply_blocks (receiving side)
 //   dynamic ratios   k_dyn_*
