@@ -112,7 +112,7 @@ int rsdgc_plan_set_path(rsdgc_plan_t *plan, int32_t path);
 int rsdgc_plan_set_work_feed(rsdgc_plan_t *plan, int32_t mode);
 
 /* A plan remembers the address of the workspace it last prepared (its tables
- * uploaded) and skips that work while the address stays the same.  Call this when the memory at that address has been freed,
+ * uploaded, counters and masks cleared) and skips that work while the address stays the same.  Call this when the memory at that address has been freed,
  * reused or overwritten in the meantime: the next call with any workspace
  * prepares it afresh.  Host side only; no GPU work.                          */
 int rsdgc_plan_forget_workspace(rsdgc_plan_t *plan);
@@ -193,9 +193,9 @@ int rsdgc_compress(rsdgc_plan_t *plan, const float *grad, const float *residual,
  *     or threads) must not overlap in time -- the later one would overwrite tables and
  *     counters the earlier one still reads.  Calls that follow each other on one stream
  *     are fine.  When the array last served another plan (or this plan with other ratios),
- *     the plan's tables are copied into it again (one host-to-device copy on `stream`)
- *     and a state the plan keeps between calls starts afresh; everything else that must
- *     start at zero is cleared by every call.
+ *     the plan's tables are copied into it again (one host-to-device copy on `stream`),
+ *     a state the plan keeps between calls starts afresh, and all counters and masks are
+ *     cleared; after that every call leaves them clear for the next.
  *   - The device current at the time of the call is the one whose array is used.      */
 #define RSDGC_STATIC_WORKSPACE_BYTES (64u << 20)
 int rsdgc_compress_static(rsdgc_plan_t *plan, const float *grad, const float *residual,

@@ -217,7 +217,7 @@ struct WsLayout {
     size_t state = 0;        // SelState[n_layers]
     size_t flags = 0;        // uint32[64]  [0]: some large layer is ranked on the full map in this call (set with the state,
                              //             raised by the kernels that send a layer there)
-    // zero when a compress call starts: cleared by the first with a workspace, then every call leaves them so
+    // zero when a compress call starts: cleared when the tables are laid down, then every compress call leaves them so
     // (hist .. hist1, list_cnt .. cmask by its last kernels; chunk_cnt .. group_ccnt before it counts)
     size_t zero_begin = 0;
     size_t hist = 0;         // uint32[n_layers][kHistBins]  first ranking digit of the layers ranked on the full map
@@ -301,7 +301,8 @@ struct rsdgc_plan_s {
     const void *uploaded_ws = nullptr;
     int calls_since_upload = 0;         // compress calls since the tables went to uploaded_ws (counted up to kSamplingCalls)
     uint64_t uploaded_version = 0;
-    bool ws_ready = false;              // uploaded_ws is as a compress call needs it: counters zero, layer states set
+    bool ws_ready = false;              // uploaded_ws is as a compress call needs it: counters zero, layer states set.  Only
+                                        // work that runs makes it so, not work recorded into a graph
     // block reading (non-overlapping p x p neighbourhoods): this plan describes the element
     // matrices; `inner` describes the block grids as layers with p = 1 and the same k_l, and
     // the selection machinery runs on it.  The workspace is this plan's tables followed by

@@ -5,7 +5,7 @@
 // those; the other layers are ranked on a full score map.  The result is the same on both.
 //   begin      zero histograms, bitmasks, counters, flags; per-layer state; for every layer on
 //              the candidate path the bound predicted from the thresholds of the two calls before.
-//              A launch of its own (k_begin) in the first call with a workspace only: every call
+//              A launch of its own (k_begin) only where the tables are laid down: every call
 //              clears what it has used and its emit sets the next call's states (NextCall)
 //   first pass every tile of the layers that are always ranked on the full score map: v = r + g
 //              (Eq. 12), NSI (Eqs. 6-10), score map, exact 12-bit histogram; during the first calls
@@ -158,9 +158,10 @@ __device__ __forceinline__ float margin_init_log2(uint32_t k) {
 }
 
 // ---------------------------------------------------------------- begin --
-// The first call with a workspace (k_begin): all workgroups but the last clear the histograms, counters and
-// bitmasks; the last one writes every layer's initial selection state.  After that every call leaves both as
-// the next one needs them (prepare_next_call).  A large layer gets its
+// When the plan's tables have been copied into a workspace, by whichever call comes first (k_begin): all workgroups
+// but the last clear the histograms, counters and bitmasks; the last one writes every layer's initial selection state.
+// After that every compress call leaves both as the next one needs them (prepare_next_call), so a call is the same
+// whether it is enqueued or replayed from a graph, and whatever came before it.  A large layer gets its
 // candidate bound here when the thresholds of its last two calls (kept in `pred`) lie close
 // together.  While a residual builds up, the threshold keeps moving in one direction by steps
 // that, on a logarithmic scale, shrink smoothly from call to call; so after a step d of
@@ -233,16 +234,21 @@ __device__ __forceinline__ bool init_layer_state(const LayerDev *__restrict__ la
     return fallback_work;
 }
 
+// What the states hold before init_states writes them: nothing (fresh memory), what a compress call ends with, or the
+// states of a call that has not been made.
+enum StatesBefore : int { kStatesNone = 0, kStatesAfterCall = 1, kStatesBeforeCall = 2 };
+
 // Every layer's state for the next call, by one workgroup of 256 threads.
 __device__ __forceinline__ void init_states(const LayerDev *__restrict__ layers, SelState *__restrict__ state, int n_layers,
                                             PredState *__restrict__ pred, uint32_t *__restrict__ flags, int sampling,
-                                            bool finished_call) {
+                                            int before) {
     bool fallback_work = false;
     for (int l = threadIdx.x; l < n_layers; l += 256) {
         uint32_t last_path = 0;
-        if (finished_call) {
+        if (before != kStatesNone) {
             const SelState s = state[l];
-            last_path = s.mode == kModeCandidates && (s.predicted & 1u) ? 3u : s.mode;
+            if (before == kStatesBeforeCall) last_path = s.predicted >> kLastPathShift;
+            else last_path = s.mode == kModeCandidates && (s.predicted & 1u) ? 3u : s.mode;
         }
         fallback_work |= init_layer_state(layers, state, l, pred, sampling, last_path);
     }
@@ -254,9 +260,9 @@ __global__ __launch_bounds__(256) void k_begin(uint4 *__restrict__ p, size_t n16
                                                const LayerDev *__restrict__ layers,
                                                SelState *__restrict__ state, int n_layers,
                                                PredState *__restrict__ pred /* nullable */,
-                                               uint32_t *__restrict__ flags, int sampling) {
+                                               uint32_t *__restrict__ flags, int sampling, int before) {
     if (blockIdx.x + 1 == gridDim.x) {
-        init_states(layers, state, n_layers, pred, flags, sampling, false);
+        init_states(layers, state, n_layers, pred, flags, sampling, before);
         return;
     }
     const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -280,7 +286,7 @@ struct NextCall {
 // True: this workgroup was the extra one and is done.  (The others' chunk is blockIdx.x - 1.)
 __device__ __forceinline__ bool prepare_next_call(const NextCall &nc) {
     if (blockIdx.x == 0) {
-        init_states(nc.layers, nc.state, nc.n_layers, nc.pred, nc.flags, nc.sampling, true);
+        init_states(nc.layers, nc.state, nc.n_layers, nc.pred, nc.flags, nc.sampling, kStatesAfterCall);
         return true;
     }
     const uint32_t stride = (gridDim.x - 1) * 256u;
@@ -4031,12 +4037,41 @@ __global__ __launch_bounds__(256) void k_dyn_count(const ChunkInfo *__restrict__
 }
 
 // ------------------------------------------------------------ host side --
+// Everything a compress call expects of the workspace beside the tables.  Recorded into a graph it prepares nothing
+// yet (the graph may never be launched, or only after an eager call): ws_ready stays false then, and every call up to
+// the next eager one brings its own preparation.
+int prepare_workspace(rsdgc_plan_s *plan, char *ws, bool sampling, StatesBefore before, hipStream_t stream) {
+    const WsLayout &w = plan->ws;
+    const bool block_grid = !plan->k_override.empty();     // always ranked on its full map: no bounds, no centre lists
+    const size_t n16 = ((block_grid ? w.cmask : w.zero_end) - w.zero_begin) / 16;
+    const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n16 + 255) / 256, 4096));
+    hipLaunchKernelGGL(k_begin, dim3(blocks + 1), dim3(256), 0, stream,
+                       reinterpret_cast<uint4 *>(ws + w.zero_begin), n16,
+                       reinterpret_cast<const LayerDev *>(ws + w.layers), reinterpret_cast<SelState *>(ws + w.state),
+                       plan->n_layers, block_grid ? nullptr : reinterpret_cast<PredState *>(ws + w.pred),
+                       reinterpret_cast<uint32_t *>(ws + w.flags), sampling ? 1 : 0, static_cast<int>(before));
+    HIP_TRY(hipGetLastError());
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &capture));
+    plan->ws_ready = capture == hipStreamCaptureStatusNone;
+    return RSDGC_OK;
+}
+
 int upload_tables(rsdgc_plan_s *plan, void *workspace, hipStream_t stream) {
     if (plan->uploaded_ws == workspace && plan->uploaded_version == plan->version) return RSDGC_OK;
+    // (new ratios or another path, the same memory: the paths of the last call are still asked for there)
+    const StatesBefore before = plan->uploaded_ws == workspace && plan->ws_ready ? kStatesBeforeCall : kStatesNone;
+    plan->uploaded_ws = nullptr;           // (until all of it is enqueued)
+    plan->ws_ready = false;
     HIP_TRY(hipMemcpyAsync(workspace, plan->table.data(), plan->ws.table_bytes,
                            hipMemcpyHostToDevice, stream));
     plan->calls_since_upload = 0;
-    plan->ws_ready = false;
+    // Whatever call lays the tables down prepares the rest too: what comes next may be the replay of a graph that was
+    // recorded on a prepared workspace.  (A block plan has its tables only; the selection runs on the inner plan's.)
+    if (!plan->blocks) {
+        const int rc = prepare_workspace(plan, static_cast<char *>(workspace), plan->any_large, before, stream);
+        if (rc != RSDGC_OK) return rc;
+    }
     plan->uploaded_ws = workspace;
     plan->uploaded_version = plan->version;
     return RSDGC_OK;
@@ -4388,15 +4423,11 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
 
     StageMarks marks(plan, stream);
-    // the first call with a workspace (or after one that failed): everything a call expects
-    if (!plan->ws_ready) {
-        const size_t n16 = (w.zero_end - w.zero_begin) / 16;
-        const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n16 + 255) / 256, 4096));
-        hipLaunchKernelGGL(k_begin, dim3(blocks + 1), dim3(256), 0, stream,
-                           reinterpret_cast<uint4 *>(ws + w.zero_begin), n16, layers, state, L, pred, flags,
-                           sampling ? 1 : 0);
-        HIP_TRY(hipGetLastError());
+    if (!plan->ws_ready) {                 // the call before failed half way
+        rc = prepare_workspace(plan, ws, sampling, kStatesNone, stream);
+        if (rc != RSDGC_OK) return rc;
     }
+    const bool ready = plan->ws_ready;     // (false: prepared by the graph that is being recorded)
     plan->ws_ready = false;                // (until all of this call is enqueued)
     const NextCall nc = next_call(plan, ws, layers, state, pred, plan->any_large && plan->calls_since_upload < kSamplingCalls);
     marks.close(0);
@@ -4457,7 +4488,7 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
                            out_centre_counts);
     marks.close(8);
     HIP_TRY(hipGetLastError());
-    plan->ws_ready = true;
+    plan->ws_ready = ready;
     return RSDGC_OK;
 }
 
@@ -4510,8 +4541,7 @@ int rsdgc_compress_static(rsdgc_plan_t *plan, const float *grad, const float *re
         slot.ptr = p;
     }
     // the array keeps what the last call left: when that was another plan (or other ratios), this
-    // plan's tables and its state between calls are laid down again; the per-call clears of
-    // rsdgc_compress take care of everything else
+    // plan's tables are laid down again and everything else a call expects is cleared and set with them
     if (slot.owner_serial != plan->serial || slot.owner_version != plan->version) plan->uploaded_ws = nullptr;
     const int rc = compress_impl(plan, grad, Momentum{}, residual, residual_out, out_idx, out_val,
                                  out_counts, out_centre_idx, out_centre_counts, slot.ptr, stream);
@@ -4596,15 +4626,11 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     const uint32_t *group_cnt = reinterpret_cast<const uint32_t *>(ws + w.group_cnt);
     float *score_map = reinterpret_cast<float *>(ws + w.nsi);
     StageMarks marks(in, stream);                      // (the inner plan never records events)
-    // (as for the element reading: the first call with a workspace sets it up, every call leaves it so.  A block grid is
-    // always ranked on its full map: no bounds, nothing to predict)
-    if (!in->ws_ready) {
-        const size_t n16 = (w.cmask - w.zero_begin) / 16;
-        const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n16 + 255) / 256, 4096));
-        hipLaunchKernelGGL(k_begin, dim3(blocks + 1), dim3(256), 0, stream,
-                           reinterpret_cast<uint4 *>(ws + w.zero_begin), n16, inner, state, L,
-                           static_cast<PredState *>(nullptr), reinterpret_cast<uint32_t *>(ws + w.flags), 0);
+    if (!in->ws_ready) {                   // the call before failed half way
+        rc = prepare_workspace(in, ws, false, kStatesNone, stream);
+        if (rc != RSDGC_OK) return rc;
     }
+    const bool ready = in->ws_ready;       // (false: prepared by the graph that is being recorded)
     in->ws_ready = false;                  // (until all of this call is enqueued)
     const NextCall nc = next_call(in, ws, inner, state, nullptr, false);
     bool have[RSDGC_MAX_P + 1] = {};
@@ -4658,7 +4684,7 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     hipLaunchKernelGGL(k_emit_blocks, dim3(in->n_chunks + 1), dim3(256), 0, stream, outer, inner_chunks, mask,
                        chunk_cnt, group_cnt, inner, residual_out, mom.out, out_block_idx, out_val, out_counts, nc);
     HIP_TRY(hipGetLastError());
-    in->ws_ready = true;
+    in->ws_ready = ready;
     return RSDGC_OK;
 }
 

@@ -231,7 +231,7 @@ int build_tables(rsdgc_plan_s *plan) {
     w.count_groups = off; off = align_up(off + sizeof(CountGroup) * plan->n_count_groups, A);
     w.pred = off;         off = align_up(off + sizeof(PredState) * L, A);
     w.table_bytes = off;
-    w.state = off;        off = align_up(off + sizeof(SelState) * L, A);   // written in full each call
+    w.state = off;        off = align_up(off + sizeof(SelState) * L, A);   // set with the tables, then by every compress call for the next
     w.flags = off;        off = align_up(off + sizeof(uint32_t) * 64, A);
     w.zero_begin = off;
     w.hist = off;         off = align_up(off + sizeof(uint32_t) * kHistBins * L, A);

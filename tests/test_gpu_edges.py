@@ -240,3 +240,82 @@ def test_plans_of_many_layers(n, p, m):
             if m is not None:
                 assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)
         resid, mom = after, u_after
+
+
+@pytest.mark.parametrize("entry", ["decompress", "apply", "nsi", "dynamic_ratios"])
+def test_a_workspace_is_prepared_by_calls_that_run(entry):
+    """Whatever call lays the tables down prepares the workspace, and one that is only recorded into a graph does not count.  In memory
+    that holds something else: another entry point first, then a compress call that is recorded and not launched, then eager ones;
+    then the graph; then the memory is overwritten, the plan told so, another entry point called and the graph launched.  A candidate
+    layer, a full-map layer, one without anything to keep and rows of odd length; every result against the oracle.  New ratios and
+    another entry point leave the last call's paths to be asked for."""
+    import torch
+    from paper_2312_17530_amd.session import Session
+    shapes, ratios, p = [(64, 512), (100, 100), (34, 300), (17, 257)], [0.01, 0.9, 0.0, 0.02], 3
+    s = Session(shapes, p, 0.5, ratios)
+    rng = np.random.default_rng(5)
+    grads = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+    resid = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+    want = [oracle.compress_layer(g, r, p, 0.5, rho) for g, r, rho in zip(grads, resid, ratios)]
+    s.set_grad(grads)
+
+    def other_entry():
+        msg = (s.out_idx, s.out_val, torch.zeros_like(s.out_counts))
+        if entry == "decompress":
+            binding.rsdgc_decompress(s.plan, *msg, torch.zeros_like(s.grad), False, s.workspace)
+        elif entry == "apply":
+            binding.rsdgc_apply(s.plan, [msg, msg], torch.zeros_like(s.grad), 0.1, s.workspace)
+        elif entry == "nsi":
+            s.nsi()
+        else:
+            binding.rsdgc_dynamic_ratios(s.plan, s.grad, 0.1, s.workspace)
+        torch.cuda.synchronize()
+
+    def check(tag):
+        after = s.unpack(s.residual)
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o = want[l]
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (tag, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (tag, l)
+
+    s.workspace.fill_(0xa5)
+    other_entry()
+    source = s.residual
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        s.compress()
+    target = s.residual
+    for call in range(3):
+        s.set_residual(resid)
+        s.compress()
+        check(f"eager call {call} after the recorded one")
+    for call in range(13):                             # beyond the calls that sample
+        s.set_residual(resid)
+        s.compress()
+    s.residual = target                                # (where the graph's results are)
+
+    def replay(tag):
+        s.pack(resid, source)
+        for t in (s.out_idx, s.out_val, s.out_counts, s.out_centre_idx, s.out_centre_counts, target):
+            t.zero_()
+        graph.replay()
+        check(tag)
+
+    for rep in range(3):
+        replay(f"replay {rep}")
+    late = torch.cuda.CUDAGraph()                      # recorded on a prepared workspace
+    s.residual, s.residual_next = source, target
+    with torch.cuda.graph(late):
+        s.compress()
+    graph = late
+    replay("recorded on a prepared workspace")
+    s.workspace.fill_(0xa5)
+    binding.rsdgc_plan_forget_workspace(s.plan)
+    other_entry()
+    for rep in range(3):
+        replay(f"replay {rep} after the workspace was recycled")
+    paths = binding.rsdgc_last_paths(s.plan, s.workspace)
+    assert paths[2] == 2 and paths[1] == 1
+    s.set_ratios(ratios)
+    other_entry()
+    assert binding.rsdgc_last_paths(s.plan, s.workspace) == paths
