@@ -146,6 +146,16 @@ __device__ __forceinline__ uint32_t wave_append(uint32_t *counter, bool flag) {
     return base + static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
 }
 
+// Whether more than `limit` items have been appended to a stage in LDS (n: its counter): the same answer in every thread.
+// The first barrier has all appends so far counted; the second keeps a wave that is already through from appending
+// again before the last one has read the counter.
+__device__ __forceinline__ bool staged_more_than(const uint32_t &n, uint32_t limit) {
+    __syncthreads();
+    const bool more = n > limit;
+    __syncthreads();
+    return more;
+}
+
 // Inclusive scan over the 256 threads of a workgroup (4 waves of 64).
 __device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t *wave_tot /*[4]*/) {
     return block_scan_incl_n<4>(v, wave_tot);
@@ -1496,9 +1506,7 @@ __device__ __forceinline__ void gather_flush_keys(GatherShared &sh, const Gather
 
 // One round of at most 1024 appends (4 per thread) is about to start: make room for it.
 __device__ __forceinline__ void gather_make_room(GatherShared &sh, const GatherList &gl) {
-    __syncthreads();                       // appends of the previous round are counted
-    if (sh.n + 1024u > static_cast<uint32_t>(kStage))            // uniform
-        gather_flush_keys(sh, gl);
+    if (staged_more_than(sh.n, static_cast<uint32_t>(kStage) - 1024u)) gather_flush_keys(sh, gl);
 }
 
 // Stages key K (of a flagged lane) and counts its second digit.  Called by whole waves.
