@@ -3696,6 +3696,36 @@ __global__ __launch_bounds__(256) void k_dyn_sample(const ChunkInfo *__restrict_
     }
 }
 
+// Keys inside the bracket, held back by a workgroup of the main pass.
+struct DynStage {
+    uint2 ent[kDynStage];
+    uint32_t n, base;
+};
+__device__ __forceinline__ void dyn_stage_key(DynStage &sh, const DynSplitArgs &a, uint2 entry) {
+    const uint32_t pos = atomicAdd(&sh.n, 1u);
+    if (pos < kDynStage) {
+        sh.ent[pos] = entry;
+    } else {                               // (a chunk full of such keys)
+        const uint32_t g = atomicAdd(&a.state->n_list, 1u);
+        if (g < a.list_cap) a.list[g] = entry;
+    }
+}
+__device__ __forceinline__ void dyn_flush_stage(DynStage &sh, const DynSplitArgs &a) {
+    __syncthreads();
+    const uint32_t n = min(sh.n, kDynStage);
+    if (threadIdx.x == 0 && n) sh.base = atomicAdd(&a.state->n_list, n);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += 256)
+        if (sh.base + i < a.list_cap) a.list[sh.base + i] = sh.ent[i];
+    __syncthreads();
+    if (threadIdx.x == 0) sh.n = 0u;
+    __syncthreads();
+}
+// After a chunk: a stage that is half full is emptied.
+__device__ __forceinline__ void dyn_make_room(DynStage &sh, const DynSplitArgs &a) {
+    if (staged_more_than(sh.n, kDynStage / 2)) dyn_flush_stage(sh, a);
+}
+
 // The main pass.  Every workgroup reads the bracket off the sample's histogram (the same one in each): the K-th key's
 // rank in the sample, give or take eight standard deviations of it, on the safe side of the bin edges.  Then it strides over
 // the chunks; reading 4 bytes per weight is what bounds it.
@@ -3704,13 +3734,13 @@ __global__ __launch_bounds__(256) void k_dyn_sample(const ChunkInfo *__restrict_
 __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
                                                    const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t sub[kDynSubBins];
-    __shared__ uint2 stage[kDynStage];
+    __shared__ DynStage stage;
     __shared__ uint32_t wave_tot[4];
-    __shared__ uint32_t s_above, s_n, s_base, s_hi_bin, s_lo_bin, s_cum_hi, s_cum_lo;
+    __shared__ uint32_t s_above, s_sampled, s_hi_bin, s_lo_bin, s_cum_hi, s_cum_lo;
     const int tid = threadIdx.x;
     for (int b = tid; b < kDynSubBins; b += 256) sub[b] = 0u;
     if (tid == 0) {
-        s_above = s_n = 0u;
+        s_above = stage.n = 0u;
         s_hi_bin = kDynSampleBins;         // (nothing is certainly above)
         s_lo_bin = 0u;
         s_cum_hi = 0u;
@@ -3726,9 +3756,9 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
             own += q.x + q.y + q.z + q.w;
         }
         const uint32_t incl = block_scan_incl(own, wave_tot);
-        if (tid == 255) { s_base = incl; s_cum_lo = incl; }
+        if (tid == 255) { s_sampled = incl; s_cum_lo = incl; }
         __syncthreads();
-        const uint32_t S = s_base;
+        const uint32_t S = s_sampled;
         const float q = static_cast<float>(static_cast<double>(a.K) / static_cast<double>(a.n_weights));
         const float r = q * static_cast<float>(S), slack = 8.f * sqrtf(r * (1.f - q)) + 16.f;
         // bins are certainly above while the sample holds at most r - slack keys from their lower edge on; the bracket
@@ -3772,17 +3802,6 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
         }
         __syncthreads();
     };
-    auto flush_stage = [&]() {
-        __syncthreads();
-        const uint32_t n = min(s_n, kDynStage);
-        if (tid == 0 && n) s_base = atomicAdd(&a.state->n_list, n);
-        __syncthreads();
-        for (uint32_t i = tid; i < n; i += 256)
-            if (s_base + i < a.list_cap) a.list[s_base + i] = stage[i];
-        __syncthreads();
-        if (tid == 0) s_n = 0u;
-        __syncthreads();
-    };
     // (each XCD reads one contiguous part of a round of chunks: 132 -> 124 us on VGG-19)
     for (uint32_t c = xcd_contiguous(blockIdx.x, gridDim.x); c < n_chunks; c += gridDim.x) {
         const ChunkInfo ci = chunk_info[c];
@@ -3795,20 +3814,13 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
             const uint32_t rel = key - lo;
             if (rel < width) {                               // rare
                 atomicAdd(&sub[rel >> sub_shift], 1u);
-                const uint32_t pos = atomicAdd(&s_n, 1u);
-                if (pos < kDynStage) {
-                    stage[pos] = make_uint2(key, cur_l);
-                } else {                                     // (a chunk full of such keys)
-                    const uint32_t g = atomicAdd(&a.state->n_list, 1u);
-                    if (g < a.list_cap) a.list[g] = make_uint2(key, cur_l);
-                }
+                dyn_stage_key(stage, a, make_uint2(key, cur_l));
             }
         });
-        __syncthreads();
-        if (s_n > kDynStage / 2) flush_stage();              // uniform
+        dyn_make_room(stage, a);
     }
     if (cur_l != 0xffffffffu) flush_layer();
-    flush_stage();
+    dyn_flush_stage(stage, a);
     if (tid == 0 && above_all) atomicAdd(&a.state->above, above_all);
     for (int b = tid; b < kDynSubBins; b += 256) {
         const uint32_t c = sub[b];

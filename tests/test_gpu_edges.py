@@ -319,3 +319,26 @@ def test_a_workspace_is_prepared_by_calls_that_run(entry):
     s.set_ratios(ratios)
     other_entry()
     assert binding.rsdgc_last_paths(s.plan, s.workspace) == paths
+
+
+def test_dynamic_ratios_with_the_rank_among_like_weights():
+    """Layers whose weights all lie in the sample's bracket -- every chunk fills the stage of the listing pass and goes past its end --
+    between layers with hardly any there; ranks at the first, the middle and the last of those weights.  Whole numbers: all agree."""
+    import torch
+    shapes = [(1, 30000), (1000, 1021), (1, 30000), (64, 147)]
+    G = [r * c for r, c in shapes]
+    rng = np.random.default_rng(23)
+    weights = [(rng.choice([-1.0, 1.0], g) * rng.uniform(1.0, 1.03, g) if sh[0] == 1 else rng.standard_normal(g) * 0.25).astype(np.float32)
+               for sh, g in zip(shapes, G)]
+    plan = binding.rsdgc_plan(shapes, 3, 0.5, [0.02] * len(shapes))
+    ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    host = np.full(plan.total_elems, np.nan, np.float32)
+    for l, g in enumerate(G):
+        host[plan.layer_offset(l):plan.layer_offset(l) + g] = weights[l]
+    arena = _dev(host)
+    larger = sum(int((np.abs(w) >= 1.03).sum()) for w in weights)
+    for rank in (larger + 1, larger + 31000, larger + 59999):
+        rho = (rank - 0.5) / sum(G)
+        want = oracle.dynamic_ratios([w.reshape(sh) for w, sh in zip(weights, shapes)], rho)
+        for _ in range(3):
+            assert binding.rsdgc_dynamic_ratios(plan, arena, rho, ws) == want, rank

@@ -94,12 +94,52 @@ static bool complete() {
 }
 """
 
+# the chunks of k_dyn_split: some within half of the stage, some that fill it, some that go past its end
+_DYN = r"""
+constexpr uint32_t kDynStage = 1024;
+struct DynSplit { uint32_t n_list; };
+struct DynSplitArgs { DynSplit *state; uint2 *list; uint32_t list_cap; };
+%s
+constexpr uint32_t kChunks = 24;
+static DynStage sh;
+static DynSplit state;
+static std::vector<uint2> out;
+static DynSplitArgs args;
+static void reset() {
+    sh.n = state.n_list = 0;
+    out.assign(4 * 1024 * kChunks, uint2{~0u, 0u});
+    args = DynSplitArgs{&state, out.data(), static_cast<uint32_t>(out.size())};
+}
+static uint32_t keys_of(uint32_t chunk, uint32_t w) {
+    static const uint32_t n[6] = {100, 20, 0, 128, 300, 7};
+    return n[chunk %% 6] + (chunk %% 2) * w;
+}
+static void wave() {
+    for (uint32_t c = 0; c < kChunks; ++c) {
+        for (uint32_t i = 0; i < keys_of(c, threadIdx.x); ++i)
+            dyn_stage_key(sh, args, make_uint2((c * kWaves + threadIdx.x) * 1024u + i, c));
+        dyn_make_room(sh, args);
+    }
+    dyn_flush_stage(sh, args);
+}
+static bool complete() {
+    std::vector<uint32_t> want, got;
+    for (uint32_t i = 0; i < min<size_t>(state.n_list, out.size()); ++i) got.push_back(out[i].x);
+    for (uint32_t c = 0; c < kChunks; ++c)
+        for (uint32_t w = 0; w < kWaves; ++w)
+            for (uint32_t i = 0; i < keys_of(c, w); ++i) want.push_back((c * kWaves + w) * 1024u + i);
+    std::sort(want.begin(), want.end());
+    std::sort(got.begin(), got.end());
+    return want == got;
+}
+"""
+
 
 def _functions(names):
     """The definitions of these device functions, with the workgroup's 256 threads replaced by one per wave."""
     src, out = open(SOURCE).read(), []
     for name in names:
-        m = re.search(r"^__device__ __forceinline__ [^\n]*\b%s\(.*?^}\n" % name, src, re.S | re.M)
+        m = re.search(r"^(struct %s \{.*?^};|__device__ __forceinline__ [^\n]*\b%s\(.*?^})\n" % (name, name), src, re.S | re.M)
         assert m, name
         out.append(m.group(0))
     return "\n".join(out).replace("i += 256", "i += kWaves")
@@ -112,7 +152,8 @@ def _run(tmp_path, program):
     return subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True, timeout=120)
 
 
-STAGES = [("gather", _GATHER, ["staged_more_than", "gather_flush_keys", "gather_make_room"])]
+STAGES = [("gather", _GATHER, ["staged_more_than", "gather_flush_keys", "gather_make_room"]),
+          ("dynamic_ratios", _DYN, ["staged_more_than", "DynStage", "dyn_stage_key", "dyn_flush_stage", "dyn_make_room"])]
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
