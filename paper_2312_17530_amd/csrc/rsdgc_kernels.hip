@@ -3411,9 +3411,11 @@ __global__ __launch_bounds__(256) void k_apply_ranges(const ChunkInfo *__restric
 
 // One workgroup per half chunk; every wave requests the pairs of its messages before any is added (one load
 // latency for all eight instead of one each), and the weights are updated by all threads side by side, 16 bytes
-// each, where any of the four sums is not +0 (a thread that walked the bits of a touched-map word had ten
-// dependent updates in a row).  Moved on VGG-19 with eight messages: 560 MB for 340 MB of pairs and weights -- windows
-// of p elements reach 60 % of the weights' 64-byte lines.  275 us -> 169 us there.  Measured and not taken: every
+// read by each where any of the four sums is not +0 (a thread that walked the bits of a touched-map word had ten
+// dependent updates in a row).  Written are the named ones only: another stream may be at work on the others.  Moved on
+// VGG-19 with eight messages: 560 MB for 340 MB of pairs and weights -- windows of p elements reach 60 % of the weights'
+// 64-byte lines.  A call there 306 us before, now 207 us; 224 us where four single weights are written however many
+// are named, and 225 us where neighbouring lanes read and write single neighbouring weights.  Measured and not taken: every
 // thread requesting a pair of every message (178 us: the waves issue four times the instructions); one stretch
 // of 1024 elements per wave without barriers (175 us, and eight times the ranges to find); of 2048 (240 us: half
 // the waves); persistent waves with a cursor into every message (296 us), or software-pipelined (213 us: 153 registers).
@@ -3495,11 +3497,15 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const ChunkInfo *__restric
         if (!any[j]) continue;
         const float t[4] = {sum[j].x, sum[j].y, sum[j].z, sum[j].w};
         if (e + 3 < len) {
-            float v[4] = {old[j].x, old[j].y, old[j].z, old[j].w};
+            const float v[4] = {old[j].x - __fmul_rn(eta, t[0]), old[j].y - __fmul_rn(eta, t[1]),
+                                old[j].z - __fmul_rn(eta, t[2]), old[j].w - __fmul_rn(eta, t[3])};
+            if (__float_as_uint(t[0]) != 0u && __float_as_uint(t[1]) != 0u && __float_as_uint(t[2]) != 0u && __float_as_uint(t[3]) != 0u) {
+                *reinterpret_cast<float4 *>(w + e) = make_float4(v[0], v[1], v[2], v[3]);
+            } else {                       // (a weight that no message names is not written)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (__float_as_uint(t[q]) != 0u) v[q] = v[q] - __fmul_rn(eta, t[q]);
-            *reinterpret_cast<float4 *>(w + e) = make_float4(v[0], v[1], v[2], v[3]);
+                for (int q = 0; q < 4; ++q)
+                    if (__float_as_uint(t[q]) != 0u) w[e + q] = v[q];
+            }
         } else {
             for (uint32_t q = 0; q < 4 && e + q < len; ++q)
                 if (__float_as_uint(t[q]) != 0u) w[e + q] = w[e + q] - __fmul_rn(eta, t[q]);

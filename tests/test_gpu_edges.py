@@ -342,3 +342,43 @@ def test_dynamic_ratios_with_the_rank_among_like_weights():
         want = oracle.dynamic_ratios([w.reshape(sh) for w, sh in zip(weights, shapes)], rho)
         for _ in range(3):
             assert binding.rsdgc_dynamic_ratios(plan, arena, rho, ws) == want, rank
+
+
+def test_apply_leaves_weights_that_no_message_names_to_others():
+    """Every fourth weight is named by some message; the three between them are counted up by another stream meanwhile.  All steps and
+    all counts arrive: not even the value that was there is written to a weight that no message names."""
+    import torch
+    shapes, n_calls, n_counts = [(64, 4096), (50, 333), (1, 8190)], 40, 400
+    G = [r * c for r, c in shapes]
+    plan = binding.rsdgc_plan(shapes, 1, 0.5, [1.0] * len(shapes))
+    ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    rng = np.random.default_rng(31)
+    msgs = []
+    for _ in range(3):
+        idx = np.zeros(plan.out_capacity, np.uint32)
+        val = np.zeros(plan.out_capacity, np.float32)
+        counts = np.zeros(len(G), np.int32)
+        for l, g in enumerate(G):
+            i = (4 * np.flatnonzero(rng.random((g + 3) // 4) < 0.7)).astype(np.uint32)
+            o = plan.out_offset(l)
+            idx[o:o + i.size], val[o:o + i.size], counts[l] = i, 1.0, i.size
+        msgs.append((_dev(idx.view(np.int32)), _dev(val), _dev(counts)))
+    named = np.zeros(plan.total_elems, np.float32)
+    for m in msgs:
+        for l in range(len(G)):
+            o, n = plan.out_offset(l), int(m[2][l])
+            named[plan.layer_offset(l) + m[0][o:o + n].cpu().numpy()] += 1.0
+    base = rng.integers(0, 1000, plan.total_elems).astype(np.float32)
+    w = _dev(base)
+    between = w.view(-1, 4)[:, 1:]
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for call in range(n_calls):
+        with torch.cuda.stream(other):
+            for _ in range(n_counts // n_calls):
+                between.add_(1.0)
+        binding.rsdgc_apply(plan, msgs, w, 0.5, ws)
+    torch.cuda.synchronize()
+    want = base - n_calls * 0.5 * named                       # (small multiples of a half: exact)
+    want.reshape(-1, 4)[:, 1:] += n_counts
+    assert np.array_equal(w.cpu().numpy(), want)
