@@ -382,3 +382,41 @@ def test_apply_leaves_weights_that_no_message_names_to_others():
     want = base - n_calls * 0.5 * named                       # (small multiples of a half: exact)
     want.reshape(-1, 4)[:, 1:] += n_counts
     assert np.array_equal(w.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("m", [None, 0.9])
+@pytest.mark.parametrize("tall", [False, True], ids=["one_launch", "by_the_flag"])
+def test_predicted_bounds_that_fail_in_plans_of_several_sides(tall, m):
+    """Layers of every side on predicted bounds, then gradients a thousand times larger: all bounds fail in one call.  A small plan
+    scores such layers in the launch that finds out; one of 16384 tiles or more has that launch for its first side only, and the other
+    sides' launches go by the flag.  A layer always ranked on the full map and one without anything to keep among them; the first
+    calls and those around the failure against the oracle."""
+    from paper_2312_17530_amd.session import Session
+    shapes = [(33, 512), (16, 256), (130, 131), (130, 600), (17, 1028), (40, 260), (31, 255), (100, 100), (48, 64)]
+    sides = [3, 1, 5, 7, 1, 5, 7, 3, 3]
+    ratios = [0.02, 0.01, 0.02, 0.1, 0.005, 0.02, 0.05, 0.9, 0.0]
+    if tall:                                           # (two columns: tiles of 32 elements)
+        shapes, sides, ratios = shapes + [(262144, 2)], sides + [3], ratios + [0.002]
+    rng = np.random.default_rng(41)
+    s = Session(shapes, 3, 0.5, ratios, sides, momentum=m)
+    for t in range(17):
+        grads = [(rng.standard_normal(sh) * (10.0 if t == 14 else 1e-2)).astype(np.float32) for sh in shapes]
+        resid = s.unpack(s.residual)
+        mom = s.unpack(s.momentum_buf) if m is not None else [np.zeros(sh, np.float32) for sh in shapes]
+        s.set_grad(grads)
+        s.compress()
+        paths = binding.rsdgc_last_paths(s.plan, s.workspace)
+        if t == 13:                                    # (a bound may miss by chance, not those of a whole side)
+            assert {p for p, x in zip(sides, paths) if x == 3} == {1, 3, 5, 7} and paths[-1] == (3 if tall else 2)
+        if t == 14:
+            assert paths == [2 if rho == 0.0 else 1 for rho in ratios]
+        if 2 <= t < 13:
+            continue
+        after = s.unpack(s.residual)
+        u_after = s.unpack(s.momentum_buf) if m is not None else mom
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o, u_new = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, sides[l], 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+            if m is not None:
+                assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)

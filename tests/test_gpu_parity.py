@@ -1450,7 +1450,7 @@ def test_compress_can_be_captured_in_a_hip_graph_and_replayed(in_place, work_fee
     """rsdgc_compress enqueues kernels only (no allocation, no synchronisation, no memset node),
     so a caller may capture it.  Every replay must reproduce the eager result, with eager work
     and synchronisations between the replays.  With the work feed forced on, every replay also
-    has to find the feed's counters cleared by the call's own first kernel."""
+    has to find the feed's counters as the last kernels of the call before it have left them: clear."""
     import torch
     w = synth.config(1)
     grads = synth.gradients(w, 0)
