@@ -227,9 +227,11 @@ int rsdgc_compress_momentum(rsdgc_plan_t *plan, const float *grad, const float *
  * first), and layer l's keep ratio is survivors_l / G_l.
  *   weights     [device, const] float32 arena laid out like the gradient arena.
  *   ratios_out  [host] double[n_layers]; feed it to rsdgc_plan_set_ratios.
- * Runs four streaming passes on `stream` and waits for them (a per-epoch step,
- * not part of the per-iteration path); uses the workspace's scratch only, so it
- * must not overlap a compress call that uses the same workspace.             */
+ * Runs on `stream` and waits (a per-epoch step, not part of the per-iteration
+ * path): one streaming pass from 2^20 weights on (and up to 4096 layers), four
+ * more where a sample of the weights misled it; otherwise four.  Uses the
+ * workspace's scratch only, so it must not overlap a compress call that uses the
+ * same workspace.                                                            */
 int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global_ratio,
                          double *ratios_out, void *workspace, void *stream);
 

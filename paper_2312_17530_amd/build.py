@@ -14,9 +14,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp
 
 
 def build_library(verbose: bool = False, extra_flags=()) -> str:
-    """Compiles the library.  The compiler's per-kernel resource remarks are read back: the NSI
-    kernels are sized to run without register spills (the main pass at 96 VGPRs under an
-    occupancy hint), and a spill there costs tens of percent silently -- so it is reported."""
+    """Compiles the library.  The compiler's per-kernel resource remarks are read back: the kernels
+    are sized to run without register spills to memory (the main pass at 96 VGPRs under an occupancy
+    hint), and a spill there costs tens of percent silently -- so it is reported.  The two counting
+    forms of k_gather are known to: their comment says what that buys."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *FLAGS, "-Rpass-analysis=kernel-resource-usage", *extra_flags]
     for s in SOURCES:
@@ -46,8 +47,8 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
 
 
 def spilling_kernels(remarks):
-    """(mangled name, scratch bytes per lane) of the NSI kernels that use scratch memory, from
-    the lines of -Rpass-analysis=kernel-resource-usage."""
+    """(mangled name, scratch bytes per lane) of the kernels that use scratch memory, from the lines of
+    -Rpass-analysis=kernel-resource-usage."""
     out, name = [], None
     for line in remarks:
         m = re.search(r"Function Name: (\S+)", line)
@@ -55,7 +56,7 @@ def spilling_kernels(remarks):
             name = m.group(1)
             continue
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
-        if m and name and "k_nsi" in name and int(m.group(1)) > 0 and (name, int(m.group(1))) not in out:
+        if m and name and int(m.group(1)) > 0 and (name, int(m.group(1))) not in out:
             out.append((name, int(m.group(1))))
     return out
 

@@ -842,7 +842,9 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
 #pragma unroll 1
             for (int rr = wave; rr < ROWS; rr += 4) {
                 // (the columns' masks are worked out row by row: held over the rows they cost the pass its scalar registers, and
-                // 4 of 234 us with p = 5 on 103 M elements whose rows never come here)
+                // 4 of 234 us with p = 5 on 103 M elements whose rows never come here.  With the work feed 12 or 13
+                // scalar registers are still spilled to vector ones; the loop that was here before, with none, was no faster
+                // there: 242 against 240 us on one card)
                 int lane = tid & 63;
                 asm("" : "+v"(lane));
                 const int x = x0 - H + rr;
@@ -1140,7 +1142,7 @@ __device__ __forceinline__ void publish_threshold(PredState *__restrict__ pred, 
 // k_count and pass no counters here.  A mask word lies in one chunk: chunks are 256 words long and
 // a layer starts at a word boundary.
 struct CountCtx {
-    uint32_t *chunk_cnt, *group_cnt;   // cleared at the start of the call; null: the plan counts with k_count instead
+    uint32_t *chunk_cnt, *group_cnt;   // cleared by the find0 launch; null: the plan counts with k_count instead
     size_t word0;                      // the layer's first mask word
     uint32_t chunk_begin, cgroup_begin;
 };
@@ -1435,9 +1437,10 @@ __global__ __launch_bounds__(256) void k_find0_fallback_all(const Find0Args f, c
 constexpr int kStage = 2048;            // staged keys per workgroup (a round adds at most 1024)
 constexpr int kSlotsPerWave = kSlotGroup / 4;   // tile slots of a group that one wave of a gather workgroup takes
 // Small plans: a workgroup takes a quarter of a group.  Their gather is one short chain per workgroup -- entry, slots, marks,
-// words -- on a chip that is mostly idle, and four workgroups get through it in less time than one.  Where all of them no longer
-// are resident at once, the words that neighbours share, and their atomics, weigh more.  By groups, whole / quarters:
-// resnet18 13.7 / 10.1 us, 256 groups 16.8 / 12.4, resnet50 (377) 19.6 / 18.3, 512 groups 18.4 / 20.7 and with p = 1 12.4 / 17.5.
+// words -- on a chip that is mostly idle, and four workgroups get through it in less time than one.  The more groups there are,
+// the more the words that neighbours share, and their atomics, weigh; where the line lies between 377 and 512 groups was not
+// looked for.  By groups, whole / quarters: resnet18 13.7 / 10.1 us, 256 groups 16.8 / 12.4, resnet50 (377) 19.6 / 18.3, 512
+// groups 18.4 / 20.7 and with p = 1 12.4 / 17.5.
 constexpr int kSlotParts = 4;
 constexpr uint32_t kSplitGroups = 512;  // groups from which a workgroup takes a whole one
 
@@ -1519,6 +1522,8 @@ __device__ __forceinline__ void gather_stage_key(GatherShared &sh, bool hit, uns
     }
 }
 
+// Held to five waves per SIMD, which costs the counting forms two spilled registers (12 bytes of scratch a lane); with four and
+// none: resnet18 9.4 us for 9.6, resnet50 16.5 for 15.8, with all its vectors 23.3 for 22.6, VGG-19 35.1 for 30.6.
 template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
@@ -2493,7 +2498,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count(const CountGroup *__res
             a += __shfl_xor(a, d, 64);
             b += __shfl_xor(b, d, 64);
         }
-        if (tid == 0) {                    // (the group totals are cleared at the start of the call)
+        if (tid == 0) {                    // (the group totals are cleared by the find0 launch)
             if (mask && a) atomicAdd(&group_cnt[static_cast<size_t>(gr.group) * gstride], a);
             if (cmask && b) atomicAdd(&group_ccnt[static_cast<size_t>(gr.group) * gstride], b);
         }
@@ -2734,10 +2739,13 @@ __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict
 }
 
 // The same for plans of many chunks: one wave per chunk, four chunks per workgroup, no barrier.  What bounds the emit there is
-// the chain entry -> mask words and prefix -> values, so as many chunks as possible have to be on their way at once: 40.8 -> 30.7 us
-// on VGG-19 (17 k chunks; of the 40.8 us, 12 were the scattered reads and writes of v), 16.1 -> 10.1 us on the 25088 x 4096 layer at
-// 0.1 %.  On a plan of few chunks a workgroup each has the shorter chain (ResNet-18's 1.4 k chunks: 6.3 against 7.6 us; 3.1 k
-// chunks with dense ones among them: 14.5 against 16.9 us).
+// the chain entry -> mask words and prefix -> values, so as many chunks as possible have to be on their way at once.  Workgroup /
+// wave per chunk, both with the mask clearing: 25088 x 4096 at 0.1 % 16.0 / 9.3 us, 4.2 k chunks 12.9 / 10.6 at 2 % and 8.5 / 5.9
+// at 0.1 %, VGG-19 (17 k chunks, 2 %) 42.8 / 37.7 us on a residual carried for dozens of calls and 40.8 / 30.7 where the kept
+// elements lie closer (the same step again from one residual).  With momentum, whose kept elements are zeroed in two arenas,
+// the carried residual has it the other way round, 51.4 / 55.7 us, the repeated step 40.5 / 28.2.  On a plan of few chunks a
+// workgroup each has the shorter chain (ResNet-18's 1.4 k chunks: 6.3 / 7.6 us; 3.1 k chunks with dense ones among them:
+// 14.5 / 16.9 us).  The line is that of the plans that count as they mark.
 constexpr int kEmitList = 1024;            // kept elements of a chunk that a wave lists at a time
 
 // What one wave has written to LDS and reads back (its DS operations are carried out in order): keeps the compiler from
@@ -3735,8 +3743,8 @@ __device__ __forceinline__ void dyn_make_room(DynStage &sh, const DynSplitArgs &
 // The main pass.  Every workgroup reads the bracket off the sample's histogram (the same one in each): the K-th key's
 // rank in the sample, give or take eight standard deviations of it, on the safe side of the bin edges.  Then it strides over
 // the chunks; reading 4 bytes per weight is what bounds it.
-// VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding before; now this one of 132 us and
-// 38 us around it (a call, with its wait and read-back, 706 -> 202 us).
+// VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding before; now this one of 125 us and
+// 31 us around it (a call, with its wait and read-back, 706 -> 184 us).  Five waves per SIMD; held to six 137 us.
 __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
                                                    const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t sub[kDynSubBins];
@@ -4161,7 +4169,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     NsiAllArgs all = {};
     uint32_t all_items = 0;
     for (const PGroup &g : plan->groups) {
-        // this launch's work-feed counters (cleared at the start of the call)
+        // this launch's work-feed counters (left clear by the call before)
         const int pass_index = PASS == kPassSample ? 0 : PASS == kPassCapture ? 1 : 2;
         a.feed = feed + static_cast<size_t>((pass_index * 4 + group_index++) % kFeedSets) * kFeedDomains * kFeedStride;
         a.ca = plan->alpha / static_cast<double>(g.p * g.p);
