@@ -420,3 +420,47 @@ def test_predicted_bounds_that_fail_in_plans_of_several_sides(tall, m):
             assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
             if m is not None:
                 assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)
+
+
+@pytest.mark.parametrize("m", [None, 0.9])
+def test_block_calls_recorded_into_a_graph(m):
+    """The block reading in memory that held something else: an eager call, one recorded and not launched, eager ones again, then the
+    graph, and the graph once more after the workspace was recycled and used by an eager call.  Every result against the oracle."""
+    import torch
+    from paper_2312_17530_amd.session import BlockSession
+    shapes, ratios, sides = [(64, 512), (100, 100), (34, 300), (17, 257)], [0.01, 0.9, 0.0, 0.02], [3, 5, 3, 7]
+    s = BlockSession(shapes, 3, 0.5, ratios, sides, in_place=True, momentum=m)
+    rng = np.random.default_rng(6)
+    grads, resid, mom = ([(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes] for _ in range(3))
+    if m is None:
+        mom = [np.zeros(sh, np.float32) for sh in shapes]
+    want = [oracle.compress_layer_blocks_momentum(g, u, r, m or 0.0, p, 0.5, rho).layer
+            for g, u, r, p, rho in zip(grads, mom, resid, sides, ratios)]
+    s.set_grad(grads)
+
+    def run(tag, call):
+        s.set_residual(resid)
+        if m is not None:
+            s.set_momentum(mom)
+        for t in (s.out_blocks, s.out_val, s.out_counts):
+            t.zero_()
+        call()
+        after = s.unpack(s.residual)
+        for l, (blocks, val) in enumerate(s.results()):
+            o = want[l]
+            assert np.array_equal(blocks, o.blocks) and np.array_equal(_bits(val), _bits(np.asarray(o.val).reshape(-1))), (tag, l)
+            assert np.array_equal(_bits(after[l]), _bits(o.r_new)), (tag, l)
+
+    s.workspace.fill_(0xa5)
+    run("first", s.compress)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        s.compress()
+    run("eager after the recorded one", s.compress)
+    for rep in range(3):
+        run(f"replay {rep}", graph.replay)
+    s.workspace.fill_(0xa5)
+    binding.rsdgc_plan_forget_workspace(s.plan)
+    run("eager in recycled memory", s.compress)
+    for rep in range(3):
+        run(f"replay {rep} after that", graph.replay)
