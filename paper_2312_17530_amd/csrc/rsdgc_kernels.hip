@@ -1447,13 +1447,20 @@ constexpr uint32_t kSplitGroups = 512;  // groups from which a workgroup takes a
 constexpr int kTileMaskWords = kTileRows * kTileCols / 32;    // mask words of one tile (rows of 8 words)
 constexpr int kGatherCountSlots = 64;                          // chunks a group of tiles counts for in LDS (the rest: directly)
 
+// The words of a group of tiles in LDS: a slot's rows are 8 words, and a slot's pitch is 8 words more than its tile, so that the
+// words of a matrix row through eight slots lie in different banks.
+constexpr int kSlotPitch = kTileMaskWords + 8;
+template <int SLOTS>
+struct GroupMarks {
+    __attribute__((aligned(16))) uint32_t bits[SLOTS * kSlotPitch];   // mask words of the group of tiles being written
+    uint32_t ccnt[kGatherCountSlots];             // bits set, per chunk from the group's first one on
+    uint2 corner[SLOTS];                          // first row and column of every tile
+};
+
 struct GatherShared {
     union {
         unsigned long long ent[kStage];               // score-map roles: staged keys
-        struct {                                      // slot role:
-            uint32_t bits[kSlotGroup * kTileMaskWords];   // mask words of the group of tiles being written
-            uint32_t ccnt[kGatherCountSlots];             // bits set, per chunk from the group's first one on
-        };
+        GroupMarks<kSlotGroup> marks;                 // slot role
     };
     uint32_t hist[kLevel1Bins];         // second-digit counts
     DigitResult res;
@@ -1522,8 +1529,156 @@ __device__ __forceinline__ void gather_stage_key(GatherShared &sh, bool hit, uns
     }
 }
 
-// Held to five waves per SIMD, which costs the counting forms two spilled registers (12 bytes of scratch a lane); with four and
-// none: resnet18 9.4 us for 9.6, resnet50 16.5 for 15.8, with all its vectors 23.3 for 22.6, VGG-19 35.1 for 30.6.
+// A group of consecutive tile slots of a layer whose rows are whole mask words: every mask word of the layer then lies in
+// exactly one tile.  The workgroup builds the words of its tiles in LDS from the group's own candidates and writes them with
+// plain stores, whole cache lines at a time -- except the words that windows of other groups' candidates can reach (the h rows
+// along a tile's upper and lower edge, the first and last word of the group's run of tiles): those, and the bits that the group's
+// windows set in other groups' tiles, are ORed into the (cleared) mask.  Words without a bit are not written.
+// COUNT: the bits are counted as they are set (an OR tells which were new), per chunk, in LDS first: a group of tiles
+// lies in a few chunks.
+// What bounds this is the number of instructions, a few hundred per wave: no division by anything but the tile's corner (once per
+// tile), a window's rows addressed from the tile it starts in, and what crosses a tile's side edge in a second round that a wave
+// only takes when one of its lanes needs it.  With the place of every row and word worked out by itself (1700 instructions per
+// wave) k_gather took 29.9 us on VGG-19, now 24.2; 25088 x 4096 at 0.1 % with p = 5 21.0, now 14.6; ResNet-50 15.2, now 14.0.
+struct GroupGeom {
+    int h, C, R, tiles_x;
+    int g0, gn;                           // the group's first tile inside the layer, and how many
+    uint32_t words_x;                     // mask words per matrix row
+    uint32_t cl0;                         // COUNT: first chunk that the group's windows can reach
+    float inv_c;                          // a little below 1 / C
+    uint32_t *mask;                       // the layer's first mask word
+    CountCtx cctx;
+};
+__device__ __forceinline__ GroupGeom group_geom(const LayerDev &L, uint32_t g0, uint32_t gn, uint32_t *mask, const CountCtx &cctx) {
+    GroupGeom q;
+    q.h = (static_cast<int>(L.p) - 1) / 2;
+    q.C = static_cast<int>(L.C);
+    q.R = static_cast<int>(L.R);
+    q.tiles_x = static_cast<int>(L.tiles_x);
+    q.g0 = static_cast<int>(g0);
+    q.gn = static_cast<int>(gn);
+    q.words_x = L.C >> 5;
+    q.cl0 = 0;
+    q.inv_c = (1.f - 4.8e-7f) / static_cast<float>(L.C);
+    q.mask = mask + (static_cast<size_t>(L.elem_off) >> 5);
+    q.cctx = cctx;
+    return q;
+}
+// Clears the words and writes the tiles' corners; a barrier has to follow.
+template <int SLOTS>
+__device__ __forceinline__ void group_clear(const GroupGeom &q, GroupMarks<SLOTS> &sh) {
+    uint4 *b = reinterpret_cast<uint4 *>(sh.bits);
+    for (int i = threadIdx.x; i < SLOTS * kSlotPitch / 4; i += 256) b[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (threadIdx.x < static_cast<uint32_t>(kGatherCountSlots)) sh.ccnt[threadIdx.x] = 0u;
+    if (threadIdx.x < static_cast<uint32_t>(q.gn)) {
+        const uint32_t local = static_cast<uint32_t>(q.g0) + threadIdx.x, tr = local / static_cast<uint32_t>(q.tiles_x);
+        sh.corner[threadIdx.x] = make_uint2(tr * kTileRows, (local - tr * static_cast<uint32_t>(q.tiles_x)) * kTileCols);
+    }
+}
+// First chunk that the group's windows can reach: that of the element h rows above and h columns left of the first tile's corner.
+__device__ __forceinline__ uint32_t group_first_chunk(const GroupGeom &q, const uint2 corner) {
+    return static_cast<uint32_t>((static_cast<size_t>(max(0, static_cast<int>(corner.x) - q.h)) * static_cast<uint32_t>(q.C) +
+                                  static_cast<size_t>(max(0, static_cast<int>(corner.y) - q.h))) / kChunk);
+}
+template <int SLOTS>
+__device__ __forceinline__ void group_count(const GroupGeom &q, GroupMarks<SLOTS> &sh, uint32_t word, uint32_t n) {
+    const uint32_t slot = (word >> 8) - q.cl0;                       // (a chunk is 256 words)
+    if (slot < static_cast<uint32_t>(kGatherCountSlots)) atomicAdd(&sh.ccnt[slot], n);
+    else count_add_chunk(q.cctx, q.cl0 + slot, n);
+}
+// The window of the candidate with flat index i, which lies in the group's tile sidx.
+template <bool COUNT, int SLOTS>
+__device__ __forceinline__ void group_mark(const GroupGeom &q, GroupMarks<SLOTS> &sh, int sidx, uint32_t i) {
+    const uint2 corner = sh.corner[sidx];
+    const uint32_t C = static_cast<uint32_t>(q.C);
+    const uint32_t d = i - (corner.x * C + corner.y);
+    // row inside the tile (below 16): the product is exact or one too low (inv_c is 2^-21 low, the roundings add up to less)
+    uint32_t dx = static_cast<uint32_t>(static_cast<float>(d) * q.inv_c);
+    uint32_t dy = d - dx * C;
+    if (dy >= C) { ++dx; dy -= C; }
+    const int h = q.h;
+    // the window's columns, counted from the tile's first one; at most one side lies in a neighbouring tile
+    const int ya = max(static_cast<int>(dy) - h, -static_cast<int>(corner.y));
+    const int yb = min(static_cast<int>(dy) + h, q.C - 1 - static_cast<int>(corner.y));
+    const int oa = max(static_cast<int>(dx) - h, -static_cast<int>(corner.x));           // ... and rows
+    const int ob = min(static_cast<int>(dx) + h, q.R - 1 - static_cast<int>(corner.x));
+    const int side = ya < 0 ? -1 : yb >= kTileCols ? 1 : 0;
+    int s = sidx, a = max(ya, 0), b = min(yb, kTileCols - 1);
+#pragma unroll 1
+    for (int part = 0;; ++part) {
+        const uint32_t w0 = static_cast<uint32_t>(a) >> 5, b0 = static_cast<uint32_t>(a) & 31u;
+        const uint32_t len = static_cast<uint32_t>(b - a + 1), run = (1u << len) - 1u;
+        const uint32_t bits0 = run << b0, bits1 = b0 + len > 32u ? run >> (32u - b0) : 0u;
+        const uint32_t col_word = ((corner.y + static_cast<uint32_t>((s - sidx) * kTileCols)) >> 5) + w0;
+#pragma unroll 1
+        for (int o = oa; o <= ob; ++o) {
+            int t = s, row = o;
+            if (o < 0) { t -= q.tiles_x; row += kTileRows; }
+            if (o >= kTileRows) { t += q.tiles_x; row -= kTileRows; }
+            if (static_cast<uint32_t>(t) < static_cast<uint32_t>(q.gn)) {
+                uint32_t *w = sh.bits + t * kSlotPitch + row * (kTileCols / 32) + w0;
+                atomicOr(w, bits0);
+                if (bits1) atomicOr(w + 1, bits1);
+            } else {                      // another group's tile: straight into the mask
+                const uint32_t word = static_cast<uint32_t>(static_cast<int>(corner.x) + o) * q.words_x + col_word;
+                uint32_t *w = q.mask + word;
+                if (!COUNT) {
+                    atomicOr(w, bits0);
+                    if (bits1) atomicOr(w + 1, bits1);
+                } else {                  // ... and the new bits counted
+#pragma unroll
+                    for (uint32_t j = 0; j < 2u; ++j) {
+                        const uint32_t bits = j == 0u ? bits0 : bits1;
+                        if (bits == 0u) continue;
+                        const uint32_t fresh = __popc(bits & ~atomicOr(w + j, bits));
+                        if (fresh) group_count(q, sh, word + j, fresh);
+                    }
+                }
+            }
+        }
+        if (part != 0 || side == 0) break;
+        s = sidx + side;
+        a = side < 0 ? ya + kTileCols : 0;
+        b = side < 0 ? kTileCols - 1 : yb - kTileCols;
+    }
+}
+// The group's words, after a barrier.  Neighbouring tiles of one tile row are neighbours in memory: consecutive threads walk
+// along a matrix row through the group's tiles, so a wave writes whole cache lines.
+template <bool COUNT, int SLOTS>
+__device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS> &sh) {
+    constexpr uint32_t ROW = SLOTS * (kTileCols / 32);              // words of one row through the group
+    const uint32_t tid = threadIdx.x, ww = tid & 7u;
+    const int sidx = static_cast<int>((tid / 8u) % static_cast<uint32_t>(SLOTS));
+    if (sidx < q.gn) {
+        const uint2 corner = sh.corner[sidx];
+        const int h = q.h, below = q.R - static_cast<int>(corner.x) - kTileRows;             // rows of the matrix below the tile
+        const bool side = (ww == 0u && sidx == 0 && corner.y > 0u) ||
+                          (ww == 7u && sidx == q.gn - 1 && static_cast<int>(corner.y) + kTileCols < q.C);
+        const uint32_t first = corner.x * q.words_x + (corner.y >> 5) + ww;
+        for (uint32_t row = tid / ROW; row < static_cast<uint32_t>(kTileRows); row += 256u / ROW) {
+            const uint32_t word = sh.bits[sidx * kSlotPitch + row * (kTileCols / 32) + ww];
+            if (word == 0u) continue;
+            const uint32_t at = first + row * q.words_x;
+            uint32_t *dst = q.mask + at;
+            const int rr = static_cast<int>(row);
+            uint32_t fresh = word;
+            if (side || (rr < h && corner.x > 0u) || (rr >= kTileRows - h && below > 0)) {
+                if (COUNT) fresh = word & ~atomicOr(dst, word);
+                else atomicOr(dst, word);
+            } else {
+                *dst = word;
+            }
+            if (COUNT && fresh) group_count(q, sh, at, __popc(fresh));
+        }
+    }
+    static_assert(kGatherCountSlots == 64, "one lane of the first wave per counted chunk");
+    if (COUNT) {
+        __syncthreads();
+        if (tid < 64) count_flush_wave0(q.cctx, q.cl0, sh.ccnt[tid]);
+    }
+}
+
+// Held to five waves per SIMD.
 template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
@@ -1534,7 +1689,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                                                               : blockIdx.x - gl.n_map_wgs - gl.n_slot_wgs;
     const uint32_t stride = role == 0 ? gl.n_map_wgs : role == 1 ? gl.n_slot_wgs
                                                                  : gridDim.x - gl.n_map_wgs - gl.n_slot_wgs;
-    constexpr uint32_t SLOTS = kSlotGroup / PARTS;
+    constexpr int SLOTS = kSlotGroup / PARTS;
     const uint32_t n_items = role == 0 ? gl.n_map_chunks : role == 1 ? gl.n_cand_groups * PARTS : gl.n_chunks;
     const DirEntry *__restrict__ dir = gl.chunk_dir;
     if (first >= n_items) return;
@@ -1569,7 +1724,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             const uint32_t s0 = (it % PARTS) * SLOTS;
             if (s0 >= ge.ntile) continue;
             ge.slot0 += s0;
-            ge.ntile = static_cast<uint8_t>(min(static_cast<uint32_t>(ge.ntile) - s0, SLOTS));
+            ge.ntile = static_cast<uint8_t>(min(static_cast<uint32_t>(ge.ntile) - s0, static_cast<uint32_t>(SLOTS)));
             ent0 = a.slot_ent + (((static_cast<uint64_t>(ge.ent0_high) << 32) | ge.ent0_low) << 1) + s0 * ge.slot_cap;
         } else {
             e = dir_advance(dir, gl.n_layers, e, it);
@@ -1672,129 +1827,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                                      (static_cast<int>(L.p) - 1) / 2};
             const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
             if ((L.C & 31u) == 0u) {
-                // Rows of whole mask words: every mask word of the layer lies in exactly one tile.  The
-                // workgroup builds the words of its group of tiles in LDS from the group's own candidates
-                // and writes them with plain stores, whole cache lines at a time -- except the words that
-                // windows of other groups' candidates can reach (the h rows along a tile's upper and lower
-                // edge, the first and last word of the group's run of tiles): those, and the bits that the
-                // group's windows set in other groups' tiles, are ORed into the (cleared) mask.
-                // The bits are counted as they are set (an OR tells which were new), per chunk, in LDS
-                // first: a group of tiles lies in a few chunks.
-                const int h = geom.h, C = geom.C, R = geom.R;
-                const int tiles_x = static_cast<int>(L.tiles_x);
-                const int g0 = static_cast<int>(ge.slot0 - L.tile_begin_all), gn = static_cast<int>(ge.ntile);
-                // first chunk that the group's windows can reach: that of the element h rows above and h
-                // columns left of the first tile's corner
-                const uint32_t cl0 = static_cast<uint32_t>(
-                    (static_cast<size_t>(max(0, (g0 / tiles_x) * kTileRows - h)) * C +
-                     static_cast<size_t>(max(0, (g0 % tiles_x) * kTileCols - h))) / kChunk);
-                __syncthreads();                                 // (the previous group's words are written)
-                for (int i = tid; i < static_cast<int>(SLOTS) * kTileMaskWords; i += 256) sh.bits[i] = 0u;
-                if (COUNT && tid < kGatherCountSlots) sh.ccnt[tid] = 0u;
+                GroupMarks<SLOTS> &marks = *reinterpret_cast<GroupMarks<SLOTS> *>(&sh.marks);      // (a quarter needs less)
+                GroupGeom q = group_geom(L, ge.slot0 - L.tile_begin_all, ge.ntile, a.mask, cctx);
+                // LPS lanes per tile slot; a round covers as many entries of each.  The first entries are requested
+                // beside the slot's count (a slot always has them; past the count they hold anything)
+                constexpr uint32_t LPS = 256 / SLOTS;
+                const int sidx = tid / static_cast<int>(LPS);
+                const uint32_t j0 = static_cast<uint32_t>(tid) % LPS;
+                const unsigned long long *__restrict__ slot = ent0 + static_cast<size_t>(sidx) * slot_cap;
+                unsigned long long K = 0;
+                uint32_t cnt = 0;
+                if (sidx < q.gn) {
+                    cnt = a.slot_cnt[ge.slot0 + static_cast<uint32_t>(sidx)];
+                    if (j0 < slot_cap) K = slot[j0];
+                    cnt = min(cnt, slot_cap);
+                }
+                if (it != first) __syncthreads();                // (the previous group's words are written)
+                group_clear(q, marks);
                 __syncthreads();
-                {
-                    // LPS lanes per tile slot; a round covers as many entries of each.  The first entries are requested
-                    // beside the slot's count (a slot always has them; past the count they hold anything)
-                    constexpr uint32_t LPS = 256 / SLOTS;
-                    const int sidx0 = tid / static_cast<int>(LPS);
-                    const uint32_t j0 = static_cast<uint32_t>(tid) % LPS;
-                    const unsigned long long *__restrict__ slot = ent0 + static_cast<size_t>(sidx0) * slot_cap;
-                    unsigned long long K0 = 0;
-                    uint32_t cnt = 0;
-                    if (sidx0 < gn) {
-                        cnt = a.slot_cnt[ge.slot0 + static_cast<uint32_t>(sidx0)];
-                        if (j0 < slot_cap) K0 = slot[j0];
-                        cnt = min(cnt, slot_cap);
-                    }
-                    for (uint32_t j = j0; j < cnt; j += LPS) {
-                        const unsigned long long K = j == j0 ? K0 : slot[j];
-                        const uint32_t score = static_cast<uint32_t>(K >> 32);
-                        if (score >= above) {                    // selected for certain: its window, tile by tile
-                            const uint32_t i = ~static_cast<uint32_t>(K);
-                            const int xc = static_cast<int>(i / static_cast<uint32_t>(C));
-                            const int yc = static_cast<int>(i - static_cast<uint32_t>(xc) * static_cast<uint32_t>(C));
-                            const int wx0 = max(0, xc - h), wx1 = min(R - 1, xc + h);
-                            const int wy0 = max(0, yc - h), wy1 = min(C - 1, yc + h);
-                            for (int tr = wx0 / kTileRows; tr <= wx1 / kTileRows; ++tr)
-                                for (int tc = wy0 / kTileCols; tc <= wy1 / kTileCols; ++tc) {
-                                    const int sidx = tr * tiles_x + tc - g0;
-                                    const bool mine = static_cast<uint32_t>(sidx) < static_cast<uint32_t>(gn);
-                                    const int r0 = tr * kTileRows, c0 = tc * kTileCols;
-                                    const int xa = max(r0, wx0), xb = min(r0 + kTileRows - 1, wx1);
-                                    const int ya = max(c0, wy0) - c0, yb = min(c0 + kTileCols - 1, wy1) - c0;
-                                    const uint32_t w0 = static_cast<uint32_t>(ya) >> 5, b0 = static_cast<uint32_t>(ya) & 31u;
-                                    const uint32_t len = static_cast<uint32_t>(yb - ya + 1);
-                                    const uint32_t run = (1u << len) - 1u;
-                                    for (int x = xa; x <= xb; ++x) {
-                                        if (mine) {
-                                            uint32_t *row = sh.bits + sidx * kTileMaskWords + (x - r0) * (kTileCols / 32);
-                                            atomicOr(&row[w0], run << b0);
-                                            if (b0 + len > 32u) atomicOr(&row[w0 + 1], run >> (32u - b0));
-                                        } else if (!COUNT) { // another group's tile: straight into the mask
-                                            uint32_t *row = a.mask + ((geom.elem_off + static_cast<size_t>(x) * C + c0) >> 5);
-                                            atomicOr(&row[w0], run << b0);
-                                            if (b0 + len > 32u) atomicOr(&row[w0 + 1], run >> (32u - b0));
-                                        } else {             // ... and the new bits counted
-                                            const size_t wrow = (static_cast<size_t>(x) * C + c0) >> 5;   // first word of the tile row, inside the layer
-                                            uint32_t *row = a.mask + (geom.elem_off >> 5) + wrow;
-#pragma unroll
-                                            for (uint32_t part = 0; part < 2u; ++part) {
-                                                const uint32_t bits = part == 0u ? run << b0 : (b0 + len > 32u ? run >> (32u - b0) : 0u);
-                                                if (bits == 0u) continue;
-                                                const uint32_t fresh = __popc(bits & ~atomicOr(&row[w0 + part], bits));
-                                                if (fresh) {
-                                                    const uint32_t slot = static_cast<uint32_t>((wrow + w0 + part) >> 8) - cl0;
-                                                    if (slot < static_cast<uint32_t>(kGatherCountSlots)) atomicAdd(&sh.ccnt[slot], fresh);
-                                                    else count_add_chunk(cctx, cl0 + slot, fresh);
-                                                }
-                                            }
-                                        }
-                                    }
-                                }
-                            if (a.cmask) {
-                                const size_t pos = geom.elem_off + i;
-                                atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
-                            }
-                        } else if (score - lo < width) {         // in the threshold bucket (never when the layer is done):
-                            const uint32_t pos = atomicAdd(list.cnt, 1u);       // few of them, one atomic each
-                            if (pos < list.cap) list.ent[pos] = K;
-                            atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
+                if (COUNT) q.cl0 = group_first_chunk(q, marks.corner[0]);
+                for (uint32_t j = j0; j < cnt; j += LPS) {
+                    if (j != j0) K = slot[j];
+                    const uint32_t score = static_cast<uint32_t>(K >> 32);
+                    if (score >= above) {                        // selected for certain
+                        const uint32_t i = ~static_cast<uint32_t>(K);
+                        group_mark<COUNT>(q, marks, sidx, i);
+                        if (a.cmask) {
+                            const size_t pos = geom.elem_off + i;
+                            atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
                         }
+                    } else if (score - lo < width) {             // in the threshold bucket (never when the layer is done):
+                        const uint32_t pos = atomicAdd(list.cnt, 1u);           // few of them, one atomic each
+                        if (pos < list.cap) list.ent[pos] = K;
+                        atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
                     }
                 }
                 __syncthreads();
-                // The group's words.  Neighbouring tiles of one tile row are neighbours in memory:
-                // consecutive threads walk along a matrix row through the group's tiles, so a wave writes
-                // whole cache lines.  Words past the end of a matrix row or below the last row do not exist.
-                for (int i = tid; i < gn * kTileMaskWords; i += 256) {
-                    const int rr = i / (gn * 8), rem = i - rr * (gn * 8), sidx = rem >> 3, ww = rem & 7;
-                    const int local = g0 + sidx, tr = local / tiles_x, tc = local - tr * tiles_x;
-                    const int x = tr * kTileRows + rr, y = tc * kTileCols + 32 * ww;
-                    if (x < R && y < C) {
-                        const uint32_t word = sh.bits[sidx * kTileMaskWords + rr * 8 + ww];
-                        const size_t e0 = static_cast<size_t>(x) * C + y;
-                        uint32_t *dst = a.mask + ((geom.elem_off + e0) >> 5);
-                        const bool shared = (rr < h && tr > 0) || (rr >= kTileRows - h && x + h >= (tr + 1) * kTileRows && (tr + 1) * kTileRows < R) ||
-                                            (ww == 0 && sidx == 0 && tc > 0) ||
-                                            (ww == 7 && sidx == gn - 1 && tc < tiles_x - 1);
-                        uint32_t fresh = word;
-                        if (!shared) *dst = word;
-                        else if (word != 0u) {
-                            if (COUNT) fresh = word & ~atomicOr(dst, word);
-                            else atomicOr(dst, word);
-                        }
-                        if (COUNT && fresh) {
-                            const uint32_t slot = static_cast<uint32_t>(e0 / kChunk) - cl0;
-                            if (slot < static_cast<uint32_t>(kGatherCountSlots)) atomicAdd(&sh.ccnt[slot], __popc(fresh));
-                            else count_add_chunk(cctx, cl0 + slot, __popc(fresh));
-                        }
-                    }
-                }
-                static_assert(kGatherCountSlots == 64, "one lane of the first wave per counted chunk");
-                if (COUNT) {
-                    __syncthreads();
-                    if (tid < 64) count_flush_wave0(cctx, cl0, sh.ccnt[tid]);
-                }
+                group_write<COUNT>(q, marks);
             } else {
             // each wave takes 4 of the group's tile slots; a round covers 64 entries of each
             uint32_t cnt[kSlotsPerWave];

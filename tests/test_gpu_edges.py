@@ -464,3 +464,28 @@ def test_block_calls_recorded_into_a_graph(m):
     run("eager in recycled memory", s.compress)
     for rep in range(3):
         run(f"replay {rep} after that", graph.replay)
+
+
+@pytest.mark.parametrize("p", [1, 3, 5, 7])
+@pytest.mark.parametrize("more, feed", [(0, False), (0, True), (4100, False)], ids=["small", "small_fed", "many_chunks"])
+def test_windows_across_the_edges_of_tiles_and_groups(p, more, feed):
+    """Rows of whole mask words: windows that reach into the tiles above, below and beside their own, of the same group of
+    tiles and of another, one tile wide, a row of them and several; last tiles of one row and of one word.  Few values, so
+    that ranks are settled among equal scores.  Four calls; every one against the oracle."""
+    from paper_2312_17530_amd.session import Session
+    shapes = [(33, 544), (16, 256), (17, 512), (300, 32), (49, 288), (18, 4640), (290, 800), (40, 992)] + [(1, 1 + l % 70) for l in range(more)]
+    ratios = [0.03, 0.05, 0.02, 0.05, 0.1, 0.03, 0.06, 0.004] + [(0.0, 1.0, 0.3)[l % 3] for l in range(more)]
+    rng = np.random.default_rng(p)
+    s = Session(shapes, p, 0.5, ratios, work_feed=2 if feed else 0)
+    resid = [np.zeros(sh, np.float32) for sh in shapes]
+    for t in range(4):
+        grads = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+        grads[4] = (rng.integers(-3, 4, shapes[4]) * 0.01).astype(np.float32)
+        s.set_grad(grads)
+        s.compress()
+        after = s.unpack(s.residual)
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o = oracle.compress_layer(grads[l], resid[l], p, 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+        resid = after
