@@ -29,6 +29,8 @@ constexpr int kListShards = 16;      // a layer's threshold-bucket list is fille
 constexpr int kGroupCntStride = 32;   // words between two chunk-group counters where many workgroups add to one: a cache line each
 constexpr uint32_t kInlineCountChunks = 4096;   // plans up to this many chunks (33 M elements) count their kept elements where the bits are set
 constexpr int kListCntStride = 32;   // uint32 between two of them (one 128-byte line each)
+constexpr uint32_t kSelectTiles = 1024;  // a plan goes through k_select while its largest layer has at most so many tiles ...
+constexpr uint32_t kSelectMaxK = 32768;  // ... and selects at most so many centres
 constexpr int kBigMapLayer = 1 << 20; // elements from which a full-map layer's bucket list goes through k_filter
 // Candidate bound predicted from the thresholds of the two calls before, on a log2 scale: used
 // while the threshold moved by at most kTrendMaxLog2 between those calls.
@@ -285,6 +287,7 @@ struct rsdgc_plan_s {
     uint64_t slot_entries = 0;          // composite keys in all tile slots together
     uint32_t n_slot_groups = 0;
     bool any_large = false;
+    bool one_select = false;            // every layer that selects something is on the candidate path and small enough for k_select
     std::vector<uint16_t> big_map_layers;   // layers of a million elements or more that are ranked on the full map
     int64_t total_elems = 0;
     int64_t out_capacity = 0;

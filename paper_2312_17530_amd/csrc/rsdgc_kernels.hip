@@ -27,6 +27,7 @@
 //              (Algorithm 1's ranking; Eq. 11's k_l) and keeps the threshold for the next calls
 //   mark       the bucket's keys that reach the threshold set the bits of their p x p window
 //              (Section III-C: whole neighbourhoods are kept); full-map layers: every centre
+//              (small plans with every layer on the candidate path: find0 to mark are one launch, k_select)
 //   count      kept elements per chunk and per group of chunks (no scan kernel: each consumer
 //              adds up its own prefix from those); small plans count as they mark
 //   emit       ordered (index, value) pairs and the residual update (Eq. 12): either only the
@@ -40,6 +41,7 @@
 //   ranking digits   block_find_digit, publish_threshold
 //   hint .. finish   k_hint, k_find0, k_find0_fallback(_all), k_gather, k_filter, k_finish: bounds and
 //                    the radix select
+//   select           k_select: find0 to mark in one launch, small plans
 //   mark             k_mark: p x p windows into the bitmask; k_mark_flat: block grids
 //   count            k_count, chunk_prefix_wave0
 //   emit             k_emit, k_emit_sparse, k_emit_waves, k_emit_centres
@@ -508,6 +510,8 @@ struct NsiArgs {
     uint32_t *slot_cnt;           // [n_tiles_all]
     unsigned long long *slot_ent; // per large layer n_tiles slots of slot_cap entries, from the layer's slot_off
     double ca, cb;                // alpha / p^2, (1 - alpha) / p^2: NSI = ca * sum|w| + cb * sqrt(p^2 * sum w^2 - (sum w)^2)
+    uint4 *counts;                // main pass: chunk counters that it clears where k_select follows (no launch of k_find0 does)
+    uint32_t n16;
     uint32_t *feed;               // work-feed counters of this launch (all but kPassMapOnly)
     uint32_t feed_shift;          // log2 of the items per domain and stretch
 };
@@ -648,6 +652,8 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             return;
         }
     }
+    if (CAPTURE && !FEED)                  // (the last kernel of the call before still read them)
+        for (uint32_t j = wg * 256u + tid; j < a.n16; j += n_wgs * 256u) a.counts[j] = make_uint4(0, 0, 0, 0);
     WorkFeed feed;
     uint32_t first;
     if (FEED) {
@@ -1296,6 +1302,23 @@ struct Find0Args {
     uint32_t n16;
     int n_layers;
 };
+// What a layer remembers of a bound that failed (st: its state, r: what the candidates' first digit gave).
+__device__ __forceinline__ void bound_failed(PredState *__restrict__ pred, uint32_t l, uint32_t k, const SelState &st,
+                                             const DigitResult &r) {
+    PredState ps = pred[l];
+    ps.cooldown = kCooldownCalls;
+    if (st.predicted & 1u) {
+        // the margin of the predicted bounds follows the way this one failed: too few centres above
+        // it -- twice the margin; a tile with too many, or a threshold beyond the bins -- the bound
+        // lay too low, and a wider margin would only repeat that: half of it, down to its start value
+        const float init = margin_init_log2(k);
+        const float m = ps.margin > 0.f ? ps.margin : init;
+        const bool too_low = st.overflow != 0u || (r.found && r.digit == static_cast<uint32_t>(kFineBins - 1));
+        ps.margin = too_low ? fmaxf(0.5f * m, init) : fminf(2.f * m, kMarginMaxLog2);
+    }
+    pred[l] = ps;
+}
+
 __device__ __forceinline__ void find0(const Find0Args &f, int l) {
     __shared__ uint32_t wave_tot[4];
     __shared__ DigitResult res;
@@ -1349,18 +1372,7 @@ __device__ __forceinline__ void find0(const Find0Args &f, int l) {
             ns.mode = kModeFullMap;
             f.state[l] = ns;
             f.flags[0] = 1u;                 // the fallback pass has work
-            PredState ps = f.pred[l];
-            ps.cooldown = kCooldownCalls;
-            if (st.predicted & 1u) {
-                // the margin of the predicted bounds follows the way this one failed: too few centres above
-                // it -- twice the margin; a tile with too many, or a threshold beyond the bins -- the bound
-                // lay too low, and a wider margin would only repeat that: half of it, down to its start value
-                const float init = margin_init_log2(f.layers[l].k);
-                const float m = ps.margin > 0.f ? ps.margin : init;
-                const bool too_low = st.overflow != 0u || (r.found && r.digit == static_cast<uint32_t>(kFineBins - 1));
-                ps.margin = too_low ? fmaxf(0.5f * m, init) : fminf(2.f * m, kMarginMaxLog2);
-            }
-            f.pred[l] = ps;
+            bound_failed(f.pred, l, f.layers[l].k, st, r);
         }
         return;
     }
@@ -1565,10 +1577,10 @@ __device__ __forceinline__ GroupGeom group_geom(const LayerDev &L, uint32_t g0, 
     return q;
 }
 // Clears the words and writes the tiles' corners; a barrier has to follow.
-template <int SLOTS>
+template <int THREADS, int SLOTS>
 __device__ __forceinline__ void group_clear(const GroupGeom &q, GroupMarks<SLOTS> &sh) {
     uint4 *b = reinterpret_cast<uint4 *>(sh.bits);
-    for (int i = threadIdx.x; i < SLOTS * kSlotPitch / 4; i += 256) b[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = threadIdx.x; i < SLOTS * kSlotPitch / 4; i += THREADS) b[i] = make_uint4(0u, 0u, 0u, 0u);
     if (threadIdx.x < static_cast<uint32_t>(kGatherCountSlots)) sh.ccnt[threadIdx.x] = 0u;
     if (threadIdx.x < static_cast<uint32_t>(q.gn)) {
         const uint32_t local = static_cast<uint32_t>(q.g0) + threadIdx.x, tr = local / static_cast<uint32_t>(q.tiles_x);
@@ -1644,7 +1656,7 @@ __device__ __forceinline__ void group_mark(const GroupGeom &q, GroupMarks<SLOTS>
 }
 // The group's words, after a barrier.  Neighbouring tiles of one tile row are neighbours in memory: consecutive threads walk
 // along a matrix row through the group's tiles, so a wave writes whole cache lines.
-template <bool COUNT, int SLOTS>
+template <bool COUNT, int THREADS, int SLOTS>
 __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS> &sh) {
     constexpr uint32_t ROW = SLOTS * (kTileCols / 32);              // words of one row through the group
     const uint32_t tid = threadIdx.x, ww = tid & 7u;
@@ -1655,7 +1667,7 @@ __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS
         const bool side = (ww == 0u && sidx == 0 && corner.y > 0u) ||
                           (ww == 7u && sidx == q.gn - 1 && static_cast<int>(corner.y) + kTileCols < q.C);
         const uint32_t first = corner.x * q.words_x + (corner.y >> 5) + ww;
-        for (uint32_t row = tid / ROW; row < static_cast<uint32_t>(kTileRows); row += 256u / ROW) {
+        for (uint32_t row = tid / ROW; row < static_cast<uint32_t>(kTileRows); row += THREADS / ROW) {
             const uint32_t word = sh.bits[sidx * kSlotPitch + row * (kTileCols / 32) + ww];
             if (word == 0u) continue;
             const uint32_t at = first + row * q.words_x;
@@ -1843,7 +1855,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                     cnt = min(cnt, slot_cap);
                 }
                 if (it != first) __syncthreads();                // (the previous group's words are written)
-                group_clear(q, marks);
+                group_clear<256>(q, marks);
                 __syncthreads();
                 if (COUNT) q.cl0 = group_first_chunk(q, marks.corner[0]);
                 for (uint32_t j = j0; j < cnt; j += LPS) {
@@ -1863,7 +1875,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                     }
                 }
                 __syncthreads();
-                group_write<COUNT>(q, marks);
+                group_write<COUNT, 256>(q, marks);
             } else {
             // each wave takes 4 of the group's tile slots; a round covers 64 entries of each
             uint32_t cnt[kSlotsPerWave];
@@ -2197,6 +2209,412 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
         state[l] = ns;
         publish_threshold(pred, l, L.large, L.k, T);
     }
+}
+
+// --------------------------------------------------------------- select --
+// Small plans, every layer on the candidate path: what find0, gather, finish and mark do on others, in one launch, where each of
+// those was a launch of 3 to 6 us for a microsecond's work.  A workgroup of 1024 threads per group of tile slots.  It reads the
+// first digit off its layer's fine bins, then -- every group of a layer the same -- the threshold bucket's keys from all
+// of the layer's slots (a few per tile: reading them again and again costs less than handing them over), ranks those in LDS, and
+// marks the windows of its own tiles' candidates that reach the threshold.  Nothing passes between workgroups.
+// A layer whose bound failed is ranked on its full score map by the workgroups of its own groups (select_full_map).
+// What bounds it is a chain of six or seven dependent loads.  Kernels, before / now (find0 to mark, four launches / k_select): 512 x 512
+// 19.7 / 10.4 us, ResNet-18 25.0 / 14.0, ResNet-50 32.0 / 21.6; calls 31.2 -> 22.6, 63.8 -> 53.1, 108.2 -> 95.9 us.  (The 48 bytes
+// of scratch belong to select_full_map: without it the kernel takes as long.)
+// The rule (build_tables): up to 4096 chunks, as for all that counts where it marks; a layer's slots' counts fit the threads
+// (kSelectTiles); and its candidates, which all of its workgroups read, are few enough (kSelectMaxK).
+constexpr int kSelectThreads = 1024;
+constexpr int kSelectWaves = kSelectThreads / 64;
+static_assert(kSelectThreads == kFineBins && kSelectWaves == kSlotGroup, "a bin per thread, a tile slot per wave");
+constexpr int kSelectList = 2048;        // keys of a threshold bucket that are ranked in LDS
+
+struct SelectArgs {
+    const LayerDev *layers;
+    const GroupEntry *groups;
+    SelState *state;
+    PredState *pred;
+    const uint32_t *hist_s;
+    const uint32_t *slot_cnt;
+    const unsigned long long *slot_ent;
+    uint32_t *mask, *cmask, *chunk_cnt, *group_cnt;
+    // where a bound failed
+    const float *grad, *resid, *mom;
+    float *v_out, *mom_out;
+    float m;
+    float *map;
+    uint32_t *hist, *list_cnt;
+    unsigned long long *list_ent;
+    double alpha;
+};
+struct SelectShared {
+    union {
+        struct {
+            GroupMarks<kSlotGroup> marks;
+            unsigned long long key[kSelectList];      // the threshold bucket's keys, less its lower edge
+            uint32_t lh[kLevel1Bins];
+        };
+        uint32_t hist[kHistBins];                     // full map
+    };
+    uint32_t wave_tot[kSelectWaves];
+    DigitResult res;
+    unsigned long long rank_key;
+    uint32_t n, ticket;
+};
+
+// The recorded candidates of a layer, by the whole workgroup: a wave takes every 16th slot, a lane's count each, and goes through
+// their entries 64 at a time, wherever one slot ends and the next begins (slots hold a few entries or many; with threads
+// tied to slots the longest slot of every wave was a chain of loads: 5.4 of 18 us on ResNet-18, 9.5 of 23 on ResNet-50).
+struct SlotScan {
+    static constexpr int U = 4;           // entries of a lane on their way at once
+    const unsigned long long *ents;
+    uint32_t cap, wave;
+    uint32_t incl, total;                 // entries of the wave's slots up to the lane's; of all of them
+    __device__ __forceinline__ void set(const LayerDev &L, const unsigned long long *slot_ent, uint32_t count /* of slot wave + 16 lane */) {
+        const uint32_t lane = threadIdx.x & 63u;
+        wave = threadIdx.x >> 6;
+        ents = slot_ent + L.slot_off;
+        cap = L.slot_cap;
+        incl = min(count, cap);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(incl, d, 64);
+            if (lane >= static_cast<uint32_t>(d)) incl += o;
+        }
+        total = __builtin_amdgcn_readlane(incl, 63);
+    }
+    __device__ __forceinline__ void load(unsigned long long (&K)[U], uint32_t e0) const {
+        const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            K[u] = 0ull;                  // (not a candidate's key: those have scores above 0)
+            const uint32_t e = e0 + 64u * u + lane;
+            uint32_t s = 0;               // slots (of the wave) that end at or before entry e
+#pragma unroll
+            for (uint32_t step = 32; step >= 1u; step >>= 1)
+                if (__shfl(incl, static_cast<int>(s + step - 1u), 64) <= e) s += step;
+            const uint32_t before = __shfl(incl, static_cast<int>(s) - 1, 64);
+            if (e < total) K[u] = ents[(wave + 16u * s) * cap + (e - (s ? before : 0u))];
+        }
+    }
+    template <typename F>
+    __device__ __forceinline__ void rest(unsigned long long (&K)[U], F f) const {      // K: the entries from 0 on
+#pragma unroll 1
+        for (uint32_t e0 = 0;;) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) f(K[u]);
+            e0 += 64u * U;
+            if (e0 >= total) break;       // (the whole wave)
+            load(K, e0);
+        }
+    }
+};
+
+// The k_rem-th largest of n numbers below 2^top: from sh.key, if they fit there, else scan(f) calls f for each of them.
+template <typename S>
+__device__ __forceinline__ unsigned long long select_rank(SelectShared &sh, uint32_t n, uint32_t k_rem, int top, S scan) {
+    const uint32_t tid = threadIdx.x;
+    if (n <= 64u) {                       // a lane per number counts the larger ones (all differ)
+        if (tid < 64u) {
+            const unsigned long long own = tid < n ? sh.key[tid] : 0ull;
+            uint32_t larger = 0;
+            for (uint32_t j = 0; j < n; ++j) {
+                const unsigned long long o = static_cast<unsigned long long>(__builtin_amdgcn_readlane(static_cast<uint32_t>(own >> 32), j)) << 32 |
+                                             static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(own), j));
+                larger += o > own ? 1u : 0u;
+            }
+            if (tid < n && larger == k_rem - 1u) sh.rank_key = own;
+        }
+        __syncthreads();
+        return sh.rank_key;
+    }
+    unsigned long long T = 0;
+#pragma unroll 1
+    for (int left = top; left > 0;) {     // digit by digit: at most five, and nearly always one
+        const int bits = min(left, kLevel1Bits), shift = left - bits, nb = 1 << bits;
+        __syncthreads();
+        for (int b = tid; b < nb; b += kSelectThreads) sh.lh[b] = 0u;
+        __syncthreads();
+        auto count = [&](unsigned long long rel) {
+            if (rel >> left == T >> left) atomicAdd(&sh.lh[static_cast<uint32_t>(rel >> shift) & (nb - 1)], 1u);
+        };
+        if (n <= static_cast<uint32_t>(kSelectList)) {
+            for (uint32_t i = tid; i < n; i += kSelectThreads) count(sh.key[i]);
+        } else {
+            scan(count);
+        }
+        __syncthreads();
+        const DigitResult d = block_find_digit<kSelectWaves>(sh.lh, nb, k_rem, sh.wave_tot, &sh.res);
+        T |= static_cast<unsigned long long>(d.digit) << shift;
+        k_rem -= d.above;
+        if (d.count == k_rem) break;      // all of them: lower digits stay 0
+        left = shift;
+    }
+    return T;
+}
+
+// A failed bound: the layer is ranked on its full score map, as the fallback kernels of other plans do it, by the workgroups of
+// its groups together.  Four steps, each cut into shares that the workgroups take by tickets in order: scores, map and first
+// digit; the threshold bucket's keys; their ranking (one share); the marks.  A share waits until all shares of the step before
+// are done.  Those have lower tickets: they were taken by workgroups that are running, and these wait, if at all, for still lower
+// ones -- so every wait ends, however few workgroups are on the GPU at a time.
+constexpr int kSelectCtl = 8;            // words of the layer's last list shard's line: the tickets, then the shares done of each step
+
+__device__ __forceinline__ void select_share_done(uint32_t *done) {
+    __threadfence();                      // (every thread: its own stores)
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(done, 1u);
+}
+__device__ __forceinline__ void select_wait(uint32_t *done, uint32_t n) {
+    if (threadIdx.x == 0)
+        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) __builtin_amdgcn_s_sleep(16);
+    __syncthreads();
+    __threadfence();
+}
+
+// v = r + g at (x, y), zero outside the matrix; with Eq. 12's momentum term v = r + (m*u + g) and `gu` that sum in brackets.
+__device__ __forceinline__ float select_v(const SelectArgs &a, const LayerDev &L, int x, int y, float *gu) {
+    if (x < 0 || x >= static_cast<int>(L.R) || y < 0 || y >= static_cast<int>(L.C)) return 0.f;
+    const size_t at = static_cast<size_t>(L.elem_off) + static_cast<size_t>(x) * L.C + y;
+    float t = a.grad[at];
+    if (a.mom) t = __fmul_rn(a.m, a.mom[at]) + t;
+    if (gu) *gu = t;
+    return a.resid[at] + t;
+}
+// Eqs. 8-10 at (x, y): the same sums in the same order as the NSI passes form them.
+__device__ __forceinline__ float select_score(const SelectArgs &a, const LayerDev &L, int x, int y) {
+    const int P = static_cast<int>(L.p), h = (P - 1) / 2;
+    const double n = static_cast<double>(P * P);
+    double sa = 0.0, ss = 0.0, sq = 0.0;
+#pragma unroll 1
+    for (int dx = -h; dx <= h; ++dx) {
+        const double w0 = static_cast<double>(select_v(a, L, x + dx, y - h, nullptr));
+        double ra = fabs(w0), rs = w0, rq = w0 * w0;
+#pragma unroll 1
+        for (int dy = 1 - h; dy <= h; ++dy) {
+            const double w = static_cast<double>(select_v(a, L, x + dx, y + dy, nullptr));
+            ra += fabs(w);
+            rs += w;
+            rq = fma(w, w, rq);
+        }
+        if (dx == -h) { sa = ra; ss = rs; sq = rq; }
+        else { sa += ra; ss += rs; sq += rq; }
+    }
+    const double nsq = __dmul_rn(n, sq);
+    double d = var_n2_one_pass(ss, nsq);
+    if (P > 1 && d < kCancelFrac * nsq) {
+        const double m = ss / n;
+        double acc = 0.0;
+#pragma unroll 1
+        for (int dx = -h; dx <= h; ++dx)
+#pragma unroll 1
+            for (int dy = -h; dy <= h; ++dy) {
+                const double e = static_cast<double>(select_v(a, L, x + dx, y + dy, nullptr)) - m;
+                acc += __dmul_rn(e, e);
+            }
+        d = __dmul_rn(n, acc);
+    }
+    return static_cast<float>(nsi_from_var(sa, d, a.alpha / n, (1.0 - a.alpha) / n));
+}
+
+// First digit of a layer's full map, from the histogram that the first step has counted.
+__device__ __forceinline__ DigitResult select_map_digit(SelectShared &sh, const uint32_t *hist, uint32_t k) {
+    __syncthreads();
+    if (threadIdx.x < 64u) {
+        const WaveBucket wb = wave_find_bucket(hist, k);
+        if (threadIdx.x == 0) sh.res = DigitResult{wb.bucket, wb.above, wb.count, wb.found};
+    }
+    __syncthreads();
+    const DigitResult r = sh.res;
+    __syncthreads();
+    return r;
+}
+
+__device__ __forceinline__ void select_full_map(const SelectArgs &a, SelectShared &sh, uint32_t l, const LayerDev &L, const SelState &st,
+                                                const DigitResult failed) {
+    const uint32_t tid = threadIdx.x, S = L.n_groups;
+    const uint32_t C = L.C;
+    uint32_t *list_cnt = a.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
+    uint32_t *ctl = list_cnt + (kListShards - 1) * kListCntStride + kSelectCtl;
+    uint32_t *hist = a.hist + static_cast<size_t>(l) * kHistBins;
+    unsigned long long *list = a.list_ent + L.list_off;
+    const uint32_t cap = L.list_cap / L.list_shards;
+    float *map = a.map + L.elem_off;
+    const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
+    const WindowGeom geom = {static_cast<size_t>(L.elem_off), static_cast<int>(L.R), static_cast<int>(L.C), (static_cast<int>(L.p) - 1) / 2};
+    const uint64_t per = (static_cast<uint64_t>(L.G) + S - 1) / S;
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) sh.ticket = atomicAdd(ctl, 1u);
+        __syncthreads();
+        const uint32_t t = sh.ticket;
+        if (t > 3u * S) return;                                       // uniform, and so is every branch on t
+        const uint32_t share = t < 2u * S ? t % S : t - 2u * S - 1u;
+        const uint64_t begin = min(share * per, static_cast<uint64_t>(L.G)), end = min(begin + per, static_cast<uint64_t>(L.G));
+        if (t < S) {
+            for (int b = tid; b < kHistBins; b += kSelectThreads) sh.hist[b] = 0u;
+            __syncthreads();
+            for (uint64_t i = begin + tid; i < end; i += kSelectThreads) {
+                const uint32_t e = static_cast<uint32_t>(i), x = e / C, y = e - x * C;
+                const float score = select_score(a, L, static_cast<int>(x), static_cast<int>(y));
+                map[e] = score;
+                atomicAdd(&sh.hist[(__float_as_uint(score) & 0x7fffffffu) >> kCoarseShift], 1u);
+                if (a.v_out) {            // (a layer that had no bound went through no pass that stores it)
+                    float gu = 0.f;
+                    a.v_out[L.elem_off + e] = select_v(a, L, static_cast<int>(x), static_cast<int>(y), &gu);
+                    if (a.mom_out) a.mom_out[L.elem_off + e] = gu;
+                }
+            }
+            __syncthreads();
+            for (int b = tid; b < kHistBins; b += kSelectThreads)
+                if (sh.hist[b]) atomicAdd(&hist[b], sh.hist[b]);
+            select_share_done(ctl + 1);
+        } else if (t < 2u * S) {
+            select_wait(ctl + 1, S);
+            const DigitResult r = select_map_digit(sh, hist, L.k);
+            if (r.found && r.count != L.k - r.above) {               // uniform; else nothing is left to rank
+                const uint32_t lo = r.digit << kCoarseShift, shard = share % L.list_shards;
+                uint32_t *cnt = list_cnt + shard * kListCntStride;
+                unsigned long long *ent = list + static_cast<size_t>(shard) * cap;
+                for (uint64_t i0 = begin; i0 < end; i0 += kSelectThreads) {
+                    const uint64_t i = i0 + tid;
+                    const uint32_t key = i < end ? __float_as_uint(map[i]) & 0x7fffffffu : 0u;
+                    const bool hit = i < end && key - lo < 1u << kCoarseShift;
+                    const uint32_t pos = wave_append(cnt, hit);
+                    if (hit && pos < cap) ent[pos] = composite_key(key, static_cast<uint32_t>(i));
+                }
+            }
+            select_share_done(ctl + 2);
+        } else if (t == 2u * S) {
+            select_wait(ctl + 2, S);
+            const DigitResult r = select_map_digit(sh, hist, L.k);
+            const uint32_t lo = r.found ? r.digit << kCoarseShift : 0u;
+            const unsigned long long base = static_cast<unsigned long long>(lo) << 32;
+            unsigned long long T = base;
+            if (r.found && r.count != L.k - r.above) {
+                if (tid == 0) sh.n = 0u;
+                __syncthreads();
+                const uint32_t n_mine = (tid & 63u) < static_cast<uint32_t>(kListShards) ? list_cnt[(tid & 63u) * kListCntStride] : 0u;
+                const bool listed = __syncthreads_and(n_mine <= cap) != 0;         // every shard of the list fits
+                auto scan = [&](auto f) {
+                    if (listed) {
+#pragma unroll 1
+                        for (int s = 0; s < kListShards; ++s) {
+                            const uint32_t n = __shfl(n_mine, s, 64);
+                            for (uint32_t i = tid; i < n; i += kSelectThreads) f(list[static_cast<size_t>(s) * cap + i] - base);
+                        }
+                    } else {
+                        for (uint64_t i = tid; i < L.G; i += kSelectThreads) {
+                            const uint32_t key = __float_as_uint(map[i]) & 0x7fffffffu;
+                            if (key - lo < 1u << kCoarseShift) f(composite_key(key, static_cast<uint32_t>(i)) - base);
+                        }
+                    }
+                };
+                scan([&](unsigned long long rel) {
+                    const uint32_t pos = atomicAdd(&sh.n, 1u);
+                    if (pos < static_cast<uint32_t>(kSelectList)) sh.key[pos] = rel;
+                });
+                __syncthreads();
+                T += select_rank(sh, sh.n, L.k - r.above, 32 + kCoarseShift, scan);
+            }
+            if (tid == 0) {
+                if (st.mode == kModeCandidates) bound_failed(a.pred, l, L.k, st, failed);
+                SelState ns = st;
+                ns.mode = kModeFullMap;
+                ns.T = T;
+                ns.lo = lo;
+                ns.span = kCoarseShift;
+                ns.done = 1u;
+                a.state[l] = ns;
+                publish_threshold(a.pred, l, 1u, L.k, T);
+            }
+            select_share_done(ctl + 3);
+        } else {
+            select_wait(ctl + 3, 1u);
+            // (written by this launch: not through the scalar cache)
+            const unsigned long long T = __hip_atomic_load(&a.state[l].T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (uint64_t i = begin + tid; i < end; i += kSelectThreads)
+                if (composite_key(__float_as_uint(map[i]), static_cast<uint32_t>(i)) >= T)
+                    mark_window<true>(geom, cctx, static_cast<uint32_t>(i), a.mask, a.cmask);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_select(const SelectArgs a) {
+    __shared__ SelectShared sh;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const GroupEntry ge = a.groups[blockIdx.x];
+    const uint32_t l = ge.layer, cap = ge.slot_cap;
+    const LayerDev L = a.layers[l];
+    const SelState st = a.state[l];
+    const uint32_t own_bin = a.hist_s[static_cast<size_t>(l) * kHistBins + (kFineBins - 1 - tid)];      // thread 0 has the top bin
+    // the layer's slots, and the wave's own one of the group: its first entries beside its count (a slot always has them; past
+    // the count they hold anything)
+    const uint32_t count = wave + 16u * lane < L.n_tiles ? a.slot_cnt[L.tile_begin_all + wave + 16u * lane] : 0u;
+    const unsigned long long *__restrict__ slot = a.slot_ent + (((static_cast<uint64_t>(ge.ent0_high) << 32) | ge.ent0_low) << 1) + wave * cap;
+    uint32_t cnt = 0;
+    unsigned long long own = 0;
+    if (wave < ge.ntile) {
+        cnt = a.slot_cnt[ge.slot0 + wave];
+        if (lane < cap) own = slot[lane];
+    }
+    const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
+    GroupGeom q = group_geom(L, ge.slot0 - L.tile_begin_all, ge.ntile, a.mask, cctx);
+    const bool words = (L.C & 31u) == 0u;            // rows of whole mask words
+    if (words) group_clear<kSelectThreads>(q, sh.marks);
+    if (tid == 0) {
+        sh.res.found = 0u;
+        sh.n = 0u;
+    }
+    SlotScan scan;
+    scan.set(L, a.slot_ent, count);
+    unsigned long long K[SlotScan::U];
+    scan.load(K, 0u);                     // (they arrive while the digit is found)
+    const uint32_t incl = block_scan_incl_n<kSelectWaves>(own_bin, sh.wave_tot), excl = incl - own_bin;
+    if (excl < L.k && L.k <= incl) sh.res = DigitResult{kFineBins - 1 - tid, excl, own_bin, 1u};
+    __syncthreads();
+    const DigitResult r = sh.res;
+    // k_find0's test of the bound
+    if (st.mode != kModeCandidates || st.hint_key == 0u || st.overflow != 0u || !r.found || r.digit == static_cast<uint32_t>(kFineBins - 1)) {
+        select_full_map(a, sh, l, L, st, r);
+        return;
+    }
+    const uint32_t lo = st.hint_key + (r.digit << kFineShift), k_rem = L.k - r.above;
+    const unsigned long long base = static_cast<unsigned long long>(lo) << 32;
+    unsigned long long T = base;                     // (the whole bucket is taken: its lower edge)
+    if (r.count != k_rem) {
+        scan.rest(K, [&](unsigned long long key) {
+            if (static_cast<uint32_t>(key >> 32) - lo < 1u << kFineShift) {
+                const uint32_t pos = atomicAdd(&sh.n, 1u);
+                if (pos < static_cast<uint32_t>(kSelectList)) sh.key[pos] = key - base;
+            }
+        });
+        __syncthreads();
+        T += select_rank(sh, sh.n, k_rem, 32 + kFineShift, [&](auto f) {
+            scan.load(K, 0u);
+            scan.rest(K, [&](unsigned long long key) {
+                if (static_cast<uint32_t>(key >> 32) - lo < 1u << kFineShift) f(key - base);
+            });
+        });
+    }
+    if (words) q.cl0 = group_first_chunk(q, sh.marks.corner[0]);
+    const WindowGeom geom = {static_cast<size_t>(L.elem_off), q.R, q.C, q.h};
+    cnt = min(cnt, cap);
+    for (uint32_t j = lane; j < cnt; j += 64u) {
+        if (j != lane) own = slot[j];
+        if (own < T) continue;
+        const uint32_t i = ~static_cast<uint32_t>(own);
+        if (words) group_mark<true>(q, sh.marks, static_cast<int>(wave), i);
+        else mark_window<true>(geom, cctx, i, a.mask, nullptr);
+        if (a.cmask) {
+            const size_t pos = geom.elem_off + i;
+            atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
+        }
+    }
+    if (words) {
+        __syncthreads();
+        group_write<true, kSelectThreads>(q, sh.marks);
+    }
+    if (q.g0 == 0 && tid == 0) publish_threshold(a.pred, l, 1u, L.k, T);
 }
 
 // ----------------------------------------------------------------- mark --
@@ -4204,8 +4622,10 @@ struct Momentum {                 // Eq. 12's momentum term; all null / 0 withou
 template <int PASS>
 int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const float *resid,
                float *nsi_out, float *v_out, const Momentum &mom, hipStream_t stream,
-               bool with_sampled_tiles = true, const Find0Args *find0_args = nullptr) {
+               bool with_sampled_tiles = true, const Find0Args *find0_args = nullptr, uint4 *counts = nullptr, uint32_t n16 = 0) {
     NsiArgs a;
+    a.counts = counts;
+    a.n16 = n16;
     a.list_cnt = reinterpret_cast<uint32_t *>(ws + plan->ws.list_cnt);
     a.n_layers = plan->n_layers;
     a.v_out = v_out;
@@ -4465,6 +4885,46 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
     return RSDGC_OK;
 }
 
+// Small plans: everything between the main pass and the emit in one launch (and the centres' counts in another, if wanted).
+static int launch_select(rsdgc_plan_s *plan, char *ws, const float *grad, const float *residual, float *v_out, const Momentum &mom,
+                         bool want_centres, StageMarks &marks, hipStream_t stream) {
+    const WsLayout &w = plan->ws;
+    SelectArgs a;
+    a.layers = reinterpret_cast<const LayerDev *>(ws + w.layers);
+    a.groups = reinterpret_cast<const GroupEntry *>(ws + w.cand_groups);
+    a.state = reinterpret_cast<SelState *>(ws + w.state);
+    a.pred = reinterpret_cast<PredState *>(ws + w.pred);
+    a.hist_s = reinterpret_cast<const uint32_t *>(ws + w.hist_s);
+    a.slot_cnt = reinterpret_cast<const uint32_t *>(ws + w.slot_cnt);
+    a.slot_ent = reinterpret_cast<const unsigned long long *>(ws + w.slot_ent);
+    a.mask = reinterpret_cast<uint32_t *>(ws + w.mask);
+    a.cmask = want_centres ? reinterpret_cast<uint32_t *>(ws + w.cmask) : nullptr;
+    a.chunk_cnt = reinterpret_cast<uint32_t *>(ws + w.chunk_cnt);
+    a.group_cnt = reinterpret_cast<uint32_t *>(ws + w.group_cnt);
+    a.grad = grad;
+    a.resid = residual;
+    a.mom = mom.in;
+    a.v_out = v_out;
+    a.mom_out = mom.out;
+    a.m = mom.m;
+    a.map = reinterpret_cast<float *>(ws + w.nsi);
+    a.hist = reinterpret_cast<uint32_t *>(ws + w.hist);
+    a.list_cnt = reinterpret_cast<uint32_t *>(ws + w.list_cnt);
+    a.list_ent = reinterpret_cast<unsigned long long *>(ws + w.list_ent);
+    a.alpha = plan->alpha;
+    hipLaunchKernelGGL(k_select, dim3(static_cast<uint32_t>(plan->cand_groups.size())), dim3(kSelectThreads), 0, stream, a);
+    marks.close(4);
+    marks.close(5);
+    if (want_centres)
+        hipLaunchKernelGGL(k_count, dim3(plan->n_count_groups), dim3(kCountThreads), 0, stream,
+                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), nullptr, a.cmask, a.chunk_cnt,
+                           reinterpret_cast<uint32_t *>(ws + w.chunk_ccnt), a.group_cnt, reinterpret_cast<uint32_t *>(ws + w.group_ccnt),
+                           static_cast<uint32_t>(kGroupCntStride));
+    HIP_TRY(hipGetLastError());
+    marks.close(6);
+    return RSDGC_OK;
+}
+
 // What the last kernel of a call with this plan clears and sets for the next (sampling: whether that one samples bounds).
 static NextCall next_call(const rsdgc_plan_s *plan, char *ws, const LayerDev *layers, SelState *state, PredState *pred,
                           bool sampling) {
@@ -4545,33 +5005,44 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
         hipLaunchKernelGGL(k_hint, dim3(L), dim3(256), 0, stream, layers, state,
                            reinterpret_cast<uint32_t *>(ws + w.hist_s), flags);
     marks.close(1);
+    // plans whose layers' candidates a workgroup can read through: everything up to the emit in one launch
+    bool one_select = plan->one_select && plan->work_feed != RSDGC_FEED_ON;
+    for (const PGroup &g : plan->groups) one_select = one_select && g.n_large_tiles < kFeedTiles;      // (no feed for the main pass)
+    uint4 *counts = reinterpret_cast<uint4 *>(ws + w.chunk_cnt);
+    const uint32_t counts_n16 = static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16);
     if (plan->any_large) {
-        rc = launch_nsi<kPassCapture>(plan, ws, grad, residual, nsi, v_out, mom, stream);
+        rc = launch_nsi<kPassCapture>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, nullptr, counts, one_select ? counts_n16 : 0u);
         if (rc != RSDGC_OK) return rc;
     }
     marks.close(2);
-    Find0Args f;
-    f.layers = layers;
-    f.state = state;
-    f.hist = hist;
-    f.hist_s = reinterpret_cast<const uint32_t *>(ws + w.hist_s);
-    f.flags = flags;
-    f.pred = pred;
-    f.counts = reinterpret_cast<uint4 *>(ws + w.chunk_cnt);
-    f.n16 = static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16);
-    f.n_layers = L;
-    // large layers whose candidate bound failed (rare): the workgroups find nothing to do otherwise.  Up to 256 layers they look
-    // for such layers themselves, in one launch with k_find0.
-    const bool one_launch = plan->any_large && L <= 256;
-    if (!one_launch) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
-    if (plan->any_large) {
-        rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, one_launch ? &f : nullptr);
+    if (one_select) {
+        marks.close(3);
+        rc = launch_select(plan, ws, grad, residual, v_out, mom, want_centres, marks, stream);
+        if (rc != RSDGC_OK) return rc;
+    } else {
+        Find0Args f;
+        f.layers = layers;
+        f.state = state;
+        f.hist = hist;
+        f.hist_s = reinterpret_cast<const uint32_t *>(ws + w.hist_s);
+        f.flags = flags;
+        f.pred = pred;
+        f.counts = counts;
+        f.n16 = counts_n16;
+        f.n_layers = L;
+        // large layers whose candidate bound failed (rare): the workgroups find nothing to do otherwise.  Up to 256 layers they look
+        // for such layers themselves, in one launch with k_find0.
+        const bool one_launch = plan->any_large && L <= 256;
+        if (!one_launch) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
+        if (plan->any_large) {
+            rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, one_launch ? &f : nullptr);
+            if (rc != RSDGC_OK) return rc;
+        }
+        marks.close(3);
+
+        rc = select_mark_count(plan, ws, want_centres, marks, pred, stream);
         if (rc != RSDGC_OK) return rc;
     }
-    marks.close(3);
-
-    rc = select_mark_count(plan, ws, want_centres, marks, pred, stream);
-    if (rc != RSDGC_OK) return rc;
     const ChunkInfo *chunk_info = reinterpret_cast<const ChunkInfo *>(ws + w.chunk_info);
     if (in_place)
         hipLaunchKernelGGL(k_emit, dim3(n_chunks + 1), dim3(256), 0, stream, layers, chunk_info, grad,

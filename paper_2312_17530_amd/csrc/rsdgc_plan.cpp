@@ -166,6 +166,9 @@ int build_tables(rsdgc_plan_s *plan) {
     }
 
     plan->n_map_tiles = static_cast<uint32_t>(plan->map_tiles.size());
+    plan->one_select = plan->any_large && plan->map_chunks.empty() && plan->n_chunks <= kInlineCountChunks;
+    for (const LayerDev &d : plan->layers)
+        plan->one_select = plan->one_select && d.n_tiles <= kSelectTiles && d.k <= kSelectMaxK;
 
     // one launch of each NSI pass per distinct neighbourhood side
     for (int p = 1; p <= RSDGC_MAX_P; p += 2) {
