@@ -1429,15 +1429,15 @@ __global__ __launch_bounds__(256) void k_find0_fallback_all(const Find0Args f, c
 // After the first digit: the keys of each layer's threshold bucket (score bits in
 // [lo, lo + 2^span)) are copied into the layer's list and their next digit is histogrammed.
 // Three kinds of workgroups share the launch:
-//   [0, n_map_wgs)              stride over the plan's list of 8192-element score-map chunks
+//   [0, n_map_chunks)           a chunk each of the plan's list of 8192-element score-map chunks
 //                               (layers that are always ranked on the full map);
-//   [n_map_wgs, +n_slot_wgs)    stride over the plan's list of slot groups (large layers,
+//   [n_map_chunks, +n_slot_wgs) stride over the plan's list of slot groups (large layers,
 //                               where they are still in candidate mode);
 //   the last n_fb_wgs           only when some large layer fell back to the full map: they
 //                               walk all chunks and take those of such layers (and find the
 //                               first digit of such a layer themselves, from the histogram the
 //                               fallback pass has counted).
-// Matches from the score map are staged in LDS and appended with one atomic per flush.
+// Matches of the fallback walk are staged in LDS and appended with one atomic per flush.
 // The recorded candidates of a large layer are nearly all decided by the first digit already
 // (its bins are fine: the threshold bucket holds a per cent or two of them): a candidate above
 // the bucket is selected whatever the later digits say, so its window is marked here and now
@@ -1478,6 +1478,7 @@ struct GatherShared {
     DigitResult res;
     uint32_t n;                         // staged keys
     uint32_t base;
+    uint32_t wave_tot[4];
 };
 
 struct GatherLists {
@@ -1485,7 +1486,7 @@ struct GatherLists {
     const ChunkEntry *map_chunks;    // [n_map_chunks]
     const GroupEntry *cand_groups;   // [n_cand_groups]
     uint32_t n_layers, n_chunks, n_map_chunks, n_cand_groups;
-    uint32_t n_map_wgs, n_slot_wgs;  // the remaining workgroups are fallback walkers
+    uint32_t n_slot_wgs;             // the remaining workgroups are fallback walkers
 };
 
 struct GatherArgs {
@@ -1538,6 +1539,75 @@ __device__ __forceinline__ void gather_stage_key(GatherShared &sh, bool hit, uns
     if (hit) {
         sh.ent[pos] = K;
         atomicAdd(&sh.hist[(static_cast<uint32_t>(K >> 32) - lo) >> shift1], 1u);
+    }
+}
+
+// A chunk of a layer that is always ranked on the full map.  All of a thread's 32 scores are requested before any is looked at, and
+// places in the list are handed out once per chunk: what bounds this is the reading.  (Workgroups that strode over
+// the chunks, a quarter of a chunk and two barriers at a time: 35.9 us for the 62 MB of VGG-19's block scores, now 30.4: an atomic per key on
+// the second digit's counts is most of what is left.)
+__device__ __forceinline__ void gather_map_chunk(const GatherArgs &a, const ChunkEntry ce, GatherShared &sh) {
+    constexpr int N = kChunk / 1024;
+    const int tid = threadIdx.x;
+    const uint32_t *__restrict__ src = a.keys + ce.arena_off;
+    uint4 q[N];
+    if (ce.len == static_cast<uint32_t>(kChunk)) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) q[j] = *reinterpret_cast<const uint4 *>(src + j * 1024 + 4 * tid);
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t e = j * 1024 + 4 * tid;
+            q[j] = make_uint4(0, 0, 0, 0);
+            if (e < ce.len) q[j].x = src[e];
+            if (e + 1 < ce.len) q[j].y = src[e + 1];
+            if (e + 2 < ce.len) q[j].z = src[e + 2];
+            if (e + 3 < ce.len) q[j].w = src[e + 3];
+        }
+    }
+    const uint32_t l = ce.layer;
+    const SelState st = a.state[l];
+    const LayerDev &L = a.layers[l];
+    const uint32_t shard = (ce.start / kChunk) % L.list_shards, cap = L.list_cap / L.list_shards;
+    uint32_t *cnt = a.list_cnt + (static_cast<size_t>(l) * kListShards + shard) * kListCntStride;
+    unsigned long long *ent = a.list_ent + L.list_off + static_cast<size_t>(shard) * cap;
+    if (st.done || st.mode != kModeFullMap) return;                  // uniform
+    for (int b = tid; b < kLevel1Bins; b += 256) sh.hist[b] = 0;
+    __syncthreads();
+    const uint32_t lo = st.lo, width = 1u << st.span, shift1 = st.span - kLevel1Bits;
+    uint32_t hits = 0;                    // a bit per score
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const uint32_t kk[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t rel = (kk[c] & 0x7fffffffu) - lo;
+            if (rel < width && static_cast<uint32_t>(j * 1024 + 4 * tid + c) < ce.len) {
+                hits |= 1u << (4 * j + c);
+                atomicAdd(&sh.hist[rel >> shift1], 1u);
+            }
+        }
+    }
+    const uint32_t own = __popc(hits), incl = block_scan_incl(own, sh.wave_tot);
+    if (tid == 255) sh.base = incl ? atomicAdd(cnt, incl) : 0u;
+    __syncthreads();
+    uint32_t pos = sh.base + incl - own;
+    if (hits) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t kk[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (hits & (1u << (4 * j + c))) {
+                    if (pos < cap) ent[pos] = composite_key(kk[c], ce.start + j * 1024 + 4 * tid + c);
+                    ++pos;
+                }
+        }
+    }
+    uint32_t *__restrict__ gh = a.hist1 + static_cast<size_t>(l) * kLevel1Bins;
+    for (int b = tid; b < kLevel1Bins; b += 256) {
+        const uint32_t c = sh.hist[b];
+        if (c) atomicAdd(&gh[b], c);
     }
 }
 
@@ -1695,14 +1765,17 @@ template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // role 0: listed score-map chunks, 1: listed slot groups, 2: fallback walk over all chunks
-    const int role = blockIdx.x < gl.n_map_wgs ? 0 : blockIdx.x < gl.n_map_wgs + gl.n_slot_wgs ? 1 : 2;
-    const uint32_t first = role == 0 ? blockIdx.x : role == 1 ? blockIdx.x - gl.n_map_wgs
-                                                              : blockIdx.x - gl.n_map_wgs - gl.n_slot_wgs;
-    const uint32_t stride = role == 0 ? gl.n_map_wgs : role == 1 ? gl.n_slot_wgs
-                                                                 : gridDim.x - gl.n_map_wgs - gl.n_slot_wgs;
+    if (blockIdx.x < gl.n_map_chunks) {
+        gather_map_chunk(a, gl.map_chunks[blockIdx.x], sh);
+        return;
+    }
+    // role 1: listed slot groups, 2: fallback walk over all chunks
+    const uint32_t wg = blockIdx.x - gl.n_map_chunks;
+    const int role = wg < gl.n_slot_wgs ? 1 : 2;
+    const uint32_t first = role == 1 ? wg : wg - gl.n_slot_wgs;
+    const uint32_t stride = role == 1 ? gl.n_slot_wgs : gridDim.x - gl.n_map_chunks - gl.n_slot_wgs;
     constexpr int SLOTS = kSlotGroup / PARTS;
-    const uint32_t n_items = role == 0 ? gl.n_map_chunks : role == 1 ? gl.n_cand_groups * PARTS : gl.n_chunks;
+    const uint32_t n_items = role == 1 ? gl.n_cand_groups * PARTS : gl.n_chunks;
     const DirEntry *__restrict__ dir = gl.chunk_dir;
     if (first >= n_items) return;
     if (role == 2 && a.flags[0] == 0u) return;
@@ -1724,13 +1797,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
 
     for (uint32_t it = first; it < n_items; it += stride) {
         uint32_t l;
-        ChunkEntry ce = {};
         GroupEntry ge = {};
         const unsigned long long *__restrict__ ent0 = nullptr;     // role 1: the group's first slot entry
-        if (role == 0) {
-            ce = gl.map_chunks[it];
-            l = ce.layer;
-        } else if (role == 1) {
+        if (role == 1) {
             ge = gl.cand_groups[it / PARTS];
             l = ge.layer;
             const uint32_t s0 = (it % PARTS) * SLOTS;
@@ -1767,7 +1836,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 if (st.done) width = 0;
             }
             if (role == 2) {
-                active = st.mode == kModeFullMap && L.large != 0u;      // the others are on the list
+                active = st.mode == kModeFullMap && L.large != 0u;      // (the others are on the list)
                 if (active) {              // uniform: first digit from the histogram of the fallback pass
                     if (tid < 64) {
                         const WaveBucket wb = wave_find_bucket(a.hist + static_cast<size_t>(l) * kHistBins, L.k);
@@ -1796,13 +1865,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             continue;
         }
         if (role != 1) {
-            if (role == 2) {
-                ce.start = (it - L.chunk_begin) * kChunk;
-                ce.len = min(static_cast<uint32_t>(kChunk), L.G - ce.start);
-                ce.arena_off = static_cast<uint64_t>(L.elem_off) + ce.start;
-            }
-            const uint32_t start = ce.start, len = ce.len;
-            const uint32_t *__restrict__ src = a.keys + ce.arena_off;
+            const uint32_t start = (it - L.chunk_begin) * kChunk, len = min(static_cast<uint32_t>(kChunk), L.G - start);
+            const uint32_t *__restrict__ src = a.keys + L.elem_off + start;
             // half a chunk is requested before any of it is used
             constexpr int NQ = kChunk / 2048;
 #pragma unroll 1
@@ -4810,13 +4874,12 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         gl.n_chunks = n_chunks;
         gl.n_map_chunks = static_cast<uint32_t>(plan->map_chunks.size());
         gl.n_cand_groups = n_cand_groups;
-        gl.n_map_wgs = std::min<uint32_t>(gl.n_map_chunks, kNumCUs * 4u);
         const bool split = inline_count && n_cand_groups < kSplitGroups;
         gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (split ? kSlotParts : 1u), kNumCUs * 8u);
         const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u;
-        if (gl.n_map_wgs + gl.n_slot_wgs + n_fb_wgs > 0)
+        if (gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs > 0)
         {
-            const dim3 grid(gl.n_map_wgs + gl.n_slot_wgs + n_fb_wgs);
+            const dim3 grid(gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs);
             if (split) hipLaunchKernelGGL((k_gather<true, kSlotParts>), grid, dim3(256), 0, stream, a, gl);
             else if (inline_count) hipLaunchKernelGGL((k_gather<true, 1>), grid, dim3(256), 0, stream, a, gl);
             else hipLaunchKernelGGL((k_gather<false, 1>), grid, dim3(256), 0, stream, a, gl);
