@@ -347,17 +347,21 @@ constexpr double kCancelFrac = 1.0 / 1048576.0;
 // With u = 2^-24, n = p*p, exact window sums SA = sum|w|, SS = sum w, SQ = sum w^2, D = n SQ - SS^2
 // (SA^2 <= n SQ, |SS| <= SA), and a bound B in [2^-40, 2^40] (nothing of weight under- or overflows):
 //   sa = SA (1 + t), |t| <= (n-1) u          (non-negative terms)
-//   n sq - ss^2 differs from D by at most (3n + 3) u * n SQ: n u from the roundings of sq and of the
-//     product with n, 2n u from ss (off by at most (n-1) u SA) squared, the rest from the last fma;
-//     d_hi = that + kSlack * n sq with kSlack = 1.3 (3n + 3) u is therefore at least D;
+//   ss is off by at most (n-1) u SA, so ss^2 <= SS^2 + (2n - 1.9) u * n SQ; sq >= SQ (1 - n u);
 //   rest = B' - ca sa with B' = B * kBoundFactor = B (1 - 2^-22 - 2.04 n u), rounded down: at most the exact
 //     B (1 - 2^-22) - ca SA whenever ca SA < 2 B, and negative otherwise;
-//   the centre stays unless rest > 0 and cb^2 d_hi < rest^2 (1 - 1e-6): the seven roundings between
-//     the two sides change their ratio by less than 8 u < 1e-6.
-// The comparison is written so that a NaN on either side keeps the centre, and an infinite sum does:
+//   e = A sq - (cb ss)^2, one fma of two rounded products, with A = cb^2 n (1 + kSlack) (1 + 2e-6) rounded up: the roundings
+//     of cb, of both products and of sq and ss take away less than (3n + 3.5) u * cb^2 n SQ, and kSlack = 1.3 (3n + 3) u is more,
+//     so e >= cb^2 D (1 + 1.9e-6) (as D <= n SQ);
+//   the centre stays unless e < t^2 with t = max(rest, 0): a centre that reaches B has cb^2 D >= (B (1 - 2^-22) - ca SA)^2 >= t^2
+//     exactly, or t = 0, and the roundings of e and t^2 are less than 1.9e-6.
+// The comparison is written so that a NaN on either side keeps the centre (the maximum takes the 0), and an infinite sum does:
 // such windows are left to the evaluation in full.  Squares of values below 2^-63 underflow; what is
 // lost (below 2^-126 each) is far less than either slack for a bound of at least 2^-40.  Outside
 // that range no bound is handed out: the layer is ranked on the full map (k_begin, k_hint).
+// Seven operations.  With d and rest scaled apart and compared in two steps (twelve, and beside them the test of the matrix's
+// edges, which is left to the evaluation in full now) the main pass took 234 us on 25088 x 4096 with p = 5, now 216; with p = 7 on 38 M
+// elements 92.6, now 86.2; VGG-19 312 -> 307, where it stores no v 255 -> 246.
 template <int P> struct PreF32 {
     static constexpr float kSlack = 1.3f * (3.f * P * P + 3.f) * 5.9604645e-8f;
     static constexpr double kBoundFactor = 1.0 - 1.0 / 4194304.0 - 2.04 * (P * P) * 5.9604645e-8;
@@ -573,7 +577,8 @@ __device__ __forceinline__ WaveBucket wave_find_bucket(const uint32_t *__restric
 // main pass (capture) runs the sweep in float32 instead and only decides there which centres
 // cannot reach the layer's bound (PreF32 above); the others it evaluates in double as said.
 // The capture variants are held to five waves per SIMD for p <= 3 and four for p = 5, 7
-// (what their registers allow without spilling; measured faster than one wave less).
+// (what their registers allow without spilling; measured faster than one wave less), those with momentum to
+// three: 485 us on VGG-19, with four, which 128 registers would allow p = 3, 497, with two 527.
 //
 // A workgroup takes tiles b, b + W, ... of the launch (W workgroups, laid out so that each XCD
 // gets one contiguous part of every stretch of W tiles: neighbouring tiles share halo rows in
@@ -582,6 +587,25 @@ __device__ __forceinline__ WaveBucket wave_find_bucket(const uint32_t *__restric
 // a launch issues few same-address global atomics.
 // MOM: with Eq. 12's momentum term (a.mom, a.mom_out, a.m).  FEED: the workgroups take their
 // tiles from the launch's work feed instead of a fixed strided share.
+// Sums of the last P row sums of a column, row by row (P compile-time indices: all of it in registers).  Pairs and pairs of
+// pairs are kept and shared by the windows: P = 5 takes three additions a row instead of four, P = 7 four instead of six (the main
+// pass with p = 7 on 38 M elements: 86.2 us without, 84.9 with).
+template <int P>
+struct ColumnSums {
+    float s[8], p[8], c[8];               // of row i (at i % 8): its sum, with the row before, with the three before
+    __device__ __forceinline__ void push(int i, float row) {
+        s[i & 7] = row;
+        if (P > 1 && i >= 1) p[i & 7] = s[(i - 1) & 7] + row;
+        if (P == 7 && i >= 3) c[i & 7] = p[(i - 2) & 7] + p[i & 7];
+    }
+    __device__ __forceinline__ float window(int i) const {
+        if (P == 1) return s[i & 7];
+        if (P == 3) return s[(i - 2) & 7] + p[i & 7];
+        if (P == 5) return (p[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
+        return (c[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
+    }
+};
+
 // Where a workgroup adds the candidates it recorded of a layer: word 1 of one of the first kRecordedParts list shards' lines
 // (several, as all workgroups of a launch end at about the same time).
 constexpr uint32_t kRecordedParts = 4;
@@ -689,7 +713,8 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     // (kernel arguments: the same in every lane, so they stay in scalar registers -- the scalar unit
     // has no floating point, a uniform value computed here would occupy vector registers)
     const double ca = a.ca, cb = a.cb;
-    const float caf = uniform_f32(static_cast<float>(ca)), cb2f = uniform_f32(static_cast<float>(cb * cb));
+    const float caf = uniform_f32(static_cast<float>(ca)), cbf = uniform_f32(static_cast<float>(cb));
+    const float pre_a = uniform_f32(__double2float_ru(cb * cb * n * (1.0 + static_cast<double>(PreF32<P>::kSlack)) * (1.0 + 2e-6)));
     float bound_lof = 0.f;                // capture: a conservative form of the candidate bound (PreF32)
     static_assert(kTileCols * (kTileRows / RPT) == 256, "one thread per RPT rows of one column");
     const int c0 = tid % kTileCols, ty = tid / kTileCols;
@@ -895,13 +920,12 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
         if (CAPTURE) {
             // Only the centres that reach the bound are wanted, and about 99.5 % do not.  A test
             // without the square root rules those out:
-            //   NSI >= B  <=>  cb*sqrt(d) >= B - ca*sa  <=>  rest <= 0  or  cb^2 * d >= rest^2
+            //   NSI >= B  <=>  cb*sqrt(d) >= B - ca*sa  <=>  cb^2 * d >= max(B - ca*sa, 0)^2
             // in float32, with the slacks of PreF32 (a window whose variance cancels is never ruled out
             // on a value that is too small).  Each thread walks down its column keeping the last P row
             // sums.  The few centres that remain are queued and evaluated in full after the sweep, one
             // per thread.
-            const float nf = static_cast<float>(P * P);
-            float fs_a[P], fs_s[P], fs_q[P];
+            ColumnSums<P> ca_, cs_, cq_;
 #pragma unroll
             for (int i = 0; i < RPT + 2 * H; ++i) {
                 const float *row = &tile[(row_base + i) * PITCH + PADL + c0 - H];
@@ -913,24 +937,16 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                         ss += row[j];
                         sq = fmaf(row[j], row[j], sq);
                     }
-                    fs_a[i % P] = sa;
-                    fs_s[i % P] = ss;
-                    fs_q[i % P] = sq;
+                    ca_.push(i, sa);
+                    cs_.push(i, ss);
+                    cq_.push(i, sq);
                 }
                 if (i >= 2 * H) {
                     const int o = i - 2 * H;
-                    float sa = fs_a[o % P], ss = fs_s[o % P], sq = fs_q[o % P];
-#pragma unroll
-                    for (int j = 1; j < P; ++j) {
-                        sa += fs_a[(o + j) % P];
-                        ss += fs_s[(o + j) % P];
-                        sq += fs_q[(o + j) % P];
-                    }
-                    const float nsq = nf * sq;
-                    const float d_hi = fmaf(PreF32<P>::kSlack, nsq, fmaf(-ss, ss, nsq));
-                    const float rest = fmaf(-caf, sa, bound_lof);
-                    const int x = x0 + row_base + o, y = y0 + c0;
-                    if ((rest <= 0.f || !(cb2f * d_hi < rest * rest * (1.f - 1e-6f))) && x < R && y < C) {
+                    const float sa = ca_.window(i), ss = cs_.window(i), sq = cq_.window(i);
+                    const float m = cbf * ss, e = fmaf(-m, m, pre_a * sq);
+                    const float t = fmaxf(fmaf(-caf, sa, bound_lof), 0.f);
+                    if (!(e < t * t)) {   // (outside the matrix too: the queue's turn to tell)
                         const uint32_t pos = atomicAdd(&nqueue, 1u);
                         if (pos < static_cast<uint32_t>(kQueueCap))
                             queue[pos] = static_cast<uint16_t>((row_base + o) * kTileCols + c0q);
@@ -994,6 +1010,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             for (uint32_t qi = tid; qi < min(nq, static_cast<uint32_t>(kQueueCap)); qi += 256) {
                 const int pos = queue[qi];
                 const int orow = pos / kTileCols, ocol = pos - orow * kTileCols;
+                if (x0 + orow >= R || y0 + ocol >= C) continue;
                 const float *win = &tile[orow * PITCH + PADL + ocol - H];
                 double sa = 0.0, ss = 0.0, sq = 0.0;
 #pragma unroll 1
@@ -1052,7 +1069,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
 }
 
 template <int P, int PASS, bool MOM, bool FEED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PASS == kPassCapture && !MOM ? (P <= 3 ? 5 : 4) : 1, 8)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PASS == kPassCapture && !MOM ? (P <= 3 ? 5 : 4) : 1, PASS == kPassCapture && MOM ? 3 : 8)))
 void k_nsi(const NsiArgs a) {
     __shared__ NsiShared<P, PASS> sh;
     nsi_pass<P, PASS, MOM, FEED>(a, sh, blockIdx.x, gridDim.x);
