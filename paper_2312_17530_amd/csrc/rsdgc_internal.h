@@ -14,7 +14,7 @@ constexpr int kTileCols = 256;       // NSI tile: output columns per workgroup
 constexpr int kChunk = 8192;         // elements per workgroup in the 1-D passes
 constexpr int kHistBins = 4096;      // widest radix digit (12 bits)
 constexpr int kLayerAlign = 64;      // arena alignment of a layer, in elements
-constexpr int kSlotCapMax = 512;     // candidate centres one tile of a layer on the candidate path can record
+constexpr int kSlotCapMax = 512;     // candidate centres one tile of a layer on the candidate path can record (single elements: up to all of its 4096)
 constexpr int kSlotGroup = 16;       // tile slots per work item of the candidate passes (one per wave)
 constexpr int kFineShift = 13;       // candidate path: the first ranking digit counts score bits in steps of 2^13
 constexpr int kFineBins = 1024;      // ... relative to the candidate bound: 1024 bins = one binade above it
@@ -30,7 +30,9 @@ constexpr int kGroupCntStride = 32;   // words between two chunk-group counters 
 constexpr uint32_t kInlineCountChunks = 4096;   // plans up to this many chunks (33 M elements) count their kept elements where the bits are set
 constexpr int kListCntStride = 32;   // uint32 between two of them (one 128-byte line each)
 constexpr uint32_t kSelectTiles = 1024;  // a plan goes through k_select while its largest layer has at most so many tiles ...
-constexpr uint32_t kSelectMaxK = 32768;  // ... and selects at most so many centres
+// ... and selects at most so many centres.  One layer, k_select / the launches it replaces: 512 x 512 with 13108 centres 30.7 / 32.3 us,
+// 1024 x 1024 with 15147 40.2 / 41.4, 2048 x 1024 with 20972 41.2 / 38.7, 2048 x 2048 with 9321 44.7 / 47.3 and with 23302 58.9 / 53.7.
+constexpr uint32_t kSelectMaxK = 16384;
 constexpr int kBigMapLayer = 1 << 20; // elements from which a full-map layer's bucket list goes through k_filter
 // Candidate bound predicted from the thresholds of the two calls before, on a log2 scale: used
 // while the threshold moved by at most kTrendMaxLog2 between those calls.

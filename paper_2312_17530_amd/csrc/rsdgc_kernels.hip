@@ -1082,6 +1082,173 @@ struct NsiAllArgs {
     uint32_t first_wg[kSides + 1];
 };
 
+// The main pass of layers whose neighbourhoods are single elements: Eqs. 8-10 leave NSI = alpha |v| there (sum|w| = |v|, the
+// variance is exactly 0; nsi_from_var's floor for it vanishes in the rounding to float32), so there is no halo, no tile in LDS
+// and no test in front of the score.  A workgroup takes tiles as in nsi_pass; what reaches the bound goes straight to the tile's
+// slot.  What bounds it is the streaming of g, r and v.  Small groups of layers with other neighbourhoods (up to kRideTiles tiles
+// a side) ride along as workgroups of the same launch: alone, a side's launch takes 8 to 15 us however few its tiles are.
+// ResNet-50 with all its vectors, p after the kernels' sides: four launches of 24.1, 23.4, 34.4 and 14.6 us before, now two of 30.3 and 37.2;
+// the call, whose magnitudes no longer need the score map, 191.7 -> 138.0 us.  2048 x 1024 at 2 % 60.0 -> 38.9 us, 8192 x 4096 232.7 -> 136.8.
+struct FlatShared {
+    uint32_t lhist[kFineBins];
+    uint32_t n[2];                        // candidates of the tile; the other one is being cleared
+};
+template <bool MOM>
+__device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, uint32_t wg, uint32_t n_wgs) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (uint32_t j = wg * 256u + tid; j < a.n16; j += n_wgs * 256u) a.counts[j] = make_uint4(0, 0, 0, 0);
+    const uint32_t first = xcd_contiguous(wg, n_wgs);
+    if (first >= a.n_tiles) return;
+    for (int b = tid; b < kFineBins; b += 256) sh.lhist[b] = 0u;
+    if (tid < 2) sh.n[tid] = 0u;
+    __syncthreads();
+    SampleEntry ahead = a.samples[first];
+    uint32_t cur_l = 0xffffffffu, hint_key = 0, recorded = 0, par = 0;
+    bool active = false;
+    LayerDev L;
+    const double ca = a.ca;
+    auto flush = [&]() {                  // the finished layer's counts
+        uint32_t *__restrict__ gh = a.hist_s + static_cast<size_t>(cur_l) * kHistBins;
+        for (int b = tid; b < kFineBins; b += 256) {
+            const uint32_t c = sh.lhist[b];
+            if (c) { atomicAdd(&gh[b], c); sh.lhist[b] = 0u; }
+        }
+        if (tid == 0 && recorded) atomicAdd(recorded_slot(a.list_cnt, cur_l, wg), recorded);
+        recorded = 0;
+    };
+    for (uint32_t t = first; t < a.n_tiles; t += n_wgs) {
+        const uint32_t l = ahead.layer, local = ahead.local_tile;
+        if (t + n_wgs < a.n_tiles) ahead = a.samples[t + n_wgs];
+        if (l != cur_l) {
+            if (active) {                 // uniform
+                flush();
+                __syncthreads();
+            }
+            cur_l = l;
+            L = a.layers[l];
+            const SelState st = a.state[l];
+            active = st.mode == kModeCandidates;
+            hint_key = st.hint_key;
+            if (active && (hint_key < kPreF32MinKey || hint_key > kPreF32MaxKey)) {      // (as in nsi_pass)
+                active = false;
+                if (tid == 0 && hint_key != 0u) a.state_rw[l].overflow = 1u;
+            }
+        }
+        if (!active) continue;
+        const int trow = static_cast<int>(local / L.tiles_x), tcol = static_cast<int>(local - static_cast<uint32_t>(trow) * L.tiles_x);
+        const int R = static_cast<int>(L.R), C = static_cast<int>(L.C), x0 = trow * kTileRows, y0 = tcol * kTileCols;
+        const float *__restrict__ g = a.grad + L.elem_off;
+        const float *__restrict__ r = a.resid + L.elem_off;
+        const float *__restrict__ u = MOM ? a.mom + L.elem_off : nullptr;
+        const uint32_t cap = L.slot_cap;
+        unsigned long long *__restrict__ dst = a.slot_ent + L.slot_off + static_cast<size_t>(local) * cap;
+        auto record = [&](float v, bool in, uint32_t index) {        // by whole waves
+            const uint32_t key = __float_as_uint(static_cast<float>(ca * static_cast<double>(fabsf(v)))) & 0x7fffffffu;
+            const bool hit = in && key >= hint_key;
+            const uint32_t pos = wave_append(&sh.n[par], hit);
+            if (hit) {
+                if (pos < cap) dst[pos] = composite_key(key, index);
+                atomicAdd(&sh.lhist[min((key - hint_key) >> kFineShift, static_cast<uint32_t>(kFineBins - 1))], 1u);
+            }
+        };
+        if ((C & 3) == 0) {               // wave w takes rows w, w + 4, ..., lane j the 16 bytes at column 4 j
+            constexpr int N = kTileRows / 4;
+            const int y = y0 + 4 * lane;
+            float4 gv[N], rv[N], uv[MOM ? N : 1];
+            bool in[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const int x = x0 + 4 * q + wave;
+                in[q] = x < R && y < C;
+                gv[q] = rv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (MOM) uv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (in[q]) {
+                    const size_t off = static_cast<size_t>(x) * C + y;
+                    gv[q] = load_streaming(g + off);
+                    rv[q] = load_streaming(r + off);
+                    if (MOM) uv[q] = load_streaming(u + off);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const uint32_t at = static_cast<uint32_t>(x0 + 4 * q + wave) * L.C + static_cast<uint32_t>(y);
+                if (MOM) {
+                    gv[q] = make_float4(__fmul_rn(a.m, uv[q].x) + gv[q].x, __fmul_rn(a.m, uv[q].y) + gv[q].y,
+                                        __fmul_rn(a.m, uv[q].z) + gv[q].z, __fmul_rn(a.m, uv[q].w) + gv[q].w);
+                    if (in[q] && a.mom_out) store_streaming(a.mom_out + L.elem_off + at, gv[q]);
+                }
+                const float4 v = make_float4(rv[q].x + gv[q].x, rv[q].y + gv[q].y, rv[q].z + gv[q].z, rv[q].w + gv[q].w);
+                if (in[q] && a.v_out) store_streaming(a.v_out + L.elem_off + at, v);
+                record(v.x, in[q], at);
+                record(v.y, in[q], at + 1u);
+                record(v.z, in[q], at + 2u);
+                record(v.w, in[q], at + 3u);
+            }
+        } else {
+#pragma unroll 1
+            for (int q = 0; q < kTileRows; q += 4) {                 // four rows' elements of a column at a time
+                float gq[4], rq[4], uq[MOM ? 4 : 1];
+                const int y = y0 + tid;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    gq[i] = rq[i] = 0.f;
+                    if (MOM) uq[i] = 0.f;
+                    if (x0 + q + i < R && y < C) {
+                        const size_t off = static_cast<size_t>(x0 + q + i) * C + y;
+                        gq[i] = g[off];
+                        rq[i] = r[off];
+                        if (MOM) uq[i] = u[off];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool in = x0 + q + i < R && y < C;
+                    const uint32_t at = static_cast<uint32_t>(x0 + q + i) * L.C + static_cast<uint32_t>(y);
+                    if (MOM) {
+                        gq[i] = __fmul_rn(a.m, uq[i]) + gq[i];
+                        if (in && a.mom_out) a.mom_out[L.elem_off + at] = gq[i];
+                    }
+                    const float v = rq[i] + gq[i];
+                    if (in && a.v_out) a.v_out[L.elem_off + at] = v;
+                    record(v, in, at);
+                }
+            }
+        }
+        __syncthreads();                  // all of the tile's candidates are recorded
+        if (tid == 0) {
+            const uint32_t n = sh.n[par];
+            recorded += n;
+            a.slot_cnt[L.tile_begin_all + local] = min(n, cap);
+            if (n > cap) a.state_rw[l].overflow = 1u;
+            sh.n[par] = 0u;               // (used again after the next tile's barrier)
+        }
+        par ^= 1u;
+    }
+    if (active) flush();
+}
+template <bool MOM>
+__global__ __launch_bounds__(256) void k_capture_flat(const NsiArgs a) {
+    __shared__ FlatShared sh;
+    capture_flat<MOM>(a, sh, blockIdx.x, gridDim.x);
+}
+// ... with the small groups of other sides: a range of workgroups each, theirs first (they take longest).
+template <bool MOM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_capture_mixed(const NsiAllArgs a) {
+    __shared__ union Shared {
+        FlatShared flat;
+        NsiShared<3, kPassCapture> s3;
+        NsiShared<5, kPassCapture> s5;
+        NsiShared<7, kPassCapture> s7;
+        __device__ Shared() {}
+    } sh;
+    const uint32_t b = blockIdx.x;
+    if (b < a.first_wg[1]) nsi_pass<7, kPassCapture, MOM, false>(a.side[3], sh.s7, b, a.first_wg[1]);
+    else if (b < a.first_wg[2]) nsi_pass<5, kPassCapture, MOM, false>(a.side[2], sh.s5, b - a.first_wg[1], a.first_wg[2] - a.first_wg[1]);
+    else if (b < a.first_wg[3]) nsi_pass<3, kPassCapture, MOM, false>(a.side[1], sh.s3, b - a.first_wg[2], a.first_wg[3] - a.first_wg[2]);
+    else capture_flat<MOM>(a.side[0], sh.flat, b - a.first_wg[3], a.first_wg[4] - a.first_wg[3]);
+}
+constexpr uint32_t kRideTiles = 256;      // tiles of a side up to which it rides along: one round of workgroups
+
 // ------------------------------------------------------- ranking digits --
 // The k_l-th largest composite key of a layer (Algorithm 1's ranking, Eq. 11's k_l) is found
 // digit by digit, most significant first:
@@ -1940,7 +2107,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 __syncthreads();
                 if (COUNT) q.cl0 = group_first_chunk(q, marks.corner[0]);
                 for (uint32_t j = j0; j < cnt; j += LPS) {
-                    if (j != j0) K = slot[j];
+                    const unsigned long long next = j + LPS < cnt ? slot[j + LPS] : 0ull;        // (on its way while this one is marked)
                     const uint32_t score = static_cast<uint32_t>(K >> 32);
                     if (score >= above) {                        // selected for certain
                         const uint32_t i = ~static_cast<uint32_t>(K);
@@ -1954,6 +2121,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                         if (pos < list.cap) list.ent[pos] = K;
                         atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
                     }
+                    K = next;
                 }
                 __syncthreads();
                 group_write<COUNT, 256>(q, marks);
@@ -4738,6 +4906,10 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     const bool together = PASS == kPassFullMap && find0_args && plan->groups.size() > 1 && plan->n_tiles_all < kFeedTiles;
     NsiAllArgs all = {};
     uint32_t all_items = 0;
+    // the main pass of single elements has a kernel of its own, which takes small groups of other sides along
+    uint32_t n_flat = 0;
+    for (const PGroup &g : plan->groups)
+        if (PASS == kPassCapture && g.p == 1) n_flat = g.n_large_tiles;
     for (const PGroup &g : plan->groups) {
         // this launch's work-feed counters (left clear by the call before)
         const int pass_index = PASS == kPassSample ? 0 : PASS == kPassCapture ? 1 : 2;
@@ -4754,7 +4926,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
                                                    : kLargeOnly ? g.n_large_tiles : g.n_tiles;
         if (items == 0) continue;
         a.n_tiles = items;
-        if (together) {
+        if (together || (n_flat != 0u && (g.p == 1 || (items <= kRideTiles && plan->work_feed != RSDGC_FEED_ON)))) {
             all.side[g.p / 2] = a;
             all_items += items;
             continue;
@@ -4793,13 +4965,34 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         }                                                                                   \
         break;                                                                              \
     }
-            RSDGC_NSI_CASE(1)
+            case 1:
+                if constexpr (PASS != kPassCapture) {
+                    switch (1) { RSDGC_NSI_CASE(1) }
+                }
+                break;
             RSDGC_NSI_CASE(3)
             RSDGC_NSI_CASE(5)
             RSDGC_NSI_CASE(7)
 #undef RSDGC_NSI_CASE
 #undef RSDGC_NSI_LAUNCH
             default: return RSDGC_EINVAL;
+        }
+        HIP_TRY(hipGetLastError());
+    }
+    if (n_flat != 0u) {
+        const bool alone = all_items == n_flat;
+        static const uint32_t resident[2][2] = {{resident_workgroups(k_capture_mixed<false>), resident_workgroups(k_capture_mixed<true>)},
+                                                {resident_workgroups(k_capture_flat<false>), resident_workgroups(k_capture_flat<true>)}};
+        const uint32_t most = resident[alone ? 1 : 0][mom.in ? 1 : 0];
+        const uint32_t rounds = (n_flat + most - 1) / most, n_wgs = (n_flat + rounds - 1) / rounds;        // (shares as below)
+        if (alone) {
+            if (mom.in) hipLaunchKernelGGL(k_capture_flat<true>, dim3(n_wgs), dim3(256), 0, stream, all.side[0]);
+            else hipLaunchKernelGGL(k_capture_flat<false>, dim3(n_wgs), dim3(256), 0, stream, all.side[0]);
+        } else {
+            for (int i = 1; i < kSides; ++i) all.first_wg[i] = all.first_wg[i - 1] + all.side[kSides - i].n_tiles;   // a tile each
+            all.first_wg[kSides] = all.first_wg[kSides - 1] + n_wgs;
+            if (mom.in) hipLaunchKernelGGL(k_capture_mixed<true>, dim3(all.first_wg[kSides]), dim3(256), 0, stream, all);
+            else hipLaunchKernelGGL(k_capture_mixed<false>, dim3(all.first_wg[kSides]), dim3(256), 0, stream, all);
         }
         HIP_TRY(hipGetLastError());
     }

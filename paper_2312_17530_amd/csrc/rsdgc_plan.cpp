@@ -40,7 +40,9 @@ int build_tables(rsdgc_plan_s *plan) {
 
     int64_t elem_off = 0, out_off = 0, centre_off = 0;
     uint32_t chunk_begin = 0, tile_begin_all = 0, group_begin = 0, cgroup_begin = 0;
+    uint32_t sized_tiles = 0, sized_groups = 0;       // what the workspace is sized for
     uint64_t list_off = 0, slot_off = 0;
+    std::vector<bool> slots_in_map(L, false);
     for (int l = 0; l < L; ++l) {
         LayerDev &d = plan->layers[l];
         int64_t R = plan->shapes[l].rows, C = plan->shapes[l].cols;
@@ -49,7 +51,21 @@ int build_tables(rsdgc_plan_s *plan) {
         // A single column is handled as a single row: the same elements at the same flat indices with
         // the same neighbours (Eq. 7's distance on one axis only), and rows are what the tiles stream.
         // (Not for a block grid, whose wire format depends on the orientation of the p x p blocks.)
-        if (C == 1 && !plan->blocks && plan->k_override.empty()) std::swap(R, C);
+        const bool elements = !plan->blocks && plan->k_override.empty();
+        if (C == 1 && elements) std::swap(R, C);
+        // Neighbourhoods of one element: which rows the elements lie in makes no difference.  Rows of 256, or of as many whole mask
+        // words as divide the layer, make a tile that many elements in a row, whatever the layer's shape (a tile of a
+        // vector or of a narrow matrix leaves most lanes idle), unless that takes more tiles.  100000 x 10 at 2 %: 232 us a call before, now 35; 1 x 1000000: 61.7, now 34.7.
+        // The workspace stays sized for the layer's own rows: its size is part of what callers rely on.
+        const uint32_t shape_tiles = static_cast<uint32_t>((C + kTileCols - 1) / kTileCols) * static_cast<uint32_t>((R + kTileRows - 1) / kTileRows);
+        const int64_t shape_slot = std::min<int64_t>(kSlotCapMax, (std::min<int64_t>(R, kTileRows) * std::min<int64_t>(C, kTileCols) + 1) & ~int64_t(1));
+        int64_t flat_cols = p == 1 && elements ? kTileCols : 0;
+        while (flat_cols > 0 && (G % flat_cols != 0 || (G / flat_cols + kTileRows - 1) / kTileRows > int64_t(shape_tiles))) flat_cols -= 32;
+        const bool flat = flat_cols > 0;
+        if (flat) {
+            R = G / flat_cols;
+            C = flat_cols;
+        }
         const int64_t k = plan->k_override.empty() ? keep_count(G, p, plan->ratio[l]) : plan->k_override[l];
         int64_t cap = k * p * p;
         if (cap > G && !plan->blocks) cap = G;   // (a kept block always sends p*p values, padding included)
@@ -103,13 +119,26 @@ int build_tables(rsdgc_plan_s *plan) {
         const double frac = d.n_tiles ? double(n_sampled) / double(d.n_tiles) : 0.0;
         const double want = 2.0 * double(k) * frac;
         const double per_tile = d.n_tiles ? 8.0 * double(k) / double(d.n_tiles) : 0.0;
-        d.large = (plan->allow_candidates && k > 0 && per_tile <= double(kSlotCapMax)) ? 1u : 0u;
+        const double per_shape_tile = shape_tiles ? 8.0 * double(k) / double(shape_tiles) : 0.0;
+        d.large = (plan->allow_candidates && k > 0 && (elements ? per_shape_tile : per_tile) <= double(kSlotCapMax)) ? 1u : 0u;
         // (a tile of a narrow or flat layer holds fewer elements than kSlotCapMax: its slots are that short.
         // The size follows from the shape alone, so the layout does not move with the ratios.)
         const int64_t tile_elems = std::min<int64_t>(R, kTileRows) * std::min<int64_t>(C, kTileCols);
         d.slot_cap = static_cast<uint32_t>(std::min<int64_t>(kSlotCapMax, (tile_elems + 1) & ~int64_t(1)));
         d.slot_off = slot_off;
-        slot_off += static_cast<uint64_t>(d.n_tiles) * d.slot_cap;
+        slot_off += elements ? static_cast<uint64_t>(shape_tiles) * static_cast<uint64_t>(shape_slot)
+                             : static_cast<uint64_t>(d.n_tiles) * d.slot_cap;
+        if (flat) {
+            // Slots as long as there is room for: where the layer's slots have their place, or in the layer's part of the score
+            // map, which is written only when the layer is not on the candidate path (any more).  So the magnitudes of a
+            // layer are eligible up to a keep ratio of about 6 %, not 1.5 %: the map costs them a pass of its own.
+            const uint64_t there = static_cast<uint64_t>(shape_tiles) * static_cast<uint64_t>(shape_slot) / d.n_tiles;
+            const uint64_t in_map = static_cast<uint64_t>(G) / 2 / d.n_tiles;
+            slots_in_map[l] = in_map > there;
+            const uint64_t most = std::min<uint64_t>(static_cast<uint64_t>(std::min<int64_t>(kTileRows * C, G)), std::max(there, in_map));
+            d.slot_cap = static_cast<uint32_t>(most & ~uint64_t(1));
+            if (plan->allow_candidates && k > 0 && per_tile <= double(d.slot_cap)) d.large = 1u;
+        }
         d.hint_target = d.large ? static_cast<uint32_t>(std::ceil(want + 4.0 * std::sqrt(want) + 8.0)) : 0u;
         plan->any_large = plan->any_large || d.large;
         if (!d.large && k > 0 && G >= kBigMapLayer) plan->big_map_layers.push_back(static_cast<uint16_t>(l));   // (l < 65536)
@@ -118,6 +147,8 @@ int build_tables(rsdgc_plan_s *plan) {
         plan->all_tile_dir.push_back(DirEntry{tile_begin_all, static_cast<uint32_t>(l)});
         chunk_begin += d.n_chunks;
         tile_begin_all += d.n_tiles;
+        sized_tiles += elements ? shape_tiles : d.n_tiles;
+        sized_groups += elements ? (shape_tiles + kSlotGroup - 1) / kSlotGroup : d.n_groups;
         group_begin += d.n_groups;
         cgroup_begin += (d.n_chunks + kChunkGroup - 1) / kChunkGroup;
         elem_off += (G + kLayerAlign - 1) / kLayerAlign * kLayerAlign;
@@ -147,11 +178,9 @@ int build_tables(rsdgc_plan_s *plan) {
         if (d.large) {
             for (uint32_t g = 0; g < d.n_groups; ++g) {
                 const uint32_t t0 = g * kSlotGroup;
-                const uint64_t ent0 = d.slot_off + static_cast<uint64_t>(t0) * d.slot_cap;
                 plan->cand_groups.push_back(GroupEntry{static_cast<uint32_t>(l), d.tile_begin_all + t0,
-                                                       static_cast<uint8_t>(std::min<uint32_t>(kSlotGroup, d.n_tiles - t0)),
-                                                       static_cast<uint8_t>(ent0 >> 33),
-                                                       static_cast<uint16_t>(d.slot_cap), static_cast<uint32_t>(ent0 >> 1)});
+                                                       static_cast<uint8_t>(std::min<uint32_t>(kSlotGroup, d.n_tiles - t0)), 0u,
+                                                       static_cast<uint16_t>(d.slot_cap), 0u});     // (its entries' place: below)
             }
         } else if (d.k > 0) {
             for (uint32_t c = 0; c < d.n_chunks; ++c) {
@@ -218,7 +247,7 @@ int build_tables(rsdgc_plan_s *plan) {
     const size_t A = 256;
     const size_t words = static_cast<size_t>(plan->total_elems / 32);
     // sized for the worst case so that new ratios never change the workspace size
-    const size_t max_samples = plan->n_tiles_all;
+    const size_t max_samples = sized_tiles;
     size_t off = 0;
     w.layers = off;       off = align_up(off + sizeof(LayerDev) * L, A);
     w.tile_dir = off;     off = align_up(off + sizeof(DirEntry) * (L + (RSDGC_MAX_P + 1) / 2), A);
@@ -228,9 +257,9 @@ int build_tables(rsdgc_plan_s *plan) {
     w.samples = off;      off = align_up(off + sizeof(SampleEntry) * (max_samples + 1), A);
     w.chunk_layer = off;  off = align_up(off + sizeof(uint32_t) * plan->n_chunks, A);
     w.chunk_info = off;   off = align_up(off + sizeof(ChunkInfo) * plan->n_chunks, A);
-    w.cand_groups = off;  off = align_up(off + sizeof(GroupEntry) * plan->n_slot_groups, A);
+    w.cand_groups = off;  off = align_up(off + sizeof(GroupEntry) * sized_groups, A);
     w.map_chunks = off;   off = align_up(off + sizeof(ChunkEntry) * plan->n_chunks, A);
-    w.map_tiles = off;    off = align_up(off + sizeof(SampleEntry) * (size_t(plan->n_tiles_all) + 1), A);
+    w.map_tiles = off;    off = align_up(off + sizeof(SampleEntry) * (size_t(sized_tiles) + 1), A);
     w.count_groups = off; off = align_up(off + sizeof(CountGroup) * plan->n_count_groups, A);
     w.pred = off;         off = align_up(off + sizeof(PredState) * L, A);
     w.table_bytes = off;
@@ -250,7 +279,7 @@ int build_tables(rsdgc_plan_s *plan) {
     w.mask = off;         off = align_up(off + sizeof(uint32_t) * words, A);
     w.cmask = off;        off = align_up(off + sizeof(uint32_t) * words, A);
     w.zero_end = off;
-    w.slot_cnt = off;     off = align_up(off + sizeof(uint32_t) * plan->n_tiles_all, A);
+    w.slot_cnt = off;     off = align_up(off + sizeof(uint32_t) * sized_tiles, A);
     // (the plan of a block grid never takes the candidate path and has no tile slots)
     w.slot_ent = off;     off = align_up(off + (plan->k_override.empty() ? sizeof(uint64_t) * size_t(plan->slot_entries) : 0), A);
     w.list_ent = off;     off = align_up(off + sizeof(uint64_t) * static_cast<size_t>(list_off), A);
@@ -262,6 +291,15 @@ int build_tables(rsdgc_plan_s *plan) {
     w.dyn = off;          off = align_up(off + 256 + sizeof(uint64_t) * kHistBins + sizeof(uint32_t) * 2 * size_t(L), A);
     w.apply_starts = off; off = align_up(off + sizeof(uint32_t) * 2 * RSDGC_MAX_MSGS * static_cast<size_t>(plan->n_chunks), A);
     w.total = off;
+
+    for (int l = 0; l < L; ++l)                // (both sections start at a multiple of 256 bytes, a layer at one of 64 elements)
+        if (slots_in_map[l]) plan->layers[l].slot_off = (w.nsi - w.slot_ent) / sizeof(uint64_t) + static_cast<uint64_t>(plan->layers[l].elem_off) / 2;
+    for (GroupEntry &e : plan->cand_groups) {
+        const LayerDev &d = plan->layers[e.layer];
+        const uint64_t ent0 = d.slot_off + static_cast<uint64_t>(e.slot0 - d.tile_begin_all) * d.slot_cap;
+        e.ent0_high = static_cast<uint8_t>(ent0 >> 33);
+        e.ent0_low = static_cast<uint32_t>(ent0 >> 1);
+    }
 
     plan->table.assign(w.table_bytes, 0);
     std::memcpy(plan->table.data() + w.layers, plan->layers.data(), sizeof(LayerDev) * L);

@@ -489,3 +489,36 @@ def test_windows_across_the_edges_of_tiles_and_groups(p, more, feed):
             assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
             assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
         resid = after
+
+
+@pytest.mark.parametrize("sides, more", [([1], 0), ([1, 3, 5, 7], 0), ([1], 4100)], ids=["alone", "with_small_sides", "many_chunks"])
+@pytest.mark.parametrize("m, in_place", [(None, False), (0.9, False), (None, True)], ids=["plain", "momentum", "in_place"])
+def test_single_element_neighbourhoods(sides, more, m, in_place):
+    """Layers that are handled in rows of 256 whatever their shape: one tile, one row, just past a tile, a few tiles, narrow, flat and
+    tall ones, and layers whose size does not allow it; keep ratios up to where a layer leaves the candidate path; a layer
+    whose candidates lie in one tile and overfill its slot; layers of other sides that ride along; a gradient that
+    jumps, so that bounds fail.  Six calls; every one against the oracle."""
+    from paper_2312_17530_amd.session import Session
+    shapes = [(1, 256), (16, 256), (17, 256), (64, 64), (1, 2048), (128, 2), (40, 512), (512, 32), (70, 300), (1, 45), (256, 256),
+              (5, 1280), (300, 64), (3, 1), (500, 10), (1, 4160), (32, 331)] + [(1, 1 + l % 70) for l in range(more)]
+    ratios = [0.02, 0.06, 0.05, 0.03, 0.2, 0.5, 0.06, 0.1, 0.015, 0.3, 0.02, 0.25, 0.001, 1.0, 0.05, 0.03, 0.04] + [(0.0, 1.0, 0.3)[l % 3] for l in range(more)]
+    ps = [sides[l % len(sides)] if 3 <= l < 14 else 1 for l in range(len(shapes))]
+    rng = np.random.default_rng(11)
+    s = Session(shapes, 1, 0.5, ratios, ps, momentum=m, in_place=in_place)
+    resid = [np.zeros(sh, np.float32) for sh in shapes]
+    mom = [np.zeros(sh, np.float32) for sh in shapes]
+    for t in range(6 if more == 0 else 3):
+        scale = 1e-2 if t < 4 else 1e-4
+        grads = [(rng.standard_normal(sh) * scale).astype(np.float32) for sh in shapes]
+        grads[10][16:28] *= np.float32(50.0)
+        s.set_grad(grads)
+        s.compress()
+        after = s.unpack(s.residual)
+        u_after = s.unpack(s.momentum_buf) if m is not None else mom
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o, u_new = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, ps[l], 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+            if m is not None:
+                assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)
+        resid, mom = after, u_after
