@@ -1631,7 +1631,6 @@ __global__ __launch_bounds__(256) void k_find0_fallback_all(const Find0Args f, c
 // the device-scope fences it needs write back the whole L2 of an XCD each time and cost more
 // than the launch they save.)
 constexpr int kStage = 2048;            // staged keys per workgroup (a round adds at most 1024)
-constexpr int kSlotsPerWave = kSlotGroup / 4;   // tile slots of a group that one wave of a gather workgroup takes
 // Small plans: a workgroup takes a quarter of a group.  Their gather is one short chain per workgroup -- entry, slots, marks,
 // words -- on a chip that is mostly idle, and four workgroups get through it in less time than one.  The more groups there are,
 // the more the words that neighbours share, and their atomics, weigh; where the line lies between 377 and 512 groups was not
@@ -1795,13 +1794,16 @@ __device__ __forceinline__ void gather_map_chunk(const GatherArgs &a, const Chun
     }
 }
 
-// A group of consecutive tile slots of a layer whose rows are whole mask words: every mask word of the layer then lies in
-// exactly one tile.  The workgroup builds the words of its tiles in LDS from the group's own candidates and writes them with
-// plain stores, whole cache lines at a time -- except the words that windows of other groups' candidates can reach (the h rows
-// along a tile's upper and lower edge, the first and last word of the group's run of tiles): those, and the bits that the group's
+// A group of consecutive tile slots of a layer.  The workgroup builds the bits of its tiles in LDS, eight words per tile row,
+// from the group's own candidates and writes them with plain stores, whole cache lines at a time -- except the mask words that others
+// write too: those that windows of other groups' candidates can reach (the h rows along a tile's upper and lower edge, the first
+// and last columns of the group's run of tiles), and, where a row is no multiple of 32 long, those that hold the
+// end of one tile row and the beginning of another.  Those, and the bits that the group's
 // windows set in other groups' tiles, are ORed into the (cleared) mask.  Words without a bit are not written.
 // COUNT: the bits are counted as they are set (an OR tells which were new), per chunk, in LDS first: a group of tiles
 // lies in a few chunks.
+// Rows that are no whole mask words took a returning atomic for every row of every window before, one after the other: calls on
+// 1448 x 1448 with p = 3 at 2 % 69.2 us, now 35.4, at 13 % 238.0, now 48.7; 999 x 1001 with p = 1 95.9, now 33.2; 20000 x 45 65.4, now 38.7.
 // What bounds this is the number of instructions, a few hundred per wave: no division by anything but the tile's corner (once per
 // tile), a window's rows addressed from the tile it starts in, and what crosses a tile's side edge in a second round that a wave
 // only takes when one of its lanes needs it.  With the place of every row and word worked out by itself (1700 instructions per
@@ -1809,7 +1811,6 @@ __device__ __forceinline__ void gather_map_chunk(const GatherArgs &a, const Chun
 struct GroupGeom {
     int h, C, R, tiles_x;
     int g0, gn;                           // the group's first tile inside the layer, and how many
-    uint32_t words_x;                     // mask words per matrix row
     uint32_t cl0;                         // COUNT: first chunk that the group's windows can reach
     float inv_c;                          // a little below 1 / C
     uint32_t *mask;                       // the layer's first mask word
@@ -1823,7 +1824,6 @@ __device__ __forceinline__ GroupGeom group_geom(const LayerDev &L, uint32_t g0, 
     q.tiles_x = static_cast<int>(L.tiles_x);
     q.g0 = static_cast<int>(g0);
     q.gn = static_cast<int>(gn);
-    q.words_x = L.C >> 5;
     q.cl0 = 0;
     q.inv_c = (1.f - 4.8e-7f) / static_cast<float>(L.C);
     q.mask = mask + (static_cast<size_t>(L.elem_off) >> 5);
@@ -1854,8 +1854,8 @@ __device__ __forceinline__ void group_count(const GroupGeom &q, GroupMarks<SLOTS
 }
 // The window of the candidate with flat index i, which lies in the group's tile sidx.
 template <bool COUNT, int SLOTS>
-__device__ __forceinline__ void group_mark(const GroupGeom &q, GroupMarks<SLOTS> &sh, int sidx, uint32_t i) {
-    const uint2 corner = sh.corner[sidx];
+__device__ __forceinline__ void group_mark(const GroupGeom &q, GroupMarks<SLOTS> &sh_, int sidx, uint32_t i) {
+    const uint2 corner = sh_.corner[sidx];
     const uint32_t C = static_cast<uint32_t>(q.C);
     const uint32_t d = i - (corner.x * C + corner.y);
     // row inside the tile (below 16): the product is exact or one too low (inv_c is 2^-21 low, the roundings add up to less)
@@ -1875,29 +1875,30 @@ __device__ __forceinline__ void group_mark(const GroupGeom &q, GroupMarks<SLOTS>
         const uint32_t w0 = static_cast<uint32_t>(a) >> 5, b0 = static_cast<uint32_t>(a) & 31u;
         const uint32_t len = static_cast<uint32_t>(b - a + 1), run = (1u << len) - 1u;
         const uint32_t bits0 = run << b0, bits1 = b0 + len > 32u ? run >> (32u - b0) : 0u;
-        const uint32_t col_word = ((corner.y + static_cast<uint32_t>((s - sidx) * kTileCols)) >> 5) + w0;
+        const uint32_t col = corner.y + static_cast<uint32_t>((s - sidx) * kTileCols + a);
 #pragma unroll 1
         for (int o = oa; o <= ob; ++o) {
             int t = s, row = o;
             if (o < 0) { t -= q.tiles_x; row += kTileRows; }
             if (o >= kTileRows) { t += q.tiles_x; row -= kTileRows; }
             if (static_cast<uint32_t>(t) < static_cast<uint32_t>(q.gn)) {
-                uint32_t *w = sh.bits + t * kSlotPitch + row * (kTileCols / 32) + w0;
+                uint32_t *w = sh_.bits + t * kSlotPitch + row * (kTileCols / 32) + w0;
                 atomicOr(w, bits0);
                 if (bits1) atomicOr(w + 1, bits1);
             } else {                      // another group's tile: straight into the mask
-                const uint32_t word = static_cast<uint32_t>(static_cast<int>(corner.x) + o) * q.words_x + col_word;
+                const uint32_t pos = static_cast<uint32_t>(static_cast<int>(corner.x) + o) * C + col, word = pos >> 5, sh = pos & 31u;
                 uint32_t *w = q.mask + word;
+                const uint32_t over = sh + len > 32u ? run >> (32u - sh) : 0u;
                 if (!COUNT) {
-                    atomicOr(w, bits0);
-                    if (bits1) atomicOr(w + 1, bits1);
+                    atomicOr(w, run << sh);
+                    if (over) atomicOr(w + 1, over);
                 } else {                  // ... and the new bits counted
 #pragma unroll
                     for (uint32_t j = 0; j < 2u; ++j) {
-                        const uint32_t bits = j == 0u ? bits0 : bits1;
+                        const uint32_t bits = j == 0u ? run << sh : over;
                         if (bits == 0u) continue;
                         const uint32_t fresh = __popc(bits & ~atomicOr(w + j, bits));
-                        if (fresh) group_count(q, sh, word + j, fresh);
+                        if (fresh) group_count(q, sh_, word + j, fresh);
                     }
                 }
             }
@@ -1909,7 +1910,19 @@ __device__ __forceinline__ void group_mark(const GroupGeom &q, GroupMarks<SLOTS>
     }
 }
 // The group's words, after a barrier.  Neighbouring tiles of one tile row are neighbours in memory: consecutive threads walk
-// along a matrix row through the group's tiles, so a wave writes whole cache lines.
+// along a matrix row through the group's tiles, so a wave writes whole cache lines.  Thread ww of the eight of a tile row writes the
+// mask word that begins with the last bits of the row's word ww - 1, if the row does not begin with a mask word; the last
+// thread then has a ninth.
+template <bool COUNT, int SLOTS>
+__device__ __forceinline__ void group_put(const GroupGeom &q, GroupMarks<SLOTS> &sh, uint32_t at, uint32_t word, bool owned) {
+    if (word == 0u) return;
+    uint32_t *dst = q.mask + at;
+    uint32_t fresh = word;
+    if (owned) *dst = word;
+    else if (COUNT) fresh = word & ~atomicOr(dst, word);
+    else atomicOr(dst, word);
+    if (COUNT && fresh) group_count(q, sh, at, __popc(fresh));
+}
 template <bool COUNT, int THREADS, int SLOTS>
 __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS> &sh) {
     constexpr uint32_t ROW = SLOTS * (kTileCols / 32);              // words of one row through the group
@@ -1918,23 +1931,22 @@ __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS
     if (sidx < q.gn) {
         const uint2 corner = sh.corner[sidx];
         const int h = q.h, below = q.R - static_cast<int>(corner.x) - kTileRows;             // rows of the matrix below the tile
-        const bool side = (ww == 0u && sidx == 0 && corner.y > 0u) ||
-                          (ww == 7u && sidx == q.gn - 1 && static_cast<int>(corner.y) + kTileCols < q.C);
-        const uint32_t first = corner.x * q.words_x + (corner.y >> 5) + ww;
+        const int cols = q.C - static_cast<int>(corner.y);                                   // ... columns from the tile's first on
+        // the columns that no other group's candidates reach and that no other tile row shares a word with
+        const int c_lo = sidx == 0 && corner.y > 0u ? h : 0;
+        const int c_hi = cols <= kTileCols ? cols : sidx == q.gn - 1 ? kTileCols - h : kTileCols;
         for (uint32_t row = tid / ROW; row < static_cast<uint32_t>(kTileRows); row += THREADS / ROW) {
-            const uint32_t word = sh.bits[sidx * kSlotPitch + row * (kTileCols / 32) + ww];
-            if (word == 0u) continue;
-            const uint32_t at = first + row * q.words_x;
-            uint32_t *dst = q.mask + at;
-            const int rr = static_cast<int>(row);
-            uint32_t fresh = word;
-            if (side || (rr < h && corner.x > 0u) || (rr >= kTileRows - h && below > 0)) {
-                if (COUNT) fresh = word & ~atomicOr(dst, word);
-                else atomicOr(dst, word);
-            } else {
-                *dst = word;
+            const uint32_t *bits = sh.bits + sidx * kSlotPitch + row * (kTileCols / 32) + ww;
+            const uint32_t pos = (corner.x + row) * static_cast<uint32_t>(q.C) + corner.y, shift = pos & 31u;
+            const int rr = static_cast<int>(row), c0 = 32 * static_cast<int>(ww) - static_cast<int>(shift);      // the word's first column
+            const bool inner = !((rr < h && corner.x > 0u) || (rr >= kTileRows - h && below > 0));
+            uint32_t word = bits[0];
+            if (shift) {                  // (uniform where rows are whole words: 0)
+                if (ww == 7u) group_put<COUNT>(q, sh, (pos >> 5) + 8u, word >> (32u - shift), inner && c0 + 64 <= c_hi);
+                word <<= shift;
+                if (ww != 0u) word |= bits[-1] >> (32u - shift);
             }
-            if (COUNT && fresh) group_count(q, sh, at, __popc(fresh));
+            group_put<COUNT>(q, sh, (pos >> 5) + ww, word, inner && c0 >= c_lo && c0 + 32 <= c_hi);
         }
     }
     static_assert(kGatherCountSlots == 64, "one lane of the first wave per counted chunk");
@@ -1948,7 +1960,7 @@ __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS
 template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     if (blockIdx.x < gl.n_map_chunks) {
         gather_map_chunk(a, gl.map_chunks[blockIdx.x], sh);
         return;
@@ -2083,85 +2095,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             }
         } else {
             const uint32_t slot_cap = ge.slot_cap;
-            const WindowGeom geom = {static_cast<size_t>(L.elem_off), static_cast<int>(L.R), static_cast<int>(L.C),
-                                     (static_cast<int>(L.p) - 1) / 2};
             const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
-            if ((L.C & 31u) == 0u) {
-                GroupMarks<SLOTS> &marks = *reinterpret_cast<GroupMarks<SLOTS> *>(&sh.marks);      // (a quarter needs less)
-                GroupGeom q = group_geom(L, ge.slot0 - L.tile_begin_all, ge.ntile, a.mask, cctx);
-                // LPS lanes per tile slot; a round covers as many entries of each.  The first entries are requested
-                // beside the slot's count (a slot always has them; past the count they hold anything)
-                constexpr uint32_t LPS = 256 / SLOTS;
-                const int sidx = tid / static_cast<int>(LPS);
-                const uint32_t j0 = static_cast<uint32_t>(tid) % LPS;
-                const unsigned long long *__restrict__ slot = ent0 + static_cast<size_t>(sidx) * slot_cap;
-                unsigned long long K = 0;
-                uint32_t cnt = 0;
-                if (sidx < q.gn) {
-                    cnt = a.slot_cnt[ge.slot0 + static_cast<uint32_t>(sidx)];
-                    if (j0 < slot_cap) K = slot[j0];
-                    cnt = min(cnt, slot_cap);
-                }
-                if (it != first) __syncthreads();                // (the previous group's words are written)
-                group_clear<256>(q, marks);
-                __syncthreads();
-                if (COUNT) q.cl0 = group_first_chunk(q, marks.corner[0]);
-                for (uint32_t j = j0; j < cnt; j += LPS) {
-                    const unsigned long long next = j + LPS < cnt ? slot[j + LPS] : 0ull;        // (on its way while this one is marked)
-                    const uint32_t score = static_cast<uint32_t>(K >> 32);
-                    if (score >= above) {                        // selected for certain
-                        const uint32_t i = ~static_cast<uint32_t>(K);
-                        group_mark<COUNT>(q, marks, sidx, i);
-                        if (a.cmask) {
-                            const size_t pos = geom.elem_off + i;
-                            atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
-                        }
-                    } else if (score - lo < width) {             // in the threshold bucket (never when the layer is done):
-                        const uint32_t pos = atomicAdd(list.cnt, 1u);           // few of them, one atomic each
-                        if (pos < list.cap) list.ent[pos] = K;
-                        atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
+            GroupMarks<SLOTS> &marks = *reinterpret_cast<GroupMarks<SLOTS> *>(&sh.marks);      // (a quarter needs less)
+            GroupGeom q = group_geom(L, ge.slot0 - L.tile_begin_all, ge.ntile, a.mask, cctx);
+            // LPS lanes per tile slot; a round covers as many entries of each.  The first entries are requested
+            // beside the slot's count (a slot always has them; past the count they hold anything)
+            constexpr uint32_t LPS = 256 / SLOTS;
+            const int sidx = tid / static_cast<int>(LPS);
+            const uint32_t j0 = static_cast<uint32_t>(tid) % LPS;
+            const unsigned long long *__restrict__ slot = ent0 + static_cast<size_t>(sidx) * slot_cap;
+            unsigned long long K = 0;
+            uint32_t cnt = 0;
+            if (sidx < q.gn) {
+                cnt = a.slot_cnt[ge.slot0 + static_cast<uint32_t>(sidx)];
+                if (j0 < slot_cap) K = slot[j0];
+                cnt = min(cnt, slot_cap);
+            }
+            if (it != first) __syncthreads();                // (the previous group's words are written)
+            group_clear<256>(q, marks);
+            __syncthreads();
+            if (COUNT) q.cl0 = group_first_chunk(q, marks.corner[0]);
+            for (uint32_t j = j0; j < cnt; j += LPS) {
+                const unsigned long long next = j + LPS < cnt ? slot[j + LPS] : 0ull;        // (on its way while this one is marked)
+                const uint32_t score = static_cast<uint32_t>(K >> 32);
+                if (score >= above) {                        // selected for certain
+                    const uint32_t i = ~static_cast<uint32_t>(K);
+                    group_mark<COUNT>(q, marks, sidx, i);
+                    if (a.cmask) {
+                        const size_t pos = static_cast<size_t>(L.elem_off) + i;
+                        atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
                     }
-                    K = next;
+                } else if (score - lo < width) {             // in the threshold bucket (never when the layer is done):
+                    const uint32_t pos = atomicAdd(list.cnt, 1u);           // few of them, one atomic each
+                    if (pos < list.cap) list.ent[pos] = K;
+                    atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
                 }
-                __syncthreads();
-                group_write<COUNT, 256>(q, marks);
-            } else {
-            // each wave takes 4 of the group's tile slots; a round covers 64 entries of each
-            uint32_t cnt[kSlotsPerWave];
-            uint32_t longest = 0;
-#pragma unroll
-            for (int c = 0; c < kSlotsPerWave; ++c) {
-                const uint32_t s = static_cast<uint32_t>(wave) + 4u * c;
-                cnt[c] = s < ge.ntile ? min(a.slot_cnt[ge.slot0 + s], slot_cap) : 0u;
-                longest = max(longest, cnt[c]);                     // wave-uniform
+                K = next;
             }
-            for (uint32_t j0 = 0; j0 < longest; j0 += 64) {
-                const uint32_t j = j0 + lane;
-                unsigned long long K[kSlotsPerWave];
-#pragma unroll
-                for (int c = 0; c < kSlotsPerWave; ++c)
-                    K[c] = j < cnt[c] ? ent0[static_cast<size_t>(wave + 4 * c) * slot_cap + j] : 0ull;
-#pragma unroll
-                for (int c = 0; c < kSlotsPerWave; ++c) {
-                    const uint32_t score = static_cast<uint32_t>(K[c] >> 32);
-                    const bool valid = j < cnt[c];
-                    if (valid && score >= above) mark_window<COUNT>(geom, cctx, ~static_cast<uint32_t>(K[c]), a.mask, a.cmask);
-                    const bool hit = valid && score < above && score - lo < width;    // (never when the layer is done)
-                    const unsigned long long m = __ballot(hit);
-                    if (m != 0ull) {       // wave-uniform
-                        const uint32_t leader = static_cast<uint32_t>(__ffsll(static_cast<long long>(m))) - 1u;
-                        uint32_t base = 0;
-                        if (static_cast<uint32_t>(lane) == leader) base = atomicAdd(list.cnt, static_cast<uint32_t>(__popcll(m)));
-                        base = __shfl(base, static_cast<int>(leader), 64);
-                        if (hit) {
-                            const uint32_t pos = base + static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
-                            if (pos < list.cap) list.ent[pos] = K[c];
-                            atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
-                        }
-                    }
-                }
-            }
-            }
+            __syncthreads();
+            group_write<COUNT, 256>(q, marks);
         }
     }
     if (active && role != 1) {
@@ -2808,8 +2780,7 @@ __global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(
     }
     const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
     GroupGeom q = group_geom(L, ge.slot0 - L.tile_begin_all, ge.ntile, a.mask, cctx);
-    const bool words = (L.C & 31u) == 0u;            // rows of whole mask words
-    if (words) group_clear<kSelectThreads>(q, sh.marks);
+    group_clear<kSelectThreads>(q, sh.marks);
     if (tid == 0) {
         sh.res.found = 0u;
         sh.n = 0u;
@@ -2845,24 +2816,20 @@ __global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(
             });
         });
     }
-    if (words) q.cl0 = group_first_chunk(q, sh.marks.corner[0]);
-    const WindowGeom geom = {static_cast<size_t>(L.elem_off), q.R, q.C, q.h};
+    q.cl0 = group_first_chunk(q, sh.marks.corner[0]);
     cnt = min(cnt, cap);
     for (uint32_t j = lane; j < cnt; j += 64u) {
         if (j != lane) own = slot[j];
         if (own < T) continue;
         const uint32_t i = ~static_cast<uint32_t>(own);
-        if (words) group_mark<true>(q, sh.marks, static_cast<int>(wave), i);
-        else mark_window<true>(geom, cctx, i, a.mask, nullptr);
+        group_mark<true>(q, sh.marks, static_cast<int>(wave), i);
         if (a.cmask) {
-            const size_t pos = geom.elem_off + i;
+            const size_t pos = static_cast<size_t>(L.elem_off) + i;
             atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
         }
     }
-    if (words) {
-        __syncthreads();
-        group_write<true, kSelectThreads>(q, sh.marks);
-    }
+    __syncthreads();
+    group_write<true, kSelectThreads>(q, sh.marks);
     if (q.g0 == 0 && tid == 0) publish_threshold(a.pred, l, 1u, L.k, T);
 }
 

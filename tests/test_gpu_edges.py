@@ -468,13 +468,26 @@ def test_block_calls_recorded_into_a_graph(m):
 
 @pytest.mark.parametrize("p", [1, 3, 5, 7])
 @pytest.mark.parametrize("more, feed", [(0, False), (0, True), (4100, False)], ids=["small", "small_fed", "many_chunks"])
+def test_windows_across_tiles_whose_rows_share_mask_words(p, more, feed):
+    """Rows that are no whole mask words: every offset of a row inside its first word, rows shorter than a word, just longer
+    than one, than a tile and than several; the same shares of windows in other tiles and groups.  Four calls; every one
+    against the oracle."""
+    _windows_across_tiles([(33, 545), (16, 257), (200, 33), (300, 7), (49, 287), (18, 4643), (290, 801), (40, 31), (64, 510), (130, 64 * 5 + 13)], p, more, feed)
+
+
+@pytest.mark.parametrize("p", [1, 3, 5, 7])
+@pytest.mark.parametrize("more, feed", [(0, False), (0, True), (4100, False)], ids=["small", "small_fed", "many_chunks"])
 def test_windows_across_the_edges_of_tiles_and_groups(p, more, feed):
     """Rows of whole mask words: windows that reach into the tiles above, below and beside their own, of the same group of
     tiles and of another, one tile wide, a row of them and several; last tiles of one row and of one word.  Few values, so
     that ranks are settled among equal scores.  Four calls; every one against the oracle."""
+    _windows_across_tiles([(33, 544), (16, 256), (17, 512), (300, 32), (49, 288), (18, 4640), (290, 800), (40, 992)], p, more, feed)
+
+
+def _windows_across_tiles(shapes, p, more, feed):
     from paper_2312_17530_amd.session import Session
-    shapes = [(33, 544), (16, 256), (17, 512), (300, 32), (49, 288), (18, 4640), (290, 800), (40, 992)] + [(1, 1 + l % 70) for l in range(more)]
-    ratios = [0.03, 0.05, 0.02, 0.05, 0.1, 0.03, 0.06, 0.004] + [(0.0, 1.0, 0.3)[l % 3] for l in range(more)]
+    ratios = ([0.03, 0.05, 0.02, 0.05, 0.1, 0.03, 0.06, 0.004] * 2)[:len(shapes)] + [(0.0, 1.0, 0.3)[l % 3] for l in range(more)]
+    shapes = shapes + [(1, 1 + l % 70) for l in range(more)]
     rng = np.random.default_rng(p)
     s = Session(shapes, p, 0.5, ratios, work_feed=2 if feed else 0)
     resid = [np.zeros(sh, np.float32) for sh in shapes]
