@@ -4349,6 +4349,8 @@ constexpr int kDynMaxLayers = 4096;                      // layers that the list
 constexpr uint32_t kDynStage = 1024;                     // listed keys a workgroup of the main pass holds back
 constexpr uint32_t kDynSamplePieces = 4;                 // 64-byte pieces sampled per chunk: one weight in 128
 constexpr int64_t kDynSplitMin = 1 << 20;                // weights from which the one-pass form is taken
+constexpr int kDynThreads = 512;                         // the main pass: threads of a workgroup
+constexpr uint32_t kDynWorkgroups = 2;                   // ... and workgroups per CU
 
 // State of the one-pass form (cleared by k_dyn_clear).
 struct DynSplit {
@@ -4432,8 +4434,9 @@ __device__ __forceinline__ void dyn_flush_stage(DynStage &sh, const DynSplitArgs
     const uint32_t n = min(sh.n, kDynStage);
     if (threadIdx.x == 0 && n) sh.base = atomicAdd(&a.state->n_list, n);
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n; i += 256)
-        if (sh.base + i < a.list_cap) a.list[sh.base + i] = sh.ent[i];
+    if (threadIdx.x < 256u)
+        for (uint32_t i = threadIdx.x; i < n; i += 256)
+            if (sh.base + i < a.list_cap) a.list[sh.base + i] = sh.ent[i];
     __syncthreads();
     if (threadIdx.x == 0) sh.n = 0u;
     __syncthreads();
@@ -4443,19 +4446,39 @@ __device__ __forceinline__ void dyn_make_room(DynStage &sh, const DynSplitArgs &
     if (staged_more_than(sh.n, kDynStage / 2)) dyn_flush_stage(sh, a);
 }
 
+// q[j] of N values in registers, j of the thread's own: by halvings, not by way of memory.
+template <int N>
+__device__ __forceinline__ uint32_t dyn_pick(const uint32_t (&q)[N], uint32_t j) {
+    if constexpr (N == 1) {
+        return q[0];
+    } else {
+        uint32_t m[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const uint32_t x = q[2 * i], y = q[2 * i + 1];
+            m[i] = j & 1u ? y : x;
+        }
+        return dyn_pick<N / 2>(m, j >> 1);
+    }
+}
+
 // The main pass.  Every workgroup reads the bracket off the sample's histogram (the same one in each): the K-th key's
 // rank in the sample, give or take eight standard deviations of it, on the safe side of the bin edges.  Then it strides over
-// the chunks; reading 4 bytes per weight is what bounds it.
-// VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding before; now this one of 125 us and
-// 31 us around it (a call, with its wait and read-back, 706 -> 184 us).  Five waves per SIMD; held to six 137 us.
-__global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
-                                                   const uint32_t *__restrict__ w, const DynSplitArgs a) {
+// the chunks; reading 4 bytes per weight is what bounds it.  A thread notes which of its keys lie inside the bracket and takes
+// those afterwards: with a branch per key a wave went through the stage's returning atomics a dozen times a chunk, for two
+// or three keys of a lane at most.  Every workgroup costs about 14 ns for the bracket and its counts at the end: half as many
+// threads twice as often take 4 us longer, four workgroups per CU 3 us, 1024 threads 3 us; looking at the stage every fourth
+// chunk only 1 us, and requesting the next chunk's keys while one is gone through 4 us.
+// VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding at first; 124 us with a branch per key and 2048
+// workgroups of 256; now 109 us and 31 us around it (a call, with its wait and read-back, 706 us at first, 180, now 166).
+__global__ __launch_bounds__(kDynThreads) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
+                                                           const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t sub[kDynSubBins];
     __shared__ DynStage stage;
-    __shared__ uint32_t wave_tot[4];
+    __shared__ uint32_t wave_tot[kDynThreads / 64];
     __shared__ uint32_t s_above, s_sampled, s_hi_bin, s_lo_bin, s_cum_hi, s_cum_lo;
     const int tid = threadIdx.x;
-    for (int b = tid; b < kDynSubBins; b += 256) sub[b] = 0u;
+    for (int b = tid; b < kDynSubBins; b += kDynThreads) sub[b] = 0u;
     if (tid == 0) {
         s_above = stage.n = 0u;
         s_hi_bin = kDynSampleBins;         // (nothing is certainly above)
@@ -4463,7 +4486,7 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
         s_cum_hi = 0u;
     }
     {
-        constexpr int per = kDynSampleBins / 256;
+        constexpr int per = kDynSampleBins / kDynThreads;
         const int top = kDynSampleBins - tid * per;          // thread 0 holds the top bins
         uint32_t v[per], own = 0;
 #pragma unroll
@@ -4472,8 +4495,8 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
             v[4 * j] = q.w; v[4 * j + 1] = q.z; v[4 * j + 2] = q.y; v[4 * j + 3] = q.x;
             own += q.x + q.y + q.z + q.w;
         }
-        const uint32_t incl = block_scan_incl(own, wave_tot);
-        if (tid == 255) { s_sampled = incl; s_cum_lo = incl; }
+        const uint32_t incl = block_scan_incl_n<kDynThreads / 64>(own, wave_tot);
+        if (tid == kDynThreads - 1) { s_sampled = incl; s_cum_lo = incl; }
         __syncthreads();
         const uint32_t S = s_sampled;
         const float q = static_cast<float>(static_cast<double>(a.K) / static_cast<double>(a.n_weights));
@@ -4519,6 +4542,12 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
         }
         __syncthreads();
     };
+    typedef uint32_t vu4 __attribute__((ext_vector_type(4)));       // (read once: streamed)
+    const uint32_t lo2 = lo << 1, width2 = width << 1;       // (a bracket of all keys would have been bad)
+    auto take = [&](uint32_t rel) {                          // a key inside the bracket
+        atomicAdd(&sub[rel >> sub_shift], 1u);
+        dyn_stage_key(stage, a, make_uint2(lo + rel, cur_l));
+    };
     // (each XCD reads one contiguous part of a round of chunks: 132 -> 124 us on VGG-19)
     for (uint32_t c = xcd_contiguous(blockIdx.x, gridDim.x); c < n_chunks; c += gridDim.x) {
         const ChunkInfo ci = chunk_info[c];
@@ -4526,20 +4555,41 @@ __global__ __launch_bounds__(256) void k_dyn_split(const ChunkInfo *__restrict__
             if (cur_l != 0xffffffffu) flush_layer();
             cur_l = ci.layer;
         }
-        dyn_for_each_key(w + ci.arena_off, ci.len, [&](uint32_t key) {
-            above += key >= hi ? 1u : 0u;
-            const uint32_t rel = key - lo;
-            if (rel < width) {                               // rare
-                atomicAdd(&sub[rel >> sub_shift], 1u);
-                dyn_stage_key(stage, a, make_uint2(key, cur_l));
+        const uint32_t *__restrict__ src = w + ci.arena_off;
+        if (ci.len == static_cast<uint32_t>(kChunk)) {
+            constexpr int N = kChunk / kDynThreads;          // keys of a thread
+            uint32_t q[N];
+#pragma unroll
+            for (int j = 0; j < N; j += 4) {
+                const vu4 v = __builtin_nontemporal_load(reinterpret_cast<const vu4 *>(src + j * kDynThreads + 4 * tid));
+                q[j] = v.x; q[j + 1] = v.y; q[j + 2] = v.z; q[j + 3] = v.w;
             }
-        });
+            uint32_t hits = 0;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                q[j] = (q[j] << 1) - lo2;                    // 2 (key - lo); a key below lo wraps past all others
+                above += q[j] <= ~lo2 ? 1u : 0u;             // key >= lo
+                hits |= q[j] < width2 ? 1u << j : 0u;
+            }
+            above -= __popc(hits);
+            while (hits) {                                   // two or three rounds of a wave
+                const uint32_t j = static_cast<uint32_t>(__ffs(hits)) - 1u;
+                hits &= hits - 1u;
+                take(dyn_pick<N>(q, j) >> 1);
+            }
+        } else {
+            for (uint32_t e = tid; e < ci.len; e += kDynThreads) {
+                const uint32_t rel = (src[e] << 1) - lo2;
+                if (rel < width2) take(rel >> 1);
+                else above += rel <= ~lo2 ? 1u : 0u;
+            }
+        }
         dyn_make_room(stage, a);
     }
     if (cur_l != 0xffffffffu) flush_layer();
     dyn_flush_stage(stage, a);
     if (tid == 0 && above_all) atomicAdd(&a.state->above, above_all);
-    for (int b = tid; b < kDynSubBins; b += 256) {
+    for (int b = tid; b < kDynSubBins; b += kDynThreads) {
         const uint32_t c = sub[b];
         if (c) atomicAdd(&a.sub_hist[b], c);
     }
@@ -5671,7 +5721,7 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
         hipLaunchKernelGGL(k_dyn_clear, dim3(16), dim3(256), 0, stream, a);
         hipLaunchKernelGGL(k_dyn_sample, dim3(std::min<uint32_t>((n_chunks * kDynSamplePieces + 15u) / 16u, kNumCUs)), dim3(256), 0, stream,
                            chunk_info, n_chunks, keys, a);
-        hipLaunchKernelGGL(k_dyn_split, dim3(std::min<uint32_t>(n_chunks, kNumCUs * 8u)), dim3(256), 0, stream, chunk_info, n_chunks, keys, a);
+        hipLaunchKernelGGL(k_dyn_split, dim3(std::min<uint32_t>(n_chunks, kNumCUs * kDynWorkgroups)), dim3(kDynThreads), 0, stream, chunk_info, n_chunks, keys, a);
         hipLaunchKernelGGL(k_dyn_list, dim3(kNumCUs), dim3(256), 0, stream, a);
         hipLaunchKernelGGL(k_dyn_last, dim3(1), dim3(1024), 0, stream, a);
         rc = read_counts();
