@@ -4351,6 +4351,7 @@ constexpr uint32_t kDynSamplePieces = 4;                 // 64-byte pieces sampl
 constexpr int64_t kDynSplitMin = 1 << 20;                // weights from which the one-pass form is taken
 constexpr int kDynThreads = 512;                         // the main pass: threads of a workgroup
 constexpr uint32_t kDynWorkgroups = 2;                   // ... and workgroups per CU
+constexpr uint32_t kDynSampleThreads = 1024;
 
 // State of the one-pass form (cleared by k_dyn_clear).
 struct DynSplit {
@@ -4380,16 +4381,19 @@ __global__ __launch_bounds__(256) void k_dyn_clear(const DynSplitArgs a) {
 }
 
 // Histogram of a sample: kDynSamplePieces pieces of 16 weights per chunk, at places given by a hash; a short chunk
-// gives each of its pieces with the probability of its share of a whole one.
-__global__ __launch_bounds__(256) void k_dyn_sample(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
-                                                    const uint32_t *__restrict__ w, const DynSplitArgs a) {
+// gives each of its pieces with the probability of its share of a whole one.  A chain of three loads and the counts' way out
+// bound it: as many threads as a workgroup can have, and all of a thread's pieces requested at once, one round on VGG-19 (68224
+// pieces; four rounds of 256 threads took 11.9 us, now 8.6).
+__global__ __launch_bounds__(kDynSampleThreads) void k_dyn_sample(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
+                                                                  const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t lhist[kDynSampleBins];
+    constexpr uint32_t kPieces = kDynSampleThreads / 16;      // a round's
     const int tid = threadIdx.x;
-    for (int b = tid; b < kDynSampleBins; b += 256) lhist[b] = 0u;
+    for (int b = tid; b < kDynSampleBins; b += kDynSampleThreads) lhist[b] = 0u;
     __syncthreads();
-    const uint32_t n_pieces = n_chunks * kDynSamplePieces, stride = gridDim.x * 16u;
-    constexpr int U = 4;                   // pieces in flight per 16 threads: the chain entry -> weight -> bin is what this kernel waits for
-    for (uint32_t i0 = blockIdx.x * 16u; i0 < n_pieces; i0 += U * stride) {
+    const uint32_t n_pieces = n_chunks * kDynSamplePieces, stride = gridDim.x * kPieces;
+    constexpr int U = 5;                   // pieces in flight per 16 threads: the chain entry -> weight -> bin is what this kernel waits for
+    for (uint32_t i0 = blockIdx.x * kPieces; i0 < n_pieces; i0 += U * stride) {
         uint64_t at[U];
         bool have[U];
         uint32_t key[U];
@@ -4409,7 +4413,7 @@ __global__ __launch_bounds__(256) void k_dyn_sample(const ChunkInfo *__restrict_
             if (have[u]) atomicAdd(&lhist[key[u] >> (31 - kDynSampleBits)], 1u);
     }
     __syncthreads();
-    for (int b = tid; b < kDynSampleBins; b += 256) {
+    for (int b = tid; b < kDynSampleBins; b += kDynSampleThreads) {
         const uint32_t c = lhist[b];
         if (c) atomicAdd(&a.sample_hist[b], c);
     }
@@ -4470,7 +4474,7 @@ __device__ __forceinline__ uint32_t dyn_pick(const uint32_t (&q)[N], uint32_t j)
 // threads twice as often take 4 us longer, four workgroups per CU 3 us, 1024 threads 3 us; looking at the stage every fourth
 // chunk only 1 us, and requesting the next chunk's keys while one is gone through 4 us.
 // VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding at first; 124 us with a branch per key and 2048
-// workgroups of 256; now 109 us and 31 us around it (a call, with its wait and read-back, 706 us at first, 180, now 166).
+// workgroups of 256; now 110 us and 28 us around it (a call, with its wait and read-back, 706 us at first, 180, now 165).
 __global__ __launch_bounds__(kDynThreads) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
                                                            const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t sub[kDynSubBins];
@@ -5719,8 +5723,8 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
         a.K = K;
         a.n_weights = static_cast<unsigned long long>(n_real);
         hipLaunchKernelGGL(k_dyn_clear, dim3(16), dim3(256), 0, stream, a);
-        hipLaunchKernelGGL(k_dyn_sample, dim3(std::min<uint32_t>((n_chunks * kDynSamplePieces + 15u) / 16u, kNumCUs)), dim3(256), 0, stream,
-                           chunk_info, n_chunks, keys, a);
+        const uint32_t sample_wgs = (16u * n_chunks * kDynSamplePieces + kDynSampleThreads - 1u) / kDynSampleThreads;
+        hipLaunchKernelGGL(k_dyn_sample, dim3(std::min<uint32_t>(sample_wgs, kNumCUs)), dim3(kDynSampleThreads), 0, stream, chunk_info, n_chunks, keys, a);
         hipLaunchKernelGGL(k_dyn_split, dim3(std::min<uint32_t>(n_chunks, kNumCUs * kDynWorkgroups)), dim3(kDynThreads), 0, stream, chunk_info, n_chunks, keys, a);
         hipLaunchKernelGGL(k_dyn_list, dim3(kNumCUs), dim3(256), 0, stream, a);
         hipLaunchKernelGGL(k_dyn_last, dim3(1), dim3(1024), 0, stream, a);
