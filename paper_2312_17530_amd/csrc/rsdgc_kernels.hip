@@ -148,6 +148,18 @@ __device__ __forceinline__ uint32_t wave_append(uint32_t *counter, bool flag) {
     return base + static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
 }
 
+// One more in bin b of a histogram in LDS for every flagged lane; the lanes whose bin is the first one's count with one atomic
+// (masses of equal scores: 64 atomics on one address are served one after the other).
+__device__ __forceinline__ void wave_count(uint32_t *h, uint32_t b, bool flag) {
+    const unsigned long long m = __ballot(flag);
+    if (m == 0ull) return;
+    const uint32_t leader = static_cast<uint32_t>(__ffsll(static_cast<long long>(m))) - 1u;
+    const uint32_t first = __builtin_amdgcn_readlane(b, leader);
+    const unsigned long long same = __ballot(flag && b == first);
+    if (flag && b != first) atomicAdd(&h[b], 1u);
+    if ((threadIdx.x & 63u) == leader) atomicAdd(&h[first], static_cast<uint32_t>(__popcll(same)));
+}
+
 // Whether more than `limit` items have been appended to a stage in LDS (n: its counter): the same answer in every thread.
 // The first barrier has all appends so far counted; the second keeps a wave that is already through from appending
 // again before the last one has read the counter.
@@ -407,6 +419,36 @@ __device__ __forceinline__ double nsi_from_var(double sa, double d, double ca, d
     return fma(cb, g, ca * sa);
 }
 
+// A window's score as float32 bits, from its sums; Eq. 10 again from the window where the one-pass variance cancels (never for
+// P = 1, where it is 0 by definition).
+template <int P>
+__device__ __forceinline__ uint32_t score_from_sums(double sa, double ss, double sq, const float *win, int pitch, double ca, double cb) {
+    const double n = static_cast<double>(P * P), nsq = __dmul_rn(n, sq);
+    double d = var_n2_one_pass(ss, nsq);
+    if (P > 1 && d < kCancelFrac * nsq) d = __dmul_rn(n, window_ssd<P>(win, pitch, ss / n));
+    return __float_as_uint(static_cast<float>(nsi_from_var(sa, d, ca, cb))) & 0x7fffffffu;
+}
+// The score of one window in full: Eqs. 8-10 in double, the sums row by row.  (Rows kept rolled: few registers that way.)
+template <int P>
+__device__ __forceinline__ uint32_t window_score(const float *win, int pitch, double ca, double cb) {
+    double sa = 0.0, ss = 0.0, sq = 0.0;
+#pragma unroll 1
+    for (int dx = 0; dx < P; ++dx) {
+        const double w0 = static_cast<double>(win[dx * pitch]);
+        double ra = fabs(w0), rs = w0, rq = w0 * w0;
+#pragma unroll
+        for (int j = 1; j < P; ++j) {
+            const double wj = static_cast<double>(win[dx * pitch + j]);
+            ra += fabs(wj);
+            rs += wj;
+            rq = fma(wj, wj, rq);
+        }
+        if (dx == 0) { sa = ra; ss = rs; sq = rq; }
+        else { sa += ra; ss += rs; sq += rq; }
+    }
+    return score_from_sums<P>(sa, ss, sq, win, pitch, ca, cb);
+}
+
 // ----------------------------------------------------------- work feed --
 // Hands the items of a launch (tiles) to its persistent workgroups.  With a fixed strided
 // share per workgroup the workgroups drift apart (measured on the VGG-19 main pass: the first
@@ -616,14 +658,15 @@ __device__ __forceinline__ uint32_t *recorded_slot(uint32_t *list_cnt, uint32_t 
 // Whether a large layer is ranked on the full map in this call: it started so, or its bound failed -- fewer than k_l
 // centres reach it, k_l or more lie in the open-ended top bin, or a tile slot overflowed.  k_find0's test, from what the
 // main pass has left, for workgroups of its own launch (which may see the mode before or after k_find0 has changed it).
-__device__ __forceinline__ bool layer_falls_back(const NsiArgs &a, uint32_t l) {
-    const SelState *st = a.state + l;
+__device__ __forceinline__ bool layer_falls_back(const LayerDev *__restrict__ layers, const SelState *state, const uint32_t *__restrict__ hist_s,
+                                                 uint32_t *list_cnt, uint32_t l) {
+    const SelState *st = state + l;
     const uint32_t mode = st->mode, hint_key = st->hint_key, overflow = st->overflow;
-    const uint32_t large = a.layers[l].large, k = a.layers[l].k;
-    const uint32_t top = a.hist_s[static_cast<size_t>(l) * kHistBins + kFineBins - 1];
+    const uint32_t large = layers[l].large, k = layers[l].k;
+    const uint32_t top = hist_s[static_cast<size_t>(l) * kHistBins + kFineBins - 1];
     uint32_t recorded = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < kRecordedParts; ++q) recorded += *recorded_slot(a.list_cnt, l, q);
+    for (uint32_t q = 0; q < kRecordedParts; ++q) recorded += *recorded_slot(list_cnt, l, q);
     if (large == 0u || mode == kModeSkip) return false;
     return mode == kModeFullMap || hint_key == 0u || overflow != 0u || recorded < k || top >= k;
 }
@@ -671,7 +714,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     const uint32_t stride = n_wgs;
     if (PASS == kPassFullMap) {            // no layer fell back: nothing to do
         if (WITH_FIND0) {
-            if (!__syncthreads_or(tid < a.n_layers && layer_falls_back(a, tid))) return;
+            if (!__syncthreads_or(tid < a.n_layers && layer_falls_back(a.layers, a.state, a.hist_s, a.list_cnt, tid))) return;
         } else if (a.flags[0] == 0u) {
             return;
         }
@@ -749,7 +792,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             whole = PASS != kPassSample || L.large == 0u;
             if (PASS == kPassFullMap || PASS == kPassCapture || (PASS == kPassSample && !whole)) {
                 const SelState st = a.state[l];
-                if (PASS == kPassFullMap) active = WITH_FIND0 ? layer_falls_back(a, l) : st.mode == kModeFullMap && L.large != 0u;
+                if (PASS == kPassFullMap) active = WITH_FIND0 ? layer_falls_back(a.layers, a.state, a.hist_s, a.list_cnt, l) : st.mode == kModeFullMap && L.large != 0u;
                 else if (PASS == kPassSample) active = st.mode == kModeCandidates && st.hint_key == 0u;   // no predicted bound
                 else active = st.mode == kModeCandidates;
                 if (CAPTURE) {
@@ -1011,26 +1054,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                 const int pos = queue[qi];
                 const int orow = pos / kTileCols, ocol = pos - orow * kTileCols;
                 if (x0 + orow >= R || y0 + ocol >= C) continue;
-                const float *win = &tile[orow * PITCH + PADL + ocol - H];
-                double sa = 0.0, ss = 0.0, sq = 0.0;
-#pragma unroll 1
-                for (int dx = 0; dx < P; ++dx) {       // (cold code: kept rolled, it needs few registers that way)
-                    const double w0 = static_cast<double>(win[dx * PITCH]);
-                    double ra = fabs(w0), rs = w0, rq = w0 * w0;
-#pragma unroll
-                    for (int j = 1; j < P; ++j) {
-                        const double wj = static_cast<double>(win[dx * PITCH + j]);
-                        ra += fabs(wj);
-                        rs += wj;
-                        rq = fma(wj, wj, rq);
-                    }
-                    if (dx == 0) { sa = ra; ss = rs; sq = rq; }
-                    else { sa += ra; ss += rs; sq += rq; }
-                }
-                const double nsq = __dmul_rn(n, sq);
-                double d = var_n2_one_pass(ss, nsq);
-                if (P > 1 && d < kCancelFrac * nsq) d = __dmul_rn(n, window_ssd<P>(win, PITCH, ss / n));
-                const uint32_t key = __float_as_uint(static_cast<float>(nsi_from_var(sa, d, ca, cb))) & 0x7fffffffu;
+                const uint32_t key = window_score<P>(&tile[orow * PITCH + PADL + ocol - H], PITCH, ca, cb);
                 if (key >= hint_key) {
                     const uint32_t x = static_cast<uint32_t>(x0 + orow), y = static_cast<uint32_t>(y0 + ocol);
                     const uint32_t cp = atomicAdd(&ncand, 1u);
@@ -2437,17 +2461,18 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
 // those was a launch of 3 to 6 us for a microsecond's work.  A workgroup of 1024 threads per group of tile slots.  It reads the
 // first digit off its layer's fine bins, then -- every group of a layer the same -- the threshold bucket's keys from all
 // of the layer's slots (a few per tile: reading them again and again costs less than handing them over), ranks those in LDS, and
-// marks the windows of its own tiles' candidates that reach the threshold.  Nothing passes between workgroups.
-// A layer whose bound failed is ranked on its full score map by the workgroups of its own groups (select_full_map).
+// marks the windows of its own tiles' candidates that reach the threshold.  Nothing passes between workgroups -- unless a layer's
+// bound failed: such a layer is ranked on its full score map (select_failed).
 // What bounds it is a chain of six or seven dependent loads.  Kernels, before / now (find0 to mark, four launches / k_select): 512 x 512
-// 19.7 / 10.4 us, ResNet-18 25.0 / 14.0, ResNet-50 32.0 / 21.6; calls 31.2 -> 22.6, 63.8 -> 53.1, 108.2 -> 95.9 us.  (The 48 bytes
-// of scratch belong to select_full_map: without it the kernel takes as long.)
+// 19.7 / 10.4 us, ResNet-18 25.0 / 14.0, ResNet-50 32.0 / 21.6; calls 31.2 -> 22.6, 63.8 -> 53.1, 108.2 -> 95.9 us.  (The 68 bytes
+// of scratch belong to select_failed: without it the kernel takes as long.)
 // The rule (build_tables): up to 4096 chunks, as for all that counts where it marks; a layer's slots' counts fit the threads
 // (kSelectTiles); and its candidates, which all of its workgroups read, are few enough (kSelectMaxK).
 constexpr int kSelectThreads = 1024;
 constexpr int kSelectWaves = kSelectThreads / 64;
 static_assert(kSelectThreads == kFineBins && kSelectWaves == kSlotGroup, "a bin per thread, a tile slot per wave");
 constexpr int kSelectList = 2048;        // keys of a threshold bucket that are ranked in LDS
+constexpr int kSelectRun = 4;            // a failed bound: tiles that a workgroup marks at a time
 
 struct SelectArgs {
     const LayerDev *layers;
@@ -2462,25 +2487,37 @@ struct SelectArgs {
     const float *grad, *resid, *mom;
     float *v_out, *mom_out;
     float m;
-    float *map;
-    uint32_t *hist, *list_cnt;
+    uint32_t *map, *hist, *hist1, *list_cnt;
     unsigned long long *list_ent;
     double alpha;
+    uint32_t n_layers, n_groups;          // workgroups from n_groups on: helpers
 };
 struct SelectShared {
     union {
         struct {
-            GroupMarks<kSlotGroup> marks;
+            union {
+                GroupMarks<kSlotGroup> marks;
+                GroupMarks<kSelectRun> run;           // a failed bound
+            };
             unsigned long long key[kSelectList];      // the threshold bucket's keys, less its lower edge
             uint32_t lh[kLevel1Bins];
         };
-        uint32_t hist[kHistBins];                     // full map
+        struct {                                      // a failed bound: a tile of v with its halo, the first digit's counts
+            float tile[(kTileRows + RSDGC_MAX_P - 1) * (kTileCols + RSDGC_MAX_P - 1)];
+            uint32_t hist[kHistBins];
+        };
     };
     uint32_t wave_tot[kSelectWaves];
     DigitResult res;
     unsigned long long rank_key;
     uint32_t n, ticket;
 };
+
+// What is the same in every lane, moved to scalar registers: branches on it go round what they skip.
+__device__ __forceinline__ uint32_t uniform_u32(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ DigitResult uniform_digit(const DigitResult &r) {
+    return DigitResult{uniform_u32(r.digit), uniform_u32(r.above), uniform_u32(r.count), uniform_u32(r.found)};
+}
 
 // The recorded candidates of a layer, by the whole workgroup: a wave takes every 16th slot, a lane's count each, and goes through
 // their entries 64 at a time, wherever one slot ends and the next begins (slots hold a few entries or many; with threads
@@ -2530,7 +2567,25 @@ struct SlotScan {
     }
 };
 
-// The k_rem-th largest of n numbers below 2^top: from sh.key, if they fit there, else scan(f) calls f for each of them.
+// block_find_digit for the nb bins of sh.lh: two a thread.
+__device__ __forceinline__ DigitResult select_digit(SelectShared &sh, int nb, uint32_t k_rem) {
+    static_assert(kLevel1Bins == 2 * kSelectThreads, "two bins a thread");
+    const int hi = nb - 2 * static_cast<int>(threadIdx.x);
+    const uint32_t v0 = hi > 0 ? sh.lh[hi - 1] : 0u, v1 = hi > 0 ? sh.lh[hi - 2] : 0u;      // (nb is even)
+    if (threadIdx.x == 0) sh.res.found = 0u;
+    const uint32_t incl = block_scan_incl_n<kSelectWaves>(v0 + v1, sh.wave_tot), excl = incl - v0 - v1;
+    if (excl < k_rem && k_rem <= incl) {
+        const bool top = excl + v0 >= k_rem;
+        sh.res = DigitResult{static_cast<uint32_t>(hi - (top ? 1 : 2)), top ? excl : excl + v0, top ? v0 : v1, 1u};
+    }
+    __syncthreads();
+    const DigitResult r = uniform_digit(sh.res);
+    __syncthreads();
+    return r;
+}
+
+// The k_rem-th largest of n numbers below 2^top: from sh.key, if they fit there, else scan(f) calls f for each of them (until what
+// is left fits).
 template <typename S>
 __device__ __forceinline__ unsigned long long select_rank(SelectShared &sh, uint32_t n, uint32_t k_rem, int top, S scan) {
     const uint32_t tid = threadIdx.x;
@@ -2556,7 +2611,7 @@ __device__ __forceinline__ unsigned long long select_rank(SelectShared &sh, uint
         for (int b = tid; b < nb; b += kSelectThreads) sh.lh[b] = 0u;
         __syncthreads();
         auto count = [&](unsigned long long rel) {
-            if (rel >> left == T >> left) atomicAdd(&sh.lh[static_cast<uint32_t>(rel >> shift) & (nb - 1)], 1u);
+            wave_count(sh.lh, static_cast<uint32_t>(rel >> shift) & (nb - 1), rel >> left == T >> left);
         };
         if (n <= static_cast<uint32_t>(kSelectList)) {
             for (uint32_t i = tid; i < n; i += kSelectThreads) count(sh.key[i]);
@@ -2564,181 +2619,396 @@ __device__ __forceinline__ unsigned long long select_rank(SelectShared &sh, uint
             scan(count);
         }
         __syncthreads();
-        const DigitResult d = block_find_digit<kSelectWaves>(sh.lh, nb, k_rem, sh.wave_tot, &sh.res);
+        const DigitResult d = select_digit(sh, nb, k_rem);
         T |= static_cast<unsigned long long>(d.digit) << shift;
         k_rem -= d.above;
         if (d.count == k_rem) break;      // all of them: lower digits stay 0
         left = shift;
+        if (n > static_cast<uint32_t>(kSelectList) && d.count <= static_cast<uint32_t>(kSelectList)) {
+            if (tid == 0) sh.n = 0u;
+            __syncthreads();
+            scan([&](unsigned long long rel) {
+                if (rel >> left != T >> left) return;
+                const uint32_t pos = atomicAdd(&sh.n, 1u);
+                if (pos < static_cast<uint32_t>(kSelectList)) sh.key[pos] = rel;
+            });
+            n = d.count;
+        }
     }
     return T;
 }
 
-// A failed bound: the layer is ranked on its full score map, as the fallback kernels of other plans do it, by the workgroups of
-// its groups together.  Four steps, each cut into shares that the workgroups take by tickets in order: scores, map and first
-// digit; the threshold bucket's keys; their ranking (one share); the marks.  A share waits until all shares of the step before
-// are done.  Those have lower tickets: they were taken by workgroups that are running, and these wait, if at all, for still lower
-// ones -- so every wait ends, however few workgroups are on the GPU at a time.
-constexpr int kSelectCtl = 8;            // words of the layer's last list shard's line: the tickets, then the shares done of each step
+// A failed bound: the layer is ranked on its full score map, as the fallback kernels of other plans do it.  Four steps, each cut
+// into shares: scores, map and first digit (a tile); the threshold bucket's keys and their second digit (a chunk); the
+// ranking (one share); the marks (a run of tiles).  Shares are taken by tickets in order: by the workgroups of the layer's own
+// groups, by those of other failed layers when theirs are done, and by workgroups that the launch of a plan of few groups has for
+// nothing else (without a failed layer they leave after one look at the layers: no difference to the call).  A share waits until all
+// shares of the step before are done.  Those have lower tickets: they were taken by workgroups that are running, which go through
+// a ticket that they hold without waiting for anything but still lower ones -- so every wait ends, however few
+// workgroups are on the GPU at a time.
+// What bounds it is the scores' arithmetic, about 5 us of a CU for a tile, and, on small layers, some thirty dependent loads and
+// atomics.  A call all of whose bounds fail, with the launches that this one replaced / with scores formed from global loads by the
+// layer's own groups alone / now: 512 x 512 with p = 3 56 / 310 / 47 us, 1024 x 1024 with p = 1 68 / 276 / 62, p = 3 64 / 371 / 60,
+// p = 7 70 / 911 / 69, 2048 x 2048 with p = 3 89 / 412 / 98, p = 7 97 / 952 / 119, ResNet-18 175 / 602 / 181, ResNet-50
+// 352 / 1225 / 343; one all-zero layer of a million elements, whose ties have one workgroup go through the map
+// again and again, 3000 / 4230 / 1590.
+constexpr int kSelectCtl = 8;            // this word of the layer's last list shards' lines: the tickets, then the shares done of the first three steps
+// Workgroups of the launch, if its groups are fewer: one per CU, two in a plan of many groups (and so of several layers: 512
+// workgroups on the tickets of one layer of 4 M elements took 125 us a call, 256 of them 98, and 256 on ResNet-18 / 50 with all
+// bounds failed 192 / 383, 512 of them 181 / 343).
+__host__ __device__ constexpr uint32_t select_workgroups(uint32_t n_groups) { return n_groups < 128u ? kNumCUs : 2u * kNumCUs; }
+static_assert(kHistBins == 4 * kSelectThreads && kChunk == 8 * kSelectThreads && kListShards == kSelectWaves && kTileRows * kTileCols == 4 * kSelectThreads,
+              "bins, keys, shards and scores per thread");
 
-__device__ __forceinline__ void select_share_done(uint32_t *done) {
-    __threadfence();                      // (every thread: its own stores)
+// What one workgroup hands to others of the launch goes through these two, past the caches of an XCD; select_shares_done waits until
+// it is out.  (A fence at device scope instead writes back and invalidates the XCD's whole L2, once per wave: a call with a failed
+// bound on 1024 x 1024 took 284 us with fences where it took 106 without.)
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void select_shares_done(uint32_t *done, uint32_t n) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // every wave: its own stores and adds
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(done, 1u);
+    if (threadIdx.x == 0) atomicAdd(done, n);
 }
 __device__ __forceinline__ void select_wait(uint32_t *done, uint32_t n) {
     if (threadIdx.x == 0)
-        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) __builtin_amdgcn_s_sleep(16);
+        while (agent_load(done) < n) __builtin_amdgcn_s_sleep(8);
     __syncthreads();
-    __threadfence();
+    asm volatile("" ::: "memory");        // (nothing is read before)
+}
+// i: 0 the tickets, 1 .. 3 the shares done.  (A cache line each: who waits reads his again and again.)
+__device__ __forceinline__ uint32_t *select_ctl(uint32_t *list_cnt, uint32_t l, int i) {
+    return list_cnt + (static_cast<size_t>(l) * kListShards + kListShards - 1 - i) * kListCntStride + kSelectCtl;
+}
+// First ticket of each step, and the number of tickets.
+struct SelectTickets {
+    uint32_t keys, rank, marks, end;
+};
+__device__ __forceinline__ SelectTickets select_tickets(const LayerDev &L) {
+    SelectTickets s;
+    s.keys = L.n_tiles;
+    s.rank = s.keys + L.n_chunks;
+    s.marks = s.rank + 1u;
+    s.end = s.marks + (L.n_tiles + kSelectRun - 1) / kSelectRun;
+    return s;
 }
 
-// v = r + g at (x, y), zero outside the matrix; with Eq. 12's momentum term v = r + (m*u + g) and `gu` that sum in brackets.
-__device__ __forceinline__ float select_v(const SelectArgs &a, const LayerDev &L, int x, int y, float *gu) {
-    if (x < 0 || x >= static_cast<int>(L.R) || y < 0 || y >= static_cast<int>(L.C)) return 0.f;
-    const size_t at = static_cast<size_t>(L.elem_off) + static_cast<size_t>(x) * L.C + y;
-    float t = a.grad[at];
-    if (a.mom) t = __fmul_rn(a.m, a.mom[at]) + t;
-    if (gu) *gu = t;
-    return a.resid[at] + t;
+// The kernel's arguments and a layer's constants, read anew where they are wanted, into scalar registers: this code shares its
+// registers with a kernel that is held to 64 of them, and what was kept in scratch memory instead cost the calls that come here 40 us.
+__device__ __forceinline__ const SelectArgs &select_args() {
+    auto *p = (const __attribute__((address_space(4))) SelectArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const SelectArgs *)p;
 }
-// Eqs. 8-10 at (x, y): the same sums in the same order as the NSI passes form them.
-__device__ __forceinline__ float select_score(const SelectArgs &a, const LayerDev &L, int x, int y) {
-    const int P = static_cast<int>(L.p), h = (P - 1) / 2;
+__device__ __forceinline__ const LayerDev &select_layer(const SelectArgs &a, uint32_t l) {
+    auto *p = (const __attribute__((address_space(4))) LayerDev *)(a.layers + l);
+    asm volatile("" : "+s"(p));
+    return *(const LayerDev *)p;
+}
+
+// The next ticket: requested by thread 0 while it works on the one before (behind that one's loads, or they would be waited for
+// together); handed to all.
+__device__ __forceinline__ uint32_t select_hand_over(SelectShared &sh, uint32_t ticket) {
+    __syncthreads();
+    if (threadIdx.x == 0) sh.ticket = ticket;
+    __syncthreads();
+    return uniform_u32(sh.ticket);
+}
+__device__ __forceinline__ uint32_t select_request(uint32_t *ctl) { return threadIdx.x == 0 ? atomicAdd(ctl, 1u) : 0u; }
+
+// v, scores and first digit of a tile (sh.hist: the workgroup's counts).  Returns the next ticket.
+template <int P>
+__device__ __forceinline__ uint32_t select_map_tile(SelectShared &sh, uint32_t l, uint32_t local, uint32_t *ctl) {
+    const SelectArgs &a = select_args();
+    const LayerDev &L = select_layer(a, l);
+    constexpr int H = (P - 1) / 2, ROWS = kTileRows + 2 * H, PITCH = kTileCols + 2 * H, N = (ROWS * PITCH + kSelectThreads - 1) / kSelectThreads;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // (or the places of a thread's pieces are worked out before the loop over the tiles, and spilled)
+    const uint32_t trow = local / L.tiles_x;
+    const int R = static_cast<int>(L.R), C = static_cast<int>(L.C);
+    const int x0 = static_cast<int>(trow) * kTileRows, y0 = static_cast<int>(local - trow * L.tiles_x) * kTileCols;
+    const float *__restrict__ g = a.grad + L.elem_off, *__restrict__ r = a.resid + L.elem_off;
+    const float *__restrict__ u = a.mom ? a.mom + L.elem_off : nullptr;
+    float gq[N], rq[N], uq[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {         // (all requested before any is used)
+        const int i = tid + j * kSelectThreads, rr = i / PITCH, x = x0 - H + rr, y = y0 - H + (i - rr * PITCH);
+        gq[j] = rq[j] = uq[j] = 0.f;
+        if (i < ROWS * PITCH && x >= 0 && x < R && y >= 0 && y < C) {
+            const size_t at = static_cast<size_t>(x) * C + y;
+            gq[j] = g[at];
+            rq[j] = r[at];
+            if (u) uq[j] = u[at];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int i = tid + j * kSelectThreads, rr = i / PITCH, cc = i - rr * PITCH, x = x0 - H + rr, y = y0 - H + cc;
+        const bool in = i < ROWS * PITCH && x >= 0 && x < R && y >= 0 && y < C;
+        const float gu = u ? __fmul_rn(a.m, uq[j]) + gq[j] : gq[j];
+        const float v = in ? rq[j] + gu : 0.f;
+        if (i < ROWS * PITCH) sh.tile[i] = v;
+        // the tile's own elements (a layer that had no bound went through no pass that stores them)
+        if (in && a.v_out && rr >= H && rr < H + kTileRows && cc >= H && cc < H + kTileCols) {
+            const size_t at = static_cast<size_t>(L.elem_off) + static_cast<size_t>(x) * C + y;
+            a.v_out[at] = v;
+            if (a.mom_out) a.mom_out[at] = gu;
+        }
+    }
+    __syncthreads();
+    const uint32_t next = select_request(ctl);
+    // a thread: four rows of a column; a row's sums go to the windows that it lies in, from the top row on
+    constexpr int RPT = kTileRows * kTileCols / kSelectThreads;
     const double n = static_cast<double>(P * P);
-    double sa = 0.0, ss = 0.0, sq = 0.0;
+    const int col = tid % kTileCols, row0 = tid / kTileCols * RPT, y = y0 + col;
+    double sa[RPT], ss[RPT], sq[RPT];
+#pragma unroll
+    for (int o = 0; o < RPT; ++o) sa[o] = ss[o] = sq[o] = 0.0;
 #pragma unroll 1
-    for (int dx = -h; dx <= h; ++dx) {
-        const double w0 = static_cast<double>(select_v(a, L, x + dx, y - h, nullptr));
+    for (int i = 0; i < RPT + 2 * H; ++i) {
+        const float *row = &sh.tile[(row0 + i) * PITCH + col];
+        const double w0 = static_cast<double>(row[0]);
         double ra = fabs(w0), rs = w0, rq = w0 * w0;
-#pragma unroll 1
-        for (int dy = 1 - h; dy <= h; ++dy) {
-            const double w = static_cast<double>(select_v(a, L, x + dx, y + dy, nullptr));
+#pragma unroll
+        for (int j = 1; j < P; ++j) {
+            const double w = static_cast<double>(row[j]);
             ra += fabs(w);
             rs += w;
             rq = fma(w, w, rq);
         }
-        if (dx == -h) { sa = ra; ss = rs; sq = rq; }
-        else { sa += ra; ss += rs; sq += rq; }
-    }
-    const double nsq = __dmul_rn(n, sq);
-    double d = var_n2_one_pass(ss, nsq);
-    if (P > 1 && d < kCancelFrac * nsq) {
-        const double m = ss / n;
-        double acc = 0.0;
-#pragma unroll 1
-        for (int dx = -h; dx <= h; ++dx)
-#pragma unroll 1
-            for (int dy = -h; dy <= h; ++dy) {
-                const double e = static_cast<double>(select_v(a, L, x + dx, y + dy, nullptr)) - m;
-                acc += __dmul_rn(e, e);
+#pragma unroll
+        for (int o = 0; o < RPT; ++o)
+            if (i >= o && i < o + P) {    // (0 + a sum is the sum: scores come from no signed zero)
+                sa[o] += ra;
+                ss[o] += rs;
+                sq[o] += rq;
             }
-        d = __dmul_rn(n, acc);
     }
-    return static_cast<float>(nsi_from_var(sa, d, a.alpha / n, (1.0 - a.alpha) / n));
+#pragma unroll
+    for (int o = 0; o < RPT; ++o) {
+        const int x = x0 + row0 + o;
+        const bool in = x < R && y < C;
+        uint32_t key = 0;
+        if (in) {
+            key = score_from_sums<P>(sa[o], ss[o], sq[o], &sh.tile[(row0 + o) * PITCH + col], PITCH, a.alpha / n, (1.0 - a.alpha) / n);
+            agent_store(a.map + static_cast<size_t>(L.elem_off) + static_cast<size_t>(x) * C + y, key);
+        }
+        wave_count(sh.hist, key >> kCoarseShift, in);
+    }
+    __syncthreads();                      // (the next tile's v goes where this one's lies)
+    return next;
 }
 
-// First digit of a layer's full map, from the histogram that the first step has counted.
+// First digit of a layer's full map, from the histogram that the first step has counted: thread 0 has the top bins.
 __device__ __forceinline__ DigitResult select_map_digit(SelectShared &sh, const uint32_t *hist, uint32_t k) {
-    __syncthreads();
-    if (threadIdx.x < 64u) {
-        const WaveBucket wb = wave_find_bucket(hist, k);
-        if (threadIdx.x == 0) sh.res = DigitResult{wb.bucket, wb.above, wb.count, wb.found};
+    const uint32_t tid = threadIdx.x;
+    const unsigned long long *bins = reinterpret_cast<const unsigned long long *>(hist) + 2 * (kSelectThreads - 1 - tid);
+    const unsigned long long q0 = agent_load(bins), q1 = agent_load(bins + 1);
+    const uint32_t v[4] = {static_cast<uint32_t>(q1 >> 32), static_cast<uint32_t>(q1), static_cast<uint32_t>(q0 >> 32), static_cast<uint32_t>(q0)};
+    const uint32_t own = v[0] + v[1] + v[2] + v[3];
+    if (tid == 0) sh.res.found = 0u;
+    const uint32_t incl = block_scan_incl_n<kSelectWaves>(own, sh.wave_tot);
+    uint32_t acc = incl - own;
+    if (acc < k && k <= incl) {
+        bool hit = false;
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+            if (!hit && acc + v[j] >= k) {
+                sh.res = DigitResult{kHistBins - 1 - 4 * tid - j, acc, v[j], 1u};
+                hit = true;
+            }
+            acc += v[j];
+        }
     }
     __syncthreads();
-    const DigitResult r = sh.res;
+    const DigitResult r = uniform_digit(sh.res);
     __syncthreads();
     return r;
 }
 
-__device__ __forceinline__ void select_full_map(const SelectArgs &a, SelectShared &sh, uint32_t l, const LayerDev &L, const SelState &st,
-                                                const DigitResult failed) {
-    const uint32_t tid = threadIdx.x, S = L.n_groups;
-    const uint32_t C = L.C;
-    uint32_t *list_cnt = a.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
-    uint32_t *ctl = list_cnt + (kListShards - 1) * kListCntStride + kSelectCtl;
-    uint32_t *hist = a.hist + static_cast<size_t>(l) * kHistBins;
-    unsigned long long *list = a.list_ent + L.list_off;
-    const uint32_t cap = L.list_cap / L.list_shards;
-    float *map = a.map + L.elem_off;
-    const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
-    const WindowGeom geom = {static_cast<size_t>(L.elem_off), static_cast<int>(L.R), static_cast<int>(L.C), (static_cast<int>(L.p) - 1) / 2};
-    const uint64_t per = (static_cast<uint64_t>(L.G) + S - 1) / S;
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) sh.ticket = atomicAdd(ctl, 1u);
-        __syncthreads();
-        const uint32_t t = sh.ticket;
-        if (t > 3u * S) return;                                       // uniform, and so is every branch on t
-        const uint32_t share = t < 2u * S ? t % S : t - 2u * S - 1u;
-        const uint64_t begin = min(share * per, static_cast<uint64_t>(L.G)), end = min(begin + per, static_cast<uint64_t>(L.G));
-        if (t < S) {
-            for (int b = tid; b < kHistBins; b += kSelectThreads) sh.hist[b] = 0u;
-            __syncthreads();
-            for (uint64_t i = begin + tid; i < end; i += kSelectThreads) {
-                const uint32_t e = static_cast<uint32_t>(i), x = e / C, y = e - x * C;
-                const float score = select_score(a, L, static_cast<int>(x), static_cast<int>(y));
-                map[e] = score;
-                atomicAdd(&sh.hist[(__float_as_uint(score) & 0x7fffffffu) >> kCoarseShift], 1u);
-                if (a.v_out) {            // (a layer that had no bound went through no pass that stores it)
-                    float gu = 0.f;
-                    a.v_out[L.elem_off + e] = select_v(a, L, static_cast<int>(x), static_cast<int>(y), &gu);
-                    if (a.mom_out) a.mom_out[L.elem_off + e] = gu;
-                }
+// Marks of a run of tiles, from the map.
+__device__ __forceinline__ uint32_t select_mark_run(SelectShared &sh, uint32_t l, uint32_t run, unsigned long long T, uint32_t *ctl) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // (as in select_map_tile)
+    const SelectArgs &a = select_args();
+    const LayerDev &L = select_layer(a, l);
+    const uint32_t g0 = run * kSelectRun, lane = tid & 63u, wave = tid >> 6;
+    GroupGeom q = group_geom(L, g0, min(static_cast<uint32_t>(kSelectRun), L.n_tiles - g0), a.mask, count_ctx(L, a.chunk_cnt, a.group_cnt));
+    group_clear<kSelectThreads>(q, sh.run);
+    __syncthreads();
+    q.cl0 = group_first_chunk(q, sh.run.corner[0]);
+    constexpr uint32_t WAVES = kSelectWaves / kSelectRun, U = kTileRows * kTileCols / 64 / WAVES, PER_ROW = kTileCols / 64;     // a tile's waves; their elements per lane
+    const uint32_t tile = wave / WAVES, e0 = wave % WAVES * U;
+    uint32_t key[U], hits = 0;
+    const bool have = static_cast<int>(tile) < q.gn;                 // (uniform in a wave; the first one's is there)
+    const uint2 corner = have ? sh.run.corner[tile] : make_uint2(0u, 0u);
+    if (have) {
+        const uint32_t *map = a.map + L.elem_off;
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) {
+            const uint32_t x = corner.x + (e0 + j) / PER_ROW, y = corner.y + (e0 + j) % PER_ROW * 64u + lane;
+            key[j] = x < L.R && y < L.C ? agent_load(map + x * L.C + y) : 0u;
+        }
+    }
+    const uint32_t next = select_request(ctl);
+    if (have) {
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) {
+            const uint32_t x = corner.x + (e0 + j) / PER_ROW, y = corner.y + (e0 + j) % PER_ROW * 64u + lane;
+            hits |= x < L.R && y < L.C && composite_key(key[j], x * L.C + y) >= T ? 1u << j : 0u;
+        }
+        while (hits) {
+            const uint32_t j = static_cast<uint32_t>(__ffs(hits)) - 1u;
+            hits &= hits - 1u;
+            const uint32_t i = (corner.x + (e0 + j) / PER_ROW) * L.C + corner.y + (e0 + j) % PER_ROW * 64u + lane;
+            group_mark<true>(q, sh.run, static_cast<int>(tile), i);
+            if (a.cmask) {
+                const size_t pos = static_cast<size_t>(L.elem_off) + i;
+                atomicOr(&a.cmask[pos >> 5], 1u << (pos & 31));
             }
-            __syncthreads();
-            for (int b = tid; b < kHistBins; b += kSelectThreads)
-                if (sh.hist[b]) atomicAdd(&hist[b], sh.hist[b]);
-            select_share_done(ctl + 1);
-        } else if (t < 2u * S) {
-            select_wait(ctl + 1, S);
-            const DigitResult r = select_map_digit(sh, hist, L.k);
-            if (r.found && r.count != L.k - r.above) {               // uniform; else nothing is left to rank
-                const uint32_t lo = r.digit << kCoarseShift, shard = share % L.list_shards;
-                uint32_t *cnt = list_cnt + shard * kListCntStride;
-                unsigned long long *ent = list + static_cast<size_t>(shard) * cap;
-                for (uint64_t i0 = begin; i0 < end; i0 += kSelectThreads) {
-                    const uint64_t i = i0 + tid;
-                    const uint32_t key = i < end ? __float_as_uint(map[i]) & 0x7fffffffu : 0u;
-                    const bool hit = i < end && key - lo < 1u << kCoarseShift;
-                    const uint32_t pos = wave_append(cnt, hit);
-                    if (hit && pos < cap) ent[pos] = composite_key(key, static_cast<uint32_t>(i));
-                }
+        }
+    }
+    __syncthreads();
+    group_write<true, kSelectThreads>(q, sh.run);
+    return next;
+}
+
+// Takes shares of layer l until all are taken.
+__device__ __forceinline__ void select_map_steps(SelectShared &sh, uint32_t l) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // (as in select_map_tile)
+    const SelectArgs &a = select_args();
+    const LayerDev &L = select_layer(a, l);
+    uint32_t *ctl = select_ctl(a.list_cnt, l, 0);
+    const SelectTickets s = select_tickets(L);
+    uint32_t t = select_hand_over(sh, select_request(ctl));
+    if (t < s.keys) {                     // scores and first digit
+        for (int b = tid; b < kHistBins; b += kSelectThreads) sh.hist[b] = 0u;
+        __syncthreads();
+        uint32_t done = 0;
+        do {
+            uint32_t next;
+            switch (L.p) {
+                case 1: next = select_map_tile<1>(sh, l, t, ctl); break;
+                case 3: next = select_map_tile<3>(sh, l, t, ctl); break;
+                case 5: next = select_map_tile<5>(sh, l, t, ctl); break;
+                default: next = select_map_tile<7>(sh, l, t, ctl); break;
             }
-            select_share_done(ctl + 2);
-        } else if (t == 2u * S) {
-            select_wait(ctl + 2, S);
-            const DigitResult r = select_map_digit(sh, hist, L.k);
-            const uint32_t lo = r.found ? r.digit << kCoarseShift : 0u;
-            const unsigned long long base = static_cast<unsigned long long>(lo) << 32;
-            unsigned long long T = base;
-            if (r.found && r.count != L.k - r.above) {
-                if (tid == 0) sh.n = 0u;
-                __syncthreads();
-                const uint32_t n_mine = (tid & 63u) < static_cast<uint32_t>(kListShards) ? list_cnt[(tid & 63u) * kListCntStride] : 0u;
-                const bool listed = __syncthreads_and(n_mine <= cap) != 0;         // every shard of the list fits
-                auto scan = [&](auto f) {
-                    if (listed) {
-#pragma unroll 1
-                        for (int s = 0; s < kListShards; ++s) {
-                            const uint32_t n = __shfl(n_mine, s, 64);
-                            for (uint32_t i = tid; i < n; i += kSelectThreads) f(list[static_cast<size_t>(s) * cap + i] - base);
-                        }
-                    } else {
-                        for (uint64_t i = tid; i < L.G; i += kSelectThreads) {
-                            const uint32_t key = __float_as_uint(map[i]) & 0x7fffffffu;
-                            if (key - lo < 1u << kCoarseShift) f(composite_key(key, static_cast<uint32_t>(i)) - base);
-                        }
+            ++done;
+            t = select_hand_over(sh, next);
+        } while (t < s.keys);
+        uint32_t *hist = a.hist + static_cast<size_t>(l) * kHistBins;
+        for (int b = tid; b < kHistBins; b += kSelectThreads)
+            if (sh.hist[b]) atomicAdd(&hist[b], sh.hist[b]);
+        select_shares_done(ctl - 1 * kListCntStride, done);
+    }
+    if (t < s.marks) {
+        select_wait(ctl - 1 * kListCntStride, s.keys);
+        const DigitResult r = select_map_digit(sh, a.hist + static_cast<size_t>(l) * kHistBins, L.k);
+        const uint32_t lo = r.found ? r.digit << kCoarseShift : 0u;
+        const bool open = r.found && r.count != L.k - r.above;       // else the whole bucket is taken
+        const uint32_t *map = a.map + L.elem_off;
+        uint32_t *list_cnt = a.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
+        uint32_t *hist1 = a.hist1 + static_cast<size_t>(l) * kLevel1Bins;
+        const uint32_t cap = L.list_cap / L.list_shards;
+        constexpr int kShift1 = kCoarseShift - kLevel1Bits, kKeys = kChunk / kSelectThreads;
+        if (t < s.rank) {                 // the bucket's keys and second digit
+            for (int b = tid; b < kLevel1Bins; b += kSelectThreads) sh.lh[b] = 0u;
+            __syncthreads();
+            uint32_t done = 0;
+            do {
+                uint32_t next;
+                if (!open) {
+                    next = select_request(ctl);
+                } else {
+                    const uint32_t start = (t - s.keys) * kChunk + tid, shard = (t - s.keys) % L.list_shards;
+                    uint32_t key[kKeys], hits = 0;
+#pragma unroll
+                    for (uint32_t j = 0; j < kKeys; ++j) {
+                        const uint32_t i = start + j * kSelectThreads;
+                        key[j] = i < L.G ? agent_load(map + i) : ~0u;            // (scores have no sign)
                     }
-                };
-                scan([&](unsigned long long rel) {
-                    const uint32_t pos = atomicAdd(&sh.n, 1u);
-                    if (pos < static_cast<uint32_t>(kSelectList)) sh.key[pos] = rel;
-                });
-                __syncthreads();
-                T += select_rank(sh, sh.n, L.k - r.above, 32 + kCoarseShift, scan);
+                    next = select_request(ctl);
+#pragma unroll
+                    for (uint32_t j = 0; j < kKeys; ++j) {
+                        const bool hit = key[j] - lo < 1u << kCoarseShift;
+                        hits |= hit ? 1u << j : 0u;
+                        wave_count(sh.lh, (key[j] - lo) >> kShift1, hit);
+                    }
+                    const uint32_t own = __popc(hits), incl = block_scan_incl_n<kSelectWaves>(own, sh.wave_tot);
+                    if (tid == kSelectThreads - 1u) sh.n = incl ? atomicAdd(list_cnt + shard * kListCntStride, incl) : 0u;
+                    __syncthreads();
+                    uint32_t pos = sh.n + incl - own;
+                    unsigned long long *ent = a.list_ent + L.list_off + static_cast<size_t>(shard) * cap;
+#pragma unroll
+                    for (uint32_t j = 0; j < kKeys; ++j)
+                        if (hits & (1u << j)) {
+                            if (pos < cap) agent_store(ent + pos, composite_key(key[j], start + j * kSelectThreads));
+                            ++pos;
+                        }
+                }
+                ++done;
+                t = select_hand_over(sh, next);
+            } while (t < s.rank);
+            for (int b = tid; b < kLevel1Bins; b += kSelectThreads)
+                if (sh.lh[b]) atomicAdd(&hist1[b], sh.lh[b]);
+            select_shares_done(ctl - 2 * kListCntStride, done);
+        }
+        if (t == s.rank) {                // the ranking
+            select_wait(ctl - 2 * kListCntStride, L.n_chunks);
+            unsigned long long T = static_cast<unsigned long long>(lo) << 32;
+            if (open) {
+                const uint32_t lane = tid & 63u, wave = tid >> 6;
+                const uint32_t listed_n = lane < static_cast<uint32_t>(kListShards) ? agent_load(list_cnt + lane * kListCntStride) : 0u;
+                for (int b = tid; b < kLevel1Bins; b += kSelectThreads) sh.lh[b] = agent_load(hist1 + b);
+                if (tid == 0) sh.n = 0u;
+                const bool listed = uniform_u32(__syncthreads_and(listed_n <= cap)) != 0u;         // every shard of the list fits
+                uint32_t k_rem = L.k - r.above;
+                const DigitResult d = select_digit(sh, kLevel1Bins, k_rem);
+                k_rem -= d.above;
+                T += static_cast<unsigned long long>(d.digit) << (32 + kShift1);
+                if (d.count != k_rem) {
+                    // f for every key with these two digits, less their value: from the list, a shard per wave, or from the map
+                    const unsigned long long base = T;
+                    const unsigned long long *ent = a.list_ent + L.list_off + static_cast<size_t>(wave) * cap;
+                    const uint32_t n = listed ? __builtin_amdgcn_readlane(listed_n, uniform_u32(wave)) : L.G;
+                    const uint32_t step = listed ? 64u : kSelectThreads, at = listed ? lane : tid;
+                    auto scan = [&](auto f) {
+                        constexpr int U = 8;
+#pragma unroll 1
+                        for (uint32_t i0 = at; i0 - at < n; i0 += U * step) {        // (the same trip count in every lane)
+                            unsigned long long rel[U];
+#pragma unroll
+                            for (int j = 0; j < U; ++j) {
+                                const uint32_t i = i0 + j * step;
+                                rel[j] = ~0ull;
+                                if (i < n) rel[j] = (listed ? agent_load(ent + i) : composite_key(agent_load(map + i), i)) - base;
+                            }
+#pragma unroll
+                            for (int j = 0; j < U; ++j)
+                                if (rel[j] >> (32 + kShift1) == 0ull) f(rel[j]);
+                        }
+                    };
+                    if (d.count <= static_cast<uint32_t>(kSelectList)) {
+                        scan([&](unsigned long long rel) {
+                            const uint32_t pos = atomicAdd(&sh.n, 1u);
+                            if (pos < static_cast<uint32_t>(kSelectList)) sh.key[pos] = rel;
+                        });
+                        __syncthreads();
+                    }
+                    T += select_rank(sh, d.count, k_rem, 32 + kShift1, scan);
+                }
             }
-            if (tid == 0) {
-                if (st.mode == kModeCandidates) bound_failed(a.pred, l, L.k, st, failed);
+            if (tid == 0) agent_store(&a.state[l].T, T);
+            select_shares_done(ctl - 3 * kListCntStride, 1u);
+            if (tid == 0) {               // (for the next calls)
+                const SelState st = a.state[l];
+                if (st.mode == kModeCandidates) {
+                    const uint32_t top = a.hist_s[static_cast<size_t>(l) * kHistBins + kFineBins - 1];
+                    bound_failed(a.pred, l, L.k, st, DigitResult{kFineBins - 1, 0u, 0u, top >= L.k ? 1u : 0u});
+                }
                 SelState ns = st;
                 ns.mode = kModeFullMap;
                 ns.T = T;
@@ -2748,20 +3018,61 @@ __device__ __forceinline__ void select_full_map(const SelectArgs &a, SelectShare
                 a.state[l] = ns;
                 publish_threshold(a.pred, l, 1u, L.k, T);
             }
-            select_share_done(ctl + 3);
-        } else {
-            select_wait(ctl + 3, 1u);
-            // (written by this launch: not through the scalar cache)
-            const unsigned long long T = __hip_atomic_load(&a.state[l].T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (uint64_t i = begin + tid; i < end; i += kSelectThreads)
-                if (composite_key(__float_as_uint(map[i]), static_cast<uint32_t>(i)) >= T)
-                    mark_window<true>(geom, cctx, static_cast<uint32_t>(i), a.mask, a.cmask);
+            t = select_hand_over(sh, select_request(ctl));
         }
+    }
+    if (t < s.end) {                      // the marks
+        select_wait(ctl - 3 * kListCntStride, 1u);
+        const unsigned long long T = agent_load(&a.state[l].T);
+        do {
+            const uint32_t next = select_mark_run(sh, l, t - s.marks, T, ctl);
+            t = select_hand_over(sh, next);
+        } while (t < s.end);
     }
 }
 
-__global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_select(const SelectArgs a) {
-    __shared__ SelectShared sh;
+__device__ __forceinline__ uint32_t select_failed_layers(const SelectArgs &a) {      // of the layers tid, tid + 1024, ...: a bit each
+    static_assert(kInlineCountChunks <= 4u * kSelectThreads, "layers per thread");
+    uint32_t failed = 0;
+    for (uint32_t j = 0, c = threadIdx.x; c < a.n_layers; ++j, c += kSelectThreads)
+        failed |= layer_falls_back(a.layers, a.state, a.hist_s, a.list_cnt, c) ? 1u << j : 0u;
+    return failed;
+}
+// The workgroups of a failed layer's groups (that layer first) and those without a group: shares of any failed layer that has some left.
+__device__ __forceinline__ void select_failed(SelectShared &sh) {
+    const SelectArgs &a = select_args();
+    uint32_t wg = blockIdx.x;
+    asm volatile("" : "+s"(wg));          // (nothing of select_group's is held for this rare case)
+    const uint32_t tid = threadIdx.x;
+    const bool helper = wg >= a.n_groups;
+    if (helper && !uniform_u32(__syncthreads_or(select_failed_layers(a) != 0u))) return;
+    // (helpers come to the layers in proportion to their groups)
+    const uint32_t first = uniform_u32(a.groups[helper ? (wg - a.n_groups) * a.n_groups / (gridDim.x - a.n_groups) : wg].layer);
+    uint32_t l = helper ? ~0u : first;
+    for (;;) {
+        if (l == ~0u) {
+            const uint32_t failed = select_failed_layers(a);
+            __syncthreads();
+            if (tid == 0) sh.n = ~0u;
+            __syncthreads();
+            for (uint32_t j = 0, c = tid; c < a.n_layers; ++j, c += kSelectThreads) {
+                if (!(failed & (1u << j))) continue;
+                if (agent_load(select_ctl(a.list_cnt, c, 0)) < select_tickets(a.layers[c]).end)
+                    atomicMin(&sh.n, c >= first ? c - first : c + a.n_layers - first);
+            }
+            __syncthreads();
+            const uint32_t next = uniform_u32(sh.n);
+            __syncthreads();
+            if (next == ~0u) return;
+            l = first + next < a.n_layers ? first + next : first + next - a.n_layers;
+        }
+        select_map_steps(sh, l);
+        l = ~0u;
+    }
+}
+
+// A group of tile slots; false: its layer's bound failed, nothing is done.
+__device__ __forceinline__ bool select_group(const SelectArgs &a, SelectShared &sh) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const GroupEntry ge = a.groups[blockIdx.x];
     const uint32_t l = ge.layer, cap = ge.slot_cap;
@@ -2792,12 +3103,10 @@ __global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(
     const uint32_t incl = block_scan_incl_n<kSelectWaves>(own_bin, sh.wave_tot), excl = incl - own_bin;
     if (excl < L.k && L.k <= incl) sh.res = DigitResult{kFineBins - 1 - tid, excl, own_bin, 1u};
     __syncthreads();
-    const DigitResult r = sh.res;
+    const DigitResult r = uniform_digit(sh.res);
     // k_find0's test of the bound
-    if (st.mode != kModeCandidates || st.hint_key == 0u || st.overflow != 0u || !r.found || r.digit == static_cast<uint32_t>(kFineBins - 1)) {
-        select_full_map(a, sh, l, L, st, r);
-        return;
-    }
+    const bool failed = st.mode != kModeCandidates || st.hint_key == 0u || st.overflow != 0u || !r.found || r.digit == static_cast<uint32_t>(kFineBins - 1);
+    if (uniform_u32(failed ? 1u : 0u)) return false;
     const uint32_t lo = st.hint_key + (r.digit << kFineShift), k_rem = L.k - r.above;
     const unsigned long long base = static_cast<unsigned long long>(lo) << 32;
     unsigned long long T = base;                     // (the whole bucket is taken: its lower edge)
@@ -2809,7 +3118,7 @@ __global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(
             }
         });
         __syncthreads();
-        T += select_rank(sh, sh.n, k_rem, 32 + kFineShift, [&](auto f) {
+        T += select_rank(sh, uniform_u32(sh.n), k_rem, 32 + kFineShift, [&](auto f) {
             scan.load(K, 0u);
             scan.rest(K, [&](unsigned long long key) {
                 if (static_cast<uint32_t>(key >> 32) - lo < 1u << kFineShift) f(key - base);
@@ -2831,6 +3140,13 @@ __global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(
     __syncthreads();
     group_write<true, kSelectThreads>(q, sh.marks);
     if (q.g0 == 0 && tid == 0) publish_threshold(a.pred, l, 1u, L.k, T);
+    return true;
+}
+
+__global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_select(const SelectArgs a) {
+    __shared__ SelectShared sh;
+    if (blockIdx.x < a.n_groups && select_group(a, sh)) return;
+    select_failed(sh);
 }
 
 // ----------------------------------------------------------------- mark --
@@ -5201,12 +5517,18 @@ static int launch_select(rsdgc_plan_s *plan, char *ws, const float *grad, const 
     a.v_out = v_out;
     a.mom_out = mom.out;
     a.m = mom.m;
-    a.map = reinterpret_cast<float *>(ws + w.nsi);
+    a.map = reinterpret_cast<uint32_t *>(ws + w.nsi);
     a.hist = reinterpret_cast<uint32_t *>(ws + w.hist);
+    a.hist1 = reinterpret_cast<uint32_t *>(ws + w.hist1);
     a.list_cnt = reinterpret_cast<uint32_t *>(ws + w.list_cnt);
     a.list_ent = reinterpret_cast<unsigned long long *>(ws + w.list_ent);
     a.alpha = plan->alpha;
-    hipLaunchKernelGGL(k_select, dim3(static_cast<uint32_t>(plan->cand_groups.size())), dim3(kSelectThreads), 0, stream, a);
+    a.n_layers = static_cast<uint32_t>(plan->n_layers);
+    a.n_groups = static_cast<uint32_t>(plan->cand_groups.size());
+    uint32_t n_tiles = 0;
+    for (const PGroup &g : plan->groups) n_tiles += g.n_large_tiles;
+    const uint32_t n_wgs = std::max(a.n_groups, std::min(a.n_groups + n_tiles, select_workgroups(a.n_groups)));
+    hipLaunchKernelGGL(k_select, dim3(n_wgs), dim3(kSelectThreads), 0, stream, a);
     marks.close(4);
     marks.close(5);
     if (want_centres)
