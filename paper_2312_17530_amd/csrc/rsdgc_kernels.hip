@@ -379,7 +379,9 @@ template <int P> struct PreF32 {
     static constexpr double kBoundFactor = 1.0 - 1.0 / 4194304.0 - 2.04 * (P * P) * 5.9604645e-8;
 };
 
-constexpr int kQueueCap = 1024;      // centres one tile can queue for full evaluation (twice the largest slot)
+// Centres one tile can queue for full evaluation: twice the largest slot, and the positions beyond the matrix's edge whose windows
+// reach into it (the test in the sweep does not ask where a position lies).
+template <int P> constexpr int kQueueCap = 1024 + (P - 1) / 2 * (kTileCols + kTileRows);
 
 __device__ __forceinline__ double var_n2_one_pass(double ss, double nsq) {
     return __dsub_rn(nsq, __dmul_rn(ss, ss));
@@ -678,7 +680,7 @@ struct NsiShared {
     __attribute__((aligned(16))) float tile[(kTileRows + P - 1) * (kTileCols + 8)];
     unsigned long long cand[kCapture ? kSlotCapMax : 1];
     uint32_t lhist[kBins];
-    uint16_t queue[kCapture ? kQueueCap : 1];
+    uint16_t queue[kCapture ? kQueueCap<P> : 1];
     uint32_t ncand, nqueue;
     uint32_t feed_slot[2];
 };
@@ -991,7 +993,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                     const float t = fmaxf(fmaf(-caf, sa, bound_lof), 0.f);
                     if (!(e < t * t)) {   // (outside the matrix too: the queue's turn to tell)
                         const uint32_t pos = atomicAdd(&nqueue, 1u);
-                        if (pos < static_cast<uint32_t>(kQueueCap))
+                        if (pos < static_cast<uint32_t>(kQueueCap<P>))
                             queue[pos] = static_cast<uint16_t>((row_base + o) * kTileCols + c0q);
                     }
                 }
@@ -1049,8 +1051,8 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             // from the tile where the one-pass variance cancels, score, and the record if it reaches
             // the bound
             const uint32_t nq = nqueue;
-            if (nq > static_cast<uint32_t>(kQueueCap) && tid == 0) a.state_rw[l].overflow = 1u;   // (more than any slot holds)
-            for (uint32_t qi = tid; qi < min(nq, static_cast<uint32_t>(kQueueCap)); qi += 256) {
+            if (nq > static_cast<uint32_t>(kQueueCap<P>) && tid == 0) a.state_rw[l].overflow = 1u;   // (more than any slot holds)
+            for (uint32_t qi = tid; qi < min(nq, static_cast<uint32_t>(kQueueCap<P>)); qi += 256) {
                 const int pos = queue[qi];
                 const int orow = pos / kTileCols, ocol = pos - orow * kTileCols;
                 if (x0 + orow >= R || y0 + ocol >= C) continue;

@@ -608,3 +608,28 @@ def test_a_failed_bound_costs_no_more_than_the_full_map(p):
             assert block == 0 or binding.rsdgc_last_paths(plan, ws) == [1]
         best.append(min(times[1:]))
     assert best[0] <= 3.0 * best[1], best
+
+
+@pytest.mark.parametrize("p", [3, 5, 7])
+def test_positions_beyond_the_edge_do_not_send_a_layer_to_the_full_map(p):
+    """Two rows, large values in the second one over the columns of a tile: nearly all of its 512 centres reach the bound, which its slot
+    holds, and so do the positions below the matrix whose windows reach that row.  The layer stays on its predicted bound."""
+    import torch
+    rows, cols = 2, 8 * 256
+    k = -(-rows * cols // (p * p))
+    plan = binding.rsdgc_plan([(rows, cols)], p, 0.5, [1.0])
+    ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    rng = np.random.default_rng(p)
+    v = rng.standard_normal((rows, cols)) * 1e-4
+    v[1, 512:768] = np.where(np.arange(256) % 2 == 0, 1.0, -1.0) * (1.0 + 1e-4 * rng.standard_normal(256))
+    g, r = _dev(v.astype(np.float32).reshape(-1)), _dev(np.zeros(rows * cols, np.float32))
+    out = torch.zeros(rows * cols, device="cuda")
+    msg = (torch.zeros(plan.out_capacity, dtype=torch.int32, device="cuda"), torch.zeros(plan.out_capacity, device="cuda"),
+           torch.zeros(1, dtype=torch.int32, device="cuda"))
+    o = oracle.compress_layer(v.astype(np.float32), np.zeros((rows, cols), np.float32), p, 0.5, 1.0)
+    assert o.k == k and o.centres.min() % cols >= 512 - p and o.centres.max() % cols < 768 + p
+    for t in range(14):
+        binding.rsdgc_compress(plan, g, r, out, *msg, ws)
+        n = int(msg[2][0])
+        assert np.array_equal(msg[0][:n].cpu().numpy().view(np.uint32), o.idx) and np.array_equal(_bits(msg[1][:n].cpu().numpy()), _bits(o.val)), t
+    assert binding.rsdgc_last_paths(plan, ws) == [3]
