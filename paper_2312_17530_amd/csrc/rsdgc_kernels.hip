@@ -1111,24 +1111,31 @@ struct NsiAllArgs {
 // The main pass of layers whose neighbourhoods are single elements: Eqs. 8-10 leave NSI = alpha |v| there (sum|w| = |v|, the
 // variance is exactly 0; nsi_from_var's floor for it vanishes in the rounding to float32), so there is no halo, no tile in LDS
 // and no test in front of the score.  A workgroup takes tiles as in nsi_pass; what reaches the bound goes straight to the tile's
-// slot.  What bounds it is the streaming of g, r and v.  Small groups of layers with other neighbourhoods (up to kRideTiles tiles
+// slot.  FEED: the tiles come from the launch's work feed, under the rule of the other sides (fixed shares / by the feed: 134 M
+// elements 415 / 399 us a call, VGG-19 434 / 412, 72 M 233 / 238, 34 M 126 / 139).
+// What bounds it is the streaming of g, r and v.  Small groups of layers with other neighbourhoods (up to kRideTiles tiles
 // a side) ride along as workgroups of the same launch: alone, a side's launch takes 8 to 15 us however few its tiles are.
 // ResNet-50 with all its vectors, p after the kernels' sides: four launches of 24.1, 23.4, 34.4 and 14.6 us before, now two of 30.3 and 37.2;
 // the call, whose magnitudes no longer need the score map, 191.7 -> 138.0 us.  2048 x 1024 at 2 % 60.0 -> 38.9 us, 8192 x 4096 232.7 -> 136.8.
 struct FlatShared {
     uint32_t lhist[kFineBins];
     uint32_t n[2];                        // candidates of the tile; the other one is being cleared
+    uint32_t feed_slot[2];
 };
-template <bool MOM>
+template <bool MOM, bool FEED>
 __device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, uint32_t wg, uint32_t n_wgs) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (uint32_t j = wg * 256u + tid; j < a.n16; j += n_wgs * 256u) a.counts[j] = make_uint4(0, 0, 0, 0);
-    const uint32_t first = xcd_contiguous(wg, n_wgs);
-    if (first >= a.n_tiles) return;
+    WorkFeed feed;
+    const uint32_t first = FEED ? feed.first(a.feed, a.n_tiles, a.feed_shift, sh.feed_slot) : xcd_contiguous(wg, n_wgs);
+    if (FEED ? first == kNoItem : first >= a.n_tiles) return;        // uniform
     for (int b = tid; b < kFineBins; b += 256) sh.lhist[b] = 0u;
     if (tid < 2) sh.n[tid] = 0u;
     __syncthreads();
-    SampleEntry ahead = a.samples[first];
+    uint32_t e = 0;                       // (as in nsi_pass)
+    SampleEntry ahead = {0u, 0u};
+    if (FEED) e = dir_lookup(a.dir, a.n_dir, first);
+    else ahead = a.samples[first];
     uint32_t cur_l = 0xffffffffu, hint_key = 0, recorded = 0, par = 0;
     bool active = false;
     LayerDev L;
@@ -1142,9 +1149,10 @@ __device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, u
         if (tid == 0 && recorded) atomicAdd(recorded_slot(a.list_cnt, cur_l, wg), recorded);
         recorded = 0;
     };
-    for (uint32_t t = first; t < a.n_tiles; t += n_wgs) {
-        const uint32_t l = ahead.layer, local = ahead.local_tile;
-        if (t + n_wgs < a.n_tiles) ahead = a.samples[t + n_wgs];
+    for (uint32_t t = first; FEED ? t != kNoItem : t < a.n_tiles; t = FEED ? feed.next(sh.feed_slot) : t + n_wgs) {
+        if (FEED) e = dir_advance(a.dir, a.n_dir, e, t);
+        const uint32_t l = FEED ? a.dir[e].layer : ahead.layer, local = FEED ? t - a.dir[e].begin : ahead.local_tile;
+        if (!FEED && t + n_wgs < a.n_tiles) ahead = a.samples[t + n_wgs];
         if (l != cur_l) {
             if (active) {                 // uniform
                 flush();
@@ -1195,6 +1203,7 @@ __device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, u
                     if (MOM) uv[q] = load_streaming(u + off);
                 }
             }
+            if (FEED) feed.stash(sh.feed_slot);
 #pragma unroll
             for (int q = 0; q < N; ++q) {
                 const uint32_t at = static_cast<uint32_t>(x0 + 4 * q + wave) * L.C + static_cast<uint32_t>(y);
@@ -1211,6 +1220,7 @@ __device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, u
                 record(v.w, in[q], at + 3u);
             }
         } else {
+            if (FEED) feed.stash(sh.feed_slot);
 #pragma unroll 1
             for (int q = 0; q < kTileRows; q += 4) {                 // four rows' elements of a column at a time
                 float gq[4], rq[4], uq[MOM ? 4 : 1];
@@ -1252,10 +1262,10 @@ __device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, u
     }
     if (active) flush();
 }
-template <bool MOM>
+template <bool MOM, bool FEED>
 __global__ __launch_bounds__(256) void k_capture_flat(const NsiArgs a) {
     __shared__ FlatShared sh;
-    capture_flat<MOM>(a, sh, blockIdx.x, gridDim.x);
+    capture_flat<MOM, FEED>(a, sh, blockIdx.x, gridDim.x);
 }
 // ... with the small groups of other sides: a range of workgroups each, theirs first (they take longest).
 template <bool MOM>
@@ -1271,7 +1281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     if (b < a.first_wg[1]) nsi_pass<7, kPassCapture, MOM, false>(a.side[3], sh.s7, b, a.first_wg[1]);
     else if (b < a.first_wg[2]) nsi_pass<5, kPassCapture, MOM, false>(a.side[2], sh.s5, b - a.first_wg[1], a.first_wg[2] - a.first_wg[1]);
     else if (b < a.first_wg[3]) nsi_pass<3, kPassCapture, MOM, false>(a.side[1], sh.s3, b - a.first_wg[2], a.first_wg[3] - a.first_wg[2]);
-    else capture_flat<MOM>(a.side[0], sh.flat, b - a.first_wg[3], a.first_wg[4] - a.first_wg[3]);
+    else capture_flat<MOM, false>(a.side[0], sh.flat, b - a.first_wg[3], a.first_wg[4] - a.first_wg[3]);
 }
 constexpr uint32_t kRideTiles = 256;      // tiles of a side up to which it rides along: one round of workgroups
 
@@ -5249,6 +5259,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     uint32_t n_flat = 0;
     for (const PGroup &g : plan->groups)
         if (PASS == kPassCapture && g.p == 1) n_flat = g.n_large_tiles;
+    const bool flat_fed = plan->work_feed != RSDGC_FEED_OFF && (plan->work_feed == RSDGC_FEED_ON || n_flat >= kFeedTiles);     // (as below; then alone)
     for (const PGroup &g : plan->groups) {
         // this launch's work-feed counters (left clear by the call before)
         const int pass_index = PASS == kPassSample ? 0 : PASS == kPassCapture ? 1 : 2;
@@ -5265,13 +5276,13 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
                                                    : kLargeOnly ? g.n_large_tiles : g.n_tiles;
         if (items == 0) continue;
         a.n_tiles = items;
-        if (together || (n_flat != 0u && (g.p == 1 || (items <= kRideTiles && plan->work_feed != RSDGC_FEED_ON)))) {
+        a.feed_shift = 7;                  // 128 items per domain and stretch: one per resident workgroup of an XCD
+        while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > items) --a.feed_shift;
+        if (together || (n_flat != 0u && (g.p == 1 || (items <= kRideTiles && !flat_fed)))) {
             all.side[g.p / 2] = a;
             all_items += items;
             continue;
         }
-        a.feed_shift = 7;                  // 128 items per domain and stretch: one per resident workgroup of an XCD
-        while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > items) --a.feed_shift;
         const dim3 block(256);
         switch (g.p) {
 #define RSDGC_NSI_LAUNCH(PP, MM, FF)                                                        \
@@ -5321,12 +5332,17 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     if (n_flat != 0u) {
         const bool alone = all_items == n_flat;
         static const uint32_t resident[2][2] = {{resident_workgroups(k_capture_mixed<false>), resident_workgroups(k_capture_mixed<true>)},
-                                                {resident_workgroups(k_capture_flat<false>), resident_workgroups(k_capture_flat<true>)}};
+                                                {resident_workgroups(k_capture_flat<false, false>), resident_workgroups(k_capture_flat<true, false>)}};
+        static const uint32_t resident_fed[2] = {resident_workgroups(k_capture_flat<false, true>), resident_workgroups(k_capture_flat<true, true>)};
         const uint32_t most = resident[alone ? 1 : 0][mom.in ? 1 : 0];
         const uint32_t rounds = (n_flat + most - 1) / most, n_wgs = (n_flat + rounds - 1) / rounds;        // (shares as below)
-        if (alone) {
-            if (mom.in) hipLaunchKernelGGL(k_capture_flat<true>, dim3(n_wgs), dim3(256), 0, stream, all.side[0]);
-            else hipLaunchKernelGGL(k_capture_flat<false>, dim3(n_wgs), dim3(256), 0, stream, all.side[0]);
+        if (flat_fed) {
+            const dim3 grid(std::min(n_flat, resident_fed[mom.in ? 1 : 0]));
+            if (mom.in) hipLaunchKernelGGL((k_capture_flat<true, true>), grid, dim3(256), 0, stream, all.side[0]);
+            else hipLaunchKernelGGL((k_capture_flat<false, true>), grid, dim3(256), 0, stream, all.side[0]);
+        } else if (alone) {
+            if (mom.in) hipLaunchKernelGGL((k_capture_flat<true, false>), dim3(n_wgs), dim3(256), 0, stream, all.side[0]);
+            else hipLaunchKernelGGL((k_capture_flat<false, false>), dim3(n_wgs), dim3(256), 0, stream, all.side[0]);
         } else {
             for (int i = 1; i < kSides; ++i) all.first_wg[i] = all.first_wg[i - 1] + all.side[kSides - i].n_tiles;   // a tile each
             all.first_wg[kSides] = all.first_wg[kSides - 1] + n_wgs;

@@ -633,3 +633,31 @@ def test_positions_beyond_the_edge_do_not_send_a_layer_to_the_full_map(p):
         n = int(msg[2][0])
         assert np.array_equal(msg[0][:n].cpu().numpy().view(np.uint32), o.idx) and np.array_equal(_bits(msg[1][:n].cpu().numpy()), _bits(o.val)), t
     assert binding.rsdgc_last_paths(plan, ws) == [3]
+
+
+@pytest.mark.parametrize("m", [None, 0.9], ids=["plain", "momentum"])
+def test_single_elements_by_the_work_feed(m):
+    """Single-element neighbourhoods whose tiles come from the work counters: rows of 256, of other whole words, of odd
+    length; a layer of one tile and of several hundred, one that is skipped in between, and one of another side beside them.
+    Three calls against the oracle."""
+    from paper_2312_17530_amd.session import Session
+    shapes = [(1, 256), (300, 2048), (64, 64), (70, 300), (33, 31), (40, 512), (1, 4160), (16, 255), (500, 10), (45, 1)]
+    ratios = [0.02, 0.01, 0.05, 0.02, 0.03, 0.0, 0.03, 0.02, 0.05, 0.1]
+    sides = [1, 1, 1, 1, 1, 1, 1, 3, 1, 1]
+    rng = np.random.default_rng(77)
+    s = Session(shapes, 1, 0.5, ratios, sides, momentum=m, work_feed=2)
+    resid = [np.zeros(sh, np.float32) for sh in shapes]
+    mom = [np.zeros(sh, np.float32) for sh in shapes]
+    for t in range(3):
+        grads = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+        s.set_grad(grads)
+        s.compress()
+        after = s.unpack(s.residual)
+        u_after = s.unpack(s.momentum_buf) if m is not None else mom
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o, u_new = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, sides[l], 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+            if m is not None:
+                assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)
+        resid, mom = after, u_after
