@@ -4710,8 +4710,8 @@ __global__ __launch_bounds__(256) void k_dyn_clear(const DynSplitArgs a) {
 
 // Histogram of a sample: kDynSamplePieces pieces of 16 weights per chunk, at places given by a hash; a short chunk
 // gives each of its pieces with the probability of its share of a whole one.  A chain of three loads and the counts' way out
-// bound it: as many threads as a workgroup can have, and all of a thread's pieces requested at once, one round on VGG-19 (68224
-// pieces; four rounds of 256 threads took 11.9 us, now 8.6).
+// bound it: as many threads as a workgroup can have (with 256 the kernel took 11.9 us on VGG-19's 140 M weights, with 1024 8.9), and
+// several of a thread's pieces requested at once.
 __global__ __launch_bounds__(kDynSampleThreads) void k_dyn_sample(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
                                                                   const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t lhist[kDynSampleBins];
@@ -4720,7 +4720,9 @@ __global__ __launch_bounds__(kDynSampleThreads) void k_dyn_sample(const ChunkInf
     for (int b = tid; b < kDynSampleBins; b += kDynSampleThreads) lhist[b] = 0u;
     __syncthreads();
     const uint32_t n_pieces = n_chunks * kDynSamplePieces, stride = gridDim.x * kPieces;
-    constexpr int U = 5;                   // pieces in flight per 16 threads: the chain entry -> weight -> bin is what this kernel waits for
+    // pieces in flight per 16 threads: the chain entry -> weight -> bin is what this kernel waits for (a call with 2 / 4 / 8 of them:
+    // 12 M weights 69.2 / 69.4 / 70.5 us, 100 M 121.0 / 120.6 / 122.1, 140 M 167.3 / 166.7 / 167.6, 400 M 316.2 / 313.4 / 314.0)
+    constexpr int U = 4;
     for (uint32_t i0 = blockIdx.x * kPieces; i0 < n_pieces; i0 += U * stride) {
         uint64_t at[U];
         bool have[U];
