@@ -377,6 +377,48 @@ constexpr double kCancelFrac = 1.0 / 1048576.0;
 template <int P> struct PreF32 {
     static constexpr float kSlack = 1.3f * (3.f * P * P + 3.f) * 5.9604645e-8f;
     static constexpr double kBoundFactor = 1.0 - 1.0 / 4194304.0 - 2.04 * (P * P) * 5.9604645e-8;
+    __device__ static __forceinline__ float square_factor(double cb) {                       // A
+        return __double2float_ru(cb * cb * static_cast<double>(P * P) * (1.0 + static_cast<double>(kSlack)) * (1.0 + 2e-6));
+    }
+    __device__ static __forceinline__ float bound(float b) { return __double2float_rd(static_cast<double>(b) * kBoundFactor); }        // B'
+    // Whether the centre stays, from its window's sums.
+    __device__ static __forceinline__ bool stays(float sa, float ss, float sq, float ca, float cb, float a, float b) {
+        const float m = cb * ss, e = fmaf(-m, m, a * sq);
+        const float t = fmaxf(fmaf(-ca, sa, b), 0.f);
+        return !(e < t * t);
+    }
+};
+
+// Sums over P neighbours of a row.
+template <int P>
+__device__ __forceinline__ void row_sums(const float *row, float &sa, float &ss, float &sq) {
+    sa = fabsf(row[0]);
+    ss = row[0];
+    sq = row[0] * row[0];
+#pragma unroll
+    for (int j = 1; j < P; ++j) {
+        sa += fabsf(row[j]);
+        ss += row[j];
+        sq = fmaf(row[j], row[j], sq);
+    }
+}
+// Sums of the last P row sums of a column, row by row (P compile-time indices: all of it in registers).  Pairs and pairs of
+// pairs are kept and shared by the windows: P = 5 takes three additions a row instead of four, P = 7 four instead of six (the main
+// pass with p = 7 on 38 M elements: 86.2 us without, 84.9 with).
+template <int P>
+struct ColumnSums {
+    static_assert(P == 3 || P == 5 || P == 7, "single elements have no windows");
+    float s[8], p[8], c[8];               // of row i (at i % 8): its sum, with the row before, with the three before
+    __device__ __forceinline__ void push(int i, float row) {
+        s[i & 7] = row;
+        if (i >= 1) p[i & 7] = s[(i - 1) & 7] + row;
+        if (P == 7 && i >= 3) c[i & 7] = p[(i - 2) & 7] + p[i & 7];
+    }
+    __device__ __forceinline__ float window(int i) const {
+        if (P == 3) return s[(i - 2) & 7] + p[i & 7];
+        if (P == 5) return (p[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
+        return (c[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
+    }
 };
 
 // Centres one tile can queue for full evaluation: twice the largest slot, and the positions beyond the matrix's edge whose windows
@@ -631,25 +673,6 @@ __device__ __forceinline__ WaveBucket wave_find_bucket(const uint32_t *__restric
 // a launch issues few same-address global atomics.
 // MOM: with Eq. 12's momentum term (a.mom, a.mom_out, a.m).  FEED: the workgroups take their
 // tiles from the launch's work feed instead of a fixed strided share.
-// Sums of the last P row sums of a column, row by row (P compile-time indices: all of it in registers).  Pairs and pairs of
-// pairs are kept and shared by the windows: P = 5 takes three additions a row instead of four, P = 7 four instead of six (the main
-// pass with p = 7 on 38 M elements: 86.2 us without, 84.9 with).
-template <int P>
-struct ColumnSums {
-    float s[8], p[8], c[8];               // of row i (at i % 8): its sum, with the row before, with the three before
-    __device__ __forceinline__ void push(int i, float row) {
-        s[i & 7] = row;
-        if (P > 1 && i >= 1) p[i & 7] = s[(i - 1) & 7] + row;
-        if (P == 7 && i >= 3) c[i & 7] = p[(i - 2) & 7] + p[i & 7];
-    }
-    __device__ __forceinline__ float window(int i) const {
-        if (P == 1) return s[i & 7];
-        if (P == 3) return s[(i - 2) & 7] + p[i & 7];
-        if (P == 5) return (p[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
-        return (c[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
-    }
-};
-
 // Where a workgroup adds the candidates it recorded of a layer: word 1 of one of the first kRecordedParts list shards' lines
 // (several, as all workgroups of a launch end at about the same time).
 constexpr uint32_t kRecordedParts = 4;
@@ -759,7 +782,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     // has no floating point, a uniform value computed here would occupy vector registers)
     const double ca = a.ca, cb = a.cb;
     const float caf = uniform_f32(static_cast<float>(ca)), cbf = uniform_f32(static_cast<float>(cb));
-    const float pre_a = uniform_f32(__double2float_ru(cb * cb * n * (1.0 + static_cast<double>(PreF32<P>::kSlack)) * (1.0 + 2e-6)));
+    const float pre_a = uniform_f32(PreF32<P>::square_factor(cb));
     float bound_lof = 0.f;                // capture: a conservative form of the candidate bound (PreF32)
     static_assert(kTileCols * (kTileRows / RPT) == 256, "one thread per RPT rows of one column");
     const int c0 = tid % kTileCols, ty = tid / kTileCols;
@@ -799,7 +822,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                 else active = st.mode == kModeCandidates;
                 if (CAPTURE) {
                     hint_key = st.hint_key;
-                    bound_lof = uniform_f32(__double2float_rd(static_cast<double>(__uint_as_float(hint_key)) * PreF32<P>::kBoundFactor));
+                    bound_lof = uniform_f32(PreF32<P>::bound(__uint_as_float(hint_key)));
                     // (k_begin and k_hint give no bound outside the range of the float32 test; should one
                     // arrive all the same, the layer is not captured and k_find0 sends it to the full map)
                     if (active && (hint_key < kPreF32MinKey || hint_key > kPreF32MaxKey)) {
@@ -962,7 +985,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
         // entries of the thread once, outside the loop over the tiles, and keeps them in registers)
         int c0q = c0;
         asm volatile("" : "+v"(c0q));
-        if (CAPTURE) {
+        if constexpr (CAPTURE) {
             // Only the centres that reach the bound are wanted, and about 99.5 % do not.  A test
             // without the square root rules those out:
             //   NSI >= B  <=>  cb*sqrt(d) >= B - ca*sa  <=>  cb^2 * d >= max(B - ca*sa, 0)^2
@@ -973,25 +996,16 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             ColumnSums<P> ca_, cs_, cq_;
 #pragma unroll
             for (int i = 0; i < RPT + 2 * H; ++i) {
-                const float *row = &tile[(row_base + i) * PITCH + PADL + c0 - H];
                 {
-                    float sa = fabsf(row[0]), ss = row[0], sq = row[0] * row[0];
-#pragma unroll
-                    for (int j = 1; j < P; ++j) {
-                        sa += fabsf(row[j]);
-                        ss += row[j];
-                        sq = fmaf(row[j], row[j], sq);
-                    }
+                    float sa, ss, sq;
+                    row_sums<P>(&tile[(row_base + i) * PITCH + PADL + c0 - H], sa, ss, sq);
                     ca_.push(i, sa);
                     cs_.push(i, ss);
                     cq_.push(i, sq);
                 }
                 if (i >= 2 * H) {
                     const int o = i - 2 * H;
-                    const float sa = ca_.window(i), ss = cs_.window(i), sq = cq_.window(i);
-                    const float m = cbf * ss, e = fmaf(-m, m, pre_a * sq);
-                    const float t = fmaxf(fmaf(-caf, sa, bound_lof), 0.f);
-                    if (!(e < t * t)) {   // (outside the matrix too: the queue's turn to tell)
+                    if (PreF32<P>::stays(ca_.window(i), cs_.window(i), cq_.window(i), caf, cbf, pre_a, bound_lof)) {   // (outside the matrix too: the queue's turn to tell)
                         const uint32_t pos = atomicAdd(&nqueue, 1u);
                         if (pos < static_cast<uint32_t>(kQueueCap<P>))
                             queue[pos] = static_cast<uint16_t>((row_base + o) * kTileCols + c0q);

@@ -1,6 +1,8 @@
 """The main pass's float32 test in the form of one comparison, e < max(rest, 0)^2, with the sums of a column's rows formed in
 pairs: replayed in numpy float32 on the windows of test_pretest_bounds and compared with exact arithmetic.  (The
-constants are typed in here as they stand in the kernel source.)"""
+constants are typed in here, and compared with those of the kernel source; test_pretest_bounds runs that source itself.)"""
+import re
+
 import numpy as np
 import pytest
 
@@ -44,6 +46,19 @@ def _kept(P, alpha, W, bound, slack=1.3, extra=2e-6, bound_terms=2.04):
         e = bounds._fma32(-m, m, (a * sq).astype(f32))
         t = np.fmax(bounds._fma32(np.full_like(sa, -caf), sa, bound_lof), f32(0))
         return ~(e < (t * t).astype(f32))
+
+
+def test_the_constants_are_the_sources():
+    """... and the replay gives what the source's code gives, window by window."""
+    pre = bounds._piece(open(bounds.SOURCE).read(), "template <int P> struct PreF32 {", "\n};")
+    assert re.search(r"kSlack = ([\d.]+)f \* \(3\.f \* P \* P \+ 3\.f\) \* ([\d.e-]+)f;", pre).groups() == ("1.3", "5.9604645e-8")
+    assert re.search(r"kBoundFactor = 1\.0 - 1\.0 / (\d+)\.0 - ([\d.]+) \* \(P \* P\) \* ([\d.e-]+);", pre).groups() == (str(2 ** 22), "2.04", "5.9604645e-8")
+    assert "* (1.0 + static_cast<double>(kSlack)) * (1.0 + 2e-6))" in pre
+    rng = np.random.default_rng(1)
+    for P in (3, 5, 7):
+        for name, W in bounds._windows(rng, P, 2000).items():
+            b = np.abs(W).mean(axis=(1, 2)).astype(f32) * rng.uniform(0.5, 2.0, len(W)).astype(f32)
+            assert np.array_equal(_kept(P, 0.5, W, b), bounds._kept(P, 0.5, W, b)), (P, name)
 
 
 @pytest.mark.parametrize("P", [1, 3, 5, 7])
