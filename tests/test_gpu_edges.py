@@ -661,3 +661,34 @@ def test_single_elements_by_the_work_feed(m):
             if m is not None:
                 assert np.array_equal(_bits(u_after[l]), _bits(u_new)), (t, l)
         resid, mom = after, u_after
+
+
+@pytest.mark.parametrize("shape, p, k", [((1024, 1024), 1, 16384), ((1024, 1024), 1, 16385), ((2048, 2048), 3, 4096), ((2064, 2048), 3, 4096)],
+                         ids=["most_centres", "one_more", "most_tiles", "a_row_more"])
+def test_plans_at_the_limits_of_the_selection_in_one_launch(shape, p, k):
+    """A layer with as many centres (16384) and as many tiles (1024) as a plan that selects in one launch may have, and with
+    more: frozen at first and noise afterwards, with bounds that fail and bounds that hold.  Against the oracle."""
+    from paper_2312_17530_amd.session import Session
+    rho = k * p * p / (shape[0] * shape[1])
+    while True:                                        # Eq. 11's k_l in double, as the plan takes it
+        got = int(np.ceil(shape[0] * shape[1] / (p * p) * rho))
+        if got == k:
+            break
+        rho *= 1.0 - 1e-12 if got > k else 1.0 + 1e-12
+    s = Session([shape], p, 0.5, [rho])
+    assert s.plan.layer_k(0) == k
+    rng = np.random.default_rng(k)
+    g = (rng.standard_normal(shape) * 1e-2).astype(np.float32)
+    paths = []
+    for t in range(14):
+        grad = np.zeros(shape, np.float32) if t == 0 else g * np.float32(32.0 if t == 12 else 1.0)
+        s.set_grad([grad])
+        s.set_residual([np.zeros(shape, np.float32)])
+        s.compress()
+        paths += binding.rsdgc_last_paths(s.plan, s.workspace)
+        if t in (0, 1, 11, 12, 13):
+            o = oracle.compress_layer(grad, np.zeros(shape, np.float32), p, 0.5, rho)
+            idx, val, centres, _ = s.results()[0]
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), t
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(s.unpack(s.residual)[0]), _bits(o.r_new)), t
+    assert paths[0] == 1 and paths[11:13] == [3, 1], paths

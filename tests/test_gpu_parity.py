@@ -817,6 +817,24 @@ def test_large_layers_with_masses_of_exact_ties(in_place):
         assert n == 8 and ex >= 7
 
 
+def test_masses_of_exact_ties_where_every_step_is_a_launch(in_place):
+    """The same where the selection is not made in one launch (the work counters ask for that; so does a layer that is always
+    ranked on the full map): the fallback pass, the gather's walk over the score map and its list that overflows, and
+    k_finish streaming the map, digit by digit."""
+    shapes = [(1024, 1024), (768, 1536), (1000, 1100), (600, 2048)]
+    rng = np.random.default_rng(4243)
+    grads = [np.zeros(shapes[0], np.float32), np.full(shapes[1], 0.0625, np.float32),
+             rng.integers(-2, 3, size=shapes[2]).astype(np.float32), (rng.standard_normal(shapes[3]) * 1e-3).astype(np.float32)]
+    n, ex = run_and_check(shapes, [3] * 4, 0.5, [0.05, 0.02, 0.03, 0.02], [grads, grads], "ties_by_launches_fed", in_place=in_place, work_feed=FEED_ON)
+    assert n == 8 and ex >= 7
+    small = (rng.standard_normal((64, 100)) * 1e-3).astype(np.float32)
+    n, ex = run_and_check(shapes + [(64, 100)], [5, 3, 1, 3, 1], 0.5, [0.3, 0.01, 0.02, 0.05, 1.0], [grads + [small]] * 2, "ties_by_launches", in_place=in_place)
+    assert n == 10 and ex >= 9
+    if not in_place:
+        n, ex = run_and_check_momentum(shapes, [3] * 4, 0.5, [0.05, 0.02, 0.03, 0.02], 0.9, [grads, grads], "ties_by_launches", work_feed=FEED_ON)
+        assert n == 8 and ex >= 7
+
+
 def test_large_layers_with_high_keep_ratios(in_place):
     """Keep ratios far above the benchmark's (up to 1, where Eq. 11 selects G/p^2 centres, and
     with p = 1 every element): the layers are ranked on the full map and the threshold bucket of
