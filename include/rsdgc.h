@@ -85,8 +85,10 @@ int rsdgc_plan_set_ratios(rsdgc_plan_t *plan, const double *keep_ratio);
 /* How the per-layer ranking (Algorithm 1) is carried out; the result is the same.
  *   RSDGC_PATH_AUTO      every layer whose keep ratio leaves room for it (8 k_l per 16 x 256
  *                        tile within a tile's 512 candidate entries: up to about 14 % for
- *                        p = 3) records only the centres whose score reaches a bound and
- *                        ranks those.  The bound comes from the thresholds the same layer
+ *                        p = 3; with p = 1 the tiles are 4096 consecutive elements with room
+ *                        for half of them: up to about 6 %, or 1.5 % if the layer's size is no
+ *                        multiple of 32) records only the centres whose score reaches a bound
+ *                        and ranks those.  The bound comes from the thresholds the same layer
  *                        ended on in the two calls before (kept in the workspace), or, in
  *                        the first ten calls with a workspace, from a sample of the
  *                        layer's tiles.  A layer falls back to the full map within the call

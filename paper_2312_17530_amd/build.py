@@ -16,7 +16,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp
 def build_library(verbose: bool = False, extra_flags=()) -> str:
     """Compiles the library.  The compiler's per-kernel resource remarks are read back: the kernels
     are sized to run without register spills to memory (the main pass at 96 VGPRs under an occupancy
-    hint), and a spill there costs tens of percent silently -- so it is reported."""
+    hint), and a spill there costs tens of percent silently -- so it is reported.  k_select's few are known:
+    they lie in what it does where a layer's bound failed."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *FLAGS, "-Rpass-analysis=kernel-resource-usage", *extra_flags]
     for s in SOURCES:

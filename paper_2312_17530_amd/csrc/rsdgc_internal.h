@@ -85,7 +85,7 @@ struct LayerDev {
     int64_t out_off;     // first pair of the layer in out_idx / out_val
     int64_t centre_off;  // first entry of the layer in out_centre_idx
     uint64_t list_off;   // first entry of the layer's threshold-bucket list
-    uint64_t slot_off;   // first entry of the layer's tile slots (large layers)
+    uint64_t slot_off;   // first entry of the layer's tile slots (large layers), from slot_ent on; p = 1: it may lie in the layer's part of the score map
     uint32_t R, C, G, k;
     uint32_t p, tiles_x, tile_begin, n_tiles;   // tile_begin: first tile inside its p-group launch
     uint32_t chunk_begin, n_chunks, cap, tile_begin_all;  // tile_begin_all: first tile over all layers
@@ -97,7 +97,8 @@ struct LayerDev {
     uint32_t n_sampled;     // sampled tiles of the layer
     uint32_t list_cap;      // capacity of the threshold-bucket list
     uint32_t list_shards;   // shards the list is split into (each list_cap / list_shards entries, own counter)
-    uint32_t slot_cap;      // entries per tile slot: kSlotCapMax, or what a tile of the layer can hold if that is less
+    uint32_t slot_cap;      // entries per tile slot: kSlotCapMax, or what a tile of the layer can hold if that is less; p = 1 in rows of
+                            //    whole mask words: what there is room for, up to half of the tile's elements or kSlotCapMax
     uint32_t cgroup_begin;  // first chunk group (kChunkGroup chunks) of the layer, numbered over all layers
     uint32_t pad_;
 };
@@ -232,8 +233,9 @@ struct WsLayout {
     size_t chunk_ccnt = 0;   // uint32[n_chunks]  selected centres per chunk
     size_t group_cnt = 0;    // uint32[n_chunk_groups * kGroupCntStride]  kept elements per chunk group, each counter on its own cache line
     size_t group_ccnt = 0;   // the same for the selected centres
-    size_t list_cnt = 0;     // uint32[n_layers][kListShards][kListCntStride]  [0] of a shard: keys gathered into it, [1]: a part of the
-                             //             layer's candidates recorded by the main pass (any share of the workgroups')
+    size_t list_cnt = 0;     // uint32[n_layers][kListShards][kListCntStride]  [0] of a shard: keys gathered into it, [1] of the first four: a part of
+                             //             the layer's candidates recorded by the main pass (any share of the workgroups'), [8] of the last four:
+                             //             k_select's tickets and shares done, where the layer's bound failed
     size_t list2_cnt = 0;    // uint32[n_layers]  of those, keys that k_filter picked for k_finish
     size_t feed = 0;         // uint32[16][8][32]  work-feed counters of the NSI launches
     size_t mask = 0;         // uint32[total_elems / 32]  kept-element bitmask
@@ -241,10 +243,11 @@ struct WsLayout {
     size_t zero_end = 0;
     // not cleared
     size_t slot_cnt = 0;     // uint32[n_tiles_all]  candidates recorded per tile
-    size_t slot_ent = 0;     // uint64[sum over the layers of n_tiles * slot_cap]  their composite keys
+    size_t slot_ent = 0;     // uint64[slot_entries]  their composite keys: slots for tiles of the layers' own rows; what p = 1 makes of the room: slot_cap
     size_t list_ent = 0;     // uint64[sum list_cap]  composite keys of each layer's threshold bucket
     size_t list2_ent = 0;    // uint64[n_layers][2048]  keys sharing the first two digits (plans with big_map_layers)
-    size_t nsi = 0;          // float[total_elems]  score map (full-map layers only)
+    size_t nsi = 0;          // float[total_elems]  score map of the layers that are ranked on it; while a layer of p = 1 is on the candidate path its
+                             //             part may hold its tile slots, which a bound that fails lets the map overwrite
     size_t dyn = 0;          // scratch of rsdgc_dynamic_ratios: DynState, uint64[kHistBins], uint32[2 * n_layers]
     size_t apply_starts = 0; // uint32[RSDGC_MAX_MSGS][n_chunks][2]  rsdgc_apply: each message's first pair of every half chunk
     size_t total = 0;

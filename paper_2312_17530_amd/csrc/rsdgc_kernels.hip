@@ -373,7 +373,8 @@ constexpr double kCancelFrac = 1.0 / 1048576.0;
 // that range no bound is handed out: the layer is ranked on the full map (k_begin, k_hint).
 // Seven operations.  With d and rest scaled apart and compared in two steps (twelve, and beside them the test of the matrix's
 // edges, which is left to the evaluation in full now) the main pass took 234 us on 25088 x 4096 with p = 5, now 216; with p = 7 on 38 M
-// elements 92.6, now 86.2; VGG-19 312 -> 307, where it stores no v 255 -> 246.
+// elements 92.6, now 86.2; VGG-19, which the streaming bounds, 312 -> 307 on one step repeated and no less on a carried residual (315,
+// 319), where it stores no v 255 -> 246.
 template <int P> struct PreF32 {
     static constexpr float kSlack = 1.3f * (3.f * P * P + 3.f) * 5.9604645e-8f;
     static constexpr double kBoundFactor = 1.0 - 1.0 / 4194304.0 - 2.04 * (P * P) * 5.9604645e-8;
@@ -585,7 +586,7 @@ struct NsiArgs {
     const SampleEntry *samples;   // the launch's tiles (kPassSample; the large layers' passes without the work feed)
     const float *grad;
     const float *resid;           // nullable: all-zero residual
-    float *nsi_out;               // score map (kPassMapOnly, kPassFullMap)
+    float *nsi_out;               // score map (kPassMapOnly, kPassFullMap; kPassSample: of the layers that are always ranked on it)
     float *v_out;                 // nullable: second residual arena that receives v = r + g
     const float *mom;             // nullable: momentum arena u (Eq. 12, first line); then v = r + (m*u + g)
     float *mom_out;               // with mom: receives m*u + g wherever v_out receives v
@@ -1382,7 +1383,7 @@ __device__ __forceinline__ void publish_threshold(PredState *__restrict__ pred, 
 // k_count and pass no counters here.  A mask word lies in one chunk: chunks are 256 words long and
 // a layer starts at a word boundary.
 struct CountCtx {
-    uint32_t *chunk_cnt, *group_cnt;   // cleared by the find0 launch; null: the plan counts with k_count instead
+    uint32_t *chunk_cnt, *group_cnt;   // cleared by the find0 launch, or by the main pass where k_select follows; null: the plan counts with k_count instead
     size_t word0;                      // the layer's first mask word
     uint32_t chunk_begin, cgroup_begin;
 };
@@ -1992,7 +1993,7 @@ __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS
             const bool inner = !((rr < h && corner.x > 0u) || (rr >= kTileRows - h && below > 0));
             uint32_t word = bits[0];
             if (shift) {                  // (uniform where rows are whole words: 0)
-                if (ww == 7u) group_put<COUNT>(q, sh, (pos >> 5) + 8u, word >> (32u - shift), inner && c0 + 64 <= c_hi);
+                if (ww == 7u) group_put<COUNT>(q, sh, (pos >> 5) + 8u, word >> (32u - shift), false);      // (it goes on beyond the tile)
                 word <<= shift;
                 if (ww != 0u) word |= bits[-1] >> (32u - shift);
             }
