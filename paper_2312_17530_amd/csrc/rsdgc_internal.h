@@ -98,7 +98,7 @@ struct LayerDev {
     uint32_t list_cap;      // capacity of the threshold-bucket list
     uint32_t list_shards;   // shards the list is split into (each list_cap / list_shards entries, own counter)
     uint32_t slot_cap;      // entries per tile slot: kSlotCapMax, or what a tile of the layer can hold if that is less; p = 1 in rows of
-                            //    whole mask words: what there is room for, up to half of the tile's elements or kSlotCapMax
+                            //    whole mask words: what there is room for (usually half of the tile's elements)
     uint32_t cgroup_begin;  // first chunk group (kChunkGroup chunks) of the layer, numbered over all layers
     uint32_t pad_;
 };

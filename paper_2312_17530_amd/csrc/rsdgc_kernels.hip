@@ -654,26 +654,6 @@ __device__ __forceinline__ WaveBucket wave_find_bucket(const uint32_t *__restric
     return r;
 }
 
-// Work unit: one 16 x 256 tile of one layer.  The tile of v = r + g plus a halo of
-// h = (P-1)/2 rows and 4 columns (16-byte aligned) goes to LDS; each thread then walks
-// down the 16 rows of one column, keeping per-row horizontal sums of |w|, w and w^2
-// for the last P rows in registers.  Every score that is stored, counted or recorded is
-// computed in double: the variance as (P^2 * sum w^2 - (sum w)^2) / P^4, or -- where that
-// form cancels -- from the tile again as Eq. 10 prints it; either way equal windows get
-// equal scores wherever they lie and a constant window gets a variance of exactly 0.  The
-// main pass (capture) runs the sweep in float32 instead and only decides there which centres
-// cannot reach the layer's bound (PreF32 above); the others it evaluates in double as said.
-// The capture variants are held to five waves per SIMD for p <= 3 and four for p = 5, 7
-// (what their registers allow without spilling; measured faster than one wave less), those with momentum to
-// three: 485 us on VGG-19, with four, which 128 registers would allow p = 3, 497, with two 527.
-//
-// A workgroup takes tiles b, b + W, ... of the launch (W workgroups, laid out so that each XCD
-// gets one contiguous part of every stretch of W tiles: neighbouring tiles share halo rows in
-// one L2), or -- FEED -- whatever the launch's work feed hands it next.  Its LDS histogram is
-// flushed to the layer's global histogram only when the layer changes or its tiles end, so
-// a launch issues few same-address global atomics.
-// MOM: with Eq. 12's momentum term (a.mom, a.mom_out, a.m).  FEED: the workgroups take their
-// tiles from the launch's work feed instead of a fixed strided share.
 // Where a workgroup adds the candidates it recorded of a layer: word 1 of one of the first kRecordedParts list shards' lines
 // (several, as all workgroups of a launch end at about the same time).
 constexpr uint32_t kRecordedParts = 4;
@@ -697,6 +677,26 @@ __device__ __forceinline__ bool layer_falls_back(const LayerDev *__restrict__ la
     return mode == kModeFullMap || hint_key == 0u || overflow != 0u || recorded < k || top >= k;
 }
 
+// Work unit: one 16 x 256 tile of one layer.  The tile of v = r + g plus a halo of
+// h = (P-1)/2 rows and 4 columns (16-byte aligned) goes to LDS; each thread then walks
+// down the 16 rows of one column, keeping per-row horizontal sums of |w|, w and w^2
+// for the last P rows in registers.  Every score that is stored, counted or recorded is
+// computed in double: the variance as (P^2 * sum w^2 - (sum w)^2) / P^4, or -- where that
+// form cancels -- from the tile again as Eq. 10 prints it; either way equal windows get
+// equal scores wherever they lie and a constant window gets a variance of exactly 0.  The
+// main pass (capture) runs the sweep in float32 instead and only decides there which centres
+// cannot reach the layer's bound (PreF32 above); the others it evaluates in double as said.
+// The capture variants are held to five waves per SIMD for p <= 3 and four for p = 5, 7
+// (what their registers allow without spilling; measured faster than one wave less), those with momentum to
+// three: 485 us on VGG-19, with four, which 128 registers would allow p = 3, 497, with two 527.
+//
+// A workgroup takes tiles b, b + W, ... of the launch (W workgroups, laid out so that each XCD
+// gets one contiguous part of every stretch of W tiles: neighbouring tiles share halo rows in
+// one L2), or -- FEED -- whatever the launch's work feed hands it next.  Its LDS histogram is
+// flushed to the layer's global histogram only when the layer changes or its tiles end, so
+// a launch issues few same-address global atomics.
+// MOM: with Eq. 12's momentum term (a.mom, a.mom_out, a.m).  FEED: the workgroups take their
+// tiles from the launch's work feed instead of a fixed strided share.
 template <int P, int PASS>
 struct NsiShared {
     static constexpr bool kCapture = PASS == kPassCapture;
