@@ -146,8 +146,10 @@ size_t  rsdgc_workspace_bytes(const rsdgc_plan_t *plan);
  *             pointers between iterations; v is stored while the scores are
  *             computed and only the kept elements are touched afterwards:
  *             12 bytes of HBM traffic per element), or residual_out == residual
- *             for an update in place (one more streaming pass over g and r:
- *             20 bytes per element).  Any other overlap is RSDGC_EINVAL.
+ *             for an update in place (large plans with p <= 5: v takes the
+ *             residual's place as it is formed, 13 bytes per element; others:
+ *             one more streaming pass over g and r, 20 bytes per element).
+ *             Any other overlap is RSDGC_EINVAL.
  *   out_idx   [device] uint32, rsdgc_out_capacity entries.  Layer l's pairs
  *   out_val   [device] float32, same length.     start at rsdgc_out_offset(l);
  *             idx is the flat row-major index x*C + y inside the layer,

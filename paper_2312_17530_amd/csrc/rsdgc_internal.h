@@ -33,6 +33,7 @@ constexpr uint32_t kSelectTiles = 1024;  // a plan goes through k_select while i
 // ... and selects at most so many centres.  One layer, k_select / the launches it replaces: 512 x 512 with 13108 centres 30.7 / 32.3 us,
 // 1024 x 1024 with 15147 40.2 / 41.4, 2048 x 1024 with 20972 41.2 / 38.7, 2048 x 2048 with 9321 44.7 / 47.3 and with 23302 58.9 / 53.7.
 constexpr uint32_t kSelectMaxK = 16384;
+constexpr int64_t kInPlaceElems = 1 << 25;  // elements (with p = 5 every other one) from which v replaces the residual as it is formed
 constexpr int kBigMapLayer = 1 << 20; // elements from which a full-map layer's bucket list goes through k_filter
 // Candidate bound predicted from the thresholds of the two calls before, on a log2 scale: used
 // while the threshold moved by at most kTrendMaxLog2 between those calls.
@@ -293,6 +294,7 @@ struct rsdgc_plan_s {
     uint32_t n_slot_groups = 0;
     bool any_large = false;
     bool one_select = false;            // every layer that selects something is on the candidate path and small enough for k_select
+    bool v_in_place = false;            // one arena: the main pass puts v in the residual's place (plans that do not go through k_select)
     std::vector<uint16_t> big_map_layers;   // layers of a million elements or more that are ranked on the full map
     int64_t total_elems = 0;
     int64_t out_capacity = 0;

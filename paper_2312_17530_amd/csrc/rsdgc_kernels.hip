@@ -15,7 +15,8 @@
 //   capture    the main pass: v = r + g and NSI for every element of the candidate-path layers;
 //              centres whose score reaches the bound are recorded per tile (no score map) and
 //              counted in fine bins above the bound; with a second residual arena v is stored
-//              there as it is formed
+//              there as it is formed; with one, in large plans, in the residual's place, and the
+//              windows across the tiles' edges follow in a launch of their own (k_seams)
 //   find0      first ranking digit of every layer; a layer whose bound caught fewer than k_l
 //              centres, or overfilled a tile, falls back to the full map (a flag tells the
 //              fallback kernels there is work)
@@ -31,13 +32,13 @@
 //   count      kept elements per chunk and per group of chunks (no scan kernel: each consumer
 //              adds up its own prefix from those); small plans count as they mark
 //   emit       ordered (index, value) pairs and the residual update (Eq. 12): either only the
-//              kept elements are touched (second arena; by workgroups or, on large plans, by
-//              waves), or g and r are streamed again (update in place)
+//              kept elements are touched (v is stored already; by workgroups or, on large plans, by
+//              waves), or g and r are streamed again (one arena, smaller plans)
 //
 // Sections of this file, in order (each starts with a "// ---- name --" line):
 //   begin            k_begin
 //   work feed        WorkFeed: tiles handed to persistent workgroups through per-XCD counters
-//   nsi              k_nsi<P, PASS, MOM, FEED>: the four NSI passes, with or without Eq. 12's momentum
+//   nsi              k_nsi<P, PASS, MOM, FEED>: the NSI passes, with or without Eq. 12's momentum; k_seams
 //   ranking digits   block_find_digit, publish_threshold
 //   hint .. finish   k_hint, k_find0, k_find0_fallback(_all), k_gather, k_filter, k_finish: bounds and
 //                    the radix select
@@ -320,6 +321,13 @@ __device__ __forceinline__ bool prepare_next_call(const NextCall &nc) {
     return false;
 }
 
+// What one wave has written to LDS and reads back (its DS operations are carried out in order): keeps the compiler from
+// moving the accesses of different lanes past each other.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // 16-byte store of data this call does not read again (the new residual / momentum arena):
 // marked non-temporal so that it does not displace the halo rows and candidate slots that
 // later tiles and kernels find in cache (measured: -12 us on the VGG-19 main pass).
@@ -420,6 +428,35 @@ struct ColumnSums {
         if (P == 5) return (p[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
         return (c[(i - 3) & 7] + p[(i - 1) & 7]) + s[i & 7];
     }
+};
+
+// With v in place of the residual the main pass may not read what another workgroup's tile holds: its neighbours may have their
+// v there already or not.  A workgroup takes kRun tiles at a time, one below the other where the layer's tiles divide so, and carries the
+// last rows of one into the windows of the next; the windows that still reach into another tile are left to k_seams.
+constexpr uint32_t kRun = 2;
+// A layer's tile number `listed` in that order, number t of the launch.
+struct RunTile {
+    int trow, tcol;
+    bool above, below;                     // whether the tile on that side is taken with it
+    __device__ __forceinline__ RunTile(const LayerDev &L, uint32_t listed, uint32_t t) {
+        const uint32_t band = listed / (kRun * L.tiles_x), rest = listed - band * kRun * L.tiles_x;
+        const uint32_t rows = min(kRun, L.n_tiles / L.tiles_x - band * kRun), col = rest / rows, i = rest - col * rows;
+        trow = static_cast<int>(band * kRun + i);
+        tcol = static_cast<int>(col);
+        above = i != 0u && t % kRun != 0u;
+        below = i + 1u < rows && (t + 1u) % kRun != 0u;
+    }
+};
+// The positions of such a tile that are left: along its edges, where there is another tile or -- the main pass ends H rows
+// before it -- the matrix's lower edge.
+template <int H>
+struct TileSeams {
+    bool top, bottom, left, right;
+    __device__ __forceinline__ TileSeams(const RunTile &rt, int R, int C)
+        : top(rt.trow > 0 && !rt.above), bottom(rt.trow * kTileRows + kTileRows - H < R && !rt.below), left(rt.tcol > 0),
+          right((rt.tcol + 1) * kTileCols < C) {}
+    __device__ __forceinline__ bool on_row(int row) const { return (row < H && top) || (row >= kTileRows - H && bottom); }
+    __device__ __forceinline__ bool on_column(int col) const { return (col < H && left) || (col >= kTileCols - H && right); }
 };
 
 // Centres one tile can queue for full evaluation: twice the largest slot, and the positions beyond the matrix's edge whose windows
@@ -576,7 +613,9 @@ enum NsiPass : int {
     kPassCapture = 2,   // candidates (score >= bound) recorded per tile, layers in candidate mode
     kPassSample = 3,    // first pass over the plan's tile list: 12-bit histogram of the sampled tiles
                         // of the large layers; score map + histogram of every tile of the others
+    kPassCaptureInPlace = 4,    // kPassCapture where v replaces the residual: windows inside a tile only (the others: k_seams)
 };
+constexpr bool pass_captures(int pass) { return pass == kPassCapture || pass == kPassCaptureInPlace; }
 
 struct NsiArgs {
     const LayerDev *layers;
@@ -587,7 +626,8 @@ struct NsiArgs {
     const float *grad;
     const float *resid;           // nullable: all-zero residual
     float *nsi_out;               // score map (kPassMapOnly, kPassFullMap; kPassSample: of the layers that are always ranked on it)
-    float *v_out;                 // nullable: second residual arena that receives v = r + g
+    float *v_out;                 // nullable: second residual arena that receives v = r + g (kPassCaptureInPlace: the residual's own)
+    int v_in_place;               // the layers' v has replaced the residual where the main pass took them (kPassFullMap: it is read there)
     const float *mom;             // nullable: momentum arena u (Eq. 12, first line); then v = r + (m*u + g)
     float *mom_out;               // with mom: receives m*u + g wherever v_out receives v
     float m;                      // momentum factor
@@ -677,6 +717,17 @@ __device__ __forceinline__ bool layer_falls_back(const LayerDev *__restrict__ la
     return mode == kModeFullMap || hint_key == 0u || overflow != 0u || recorded < k || top >= k;
 }
 
+// Beside them (below: k_seams) the main pass keeps the first and the last few columns of every tile row in the layer's part of the
+// score map, which is free while the layer is on the candidate path: out of the matrix they would be a cache line each.
+template <int P> constexpr int kSeamCols = P <= 5 ? 4 : 8;           // at least P - 1
+template <int P>
+__device__ __forceinline__ float *seam_columns(float *map, const LayerDev &L, int x, int tcol, int side) {
+    return map + L.elem_off + (static_cast<size_t>(2 * tcol + side) * L.R + x) * kSeamCols<P>;
+}
+
+// Whether the main pass takes a layer with this candidate bound (0: none).  It stays as it is from the main pass to the emit.
+__device__ __forceinline__ bool bound_in_range(uint32_t hint_key) { return hint_key >= kPreF32MinKey && hint_key <= kPreF32MaxKey; }
+
 // Work unit: one 16 x 256 tile of one layer.  The tile of v = r + g plus a halo of
 // h = (P-1)/2 rows and 4 columns (16-byte aligned) goes to LDS; each thread then walks
 // down the 16 rows of one column, keeping per-row horizontal sums of |w|, w and w^2
@@ -699,13 +750,14 @@ __device__ __forceinline__ bool layer_falls_back(const LayerDev *__restrict__ la
 // tiles from the launch's work feed instead of a fixed strided share.
 template <int P, int PASS>
 struct NsiShared {
-    static constexpr bool kCapture = PASS == kPassCapture;
+    static constexpr bool kCapture = pass_captures(PASS);
     static constexpr int kBins = PASS == kPassFullMap || PASS == kPassSample ? kHistBins : (kCapture ? kFineBins : 1);
     __attribute__((aligned(16))) float tile[(kTileRows + P - 1) * (kTileCols + 8)];
     unsigned long long cand[kCapture ? kSlotCapMax : 1];
     uint32_t lhist[kBins];
     uint16_t queue[kCapture ? kQueueCap<P> : 1];
     uint32_t ncand, nqueue;
+    uint32_t nabove;                      // kPassCaptureInPlace: candidates in the tile above
     uint32_t feed_slot[2];
 };
 
@@ -721,7 +773,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     // sums costs 18 registers and a wave per SIMD).
     constexpr int RPT = kTileRows * kTileCols / 256;           // output rows per thread
     constexpr bool MAP = PASS == kPassMapOnly || PASS == kPassFullMap;
-    constexpr bool CAPTURE = PASS == kPassCapture;
+    constexpr bool CAPTURE = pass_captures(PASS), IN_PLACE = PASS == kPassCaptureInPlace;
     constexpr bool FULLHIST = PASS == kPassFullMap || PASS == kPassSample;
     constexpr bool STORE_V = PASS != kPassMapOnly;
     constexpr int NBINS = NsiShared<P, PASS>::kBins;
@@ -736,7 +788,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     // the launch's work items (tiles, or sampled tiles): at any moment the resident workgroups
     // work on one compact stretch of tiles, so neighbouring tiles' halo rows are still in
     // cache; inside a stretch each XCD takes one contiguous part
-    const uint32_t n_items = a.n_tiles;
+    const uint32_t n_items = IN_PLACE ? (a.n_tiles + kRun - 1u) / kRun : a.n_tiles;
     const uint32_t stride = n_wgs;
     if (PASS == kPassFullMap) {            // no layer fell back: nothing to do
         if (WITH_FIND0) {
@@ -760,22 +812,26 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     if (NBINS > 1)
         for (int b = tid; b < NBINS; b += 256) lhist[b] = 0;
     if (CAPTURE && tid == 0) { ncand = 0; nqueue = 0; }
+    if (IN_PLACE && tid == 0) sh.nabove = 0;
+    if (IN_PLACE)                          // (no halo is loaded: the columns beside the tile's own stay as they are)
+        for (int j = tid; j < ROWS * PITCH; j += 256) tile[j] = 0.f;
     __syncthreads();
 
     // Where the next tile is known beforehand its list entry is requested a tile ahead: a first tile costs one load where
     // the directory takes a bisection (161 layers: 34.2 -> 32.2 us; 21 layers: no difference).  With the work
     // feed the directory's neighbouring entry, usually cached, is the shorter way.
-    constexpr bool LISTED = !FEED && PASS != kPassMapOnly;
+    constexpr bool LISTED = !FEED && PASS != kPassMapOnly && !IN_PLACE;
     uint32_t e = 0;                       // directory entry of the current layer
     SampleEntry ahead = {0u, 0u};
     if (LISTED) ahead = a.samples[first];
-    else e = dir_lookup(a.dir, a.n_dir, first);
+    else e = dir_lookup(a.dir, a.n_dir, IN_PLACE ? first * kRun : first);
     uint32_t cur_l = 0xffffffffu;         // layer whose counts sit in lhist
     uint32_t hint_key = 0;
     uint32_t *hist_base = CAPTURE ? a.hist_s : a.hist;         // first pass: a.hist_s for the sampled tiles of a large layer
     uint32_t recorded = 0;                // main pass: the workgroup's candidates of layer cur_l
     bool active = true;
     bool whole = true;                    // every tile of the layer is visited: v and the scores go out
+    bool v_stored = false;                // kPassFullMap: the layer's residual holds v already
     LayerDev L;
 
     const double n = static_cast<double>(P * P);
@@ -789,7 +845,17 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
     const int c0 = tid % kTileCols, ty = tid / kTileCols;
     const int row_base = ty * RPT;
 
-    for (uint32_t t = first; FEED ? t != kNoItem : t < n_items; t = FEED ? feed.next(feed_slot) : t + stride) {
+    // (IN_PLACE: an item is a run of tiles, of which t is one)
+    uint32_t run = first;
+    float carry[H > 0 ? 2 * H : 1] = {};  // ... the last rows of the tile above: the thread's column
+    uint32_t n_above = 0;                 // ... and its candidates
+    auto after = [&](uint32_t t) {
+        if (IN_PLACE && (t + 1u) % kRun != 0u && t + 1u < a.n_tiles) return t + 1u;
+        if (!IN_PLACE) return FEED ? feed.next(feed_slot) : t + stride;
+        run = FEED ? feed.next(feed_slot) : run + stride;
+        return FEED && run == kNoItem ? kNoItem : run * kRun;
+    };
+    for (uint32_t t = IN_PLACE ? first * kRun : first; FEED ? t != kNoItem : t < a.n_tiles; t = after(t)) {
         uint32_t l, local;
         if (LISTED) {
             l = ahead.layer;
@@ -816,17 +882,18 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             active = true;
             hint_key = 0;
             whole = PASS != kPassSample || L.large == 0u;
-            if (PASS == kPassFullMap || PASS == kPassCapture || (PASS == kPassSample && !whole)) {
+            if (PASS == kPassFullMap || CAPTURE || (PASS == kPassSample && !whole)) {
                 const SelState st = a.state[l];
                 if (PASS == kPassFullMap) active = WITH_FIND0 ? layer_falls_back(a.layers, a.state, a.hist_s, a.list_cnt, l) : st.mode == kModeFullMap && L.large != 0u;
                 else if (PASS == kPassSample) active = st.mode == kModeCandidates && st.hint_key == 0u;   // no predicted bound
                 else active = st.mode == kModeCandidates;
+                if (PASS == kPassFullMap) v_stored = a.v_in_place && bound_in_range(st.hint_key);
                 if (CAPTURE) {
                     hint_key = st.hint_key;
                     bound_lof = uniform_f32(PreF32<P>::bound(__uint_as_float(hint_key)));
                     // (k_begin and k_hint give no bound outside the range of the float32 test; should one
                     // arrive all the same, the layer is not captured and k_find0 sends it to the full map)
-                    if (active && (hint_key < kPreF32MinKey || hint_key > kPreF32MaxKey)) {
+                    if (active && !bound_in_range(hint_key)) {
                         active = false;
                         if (tid == 0 && hint_key != 0u) a.state_rw[l].overflow = 1u;
                     }
@@ -835,16 +902,32 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             if (PASS == kPassSample) hist_base = whole ? a.hist : a.hist_s;
         }
         if (!active) {                    // skip the rest of this layer
-            if (!FEED && !LISTED) {
+            if (!FEED && !LISTED && !IN_PLACE) {
                 const uint32_t nb = a.dir[e + 1].begin;          // first tile of the next layer
                 t += (nb - t + stride - 1) / stride * stride - stride;   // loop increment adds the last stride
             }
             continue;
         }
 
-        const int trow = static_cast<int>(local / L.tiles_x);
-        const int tcol = static_cast<int>(local - static_cast<uint32_t>(trow) * L.tiles_x);
+        int trow = static_cast<int>(local / L.tiles_x);
+        int tcol = static_cast<int>(local - static_cast<uint32_t>(trow) * L.tiles_x);
+        bool above = false;               // IN_PLACE: the tile before was the one above
+        float bound_above = bound_lof, bound_top = bound_lof, bound_rest = bound_lof;      // infinite where the windows are k_seams'
         const int R = static_cast<int>(L.R), C = static_cast<int>(L.C);
+        if constexpr (IN_PLACE) {
+            const RunTile rt(L, local, t);
+            const TileSeams<H> seam(rt, R, C);
+            trow = rt.trow;
+            tcol = rt.tcol;
+            local = static_cast<uint32_t>(trow) * L.tiles_x + static_cast<uint32_t>(tcol);
+            above = rt.above;
+            const float never = __uint_as_float(0x7f800000u);
+            if (seam.on_column(c0)) bound_rest = never;
+            bound_above = above ? bound_rest : never;
+            bound_top = seam.top ? never : bound_rest;
+#pragma unroll
+            for (int i = 0; i < 2 * H; ++i) tile[i * PITCH + PADL + c0] = above ? carry[i] : 0.f;
+        }
         const int x0 = trow * kTileRows, y0 = tcol * kTileCols;
         const float *__restrict__ g = a.grad + L.elem_off;
         const float *__restrict__ r = a.resid ? a.resid + L.elem_off : nullptr;
@@ -857,32 +940,39 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             // piece, which the compiler computes once and then keeps in a dozen registers).  The
             // column halo, H floats on either side of every row, is loaded as single floats by the
             // first 2 H ROWS threads.
-            constexpr int ITER = (ROWS + 3) / 4;
+            constexpr int ROW0 = IN_PLACE ? H : 0;             // rows loaded, from the halo's first on; rows further down that they lie in LDS
+            constexpr int ROW1 = IN_PLACE ? H + kTileRows : ROWS, DOWN = IN_PLACE ? H : 0;
+            constexpr int ITER = (ROW1 - ROW0 + 3) / 4;
             const int wave = tid >> 6, lane = tid & 63;
             const int ym = y0 + 4 * lane;
             const int hrow = H > 0 ? tid / (2 * H > 0 ? 2 * H : 1) : 0;
             const int hc = H > 0 ? tid - hrow * 2 * H : 0;              // 0 .. H-1 left of the tile, H .. 2H-1 right of it
             const int hy = hc < H ? y0 - 1 - hc : y0 + kTileCols + (hc - H);
             const int hx = x0 - H + hrow;
-            const bool halo_thread = H > 0 && tid < 2 * H * ROWS;
+            const bool halo_thread = !IN_PLACE && H > 0 && tid < 2 * H * ROWS;
             const bool halo_in = halo_thread && hx >= 0 && hx < R && hy >= 0 && hy < C;
             const size_t hoff = halo_in ? static_cast<size_t>(hx) * C + hy : 0;
             float4 gv[ITER], rv[ITER];
             float gh = 0.f, rh = 0.f;
 #pragma unroll
             for (int it = 0; it < ITER; ++it) {
-                const int rr = 4 * it + wave;
+                const int rr = ROW0 + 4 * it + wave;
                 const int x = x0 - H + rr;
                 gv[it] = make_float4(0.f, 0.f, 0.f, 0.f);
                 rv[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (rr < ROWS && x >= 0 && x < R && ym < C) {
+                if (rr < ROW1 && x >= 0 && x < R && ym < C) {
                     const size_t off = static_cast<size_t>(x) * C + ym;
-                    gv[it] = *reinterpret_cast<const float4 *>(g + off);
+                    if (IN_PLACE) {       // (no other workgroup reads them: with plain loads the pass takes 339 us on VGG-19, with these 288)
+                        gv[it] = load_streaming(g + off);
+                        rv[it] = load_streaming(r + off);
+                        continue;
+                    }
+                    if (!(PASS == kPassFullMap && v_stored)) gv[it] = *reinterpret_cast<const float4 *>(g + off);
                     if (r) rv[it] = *reinterpret_cast<const float4 *>(r + off);
                 }
             }
             if (halo_in) {
-                gh = g[hoff];
+                if (!(PASS == kPassFullMap && v_stored)) gh = g[hoff];
                 if (r) rh = r[hoff];
             }
             if (MOM) {                    // Eq. 12, first line: the gradient term becomes u = m*u + g
@@ -917,18 +1007,20 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             if (FEED) feed.stash(feed_slot);       // the loads are out, no store of this tile yet
 #pragma unroll
             for (int it = 0; it < ITER; ++it) {
-                const int rr = 4 * it + wave;
-                if (rr < ROWS) {
+                const int rr = ROW0 + 4 * it + wave;
+                if (rr < ROW1) {
                     float4 v;
                     v.x = rv[it].x + gv[it].x;
                     v.y = rv[it].y + gv[it].y;
                     v.z = rv[it].z + gv[it].z;
                     v.w = rv[it].w + gv[it].w;
-                    *reinterpret_cast<float4 *>(&tile[rr * PITCH + PADL + 4 * lane]) = v;
+                    *reinterpret_cast<float4 *>(&tile[(rr + DOWN) * PITCH + PADL + 4 * lane]) = v;
                     if (STORE_V && a.v_out && whole) {     // the tile's own elements (not the halo) go out once
                         const int x = x0 - H + rr;
                         if (rr >= H && rr < H + kTileRows && x < R && ym < C)
                             store_streaming(a.v_out + L.elem_off + static_cast<size_t>(x) * C + ym, v);
+                        if (IN_PLACE && L.tiles_x > 1u && x < R && (lane < kSeamCols<P> / 4 || lane >= 64 - kSeamCols<P> / 4))
+                            *reinterpret_cast<float4 *>(seam_columns<P>(a.nsi_out, L, x, tcol, lane < 32 ? 0 : 1) + 4 * lane % kSeamCols<P>) = v;
                     }
                 }
             }
@@ -940,7 +1032,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             constexpr int N = (PITCH + 63) / 64;
             const int wave = tid >> 6;
 #pragma unroll 1
-            for (int rr = wave; rr < ROWS; rr += 4) {
+            for (int rr = (IN_PLACE ? H : 0) + wave; rr < (IN_PLACE ? H + kTileRows : ROWS); rr += 4) {
                 // (the columns' masks are worked out row by row: held over the rows they cost the pass its scalar registers, and
                 // 4 of 234 us with p = 5 on 103 M elements whose rows never come here.  With the work feed 12 or 13
                 // scalar registers are still spilled to vector ones; the loop that was here before, with none, was no faster
@@ -955,8 +1047,8 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                     const int j = lane + 64 * q, y = y0 - PADL + j;
                     gq[q] = rq[q] = 0.f;
                     if (MOM) uq[q] = 0.f;
-                    if (x >= 0 && x < R && j < PITCH && y >= 0 && y < C) {
-                        gq[q] = (g + row)[y];
+                    if (x >= 0 && x < R && j < PITCH && y >= 0 && y < C && (!IN_PLACE || (j >= PADL && j < PADL + kTileCols))) {
+                        if (!(PASS == kPassFullMap && v_stored)) gq[q] = (g + row)[y];
                         if (r) rq[q] = (r + row)[y];
                         if (MOM) uq[q] = (a.mom + L.elem_off + row)[y];
                     }
@@ -965,7 +1057,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                 for (int q = 0; q < N; ++q) {
                     const int j = lane + 64 * q, y = y0 - PADL + j;
                     float v = 0.f;
-                    if (x >= 0 && x < R && j < PITCH && y >= 0 && y < C) {
+                    if (x >= 0 && x < R && j < PITCH && y >= 0 && y < C && (!IN_PLACE || (j >= PADL && j < PADL + kTileCols))) {
                         const bool own = rr >= H && rr < H + kTileRows && j >= PADL && j < PADL + kTileCols;
                         float gu = gq[q];
                         if (MOM) {
@@ -974,8 +1066,13 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
                         }
                         v = rq[q] + gu;
                         if (STORE_V && a.v_out && whole && own) (a.v_out + L.elem_off + row)[y] = v;
+                        if (IN_PLACE && L.tiles_x > 1u) {
+                            const int col = j - PADL;
+                            if (col < kSeamCols<P>) seam_columns<P>(a.nsi_out, L, x, tcol, 0)[col] = v;
+                            if (col >= kTileCols - kSeamCols<P>) seam_columns<P>(a.nsi_out, L, x, tcol, 1)[col - (kTileCols - kSeamCols<P>)] = v;
+                        }
                     }
-                    if (j < PITCH) tile[rr * PITCH + j] = v;
+                    if (j < PITCH && (!IN_PLACE || (j >= PADL && j < PADL + kTileCols))) tile[(rr + (IN_PLACE ? H : 0)) * PITCH + j] = v;
                 }
             }
         }
@@ -999,14 +1096,17 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             for (int i = 0; i < RPT + 2 * H; ++i) {
                 {
                     float sa, ss, sq;
-                    row_sums<P>(&tile[(row_base + i) * PITCH + PADL + c0 - H], sa, ss, sq);
+                    const float *row = &tile[(row_base + i) * PITCH + PADL + c0 - H];
+                    row_sums<P>(row, sa, ss, sq);
+                    if (IN_PLACE && i >= kTileRows) carry[i - kTileRows] = row[H];
                     ca_.push(i, sa);
                     cs_.push(i, ss);
                     cq_.push(i, sq);
                 }
                 if (i >= 2 * H) {
                     const int o = i - 2 * H;
-                    if (PreF32<P>::stays(ca_.window(i), cs_.window(i), cq_.window(i), caf, cbf, pre_a, bound_lof)) {   // (outside the matrix too: the queue's turn to tell)
+                    const float lo = !IN_PLACE ? bound_lof : o < H ? bound_above : o < 2 * H ? bound_top : bound_rest;     // (in place: row o - H of the tile)
+                    if (PreF32<P>::stays(ca_.window(i), cs_.window(i), cq_.window(i), caf, cbf, pre_a, lo)) {   // (outside the matrix too: the queue's turn to tell)
                         const uint32_t pos = atomicAdd(&nqueue, 1u);
                         if (pos < static_cast<uint32_t>(kQueueCap<P>))
                             queue[pos] = static_cast<uint16_t>((row_base + o) * kTileCols + c0q);
@@ -1069,13 +1169,22 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             if (nq > static_cast<uint32_t>(kQueueCap<P>) && tid == 0) a.state_rw[l].overflow = 1u;   // (more than any slot holds)
             for (uint32_t qi = tid; qi < min(nq, static_cast<uint32_t>(kQueueCap<P>)); qi += 256) {
                 const int pos = queue[qi];
-                const int orow = pos / kTileCols, ocol = pos - orow * kTileCols;
+                const int wrow = pos / kTileCols, ocol = pos - wrow * kTileCols, orow = IN_PLACE ? wrow - H : wrow;
                 if (x0 + orow >= R || y0 + ocol >= C) continue;
-                const uint32_t key = window_score<P>(&tile[orow * PITCH + PADL + ocol - H], PITCH, ca, cb);
+                if (IN_PLACE) {            // (a window whose sums are not finite is queued whatever the bound)
+                    if ((orow < 0 && !above) || (orow >= 0 && orow < H && trow > 0 && !above) || (ocol < H && tcol > 0) || (ocol >= kTileCols - H && y0 + kTileCols < C)) continue;
+                }
+                const uint32_t key = window_score<P>(&tile[wrow * PITCH + PADL + ocol - H], PITCH, ca, cb);
                 if (key >= hint_key) {
                     const uint32_t x = static_cast<uint32_t>(x0 + orow), y = static_cast<uint32_t>(y0 + ocol);
-                    const uint32_t cp = atomicAdd(&ncand, 1u);
-                    if (cp < static_cast<uint32_t>(kSlotCapMax)) cand[cp] = composite_key(key, x * L.C + y);
+                    if (IN_PLACE && orow < 0) {
+                        const uint32_t cp = n_above + atomicAdd(&sh.nabove, 1u);
+                        if (cp < L.slot_cap)
+                            a.slot_ent[L.slot_off + static_cast<size_t>(local - L.tiles_x) * L.slot_cap + cp] = composite_key(key, x * L.C + y);
+                    } else {
+                        const uint32_t cp = atomicAdd(&ncand, 1u);
+                        if (cp < static_cast<uint32_t>(kSlotCapMax)) cand[cp] = composite_key(key, x * L.C + y);
+                    }
                     // fine bins upwards from the bound; the last one is open-ended
                     const uint32_t rel = (key - hint_key) >> kFineShift;
                     atomicAdd(&lhist[min(rel, static_cast<uint32_t>(kFineBins - 1))], 1u);
@@ -1087,6 +1196,15 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
         if (CAPTURE) {
             const uint32_t nc = ncand, cap = L.slot_cap;
             recorded += nc;
+            if (IN_PLACE) {
+                const uint32_t more = sh.nabove;
+                recorded += more;
+                if (tid == 0 && more != 0u) {
+                    a.slot_cnt[L.tile_begin_all + local - L.tiles_x] = min(n_above + more, cap);
+                    if (n_above + more > cap) a.state_rw[l].overflow = 1u;
+                }
+                n_above = nc;
+            }
             unsigned long long *__restrict__ dst = a.slot_ent + L.slot_off + static_cast<size_t>(local) * cap;
             for (uint32_t i = tid; i < min(nc, cap); i += 256) dst[i] = cand[i];
             if (tid == 0) {
@@ -1095,6 +1213,7 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
             }
             __syncthreads();
             if (tid == 0) { ncand = 0; nqueue = 0; }
+            if (IN_PLACE && tid == 0) sh.nabove = 0;
             // the next tile's first barrier orders this reset before any new append
         }
     }
@@ -1110,10 +1229,267 @@ __device__ __forceinline__ void nsi_pass(const NsiArgs &a, NsiShared<P, PASS> &s
 }
 
 template <int P, int PASS, bool MOM, bool FEED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PASS == kPassCapture && !MOM ? (P <= 3 ? 5 : 4) : 1, PASS == kPassCapture && MOM ? 3 : 8)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pass_captures(PASS) && !MOM ? (P <= 3 ? 5 : 4) : 1, PASS == kPassCapture && MOM ? 3 : 8)))
 void k_nsi(const NsiArgs a) {
     __shared__ NsiShared<P, PASS> sh;
     nsi_pass<P, PASS, MOM, FEED>(a, sh, blockIdx.x, gridDim.x);
+}
+
+// The windows across the tiles' edges where v replaces the residual (one arena).  VGG-19: main pass 257 us and an emit that forms v once
+// more 271, now 288 (of which the columns it keeps for this pass about 8), this pass 48 and an emit of the kept elements 41; the call 572 -> 460 us.
+// What bounds this pass is its chain of loads, LDS and the evaluation in double on four waves per SIMD; its loads alone take 28 us.  The main pass stores v in the arena it reads,
+// so no workgroup may read what another's tile holds; it scores the windows inside its run of tiles, and this pass, after it, those
+// that reach further, from v.  A wave takes the positions along a run's edges, so that a tile's slot stays one
+// wave's: the 3 H rows around the upper and the lower edge, lane j the columns from 4 j on, and the columns around the sides from where
+// the main pass has put them.  The next run's are requested before this one's are looked at; the four waves of a workgroup share
+// nothing but the candidates' counts: bins for one layer, that of the launch's middle tile, a list for the others (a
+// few hundred candidates a workgroup in all).  They go to memory at the end: an atomic that is on its way holds up the next
+// run's loads (59.6 us where each of the others' candidates was added at once, of which a quarter of the elements had
+// them).
+template <int P>
+struct SeamWave {
+    static constexpr int kH = (P - 1) / 2, kRows = 6 * kH, kRunRows = kRun * kTileRows;      // rows around the edges, the upper one's first
+    static constexpr int kPitch = kTileCols + 8, kSidePitch = (3 * kH) | 1;
+    __attribute__((aligned(16))) float rows[kRows * kPitch];
+    float side[2][(kRunRows + 2 * kH) * kSidePitch];                     // H columns of the tile on that side, 2 H own (to the right: the other way round)
+    uint16_t queue[2 * kH * (kTileCols + kRunRows)];                     // every position along the edges
+    uint32_t ncand[kRun], nqueue;
+};
+template <int P>
+struct SeamShared {
+    static constexpr uint32_t kOthers = 704;
+    SeamWave<P> wave[4];
+    uint32_t lhist[kFineBins];             // counts of the launch's main layer
+    uint32_t others[kOthers], n_others;    // the other layers' candidates: layer and bin
+};
+template <int P>
+__global__ __launch_bounds__(256) void k_seams(const NsiArgs a) {
+    constexpr int H = (P - 1) / 2, PADL = 4, PITCH = SeamWave<P>::kPitch, SP = SeamWave<P>::kSidePitch;
+    constexpr int EDGE = 3 * H, NR = 2 * EDGE, W = kSeamCols<P>, NS = (NR * 2 * H + 63) / 64;
+    static_assert(NR < kTileRows + 2 * H && kRun == 2u, "the rows around the two edges are different rows; two tiles' rows, a lane per row's four pieces");
+    __shared__ SeamShared<P> shared;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    SeamWave<P> &sh = shared.wave[wave];
+    const uint32_t n_runs = (a.n_tiles + kRun - 1u) / kRun, step = gridDim.x * 4u;
+    const uint32_t hist_l = a.samples[a.n_tiles / 2u].layer;
+    for (int b = threadIdx.x; b < kFineBins; b += 256) shared.lhist[b] = 0u;
+    if (threadIdx.x == 0) shared.n_others = 0u;
+    for (uint32_t i = lane; i < 2u * (kRun * kTileRows + 2 * H) * SP; i += 64) sh.side[0][i] = 0.f;    // (the rows above and below stay so)
+    if (lane == 0) sh.ncand[0] = sh.ncand[1] = sh.nqueue = 0u;
+    __syncthreads();
+
+    // The next tiles, as requested: a run's two, or one of them.
+    struct Unit {
+        uint32_t t, tiles, slot;          // first tile; how many; the first one's slot (the second's: L.tiles_x further)
+        int x0, y0;
+        bool top, bottom, left, right;
+    } u = {};
+    LayerDev L;
+    uint32_t l = 0xffffffffu, hint_key = 0, n0 = 0, n1 = 0;  // the layer that L is; candidates in the slots
+    bool active = false;
+    float4 f[NR], sd[2][W / 4];
+    float hs[NS];
+    auto row_of = [](int q, int height) { return q < EDGE ? q - H : height - NR + H + q; };  // rows around the edges in order
+    auto request = [&](uint32_t t) {
+        const SampleEntry at = a.samples[t];
+        if (at.layer != l) {
+            l = at.layer;
+            L = a.layers[l];
+            hint_key = a.state[l].hint_key;
+            active = a.state[l].mode == kModeCandidates && bound_in_range(hint_key);
+        }
+        const RunTile rt(L, at.local_tile, t);
+        const int R = static_cast<int>(L.R), C = static_cast<int>(L.C), tcol = rt.tcol;
+        u.t = t;
+        u.tiles = rt.below ? 2u : 1u;
+        u.slot = static_cast<uint32_t>(rt.trow) * L.tiles_x + static_cast<uint32_t>(tcol);
+        u.x0 = rt.trow * kTileRows;
+        u.y0 = tcol * kTileCols;
+        const int height = static_cast<int>(u.tiles) * kTileRows;
+        u.top = rt.trow > 0;
+        u.bottom = u.x0 + height - H < R;
+        u.left = tcol > 0;
+        u.right = u.y0 + kTileCols < C;
+        if (!active) return;
+        const float *v = a.v_out + L.elem_off;
+        const int y = u.y0 + 4 * static_cast<int>(lane);
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            const int x = u.x0 + row_of(q, height);
+            f[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!(q < EDGE ? u.top : u.bottom) || x < 0 || x >= R || y >= C) continue;
+            const float *row = v + static_cast<size_t>(x) * C + y;
+            if ((C & 3) == 0) {
+                f[q] = *reinterpret_cast<const float4 *>(row);
+            } else {
+                f[q].x = row[0];
+                if (y + 1 < C) f[q].y = row[1];
+                if (y + 2 < C) f[q].z = row[2];
+                if (y + 3 < C) f[q].w = row[3];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {                       // the columns beside those rows
+            const int e = static_cast<int>(lane) + 64 * i, q = e / (2 * H), c = e - q * 2 * H;
+            const int x = u.x0 + row_of(q, height), hy = c < H ? u.y0 - 1 - c : u.y0 + kTileCols + (c - H);
+            hs[i] = q < NR && x >= 0 && x < R && hy >= 0 && hy < C ? v[static_cast<size_t>(x) * C + hy] : 0.f;
+        }
+        const int which = static_cast<int>(lane & 3u);       // left tile's last columns, own first, own last, right tile's first
+        const int c = which == 0 ? tcol - 1 : which == 3 ? tcol + 1 : tcol;
+        const bool there = (u.left || u.right) && c >= 0 && c < static_cast<int>(L.tiles_x);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int row = k * kTileRows + static_cast<int>(lane >> 2), x = u.x0 + row;
+#pragma unroll
+            for (int i = 0; i < W / 4; ++i) {
+                sd[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (there && row < height && x < R)
+                    sd[k][i] = *reinterpret_cast<const float4 *>(seam_columns<P>(a.nsi_out, L, x, c, which == 0 || which == 2 ? 1 : 0) + 4 * i);
+            }
+        }
+        n0 = a.slot_cnt[L.tile_begin_all + u.slot];
+        if (u.tiles == 2u) n1 = a.slot_cnt[L.tile_begin_all + u.slot + L.tiles_x];
+    };
+
+    const double ca = a.ca, cb = a.cb;
+    const float caf = uniform_f32(static_cast<float>(ca)), cbf = uniform_f32(static_cast<float>(cb));
+    const float pre_a = uniform_f32(PreF32<P>::square_factor(cb));
+    uint32_t cur_l = 0xffffffffu, recorded = 0;              // the layer that was looked at last, and its candidates
+    uint32_t run = xcd_contiguous(blockIdx.x, gridDim.x) * 4u + wave;
+    uint32_t t = run < n_runs ? run * kRun : kNoItem;
+    if (t != kNoItem) request(t);
+    while (t != kNoItem) {                                   // the same in all lanes
+        const Unit me = u;
+        const uint32_t ml = l, key0 = hint_key, had0 = n0, had1 = n1, C32 = L.C, cap = L.slot_cap, tiles_x = L.tiles_x, cnt0 = L.tile_begin_all + me.slot;
+        const int R = static_cast<int>(L.R), C = static_cast<int>(C32), height = static_cast<int>(me.tiles) * kTileRows;
+        unsigned long long *__restrict__ dst = a.slot_ent + L.slot_off + static_cast<size_t>(me.slot) * cap;
+        const bool on = active && (me.top || me.bottom || me.left || me.right);
+        if (on) {
+            wave_lds_order();
+#pragma unroll
+            for (int q = 0; q < NR; ++q) *reinterpret_cast<float4 *>(&sh.rows[q * PITCH + PADL + 4 * lane]) = f[q];
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const int e = static_cast<int>(lane) + 64 * i, q = e / (2 * H), c = e - q * 2 * H;
+                if (q < NR) sh.rows[q * PITCH + PADL + (c < H ? -1 - c : kTileCols + (c - H))] = hs[i];
+            }
+            const int which = static_cast<int>(lane & 3u), first = which == 0 ? H - W : which == 1 ? H : which == 2 ? 2 * H - W : 2 * H;
+            const int inside = C - me.y0 - (which == 1 ? 0 : kTileCols);         // (a tile's first columns beyond the matrix's edge are 0)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                float *to = &sh.side[which >> 1][(k * kTileRows + static_cast<int>(lane >> 2) + H) * SP];
+#pragma unroll
+                for (int i = 0; i < W / 4; ++i) {
+                    const float e[4] = {sd[k][i].x, sd[k][i].y, sd[k][i].z, sd[k][i].w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int col = first + 4 * i + j;
+                        if (col >= 0 && col < EDGE) to[col] = (which & 1) != 0 && 4 * i + j >= inside ? 0.f : e[j];
+                    }
+                }
+            }
+        }
+        // the run's other tile, if it was not taken with this one; else the next run
+        t = me.tiles == 1u && me.t % kRun == 0u && me.t + 1u < a.n_tiles ? me.t + 1u : kNoItem;
+        if (t == kNoItem) {
+            run += step;
+            if (run < n_runs) t = run * kRun;
+        }
+        if (t != kNoItem) request(t);
+        if (!on) continue;
+        if (ml != cur_l) {
+            if (lane == 0 && recorded) atomicAdd(recorded_slot(a.list_cnt, cur_l, wave), recorded);
+            recorded = 0;
+            cur_l = ml;
+        }
+        const float bound = uniform_f32(PreF32<P>::bound(__uint_as_float(key0)));
+        wave_lds_order();
+
+        auto on_row = [&](int row) { return (row < H && me.top) || (row >= height - H && me.bottom); };
+        auto queue = [&](int row, int col) { sh.queue[atomicAdd(&sh.nqueue, 1u)] = static_cast<uint16_t>(row * kTileCols + col); };
+#pragma unroll
+        for (int edge = 0; edge < 2; ++edge) {               // four columns a lane
+            if (edge == 0 ? !me.top : !me.bottom) continue;
+            ColumnSums<P> ca_[4], cs_[4], cq_[4];
+#pragma unroll
+            for (int i = 0; i < EDGE; ++i) {
+                const float4 *row = reinterpret_cast<const float4 *>(&sh.rows[(edge * EDGE + i) * PITCH + 4 * lane]);      // from 4 columns to the left on
+                const float4 q0 = row[0], q1 = row[1], q2 = row[2];
+                const float w[12] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w, q2.x, q2.y, q2.z, q2.w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float sa, ss, sq;
+                    row_sums<P>(w + PADL + c - H, sa, ss, sq);
+                    ca_[c].push(i, sa);
+                    cs_[c].push(i, ss);
+                    cq_[c].push(i, sq);
+                    if (i >= 2 * H && PreF32<P>::stays(ca_[c].window(i), cs_[c].window(i), cq_[c].window(i), caf, cbf, pre_a, bound))
+                        queue((edge == 0 ? 0 : height - H) + i - 2 * H, 4 * static_cast<int>(lane) + c);
+                }
+            }
+        }
+        // along the sides, where they are not in the rows above
+        auto side_window = [&](int row, int col) { return &sh.side[col < H ? 0 : 1][row * SP + (col < H ? col : col - (kTileCols - H))]; };
+        if (me.left || me.right) {
+            for (int i = static_cast<int>(lane); i < height * 2 * H; i += 64) {
+                const int row = i / (2 * H), c = i - row * 2 * H, col = c < H ? c : kTileCols - 2 * H + c;
+                if (on_row(row) || !(c < H ? me.left : me.right)) continue;
+                const float *win = side_window(row, col);
+                float sa = 0.f, ss = 0.f, sq = 0.f;
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    float ra, rs, rq;
+                    row_sums<P>(win + k * SP, ra, rs, rq);
+                    sa += ra;
+                    ss += rs;
+                    sq += rq;
+                }
+                if (PreF32<P>::stays(sa, ss, sq, caf, cbf, pre_a, bound)) queue(row, col);
+            }
+        }
+        wave_lds_order();
+        const uint32_t nq = sh.nqueue;
+        for (uint32_t qi = lane; qi < nq; qi += 64) {        // in full, as in nsi_pass
+            const int pos = sh.queue[qi], row = pos / kTileCols, col = pos - row * kTileCols;
+            if (me.x0 + row >= R || me.y0 + col >= C) continue;
+            const bool along = on_row(row);
+            const float *win = along ? &sh.rows[(row < H && me.top ? row : EDGE + row - (height - H)) * PITCH + PADL + col - H] : side_window(row, col);
+            const uint32_t key = window_score<P>(win, along ? PITCH : SP, ca, cb);
+            if (key >= key0) {
+                const bool second = row >= kTileRows;
+                const uint32_t cp = (second ? had1 : had0) + atomicAdd(&sh.ncand[second ? 1 : 0], 1u);
+                if (cp < cap)
+                    dst[(second ? static_cast<size_t>(tiles_x) * cap : 0u) + cp] = composite_key(key, static_cast<uint32_t>(me.x0 + row) * C32 + static_cast<uint32_t>(me.y0 + col));
+                const uint32_t bin = min((key - key0) >> kFineShift, static_cast<uint32_t>(kFineBins - 1));
+                if (ml == hist_l) {
+                    atomicAdd(&shared.lhist[bin], 1u);
+                } else {
+                    const uint32_t at = ml < (1u << 22) ? atomicAdd(&shared.n_others, 1u) : shared.kOthers;
+                    if (at < shared.kOthers) shared.others[at] = ml << 10 | bin;
+                    else atomicAdd(&a.hist_s[static_cast<size_t>(ml) * kHistBins + bin], 1u);
+                }
+            }
+        }
+        wave_lds_order();
+        const uint32_t nc0 = sh.ncand[0], nc1 = sh.ncand[1];
+        recorded += nc0 + nc1;
+        if (lane == 0) {
+            if (nc0 != 0u) a.slot_cnt[cnt0] = min(had0 + nc0, cap);
+            if (nc1 != 0u) a.slot_cnt[cnt0 + tiles_x] = min(had1 + nc1, cap);
+            if ((nc0 != 0u && had0 + nc0 > cap) || (nc1 != 0u && had1 + nc1 > cap)) a.state_rw[ml].overflow = 1u;
+            sh.ncand[0] = sh.ncand[1] = sh.nqueue = 0u;
+        }
+    }
+    if (lane == 0 && recorded) atomicAdd(recorded_slot(a.list_cnt, cur_l, wave), recorded);
+    __syncthreads();
+    uint32_t *__restrict__ gh = a.hist_s + static_cast<size_t>(hist_l) * kHistBins;
+    for (int b = threadIdx.x; b < kFineBins; b += 256) {
+        const uint32_t n = shared.lhist[b];
+        if (n) atomicAdd(&gh[b], n);
+    }
+    static_assert(kFineBins == 1 << 10, "a list entry's lower bits");
+    for (uint32_t i = threadIdx.x; i < min(shared.n_others, shared.kOthers); i += 256)
+        atomicAdd(&a.hist_s[static_cast<size_t>(shared.others[i] >> 10) * kHistBins + (shared.others[i] & (kFineBins - 1))], 1u);
 }
 
 // All sides' launches in one (the fallback pass of small plans): a range of workgroups each.
@@ -1178,7 +1554,7 @@ __device__ __forceinline__ void capture_flat(const NsiArgs &a, FlatShared &sh, u
             const SelState st = a.state[l];
             active = st.mode == kModeCandidates;
             hint_key = st.hint_key;
-            if (active && (hint_key < kPreF32MinKey || hint_key > kPreF32MaxKey)) {      // (as in nsi_pass)
+            if (active && !bound_in_range(hint_key)) {                // (as in nsi_pass)
                 active = false;
                 if (tid == 0 && hint_key != 0u) a.state_rw[l].overflow = 1u;
             }
@@ -3223,6 +3599,8 @@ struct MarkArgs {
     const uint32_t *keys;            // score map
     uint32_t *mask, *cmask;
     uint32_t *chunk_cnt, *group_cnt; // kept elements per chunk / chunk group, counted as the bits are set
+    const float *grad;               // v replaces the residual: of the layers that the main pass did not take, here (nullable)
+    float *resid;
 };
 
 template <bool COUNT>
@@ -3284,7 +3662,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     if (COUNT && tid < kMarkCountSlots) ccnt[tid] = 0u;       // (the tile loop's barriers come before the first use)
     uint32_t e = listed ? 0u : dir_lookup(dir, n_layers, first);
     uint32_t cur_l = 0xffffffffu;
-    bool active = false;
+    bool active = false, form_v = false;
     unsigned long long T = 0;
     LayerDev L;
     for (uint32_t t = first; t < n_items; t += stride) {
@@ -3304,6 +3682,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
             const SelState st = state[l];
             active = st.mode == kModeFullMap && (listed || L.large != 0u);
             T = st.T;
+            form_v = m.resid != nullptr && !(L.large != 0u && bound_in_range(st.hint_key));
         }
         if (!active) {
             if (!listed) {
@@ -3418,6 +3797,20 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
                     }
                 }
                 if (cmask) or_bits_shared(cmask, pos, own);
+            }
+        }
+        if (form_v) {                           // the tile's own elements, each by one thread: nothing reads its neighbours any more
+            float *__restrict__ res = m.resid + L.elem_off;
+            const float *__restrict__ g = m.grad + L.elem_off;
+            const int y = y0 + 4 * lane;
+            for (int row = x0 + wave; row < min(x0 + kTileRows, R); row += 4) {
+                const size_t at = static_cast<size_t>(row) * C + y;
+                if ((C & 3) == 0 && y < C) {
+                    const float4 rv = *reinterpret_cast<const float4 *>(res + at), gv = *reinterpret_cast<const float4 *>(g + at);
+                    *reinterpret_cast<float4 *>(res + at) = make_float4(rv.x + gv.x, rv.y + gv.y, rv.z + gv.z, rv.w + gv.w);
+                } else {
+                    for (int q = 0; q < 4 && y + q < C; ++q) res[at + q] += g[at + q];
+                }
             }
         }
         __syncthreads();                        // the ballot words are reused by the next tile
@@ -3793,13 +4186,6 @@ __global__ __launch_bounds__(256) void k_emit_sparse(const ChunkInfo *__restrict
 // workgroup each has the shorter chain (ResNet-18's 1.4 k chunks: 6.3 / 7.6 us; 3.1 k chunks with dense ones among them:
 // 14.5 / 16.9 us).  The line is that of the plans that count as they mark.
 constexpr int kEmitList = 1024;            // kept elements of a chunk that a wave lists at a time
-
-// What one wave has written to LDS and reads back (its DS operations are carried out in order): keeps the compiler from
-// moving the accesses of different lanes past each other.
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // The 128 mask bits that a lane of the wave holds of its chunk, and the kept elements before them.
 struct ChunkBits {
@@ -5237,8 +5623,11 @@ struct Momentum {                 // Eq. 12's momentum term; all null / 0 withou
 template <int PASS>
 int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const float *resid,
                float *nsi_out, float *v_out, const Momentum &mom, hipStream_t stream,
-               bool with_sampled_tiles = true, const Find0Args *find0_args = nullptr, uint4 *counts = nullptr, uint32_t n16 = 0) {
+               bool with_sampled_tiles = true, const Find0Args *find0_args = nullptr, uint4 *counts = nullptr, uint32_t n16 = 0,
+               bool v_in_place = false) {
+    constexpr bool kCaptures = pass_captures(PASS);
     NsiArgs a;
+    a.v_in_place = v_in_place ? 1 : 0;
     a.counts = counts;
     a.n16 = n16;
     a.list_cnt = reinterpret_cast<uint32_t *>(ws + plan->ws.list_cnt);
@@ -5262,7 +5651,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     const DirEntry *tile_dir = reinterpret_cast<const DirEntry *>(ws + plan->ws.tile_dir);
     const DirEntry *large_dir = reinterpret_cast<const DirEntry *>(ws + plan->ws.large_dir);
     // the main pass and its fallback concern the large layers only: they walk those layers' tiles
-    constexpr bool kLargeOnly = PASS == kPassCapture || PASS == kPassFullMap;
+    constexpr bool kLargeOnly = kCaptures || PASS == kPassFullMap;
     const SampleEntry *samples = reinterpret_cast<const SampleEntry *>(ws + plan->ws.samples);
     const SampleEntry *large_tiles = reinterpret_cast<const SampleEntry *>(ws + plan->ws.map_tiles);
     uint32_t *feed = reinterpret_cast<uint32_t *>(ws + plan->ws.feed);
@@ -5275,11 +5664,11 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     // the main pass of single elements has a kernel of its own, which takes small groups of other sides along
     uint32_t n_flat = 0;
     for (const PGroup &g : plan->groups)
-        if (PASS == kPassCapture && g.p == 1) n_flat = g.n_large_tiles;
+        if (kCaptures && g.p == 1) n_flat = g.n_large_tiles;
     const bool flat_fed = plan->work_feed != RSDGC_FEED_OFF && (plan->work_feed == RSDGC_FEED_ON || n_flat >= kFeedTiles);     // (as below; then alone)
     for (const PGroup &g : plan->groups) {
         // this launch's work-feed counters (left clear by the call before)
-        const int pass_index = PASS == kPassSample ? 0 : PASS == kPassCapture ? 1 : 2;
+        const int pass_index = PASS == kPassSample ? 0 : kCaptures ? 1 : 2;
         a.feed = feed + static_cast<size_t>((pass_index * 4 + group_index++) % kFeedSets) * kFeedDomains * kFeedStride;
         a.ca = plan->alpha / static_cast<double>(g.p * g.p);
         a.cb = (1.0 - plan->alpha) / static_cast<double>(g.p * g.p);
@@ -5294,8 +5683,9 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         if (items == 0) continue;
         a.n_tiles = items;
         a.feed_shift = 7;                  // 128 items per domain and stretch: one per resident workgroup of an XCD
-        while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > items) --a.feed_shift;
-        if (together || (n_flat != 0u && (g.p == 1 || (items <= kRideTiles && !flat_fed)))) {
+        const uint32_t shares = PASS == kPassCaptureInPlace ? (items + kRun - 1) / kRun : items;       // what the workgroups take at a time
+        while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > shares) --a.feed_shift;
+        if (together || (n_flat != 0u && (g.p == 1 || (items <= kRideTiles && !flat_fed && PASS != kPassCaptureInPlace)))) {
             all.side[g.p / 2] = a;
             all_items += items;
             continue;
@@ -5308,24 +5698,29 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         /* fixed shares: as many workgroups as give every one the same number of tiles    \
            (2786 tiles on 1280 resident workgroups take three rounds either way; 929       \
            workgroups of three tiles each leave the CUs less crowded in all three) */      \
-        const uint32_t rounds = (items + resident - 1) / resident;                          \
-        const dim3 grid(FF ? std::min<uint32_t>(items, resident) : (items + rounds - 1) / rounds); \
+        const uint32_t rounds = (shares + resident - 1) / resident;                         \
+        const dim3 grid(FF ? std::min<uint32_t>(shares, resident) : (shares + rounds - 1) / rounds); \
         if (PASS == kPassFullMap && find0_args) {                                           \
             hipLaunchKernelGGL((k_find0_fallback<PP, MM>), dim3(grid.x + find0_args->n_layers), block, 0, stream, *find0_args, a); \
             find0_args = nullptr;          /* (the other sides' launches, if any, go by the flag) */ \
         } else                                                                              \
             hipLaunchKernelGGL((k_nsi<PP, PASS, MM, FF>), grid, block, 0, stream, a);       \
+        if constexpr (PASS == kPassCaptureInPlace) {                                        \
+            static const uint32_t seam_wgs = resident_workgroups(k_seams<PP>);              \
+            hipLaunchKernelGGL(k_seams<PP>, dim3(std::min<uint32_t>((shares + 3) / 4, seam_wgs)), block, 0, stream, a); \
+        }                                                                                   \
     }
 #define RSDGC_NSI_CASE(PP)                                                                  \
     case PP: {                                                                              \
         /* the work feed pays when a workgroup gets many tiles (its start and its end cost  \
            a few round trips to the counters); built for the main pass */                   \
-        constexpr bool kFeedBuilt = PASS == kPassCapture;                                   \
+        constexpr bool kFeedBuilt = kCaptures;                                              \
         const bool fed = kFeedBuilt && plan->work_feed != RSDGC_FEED_OFF &&                 \
                          (plan->work_feed == RSDGC_FEED_ON || items >= kFeedTiles);         \
+        constexpr bool kMomBuilt = PASS != kPassCaptureInPlace;   /* (no momentum with one arena) */ \
         if (mom.in) {                                                                       \
-            if (fed) RSDGC_NSI_LAUNCH(PP, true, kFeedBuilt)                                 \
-            else RSDGC_NSI_LAUNCH(PP, true, false)                                          \
+            if (fed) RSDGC_NSI_LAUNCH(PP, kMomBuilt, kFeedBuilt)                            \
+            else RSDGC_NSI_LAUNCH(PP, kMomBuilt, false)                                     \
         } else {                                                                            \
             if (fed) RSDGC_NSI_LAUNCH(PP, false, kFeedBuilt)                                \
             else RSDGC_NSI_LAUNCH(PP, false, false)                                         \
@@ -5333,7 +5728,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         break;                                                                              \
     }
             case 1:
-                if constexpr (PASS != kPassCapture) {
+                if constexpr (!kCaptures) {
                     switch (1) { RSDGC_NSI_CASE(1) }
                 }
                 break;
@@ -5411,7 +5806,7 @@ const char *rsdgc_last_hip_error(void) { return g_hip_error; }
 // The part of a compress call between the NSI passes and the emit: radix select of every
 // layer's threshold, marking of the kept elements, kept counts per chunk and chunk group.
 static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, StageMarks &marks,
-                             PredState *pred, hipStream_t stream) {
+                             PredState *pred, hipStream_t stream, const float *grad = nullptr, float *v_in_place = nullptr) {
     const WsLayout &w = plan->ws;
     const int L = plan->n_layers;
     const uint32_t n_chunks = plan->n_chunks;
@@ -5486,6 +5881,8 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         MarkArgs m;
         m.layers = layers;
         m.state = state;
+        m.grad = grad;
+        m.resid = v_in_place;
         m.dir = reinterpret_cast<const DirEntry *>(ws + w.all_tile_dir);
         m.n_layers = static_cast<uint32_t>(L);
         m.n_tiles = plan->n_tiles_all;
@@ -5636,6 +6033,12 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     uint32_t *cmask = want_centres ? reinterpret_cast<uint32_t *>(ws + w.cmask) : nullptr;
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
 
+    // plans whose layers' candidates a workgroup can read through: everything up to the emit in one launch
+    bool one_select = plan->one_select && plan->work_feed != RSDGC_FEED_ON;
+    for (const PGroup &g : plan->groups) one_select = one_select && g.n_large_tiles < kFeedTiles;      // (no feed for the main pass)
+    // one arena: the main pass puts v in the residual's place as it goes (as a test asks for with the work feed)
+    const bool v_in_place = in_place && plan->any_large && !one_select && (plan->v_in_place || plan->work_feed == RSDGC_FEED_ON);
+
     StageMarks marks(plan, stream);
     if (!plan->ws_ready) {                 // the call before failed half way
         rc = prepare_workspace(plan, ws, sampling, kStatesNone, stream);
@@ -5656,12 +6059,12 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
         hipLaunchKernelGGL(k_hint, dim3(L), dim3(256), 0, stream, layers, state,
                            reinterpret_cast<uint32_t *>(ws + w.hist_s), flags);
     marks.close(1);
-    // plans whose layers' candidates a workgroup can read through: everything up to the emit in one launch
-    bool one_select = plan->one_select && plan->work_feed != RSDGC_FEED_ON;
-    for (const PGroup &g : plan->groups) one_select = one_select && g.n_large_tiles < kFeedTiles;      // (no feed for the main pass)
     uint4 *counts = reinterpret_cast<uint4 *>(ws + w.chunk_cnt);
     const uint32_t counts_n16 = static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16);
-    if (plan->any_large) {
+    if (v_in_place) {
+        rc = launch_nsi<kPassCaptureInPlace>(plan, ws, grad, residual, nsi, residual_out, mom, stream);
+        if (rc != RSDGC_OK) return rc;
+    } else if (plan->any_large) {
         rc = launch_nsi<kPassCapture>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, nullptr, counts, one_select ? counts_n16 : 0u);
         if (rc != RSDGC_OK) return rc;
     }
@@ -5686,16 +6089,16 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
         const bool one_launch = plan->any_large && L <= 256;
         if (!one_launch) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
         if (plan->any_large) {
-            rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, one_launch ? &f : nullptr);
+            rc = launch_nsi<kPassFullMap>(plan, ws, grad, residual, nsi, v_out, mom, stream, true, one_launch ? &f : nullptr, nullptr, 0u, v_in_place);
             if (rc != RSDGC_OK) return rc;
         }
         marks.close(3);
 
-        rc = select_mark_count(plan, ws, want_centres, marks, pred, stream);
+        rc = select_mark_count(plan, ws, want_centres, marks, pred, stream, grad, v_in_place ? residual_out : nullptr);
         if (rc != RSDGC_OK) return rc;
     }
     const ChunkInfo *chunk_info = reinterpret_cast<const ChunkInfo *>(ws + w.chunk_info);
-    if (in_place)
+    if (in_place && !v_in_place)
         hipLaunchKernelGGL(k_emit, dim3(n_chunks + 1), dim3(256), 0, stream, layers, chunk_info, grad,
                            residual_out, mask, chunk_cnt, group_cnt, out_idx, out_val, out_counts, nc);
     else if (n_chunks > kInlineCountChunks)

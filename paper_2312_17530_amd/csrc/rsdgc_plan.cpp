@@ -198,6 +198,18 @@ int build_tables(rsdgc_plan_s *plan) {
     plan->one_select = plan->any_large && plan->map_chunks.empty() && plan->n_chunks <= kInlineCountChunks;
     for (const LayerDev &d : plan->layers)
         plan->one_select = plan->one_select && d.n_tiles <= kSelectTiles && d.k <= kSelectMaxK;
+    // One arena: whether the main pass puts v in the residual's place, with a pass over the tiles' edges (k_seams) behind it, or the emit
+    // forms v from g and r once more.  The extra reading of g and r is cheap while the arenas fit the 256 MB of memory-side cache, and
+    // the edges are more of a tile the wider the windows (p = 7: nearly all of it).  The call without / with the edges' pass, us, one
+    // layer: p = 3 4096 x 4096 100 / 103, 6144 x 5120 157 / 150, 8192 x 6144 223 / 196, 9216 x 8192 320 / 264; p = 5 6144 x 6144 176 / 189,
+    // 8192 x 6144 219 / 221, 9216 x 8192 322 / 264; p = 7 25088 x 4096 423 / 454.  Rows that are no multiple of 16 bytes: p = 3 6000 x 6001
+    // 224 / 223, p = 5 8001 x 9001 395 / 391.  Single elements have no edges: 1024 x 1024 40 / 39, 4096 x 2048 93 / 84, 25088 x 4096 411 / 292.
+    {
+        int64_t of_side[RSDGC_MAX_P + 1] = {};
+        for (const LayerDev &d : plan->layers) of_side[d.p] += d.G;
+        const int64_t all = of_side[1] + of_side[3] + of_side[5] + of_side[7];
+        plan->v_in_place = all == of_side[1] || (of_side[7] <= all / 16 && of_side[1] + of_side[3] + of_side[5] / 2 >= kInPlaceElems);
+    }
 
     // one launch of each NSI pass per distinct neighbourhood side
     for (int p = 1; p <= RSDGC_MAX_P; p += 2) {
