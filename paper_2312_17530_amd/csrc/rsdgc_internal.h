@@ -27,6 +27,7 @@ constexpr int kCountChunks = 16;     // chunks per workgroup of the count pass
 constexpr int kChunkGroup = 64;      // chunks per group in the two-level chunk prefix
 constexpr int kListShards = 16;      // a layer's threshold-bucket list is filled through this many counters
 constexpr int kGroupCntStride = 32;   // words between two chunk-group counters where many workgroups add to one: a cache line each
+constexpr int kGroupCntStrideLarge = 8;   // ... in plans of more than kInlineCountChunks chunks: few adds, but an emit that reads hundreds of them per chunk
 constexpr uint32_t kInlineCountChunks = 4096;   // plans up to this many chunks (33 M elements) count their kept elements where the bits are set
 constexpr int kListCntStride = 32;   // uint32 between two of them (one 128-byte line each)
 constexpr uint32_t kSelectTiles = 1024;  // a plan goes through k_select while its largest layer has at most so many tiles ...
@@ -198,8 +199,8 @@ struct ChunkInfo {
     uint32_t group_first_chunk;  // first chunk of that group
     uint32_t layer_first_group;  // first group of the layer
     uint32_t last;               // 1: the layer's last chunk (it reports the layer's total)
-    uint32_t gstride;            // words between two chunk-group counters: kGroupCntStride in a plan that counts
-    uint32_t pad_;               // its kept elements where their bits are set (many adds per counter), else 1
+    uint32_t gstride;            // words between two chunk-group counters: kGroupCntStride or kGroupCntStrideLarge
+    uint32_t pad_;
 };
 static_assert(sizeof(ChunkInfo) == 56, "ChunkInfo layout");
 

@@ -30,7 +30,8 @@
 //              (Section III-C: whole neighbourhoods are kept); full-map layers: every centre
 //              (small plans with every layer on the candidate path: find0 to mark are one launch, k_select)
 //   count      kept elements per chunk and per group of chunks (no scan kernel: each consumer
-//              adds up its own prefix from those); small plans count as they mark
+//              adds up its own prefix from those): small plans count as they mark, large ones beside the
+//              ranking; a launch of its own for the centres only, where their lists are wanted
 //   emit       ordered (index, value) pairs and the residual update (Eq. 12): either only the
 //              kept elements are touched (v is stored already; by workgroups or, on large plans, by
 //              waves), or g and r are streamed again (one arena, smaller plans)
@@ -1753,18 +1754,19 @@ __device__ __forceinline__ void publish_threshold(PredState *__restrict__ pred, 
 
 // Small plans: whoever sets mask bits also counts them -- the kept elements per 8192-element chunk
 // and per group of kChunkGroup chunks, which the emit turns into output positions -- and the
-// counting pass over the finished mask (k_count, a launch of its own) is not needed.  A call on a
-// small plan is a chain of launches of a few microseconds each; on a large one the extra atomics
-// cost more than the launch (measured: VGG-19 +12 us, ResNet-18 -7 us), so large plans keep
-// k_count and pass no counters here.  A mask word lies in one chunk: chunks are 256 words long and
-// a layer starts at a word boundary.
+// pass over the mask is not needed.  A call on a
+// small plan is a chain of launches of a few microseconds each; on a large one the extra atomics of the gather
+// cost more than a pass (measured: VGG-19 +12 us, ResNet-18 -7 us), so there the gather counts nothing, k_finish's launch counts what it
+// has marked (CountShare), and only k_mark, which sets few bits, counts as it goes.  A mask word lies in one chunk: chunks
+// are 256 words long and a layer starts at a word boundary.
 struct CountCtx {
-    uint32_t *chunk_cnt, *group_cnt;   // cleared by the find0 launch, or by the main pass where k_select follows; null: the plan counts with k_count instead
+    uint32_t *chunk_cnt, *group_cnt;   // cleared by the find0 launch, or by the main pass where k_select follows; null: nothing is counted
     size_t word0;                      // the layer's first mask word
     uint32_t chunk_begin, cgroup_begin;
+    uint32_t gstride;                  // words between two chunk groups' counters
 };
-__device__ __forceinline__ CountCtx count_ctx(const LayerDev &L, uint32_t *chunk_cnt, uint32_t *group_cnt) {
-    return CountCtx{chunk_cnt, group_cnt, static_cast<size_t>(L.elem_off) >> 5, L.chunk_begin, L.cgroup_begin};
+__device__ __forceinline__ CountCtx count_ctx(const LayerDev &L, uint32_t *chunk_cnt, uint32_t *group_cnt, uint32_t gstride = kGroupCntStride) {
+    return CountCtx{chunk_cnt, group_cnt, static_cast<size_t>(L.elem_off) >> 5, L.chunk_begin, L.cgroup_begin, gstride};
 }
 // n more kept elements in the layer's chunk number cl / in its chunk group number gl.  Many
 // workgroups add to one group counter, so each has a cache line of its own (atomics on one line
@@ -1773,7 +1775,7 @@ __device__ __forceinline__ void count_add_chunk_only(const CountCtx &c, uint32_t
     atomicAdd(&c.chunk_cnt[c.chunk_begin + cl], n);
 }
 __device__ __forceinline__ void count_add_group(const CountCtx &c, uint32_t gl, uint32_t n) {
-    atomicAdd(&c.group_cnt[static_cast<size_t>(c.cgroup_begin + gl) * kGroupCntStride], n);
+    atomicAdd(&c.group_cnt[static_cast<size_t>(c.cgroup_begin + gl) * c.gstride], n);
 }
 __device__ __forceinline__ void count_add_chunk(const CountCtx &c, uint32_t cl, uint32_t n) {
     count_add_chunk_only(c, cl, n);
@@ -1810,32 +1812,54 @@ __device__ __forceinline__ void or_counted(const CountCtx &c, uint32_t *__restri
     if (n) count_add_chunk(c, static_cast<uint32_t>((w - c.word0) >> 8), n);
 }
 
-// Set nbits (<= RSDGC_MAX_P) consecutive mask bits starting at bit position pos.
-template <bool COUNT>
-__device__ __forceinline__ void set_bits(const CountCtx &c, uint32_t *__restrict__ mask, size_t pos, uint32_t nbits) {
-    const size_t w = pos >> 5;
-    const uint32_t b = static_cast<uint32_t>(pos & 31);
-    const uint32_t bits = (1u << nbits) - 1u;
-    or_counted<COUNT>(c, mask, w, bits << b);
-    if (b + nbits > 32) or_counted<COUNT>(c, mask, w + 1, bits >> (32 - b));
-}
-
 // A selected centre (flat index i inside its layer) ORs the bits of its p x p window into the
-// (cleared) mask -- Section III-C: whole neighbourhoods are kept -- and its own bit into the
-// centre mask when centre lists are wanted.  The words touched by different centres are nearly
-// all distinct, which is the case global atomics handle well.
+// mask -- Section III-C: whole neighbourhoods are kept -- and its own bit into the
+// centre mask when centre lists are wanted; bits that were not set before are counted, on large plans, whose groups' counters share
+// cache lines, a chunk group's in LDS (`groups`: as many of the layer's first ones as the array holds).  The words touched by different centres are nearly
+// all distinct, which is the case global atomics handle well; all of a window's are on their way before the first one's old value
+// is looked at.
 struct WindowGeom {
     size_t elem_off;
     int R, C, h;
 };
-template <bool COUNT>
-__device__ __forceinline__ void mark_window(const WindowGeom &g, const CountCtx &c, uint32_t i,
+constexpr uint32_t kMarkGroups = 512;      // (2^28 elements)
+template <bool LARGE>
+__device__ __forceinline__ void mark_window(const WindowGeom &g, const CountCtx &c, uint32_t *groups /*[kMarkGroups], LDS*/, uint32_t i,
                                             uint32_t *__restrict__ mask, uint32_t *__restrict__ cmask) {
     const int xc = static_cast<int>(i / static_cast<uint32_t>(g.C));
     const int yc = static_cast<int>(i - static_cast<uint32_t>(xc) * static_cast<uint32_t>(g.C));
-    const int ylo = max(0, yc - g.h), yhi = min(g.C - 1, yc + g.h);
-    for (int x = max(0, xc - g.h); x <= min(g.R - 1, xc + g.h); ++x)
-        set_bits<COUNT>(c, mask, g.elem_off + static_cast<size_t>(x) * g.C + ylo, static_cast<uint32_t>(yhi - ylo + 1));
+    const int ylo = max(0, yc - g.h), nbits = min(g.C - 1, yc + g.h) - ylo + 1;
+    const uint32_t bits = (1u << nbits) - 1u;
+    size_t word[RSDGC_MAX_P];
+    uint32_t lo[RSDGC_MAX_P], hi[RSDGC_MAX_P], old_lo[RSDGC_MAX_P], old_hi[RSDGC_MAX_P];
+#pragma unroll
+    for (int d = 0; d < RSDGC_MAX_P; ++d) {
+        const int x = xc - g.h + d;
+        lo[d] = hi[d] = old_lo[d] = old_hi[d] = 0u;
+        word[d] = 0;
+        if (d > 2 * g.h || x < 0 || x >= g.R) continue;
+        const size_t pos = g.elem_off + static_cast<size_t>(x) * g.C + ylo;
+        const uint32_t b = static_cast<uint32_t>(pos & 31);
+        word[d] = pos >> 5;
+        lo[d] = bits << b;
+        old_lo[d] = atomicOr(&mask[word[d]], lo[d]);
+        if (b + nbits > 32u) {
+            hi[d] = bits >> (32u - b);
+            old_hi[d] = atomicOr(&mask[word[d] + 1], hi[d]);
+        }
+    }
+    auto count = [&](size_t w, uint32_t n) {
+        if (n == 0u) return;
+        const uint32_t cl = static_cast<uint32_t>((w - c.word0) >> 8), gl = cl / kChunkGroup;
+        count_add_chunk_only(c, cl, n);
+        if (LARGE && gl < kMarkGroups) atomicAdd(&groups[gl], n);
+        else count_add_group(c, gl, n);
+    };
+#pragma unroll
+    for (int d = 0; d < RSDGC_MAX_P; ++d) {
+        count(word[d], __popc(lo[d] & ~old_lo[d]));
+        count(word[d] + 1, __popc(hi[d] & ~old_hi[d]));
+    }
     if (cmask) {
         const size_t pos = g.elem_off + i;
         atomicOr(&cmask[pos >> 5], 1u << (pos & 31));
@@ -2696,7 +2720,51 @@ __device__ __forceinline__ void for_each_list_key(const unsigned long long *__re
     }
 }
 
-__global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__restrict__ layers,
+// The plans that do not count as they gather (CountCtx): the kept elements that the gather has marked, counted by workgroups of this launch
+// beside the ranking, which leaves most of the chip idle; k_mark adds the few that the threshold buckets contribute.  Ranking, marks and
+// a counting launch behind them / ranking with counts and marks that count: VGG-19 6.4 + 4.5 + 9.3 / 12.1 + 6.2 us, in one arena, where
+// more keys lie in the buckets, 9.8 + 6.4 + 9.1 / 10.8 + 8.2, 25088 x 4096 with p = 5 the call 250.9 -> 247.5.
+struct CountShare {
+    const CountGroup *groups;      // null: nothing is counted here
+    uint32_t n_groups;
+    const uint32_t *mask;
+    uint32_t *chunk_cnt, *group_cnt;
+    uint32_t gstride;
+};
+// By whole workgroups of NW waves; a wave takes four chunks, 16 lanes and 256 mask words each, four waves a CountGroup.
+template <int NW>
+__device__ __forceinline__ void count_chunks(const CountShare &cs, uint32_t wg, uint32_t *wave_tot /*[NW], LDS*/) {
+    static_assert(kCountChunks == 16 && NW % 4 == 0, "four waves of four chunks");
+    constexpr int N = kChunk / 32 / 32;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, which = wg * (NW / 4) + wave / 4u;
+    uint32_t n = 0;
+    if (which < cs.n_groups) {
+        const CountGroup gr = cs.groups[which];
+        const uint32_t chunk = wave % 4u * 4u + lane / 16u, first = chunk * (kChunk / 32);
+        uint2 w[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {      // (a layer starts at a whole pair of words and is padded to one)
+            const uint32_t i = first + 2u * (lane % 16u + 16u * j);
+            w[j] = i < gr.n_words ? *reinterpret_cast<const uint2 *>(cs.mask + gr.word0 + i) : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) n += __popc(w[j].x) + __popc(w[j].y);
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+        if (lane % 16u == 0u && n != 0u) cs.chunk_cnt[gr.first_chunk + chunk] = n;      // (cleared by the find0 launch)
+        n += __shfl_xor(n, 16, 64);
+        n += __shfl_xor(n, 32, 64);
+    }
+    if (lane == 0u) wave_tot[wave] = n;
+    __syncthreads();
+    const uint32_t mine = wg * (NW / 4) + threadIdx.x;
+    if (threadIdx.x < static_cast<uint32_t>(NW / 4) && mine < cs.n_groups) {
+        n = wave_tot[4 * threadIdx.x] + wave_tot[4 * threadIdx.x + 1] + wave_tot[4 * threadIdx.x + 2] + wave_tot[4 * threadIdx.x + 3];
+        if (n != 0u) atomicAdd(&cs.group_cnt[static_cast<size_t>(cs.groups[mine].group) * cs.gstride], n);
+    }
+}
+
+__global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__restrict__ layers, uint32_t n_layers, const CountShare cs,
                                                            SelState *__restrict__ state,
                                                            const uint32_t *__restrict__ hist,
                                                            const uint32_t *__restrict__ hist1,
@@ -2715,6 +2783,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
     __shared__ uint32_t nstage;
     __shared__ unsigned long long rank_key;
     const int l = blockIdx.x, tid = threadIdx.x;
+    if (blockIdx.x >= n_layers) {
+        count_chunks<kFinishWaves>(cs, blockIdx.x - n_layers, wave_tot);
+        return;
+    }
     if (tid == 0) rank_key = 0ull;
     // lane s of every wave reads shard s's counter (unused shards stay 0); issued with the other loads
     const uint32_t *__restrict__ cnt = list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
@@ -3581,12 +3653,15 @@ __device__ __forceinline__ void or_bits_shared(uint32_t *__restrict__ mask, size
 // next n_list_wgs workgroups stride over the plan's list of tiles of the layers that are
 // always ranked on the full map; the others run only when some large layer fell back to it,
 // walk all tiles and take those of such layers.
+// Large plans: several workgroups per shard, a key per thread (a window's marks are two round trips to memory: in one arena on
+// VGG-19 12.2 us with one, 8.2 with four).
+constexpr uint32_t mark_parts(bool large) { return large ? 4u : 1u; }
 constexpr int kMarkCountSlots = 64;   // chunks a tile counts for in LDS (more only for rows beyond 32 K elements: directly)
 
 struct MarkArgs {
     const LayerDev *layers;
     const SelState *state;
-    uint32_t n_bucket_wgs;           // n_layers * kListShards
+    uint32_t n_bucket_wgs;           // n_layers * kListShards * mark_parts
     const uint32_t *list_cnt;
     const unsigned long long *list_ent;
     const uint32_t *slot_cnt;
@@ -3599,17 +3674,19 @@ struct MarkArgs {
     const uint32_t *keys;            // score map
     uint32_t *mask, *cmask;
     uint32_t *chunk_cnt, *group_cnt; // kept elements per chunk / chunk group, counted as the bits are set
+    uint32_t gstride;                // words between two groups' counters
     const float *grad;               // v replaces the residual: of the layers that the main pass did not take, here (nullable)
     float *resid;
 };
 
-template <bool COUNT>
+template <bool LARGE>
 __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     constexpr int MAXH = (RSDGC_MAX_P - 1) / 2;
     constexpr int NSEG = kTileCols / 64;       // 64-column segments of a tile row
     static_assert(kTileRows * NSEG == 64, "one lane of wave 0 per row segment");
     __shared__ unsigned long long bits[kTileRows + 2 * MAXH][NSEG + 2];   // [row][left, segments, right]
     __shared__ uint32_t ccnt[kMarkCountSlots];      // bits set by the tile, per chunk from the tile's first one on
+    __shared__ uint32_t groups[LARGE ? kMarkGroups : 1];      // bits set by the bucket keys, per chunk group
     const LayerDev *__restrict__ layers = m.layers;
     const DirEntry *__restrict__ dir = m.dir;
     const SampleEntry *__restrict__ map_tiles = m.map_tiles;
@@ -3620,7 +3697,8 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     const uint32_t n_layers = m.n_layers;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x < m.n_bucket_wgs) {
-        const uint32_t l = blockIdx.x / kListShards, shard = blockIdx.x % kListShards;
+        constexpr uint32_t PARTS = mark_parts(LARGE);
+        const uint32_t l = blockIdx.x / (kListShards * PARTS), shard = blockIdx.x % kListShards, part = blockIdx.x / kListShards % PARTS;
         const uint32_t *__restrict__ cnt = m.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
         const uint32_t c = static_cast<uint32_t>(lane) < kListShards ? cnt[lane * kListCntStride] : 0u;
         const SelState st = state[l];
@@ -3631,24 +3709,33 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
                                  (static_cast<int>(Lc.p) - 1) / 2};
         const uint32_t shards = Lc.list_shards, cap = Lc.list_cap / shards;
         if (shard >= shards) return;
-        const CountCtx cctx = count_ctx(Lc, m.chunk_cnt, m.group_cnt);
+        if (LARGE) {
+            for (uint32_t b = tid; b < kMarkGroups; b += 256) groups[b] = 0u;
+            __syncthreads();
+        }
+        const CountCtx cctx = count_ctx(Lc, m.chunk_cnt, m.group_cnt, m.gstride);
         if (__ballot(c > cap) == 0ull) {       // every shard fits: this workgroup takes its shard
             const uint32_t n = __shfl(c, static_cast<int>(shard), 64);
-            const unsigned long long *__restrict__ part = m.list_ent + Lc.list_off + static_cast<size_t>(shard) * cap;
-            for (uint32_t i = tid; i < n; i += 256) {
-                const unsigned long long K = part[i];
-                if (K >= Tc) mark_window<COUNT>(geom, cctx, ~static_cast<uint32_t>(K), mask, cmask);
+            const unsigned long long *__restrict__ keys = m.list_ent + Lc.list_off + static_cast<size_t>(shard) * cap;
+            for (uint32_t i = part * 256u + tid; i < n; i += 256u * PARTS) {
+                const unsigned long long K = keys[i];
+                if (K >= Tc) mark_window<LARGE>(geom, cctx, groups, ~static_cast<uint32_t>(K), mask, cmask);
             }
         } else {                               // the list overflowed: the bucket's keys are still in the tile slots
             const unsigned long long bucket_end = (static_cast<unsigned long long>(st.lo) + (1ull << st.span)) << 32;
-            for (uint32_t t = shard; t < Lc.n_tiles; t += shards) {
+            for (uint32_t t = shard + shards * part; t < Lc.n_tiles; t += shards * PARTS) {
                 const uint32_t n = min(m.slot_cnt[Lc.tile_begin_all + t], Lc.slot_cap);
                 const unsigned long long *__restrict__ ent = m.slot_ent + Lc.slot_off + static_cast<size_t>(t) * Lc.slot_cap;
                 for (uint32_t i = tid; i < n; i += 256) {
                     const unsigned long long K = ent[i];
-                    if (K >= Tc && K < bucket_end) mark_window<COUNT>(geom, cctx, ~static_cast<uint32_t>(K), mask, cmask);
+                    if (K >= Tc && K < bucket_end) mark_window<LARGE>(geom, cctx, groups, ~static_cast<uint32_t>(K), mask, cmask);
                 }
             }
+        }
+        if (LARGE) {
+            __syncthreads();
+            for (uint32_t b = tid; b < min(kMarkGroups, (Lc.n_chunks + kChunkGroup - 1) / kChunkGroup); b += 256)
+                if (groups[b]) count_add_group(cctx, b, groups[b]);
         }
         return;
     }
@@ -3659,7 +3746,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     const uint32_t n_items = listed ? m.n_map_tiles : m.n_tiles;
     if (first >= n_items) return;
     if (!listed && m.flags[0] == 0u) return;
-    if (COUNT && tid < kMarkCountSlots) ccnt[tid] = 0u;       // (the tile loop's barriers come before the first use)
+    if (tid < kMarkCountSlots) ccnt[tid] = 0u;       // (the tile loop's barriers come before the first use)
     uint32_t e = listed ? 0u : dir_lookup(dir, n_layers, first);
     uint32_t cur_l = 0xffffffffu;
     bool active = false, form_v = false;
@@ -3698,7 +3785,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
         const int R = static_cast<int>(L.R), C = static_cast<int>(L.C);
         const int x0 = trow * kTileRows, y0 = tcol * kTileCols;
         const uint32_t *__restrict__ src = keys + L.elem_off;
-        const CountCtx cctx = count_ctx(L, m.chunk_cnt, m.group_cnt);
+        const CountCtx cctx = count_ctx(L, m.chunk_cnt, m.group_cnt, m.gstride);
         const uint32_t cl0 = static_cast<uint32_t>((static_cast<size_t>(x0) * C + y0) / kChunk);   // the tile's first chunk
 
         // wave w takes segment w of every row: all its keys are requested before any is compared
@@ -3770,16 +3857,13 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
                 // its bits, per chunk (the two words may lie in different chunks)
 #pragma unroll
                 for (int part = 0; part < 2; ++part) {
-                    const uint32_t n = COUNT ? __popc(static_cast<uint32_t>(acc >> (32 * part))) : 0u;
+                    const uint32_t n = __popc(static_cast<uint32_t>(acc >> (32 * part)));
                     if (n) {
                         const uint32_t slot = static_cast<uint32_t>((w + part - cctx.word0) >> 8) - cl0;
                         if (slot < static_cast<uint32_t>(kMarkCountSlots)) atomicAdd(&ccnt[slot], n);
                         else count_add_chunk(cctx, cl0 + slot, n);
                     }
                 }
-            } else if (!COUNT) {
-                or_bits_shared(mask, pos, acc);
-                if (cmask) or_bits_shared(cmask, pos, own);
             } else {                                 // shared words: an OR tells which bits were new
                 const size_t w = pos >> 5;
                 const uint32_t b = static_cast<uint32_t>(pos & 31);
@@ -3815,7 +3899,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
         }
         __syncthreads();                        // the ballot words are reused by the next tile
         static_assert(kMarkCountSlots == 64, "one lane of the first wave per counted chunk");
-        if (COUNT && tid < 64) {
+        if (tid < 64) {
             count_flush_wave0(cctx, cl0, ccnt[tid]);
             ccnt[tid] = 0u;
         }
@@ -3825,13 +3909,12 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
 // The mark of block grids (neighbourhoods of one "element", every layer on the full map): the mask is the comparison itself, so
 // there is no tile and no halo.  One wave per kFlatKeys consecutive scores -- a ballot over 64 of them is two mask words --, no
 // barrier, few registers: all waves of a plan as large as VGG-19 (62 MB of scores) are on their way at once.  28.5 us by tiles
-// in k_mark, now 16.0 us.  Counts as it marks (kCount), as k_mark does.
+// in k_mark, now 16.0 us.  Counts as it marks, as k_mark does.
 constexpr int kFlatKeys = 2048;
-template <bool COUNT>
 __global__ __launch_bounds__(256) void k_mark_flat(const LayerDev *__restrict__ layers, const SelState *__restrict__ state,
                                                    const ChunkEntry *__restrict__ chunks, uint32_t n_chunks,
                                                    const uint32_t *__restrict__ keys, uint32_t *__restrict__ mask,
-                                                   uint32_t *__restrict__ chunk_cnt, uint32_t *__restrict__ group_cnt) {
+                                                   uint32_t *__restrict__ chunk_cnt, uint32_t *__restrict__ group_cnt, uint32_t gstride) {
     constexpr uint32_t N = kFlatKeys / 64, PER = kChunk / kFlatKeys;
     static_assert(PER == 4 && N == 32, "four waves, a workgroup, per chunk");
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -3861,87 +3944,23 @@ __global__ __launch_bounds__(256) void k_mark_flat(const LayerDev *__restrict__ 
     }
     // (chunks and layers start at whole pairs of words, and layers are padded to one)
     if (64u * lane < len) *reinterpret_cast<unsigned long long *>(mask + ((ce.arena_off + first) >> 5) + 2 * lane) = mine;
-    if (COUNT) {
-        uint32_t n = lane < N ? static_cast<uint32_t>(__popcll(mine)) : 0u;
+    uint32_t n = lane < N ? static_cast<uint32_t>(__popcll(mine)) : 0u;
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
-        if (lane == 0 && n != 0u) {
-            const CountCtx c = {chunk_cnt, group_cnt, 0, layers[ce.layer].chunk_begin, layers[ce.layer].cgroup_begin};
-            count_add_chunk(c, ce.start / kChunk, n);
-        }
+    for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+    if (lane == 0 && n != 0u) {
+        const CountCtx c = {chunk_cnt, group_cnt, 0, layers[ce.layer].chunk_begin, layers[ce.layer].cgroup_begin, gstride};
+        count_add_chunk(c, ce.start / kChunk, n);
     }
 }
 
 // ---------------------------------------------------------------- count --
-// Kept elements (and selected centres) per chunk and per group of kChunkGroup chunks, from the
-// finished masks -- for plans of many chunks; a small plan's kept elements are counted where their
-// bits are set (CountCtx) and `mask` is null here.  One workgroup per kCountChunks = 16 chunks; 16 adjacent threads read the 256 mask words of one
-// chunk (16 consecutive words each, as independent 8-byte loads) and add their popcounts with
-// four shuffles.  A workgroup adds its total to its chunk group's with one atomic -- four per
-// group (one atomic per chunk put 17 k of them on 9 cache lines and cost 18 us).
+// Selected centres per chunk and per group of kChunkGroup chunks, from the finished mask, where their lists are wanted.  (Kept
+// elements: CountCtx, CountShare.)  One workgroup per kCountChunks = 16 chunks, four per wave.
 constexpr int kCountThreads = 16 * kCountChunks;
-
-__global__ __launch_bounds__(kCountThreads) void k_count(const CountGroup *__restrict__ groups,
-                                                         const uint32_t *__restrict__ mask,
-                                                         const uint32_t *__restrict__ cmask,
-                                                         uint32_t *__restrict__ chunk_cnt,
-                                                         uint32_t *__restrict__ chunk_ccnt,
-                                                         uint32_t *__restrict__ group_cnt,
-                                                         uint32_t *__restrict__ group_ccnt, uint32_t gstride) {
-    constexpr int kPerThread = kChunk / 32 / 16;    // 16 words
-    static_assert(kCountChunks <= 64, "one lane of the first wave per chunk");
-    __shared__ uint32_t lcnt[2][kCountChunks];
-    const int tid = threadIdx.x;
-    const CountGroup gr = groups[blockIdx.x];
-    const uint32_t i0 = static_cast<uint32_t>(tid) * kPerThread;
-    // (a layer starts at a multiple of 64 elements, so word0 and i0 are even: 8-byte loads)
-    uint2 wa[kPerThread / 2], wb[kPerThread / 2];
-#pragma unroll
-    for (int j = 0; j < kPerThread / 2; ++j) {
-        const uint32_t i = i0 + 2 * j;
-        wa[j] = make_uint2(0u, 0u);
-        wb[j] = make_uint2(0u, 0u);
-        if (i + 1 < gr.n_words) {
-            if (mask) wa[j] = *reinterpret_cast<const uint2 *>(mask + gr.word0 + i);
-            if (cmask) wb[j] = *reinterpret_cast<const uint2 *>(cmask + gr.word0 + i);
-        } else if (i < gr.n_words) {
-            if (mask) wa[j].x = mask[gr.word0 + i];
-            if (cmask) wb[j].x = cmask[gr.word0 + i];
-        }
-    }
-    uint32_t a = 0, b = 0;
-#pragma unroll
-    for (int j = 0; j < kPerThread / 2; ++j) {
-        a += __popc(wa[j].x) + __popc(wa[j].y);
-        b += __popc(wb[j].x) + __popc(wb[j].y);
-    }
-#pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) {
-        a += __shfl_xor(a, d, 64);
-        b += __shfl_xor(b, d, 64);
-    }
-    if ((tid & 15) == 0) {
-        lcnt[0][tid >> 4] = a;
-        lcnt[1][tid >> 4] = b;
-    }
-    __syncthreads();
-    if (tid < 64) {                        // the first wave: one lane per chunk
-        a = tid < kCountChunks ? lcnt[0][tid] : 0u;
-        b = tid < kCountChunks ? lcnt[1][tid] : 0u;
-        if (static_cast<uint32_t>(tid) < gr.n_chunks) {
-            if (mask) chunk_cnt[gr.first_chunk + tid] = a;
-            if (cmask) chunk_ccnt[gr.first_chunk + tid] = b;
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            a += __shfl_xor(a, d, 64);
-            b += __shfl_xor(b, d, 64);
-        }
-        if (tid == 0) {                    // (the group totals are cleared by the find0 launch)
-            if (mask && a) atomicAdd(&group_cnt[static_cast<size_t>(gr.group) * gstride], a);
-            if (cmask && b) atomicAdd(&group_ccnt[static_cast<size_t>(gr.group) * gstride], b);
-        }
-    }
+__global__ __launch_bounds__(kCountThreads) void k_count(const CountGroup *__restrict__ groups, const uint32_t *__restrict__ cmask,
+                                                         uint32_t *__restrict__ chunk_ccnt, uint32_t *__restrict__ group_ccnt, uint32_t gstride) {
+    __shared__ uint32_t wave_tot[kCountThreads / 64];
+    count_chunks<kCountThreads / 64>(CountShare{groups, gridDim.x, cmask, chunk_ccnt, group_ccnt, gstride}, blockIdx.x, wave_tot);
 }
 
 // The chunk's prefix -- kept elements of its layer before it -- is the sum of the totals of
@@ -5820,7 +5839,8 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
     uint32_t *mask = reinterpret_cast<uint32_t *>(ws + w.mask);
     uint32_t *cmask = want_centres ? reinterpret_cast<uint32_t *>(ws + w.cmask) : nullptr;
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
-    const bool inline_count = n_chunks <= kInlineCountChunks;    // small plan: count where the bits are set, no k_count
+    const bool inline_count = n_chunks <= kInlineCountChunks;    // small plan: the gather counts as it sets the bits
+    const uint32_t gstride = inline_count ? kGroupCntStride : kGroupCntStrideLarge;
     const GroupEntry *cand_groups = reinterpret_cast<const GroupEntry *>(ws + w.cand_groups);
     const uint32_t n_cand_groups = static_cast<uint32_t>(plan->cand_groups.size());
     const uint32_t *slot_cnt = reinterpret_cast<const uint32_t *>(ws + w.slot_cnt);
@@ -5871,7 +5891,17 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
             hipLaunchKernelGGL(k_filter, dim3((fl.listed ? static_cast<uint32_t>(n_big) : static_cast<uint32_t>(L)) * kFilterSplit),
                                dim3(kFilterThreads), 0, stream, fl, layers, state, a.hist1, a.list_cnt, a.list_ent, list2_cnt, list2_ent);
         }
-        hipLaunchKernelGGL(k_finish, dim3(L), dim3(kFinishThreads), 0, stream, layers, state, hist, a.hist1,
+        CountShare cs = {};
+        if (!inline_count && plan->any_large) {
+            cs.groups = reinterpret_cast<const CountGroup *>(ws + w.count_groups);
+            cs.n_groups = plan->n_count_groups;
+            cs.mask = mask;
+            cs.chunk_cnt = chunk_cnt;
+            cs.group_cnt = reinterpret_cast<uint32_t *>(ws + w.group_cnt);
+            cs.gstride = gstride;
+        }
+        const uint32_t count_wgs = (cs.n_groups * 4u + kFinishWaves - 1u) / kFinishWaves;
+        hipLaunchKernelGGL(k_finish, dim3(L + count_wgs), dim3(kFinishThreads), 0, stream, layers, static_cast<uint32_t>(L), cs, state, hist, a.hist1,
                            a.list_cnt, a.list_ent, a.keys, slot_cnt, slot_ent, list2_cnt, list2_ent, pred);
     }
     HIP_TRY(hipGetLastError());
@@ -5893,10 +5923,11 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         m.keys = reinterpret_cast<const uint32_t *>(nsi);
         m.mask = mask;
         m.cmask = cmask;
-        m.chunk_cnt = inline_count ? chunk_cnt : nullptr;
-        m.group_cnt = inline_count ? reinterpret_cast<uint32_t *>(ws + w.group_cnt) : nullptr;
+        m.chunk_cnt = chunk_cnt;
+        m.group_cnt = reinterpret_cast<uint32_t *>(ws + w.group_cnt);
+        m.gstride = gstride;
         const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(plan->n_tiles_all, kNumCUs * 4u) : 0u;
-        m.n_bucket_wgs = plan->any_large ? static_cast<uint32_t>(L) * kListShards : 0u;
+        m.n_bucket_wgs = plan->any_large ? static_cast<uint32_t>(L) * kListShards * mark_parts(!inline_count) : 0u;
         m.list_cnt = reinterpret_cast<const uint32_t *>(ws + w.list_cnt);
         m.list_ent = reinterpret_cast<const unsigned long long *>(ws + w.list_ent);
         m.slot_cnt = slot_cnt;
@@ -5905,24 +5936,19 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         if (!plan->k_override.empty()) {                   // a block grid: no candidates, no centre masks
             const ChunkEntry *chunks = reinterpret_cast<const ChunkEntry *>(ws + w.map_chunks);
             const uint32_t n = static_cast<uint32_t>(plan->map_chunks.size());
-            if (n != 0u && inline_count)
-                hipLaunchKernelGGL(k_mark_flat<true>, dim3(n), dim3(256), 0, stream, layers, state, chunks, n, m.keys, mask, m.chunk_cnt, m.group_cnt);
-            else if (n != 0u)
-                hipLaunchKernelGGL(k_mark_flat<false>, dim3(n), dim3(256), 0, stream, layers, state, chunks, n, m.keys, mask, nullptr, nullptr);
+            if (n != 0u)
+                hipLaunchKernelGGL(k_mark_flat, dim3(n), dim3(256), 0, stream, layers, state, chunks, n, m.keys, mask, m.chunk_cnt, m.group_cnt, gstride);
         } else if (n_wgs > 0) {
-            if (inline_count) hipLaunchKernelGGL(k_mark<true>, dim3(n_wgs), dim3(256), 0, stream, m);
-            else hipLaunchKernelGGL(k_mark<false>, dim3(n_wgs), dim3(256), 0, stream, m);
+            if (inline_count) hipLaunchKernelGGL(k_mark<false>, dim3(n_wgs), dim3(256), 0, stream, m);
+            else hipLaunchKernelGGL(k_mark<true>, dim3(n_wgs), dim3(256), 0, stream, m);
         }
     }
     marks.close(5);
-    // a small plan's kept elements were counted by the kernels that set their bits; the selected
-    // centres, when their lists are wanted, are counted from the centre mask either way
-    if (!inline_count || cmask)
+    // the selected centres, when their lists are wanted, are counted from their mask
+    if (cmask)
         hipLaunchKernelGGL(k_count, dim3(plan->n_count_groups), dim3(kCountThreads), 0, stream,
-                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), inline_count ? nullptr : mask,
-                           cmask, chunk_cnt, chunk_ccnt, reinterpret_cast<uint32_t *>(ws + w.group_cnt),
-                           reinterpret_cast<uint32_t *>(ws + w.group_ccnt),
-                           inline_count ? static_cast<uint32_t>(kGroupCntStride) : 1u);
+                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), cmask, chunk_ccnt,
+                           reinterpret_cast<uint32_t *>(ws + w.group_ccnt), gstride);
     marks.close(6);
     return RSDGC_OK;
 }
@@ -5965,8 +5991,8 @@ static int launch_select(rsdgc_plan_s *plan, char *ws, const float *grad, const 
     marks.close(5);
     if (want_centres)
         hipLaunchKernelGGL(k_count, dim3(plan->n_count_groups), dim3(kCountThreads), 0, stream,
-                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), nullptr, a.cmask, a.chunk_cnt,
-                           reinterpret_cast<uint32_t *>(ws + w.chunk_ccnt), a.group_cnt, reinterpret_cast<uint32_t *>(ws + w.group_ccnt),
+                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), a.cmask,
+                           reinterpret_cast<uint32_t *>(ws + w.chunk_ccnt), reinterpret_cast<uint32_t *>(ws + w.group_ccnt),
                            static_cast<uint32_t>(kGroupCntStride));
     HIP_TRY(hipGetLastError());
     marks.close(6);

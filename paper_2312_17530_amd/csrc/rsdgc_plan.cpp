@@ -353,7 +353,7 @@ int build_tables(rsdgc_plan_s *plan) {
                                                   first_group + c / kChunkGroup,
                                                   d.chunk_begin + c / kChunkGroup * kChunkGroup, first_group,
                                                   c + 1 == d.n_chunks ? 1u : 0u,
-                                                  plan->n_chunks <= kInlineCountChunks ? uint32_t(kGroupCntStride) : 1u, 0u};
+                                                  uint32_t(plan->n_chunks <= kInlineCountChunks ? kGroupCntStride : kGroupCntStrideLarge), 0u};
             }
             first_group += (d.n_chunks + kChunkGroup - 1) / kChunkGroup;
         }
