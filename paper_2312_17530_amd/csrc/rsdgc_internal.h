@@ -314,6 +314,10 @@ struct rsdgc_plan_s {
     uint64_t uploaded_version = 0;
     bool ws_ready = false;              // uploaded_ws is as a compress call needs it: counters zero, layer states set.  Only
                                         // work that runs makes it so, not work recorded into a graph
+    // rsdgc_dynamic_ratios: the counts' place in host memory, and whether the call before left its histogram clear in uploaded_ws
+    uint32_t *dyn_out = nullptr;
+    void (*dyn_free)(void *) = nullptr;
+    bool dyn_clear = false;
     // block reading (non-overlapping p x p neighbourhoods): this plan describes the element
     // matrices; `inner` describes the block grids as layers with p = 1 and the same k_l, and
     // the selection machinery runs on it.  The workspace is this plan's tables followed by

@@ -5101,7 +5101,7 @@ constexpr int kDynThreads = 512;                         // the main pass: threa
 constexpr uint32_t kDynWorkgroups = 2;                   // ... and workgroups per CU
 constexpr uint32_t kDynSampleThreads = 1024;
 
-// State of the one-pass form (cleared by k_dyn_clear).
+// State of the one-pass form (cleared by k_dyn_sample).
 struct DynSplit {
     unsigned long long above;  // keys above the bracket, all layers
     uint32_t lo, hi;           // the bracket: lo <= key < hi
@@ -5118,14 +5118,13 @@ struct DynSplitArgs {
     uint2 *list;               // [list_cap]
     uint32_t list_cap, n_layers;
     unsigned long long K, n_weights;
+    uint32_t *out;             // [n_layers][2]  the counts, in host memory
 };
 
+// The sample's histogram, for a call that finds it as something else left it (k_dyn_list leaves it clear; a launch in front of every call cost
+// 4 us).
 __global__ __launch_bounds__(256) void k_dyn_clear(const DynSplitArgs a) {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x, stride = gridDim.x * 256u;
-    if (i == 0) *a.state = DynSplit{0ull, 0u, 0u, 0u, 0u, 0u, 0u};
-    for (uint32_t b = i; b < kDynSampleBins; b += stride) a.sample_hist[b] = 0u;
-    for (uint32_t b = i; b < kDynSubBins; b += stride) a.sub_hist[b] = 0u;
-    for (uint32_t b = i; b < 2u * a.n_layers; b += stride) a.cnt[b] = 0u;
+    a.sample_hist[blockIdx.x * 256u + threadIdx.x] = 0u;
 }
 
 // Histogram of a sample: kDynSamplePieces pieces of 16 weights per chunk, at places given by a hash; a short chunk
@@ -5138,6 +5137,12 @@ __global__ __launch_bounds__(kDynSampleThreads) void k_dyn_sample(const ChunkInf
     constexpr uint32_t kPieces = kDynSampleThreads / 16;      // a round's
     const int tid = threadIdx.x;
     for (int b = tid; b < kDynSampleBins; b += kDynSampleThreads) lhist[b] = 0u;
+    {                                      // what the passes that follow count in
+        const uint32_t i = blockIdx.x * kDynSampleThreads + threadIdx.x, all = gridDim.x * kDynSampleThreads;
+        if (i == 0) *a.state = DynSplit{0ull, 0u, 0u, 0u, 0u, 0u, 0u};
+        for (uint32_t b = i; b < kDynSubBins; b += all) a.sub_hist[b] = 0u;
+        for (uint32_t b = i; b < 2u * a.n_layers; b += all) a.cnt[b] = 0u;
+    }
     __syncthreads();
     const uint32_t n_pieces = n_chunks * kDynSamplePieces, stride = gridDim.x * kPieces;
     // pieces in flight per 16 threads: the chain entry -> weight -> bin is what this kernel waits for (a call with 2 / 4 / 8 of them:
@@ -5224,7 +5229,9 @@ __device__ __forceinline__ uint32_t dyn_pick(const uint32_t (&q)[N], uint32_t j)
 // threads twice as often take 4 us longer, four workgroups per CU 3 us, 1024 threads 3 us; looking at the stage every fourth
 // chunk only 1 us, and requesting the next chunk's keys while one is gone through 4 us.
 // VGG-19 (139.7 M weights): four passes of 104 .. 281 us and 23 us of finding at first; 124 us with a branch per key and 2048
-// workgroups of 256; now 110 us and 28 us around it (a call, with its wait and read-back, 706 us at first, 180, now 165).
+// workgroups of 256; now 109 us (a read of as much that does nothing else takes 80 to 84)
+// and 23 us around it; a call, with its wait, 706 us at first, 180, 165, with the counts written to the host and no clearing launch 149.  11.5 M
+// weights 78 -> 66, 49 M 89 -> 77.
 __global__ __launch_bounds__(kDynThreads) void k_dyn_split(const ChunkInfo *__restrict__ chunk_info, uint32_t n_chunks,
                                                            const uint32_t *__restrict__ w, const DynSplitArgs a) {
     __shared__ uint32_t sub[kDynSubBins];
@@ -5283,11 +5290,12 @@ __global__ __launch_bounds__(kDynThreads) void k_dyn_split(const ChunkInfo *__re
         a.state->hi = hi;
         a.state->sub_shift = sub_shift;
     }
-    uint32_t cur_l = 0xffffffffu, above = 0;               // this thread's count for cur_l
+    uint32_t cur_l = 0xffffffffu, above = 0, above_wave = 0; // this thread's count for cur_l, and its wave's
     unsigned long long above_all = 0;                        // thread 0: the workgroup's, all layers
     auto flush_layer = [&]() {
+        if ((tid & 63) == 0) above += above_wave;
         if (above) atomicAdd(&s_above, above);
-        above = 0;
+        above = above_wave = 0;
         __syncthreads();
         if (tid == 0 && s_above) {
             atomicAdd(&a.cnt[2 * cur_l], s_above);
@@ -5297,14 +5305,16 @@ __global__ __launch_bounds__(kDynThreads) void k_dyn_split(const ChunkInfo *__re
         __syncthreads();
     };
     typedef uint32_t vu4 __attribute__((ext_vector_type(4)));       // (read once: streamed)
-    const uint32_t lo2 = lo << 1, width2 = width << 1;       // (a bracket of all keys would have been bad)
-    auto take = [&](uint32_t rel) {                          // a key inside the bracket
-        atomicAdd(&sub[rel >> sub_shift], 1u);
-        dyn_stage_key(stage, a, make_uint2(lo + rel, cur_l));
+    auto take = [&](uint32_t key) {                          // a key inside the bracket
+        atomicAdd(&sub[(key - lo) >> sub_shift], 1u);
+        dyn_stage_key(stage, a, make_uint2(key, cur_l));
     };
-    // (each XCD reads one contiguous part of a round of chunks: 132 -> 124 us on VGG-19)
-    for (uint32_t c = xcd_contiguous(blockIdx.x, gridDim.x); c < n_chunks; c += gridDim.x) {
-        const ChunkInfo ci = chunk_info[c];
+    // (each XCD reads one contiguous part of a round of chunks: 132 -> 124 us on VGG-19.  A chunk's entry is requested a chunk ahead)
+    uint32_t c = xcd_contiguous(blockIdx.x, gridDim.x);
+    ChunkInfo next = chunk_info[min(c, n_chunks - 1u)];
+    for (; c < n_chunks; c += gridDim.x) {
+        const ChunkInfo ci = next;
+        next = chunk_info[min(c + gridDim.x, n_chunks - 1u)];
         if (ci.layer != cur_l) {                             // uniform
             if (cur_l != 0xffffffffu) flush_layer();
             cur_l = ci.layer;
@@ -5318,24 +5328,24 @@ __global__ __launch_bounds__(kDynThreads) void k_dyn_split(const ChunkInfo *__re
                 const vu4 v = __builtin_nontemporal_load(reinterpret_cast<const vu4 *>(src + j * kDynThreads + 4 * tid));
                 q[j] = v.x; q[j + 1] = v.y; q[j + 2] = v.z; q[j + 3] = v.w;
             }
-            uint32_t hits = 0;
+            uint32_t hits = 0;                               // key j: bit N - 1 - j
 #pragma unroll
             for (int j = 0; j < N; ++j) {
-                q[j] = (q[j] << 1) - lo2;                    // 2 (key - lo); a key below lo wraps past all others
-                above += q[j] <= ~lo2 ? 1u : 0u;             // key >= lo
-                hits |= q[j] < width2 ? 1u << j : 0u;
+                const uint32_t key = q[j] & 0x7fffffffu;
+                const bool over = key >= hi;
+                above_wave += static_cast<uint32_t>(__popcll(__ballot(over)));       // (counted by the scalar unit)
+                hits += hits + (key >= lo && !over ? 1u : 0u);
             }
-            above -= __popc(hits);
             while (hits) {                                   // two or three rounds of a wave
                 const uint32_t j = static_cast<uint32_t>(__ffs(hits)) - 1u;
                 hits &= hits - 1u;
-                take(dyn_pick<N>(q, j) >> 1);
+                take(dyn_pick<N>(q, N - 1u - j) & 0x7fffffffu);
             }
         } else {
             for (uint32_t e = tid; e < ci.len; e += kDynThreads) {
-                const uint32_t rel = (src[e] << 1) - lo2;
-                if (rel < width2) take(rel >> 1);
-                else above += rel <= ~lo2 ? 1u : 0u;
+                const uint32_t key = src[e] & 0x7fffffffu;
+                if (key >= hi) ++above;
+                else if (key >= lo) take(key);
             }
         }
         dyn_make_room(stage, a);
@@ -5368,6 +5378,7 @@ __global__ __launch_bounds__(256) void k_dyn_list(const DynSplitArgs a) {
     __shared__ uint32_t cnt[kDynMaxLayers];
     __shared__ uint32_t wave_tot[4];
     __shared__ DigitResult res;
+    for (uint32_t b = blockIdx.x * 256u + threadIdx.x; b < kDynSampleBins; b += gridDim.x * 256u) a.sample_hist[b] = 0u;       // (for the next call)
     const DigitResult r = dyn_sub_bin<4>(a, lh, wave_tot, &res);
     if (!r.found) return;                                    // uniform
     for (uint32_t i = threadIdx.x; i < a.n_layers; i += 256) cnt[i] = 0u;
@@ -5396,22 +5407,24 @@ __global__ __launch_bounds__(256) void k_dyn_list(const DynSplitArgs a) {
         if (cnt[i]) atomicAdd(&a.cnt[2 * i], cnt[i]);
 }
 
-// One workgroup: the K-th key itself, then the final list's keys above and at it per layer.  cnt[0] = ~0 tells the host that the
-// sample's bracket did not serve.
+// One workgroup: the K-th key itself, then the final list's keys above and at it per layer, and all counts to the host (a copy
+// behind the kernel, to memory that is not pinned, cost the call 10 us).  out[0] = ~0 tells the host that the sample's bracket did not serve.
 __global__ __launch_bounds__(1024) void k_dyn_last(const DynSplitArgs a) {
     __shared__ uint32_t lh[kDynSubBins];
     __shared__ uint2 keys[kDynFinalCap];
+    __shared__ uint32_t cnt[2 * kDynMaxLayers];
     __shared__ uint32_t wave_tot[16];
     __shared__ DigitResult res;
     const uint32_t tid = threadIdx.x;
     const DigitResult r = dyn_sub_bin<16>(a, lh, wave_tot, &res);
     const DynSplit st = *a.state;
     if (!r.found || st.n_final > kDynFinalCap) {             // uniform
-        if (tid == 0) a.cnt[0] = 0xffffffffu;
+        if (tid == 0) a.out[0] = 0xffffffffu;
         return;
     }
     const uint32_t n = st.n_final;
     for (uint32_t i = tid; i < n; i += 1024) keys[i] = a.final_list[i];
+    for (uint32_t i = tid; i < 2u * a.n_layers; i += 1024) cnt[i] = a.cnt[i];
     const uint32_t base = st.lo + (r.digit << st.sub_shift);
     uint32_t k_rem = static_cast<uint32_t>(a.K - st.above) - r.above;        // >= 1, <= n
     uint32_t T = 0;                                          // key - base, digit by digit: at most 11 bits each
@@ -5433,9 +5446,11 @@ __global__ __launch_bounds__(1024) void k_dyn_last(const DynSplitArgs a) {
     __syncthreads();
     for (uint32_t i = tid; i < n; i += 1024) {
         const uint32_t rel = keys[i].x - base;
-        if (rel > T) atomicAdd(&a.cnt[2 * keys[i].y], 1u);
-        else if (rel == T) atomicAdd(&a.cnt[2 * keys[i].y + 1], 1u);
+        if (rel > T) atomicAdd(&cnt[2 * keys[i].y], 1u);
+        else if (rel == T) atomicAdd(&cnt[2 * keys[i].y + 1], 1u);
     }
+    __syncthreads();
+    for (uint32_t i = tid; i < 2u * a.n_layers; i += 1024) a.out[i] = cnt[i];
 }
 
 // ---- the general path
@@ -5607,6 +5622,7 @@ int upload_tables(rsdgc_plan_s *plan, void *workspace, hipStream_t stream) {
     HIP_TRY(hipMemcpyAsync(workspace, plan->table.data(), plan->ws.table_bytes,
                            hipMemcpyHostToDevice, stream));
     plan->calls_since_upload = 0;
+    plan->dyn_clear = false;
     // Whatever call lays the tables down prepares the rest too: what comes next may be the replay of a graph that was
     // recorded on a prepared workspace.  (A block plan has its tables only; the selection runs on the inner plan's.)
     if (!plan->blocks) {
@@ -6452,6 +6468,20 @@ int rsdgc_apply_blocks(rsdgc_plan_t *plan, int32_t n_msgs, const uint32_t *const
     return RSDGC_OK;
 }
 
+// The plan's host memory for the counts of rsdgc_dynamic_ratios (null: there is none to be had).
+static uint32_t *pinned_counts(rsdgc_plan_s *plan) {
+    if (!plan->dyn_out) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, 2 * sizeof(uint32_t) * static_cast<size_t>(plan->n_layers), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        plan->dyn_out = static_cast<uint32_t *>(p);
+        plan->dyn_free = [](void *q) { (void)hipHostFree(q); };
+    }
+    return plan->dyn_out;
+}
+
 int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global_ratio,
                          double *ratios_out, void *workspace, void *stream_) {
     if (!plan || plan->blocks || !weights || !ratios_out || !workspace) return RSDGC_EINVAL;
@@ -6494,8 +6524,9 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
     // One pass, where it is the better one: from a million weights on (below, both forms are a chain of launches), and with a
     // counter per layer in LDS.  Its lists lie where a compress call keeps its score map.
     bool counted = false;
-    if (n_real >= static_cast<double>(kDynSplitMin) && L <= kDynMaxLayers) {
+    if (n_real >= static_cast<double>(kDynSplitMin) && L <= kDynMaxLayers && pinned_counts(plan)) {
         DynSplitArgs a;
+        a.out = plan->dyn_out;
         char *area = ws + w.nsi;
         a.state = reinterpret_cast<DynSplit *>(ws + w.dyn);
         a.sample_hist = reinterpret_cast<uint32_t *>(hist);
@@ -6508,17 +6539,22 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
         a.n_layers = static_cast<uint32_t>(L);
         a.K = K;
         a.n_weights = static_cast<unsigned long long>(n_real);
-        hipLaunchKernelGGL(k_dyn_clear, dim3(16), dim3(256), 0, stream, a);
+        const bool clear = plan->dyn_clear;
+        plan->dyn_clear = false;                          // (until all of this call is enqueued)
+        if (!clear) hipLaunchKernelGGL(k_dyn_clear, dim3(kDynSampleBins / 256), dim3(256), 0, stream, a);
         const uint32_t sample_wgs = (16u * n_chunks * kDynSamplePieces + kDynSampleThreads - 1u) / kDynSampleThreads;
         hipLaunchKernelGGL(k_dyn_sample, dim3(std::min<uint32_t>(sample_wgs, kNumCUs)), dim3(kDynSampleThreads), 0, stream, chunk_info, n_chunks, keys, a);
         hipLaunchKernelGGL(k_dyn_split, dim3(std::min<uint32_t>(n_chunks, kNumCUs * kDynWorkgroups)), dim3(kDynThreads), 0, stream, chunk_info, n_chunks, keys, a);
         hipLaunchKernelGGL(k_dyn_list, dim3(kNumCUs), dim3(256), 0, stream, a);
         hipLaunchKernelGGL(k_dyn_last, dim3(1), dim3(1024), 0, stream, a);
-        rc = read_counts();
-        if (rc != RSDGC_OK) return rc;
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(stream));
+        std::copy(a.out, a.out + host.size(), host.begin());
         counted = host[0] != 0xffffffffu;                 // (no layer has that many weights: rows * cols < 2^32)
+        plan->dyn_clear = counted;                        // (the general path counts in the same place)
     }
     if (!counted) {
+        plan->dyn_clear = false;
         hipLaunchKernelGGL(k_dyn_init, dim3(1), dim3(256), 0, stream, state, hist, cnt,
                            static_cast<uint32_t>(2 * L), K);
         int prev_shift = 31;

@@ -498,6 +498,7 @@ void rsdgc_plan_destroy(rsdgc_plan_t *plan) {
         int32_t n = 0;
         double ms[RSDGC_N_STAGES];
         if (!plan->prof_events.empty()) rsdgc_profile_end(plan, ms, &n);   // releases the events
+        if (plan->dyn_free) plan->dyn_free(plan->dyn_out);
         delete plan;
     }
 }
