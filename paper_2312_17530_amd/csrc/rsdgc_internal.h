@@ -55,6 +55,7 @@ constexpr int kSamplingCalls = 10;             // first calls with a workspace: 
 // Tile of the block-score kernel (block reading): kBlockTileRows block rows by
 // block_tile_cols(p) block columns, i.e. 8p x (8 .. 256)p elements.
 constexpr int kBlockTileRows = 8;
+constexpr uint32_t kBlockSlotMin = 64;       // entries of a tile slot from which a block grid takes the candidate path
 #if defined(__HIPCC__)
 __host__ __device__
 #endif
@@ -325,6 +326,7 @@ struct rsdgc_plan_s {
     bool blocks = false;
     rsdgc_plan_s *inner = nullptr;
     std::vector<int64_t> k_override;    // inner plan only: k_l taken from the outer plan
+    std::vector<int32_t> block_p;       // ... and the sides of its blocks
     ~rsdgc_plan_s() { delete inner; }
     bool allow_candidates = true;       // false forces the full-map path for every layer
     // optional per-stage timing: (RSDGC_N_STAGES + 1) events per recorded call (hipEvent_t)

@@ -2090,6 +2090,8 @@ constexpr int kStage = 2048;            // staged keys per workgroup (a round ad
 constexpr int kSlotParts = 4;
 constexpr uint32_t kSplitGroups = 512;  // groups from which a workgroup takes a whole one
 
+constexpr uint32_t kWideGrid = 32768;       // block columns from which a grid's gather counts by row ...
+constexpr uint32_t kWideSlots = 4;          // ... so many chunks of each
 constexpr int kTileMaskWords = kTileRows * kTileCols / 32;    // mask words of one tile (rows of 8 words)
 constexpr int kGatherCountSlots = 64;                          // chunks a group of tiles counts for in LDS (the rest: directly)
 
@@ -2421,8 +2423,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const int role = wg < gl.n_slot_wgs ? 1 : 2;
     const uint32_t first = role == 1 ? wg : wg - gl.n_slot_wgs;
     const uint32_t stride = role == 1 ? gl.n_slot_wgs : gridDim.x - gl.n_map_chunks - gl.n_slot_wgs;
-    constexpr int SLOTS = kSlotGroup / PARTS;
-    const uint32_t n_items = role == 1 ? gl.n_cand_groups * PARTS : gl.n_chunks;
+    constexpr bool BLOCKS = PARTS == 0;       // block grids: whole groups of slots, and single bits
+    constexpr int SHARES = BLOCKS ? 1 : PARTS, SLOTS = kSlotGroup / SHARES;
+    const uint32_t n_items = role == 1 ? gl.n_cand_groups * SHARES : gl.n_chunks;
     const DirEntry *__restrict__ dir = gl.chunk_dir;
     if (first >= n_items) return;
     if (role == 2 && a.flags[0] == 0u) return;
@@ -2447,9 +2450,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
         GroupEntry ge = {};
         const unsigned long long *__restrict__ ent0 = nullptr;     // role 1: the group's first slot entry
         if (role == 1) {
-            ge = gl.cand_groups[it / PARTS];
+            ge = gl.cand_groups[it / SHARES];
             l = ge.layer;
-            const uint32_t s0 = (it % PARTS) * SLOTS;
+            const uint32_t s0 = (it % SHARES) * SLOTS;
             if (s0 >= ge.ntile) continue;
             ge.slot0 += s0;
             ge.ntile = static_cast<uint8_t>(min(static_cast<uint32_t>(ge.ntile) - s0, static_cast<uint32_t>(SLOTS)));
@@ -2543,6 +2546,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                         gather_stage_key(sh, hit, composite_key(kk[c], start + e4 + c), lo, shift1);
                     }
                 }
+            }
+        } else if constexpr (BLOCKS) {
+            // A block is one bit, and every bit is one key's: nothing is built in LDS but the counts.
+            const uint32_t slot_cap = ge.slot_cap, sidx = tid / 16u, j0 = tid % 16u;
+            const CountCtx cctx = count_ctx(L, a.chunk_cnt, a.group_cnt);
+            uint32_t *const ccnt = sh.marks.ccnt;
+            const unsigned long long *__restrict__ slot = ent0 + static_cast<size_t>(sidx) * slot_cap;
+            unsigned long long K = 0;
+            uint32_t cnt = 0;
+            if (sidx < ge.ntile) {
+                cnt = min(a.slot_cnt[ge.slot0 + sidx], slot_cap);
+                if (j0 < slot_cap) K = slot[j0];
+            }
+            // the first chunk that the group's tiles reach into (of the tile row of its first one).  The rows of a wide grid lie many
+            // chunks apart, but at most two tile rows are meant, and of a row at most two chunks: counted by row.
+            const uint32_t tile0 = ge.slot0 - L.tile_begin_all, trow0 = tile0 / L.tiles_x, row0 = trow0 * kBlockTileRows;
+            const uint32_t cl0 = static_cast<uint32_t>(static_cast<uint64_t>(row0) * L.C / kChunk);
+            const bool wide = L.C >= kWideGrid;
+            const uint32_t col0 = wide ? (tile0 - trow0 * L.tiles_x) * (L.C / L.tiles_x) : 0u;      // (not past the first tile's first column)
+            auto row_chunk = [&](uint32_t row) { return (row * L.C + (row < row0 + kBlockTileRows ? col0 : 0u)) / kChunk; };
+            if (COUNT) {
+                if (it != first) __syncthreads();
+                if (tid < kGatherCountSlots) ccnt[tid] = 0u;
+                __syncthreads();
+            }
+            for (uint32_t j = j0; j < cnt; j += 16u) {
+                const unsigned long long next = j + 16u < cnt ? slot[j + 16u] : 0ull;
+                const uint32_t score = static_cast<uint32_t>(K >> 32);
+                if (score >= above) {
+                    const uint32_t i = ~static_cast<uint32_t>(K), cl = i / kChunk;
+                    const size_t pos = static_cast<size_t>(L.elem_off) + i;
+                    atomicOr(&a.mask[pos >> 5], 1u << (pos & 31));
+                    if (COUNT) {
+                        uint32_t at = cl - cl0;
+                        if (wide) {
+                            const uint32_t row = i / L.C, in_row = cl - row_chunk(row);
+                            at = in_row < kWideSlots ? (row - row0) * kWideSlots + in_row : static_cast<uint32_t>(kGatherCountSlots);
+                        }
+                        if (at < static_cast<uint32_t>(kGatherCountSlots)) atomicAdd(&ccnt[at], 1u);
+                        else count_add_chunk(cctx, cl, 1u);
+                    }
+                } else if (score - lo < width) {
+                    const uint32_t pos = atomicAdd(list.cnt, 1u);
+                    if (pos < list.cap) list.ent[pos] = K;
+                    atomicAdd(&a.hist1[l * kLevel1Bins + ((score - lo) >> shift1)], 1u);
+                }
+                K = next;
+            }
+            if (COUNT) {
+                __syncthreads();
+                if (tid < kGatherCountSlots && !wide) count_flush_wave0(cctx, cl0, ccnt[tid]);
+                else if (tid < kGatherCountSlots && ccnt[tid] != 0u) count_add_chunk(cctx, row_chunk(row0 + tid / kWideSlots) + tid % kWideSlots, ccnt[tid]);
             }
         } else {
             const uint32_t slot_cap = ge.slot_cap;
@@ -3906,23 +3961,33 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     }
 }
 
-// The mark of block grids (neighbourhoods of one "element", every layer on the full map): the mask is the comparison itself, so
+// The mark of block grids (neighbourhoods of one "element").  Layers ranked on the full map: the mask is the comparison itself, so
 // there is no tile and no halo.  One wave per kFlatKeys consecutive scores -- a ballot over 64 of them is two mask words --, no
 // barrier, few registers: all waves of a plan as large as VGG-19 (62 MB of scores) are on their way at once.  28.5 us by tiles
-// in k_mark, now 16.0 us.  Counts as it marks, as k_mark does.
+// in k_mark, 16.0 us so.  Layers on the candidate path: the keys of the threshold bucket's list that reach the threshold, a bit
+// each.  Counts as it marks, as k_mark does.  Workgroups, as there: the listed chunks, a layer's list shards, and those that walk all
+// chunks if some layer fell back.
 constexpr int kFlatKeys = 2048;
-__global__ __launch_bounds__(256) void k_mark_flat(const LayerDev *__restrict__ layers, const SelState *__restrict__ state,
-                                                   const ChunkEntry *__restrict__ chunks, uint32_t n_chunks,
-                                                   const uint32_t *__restrict__ keys, uint32_t *__restrict__ mask,
-                                                   uint32_t *__restrict__ chunk_cnt, uint32_t *__restrict__ group_cnt, uint32_t gstride) {
+struct MarkFlatArgs {
+    const LayerDev *layers;
+    const SelState *state;
+    const ChunkEntry *map_chunks;
+    const ChunkInfo *chunks;
+    uint32_t n_map_chunks, n_bucket_wgs, n_chunks;
+    const uint32_t *list_cnt, *slot_cnt, *flags, *keys;
+    const unsigned long long *list_ent, *slot_ent;
+    uint32_t *mask, *chunk_cnt, *group_cnt;
+    uint32_t gstride;
+};
+// A quarter of a chunk, by one wave.
+__device__ __forceinline__ void mark_flat_quarter(const MarkFlatArgs &m, uint32_t layer, uint32_t chunk_start, uint32_t chunk_len, uint64_t arena_off) {
     constexpr uint32_t N = kFlatKeys / 64, PER = kChunk / kFlatKeys;
     static_assert(PER == 4 && N == 32, "four waves, a workgroup, per chunk");
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const ChunkEntry ce = chunks[blockIdx.x];
     const uint32_t first = wave * kFlatKeys;                 // inside the chunk
-    if (first >= ce.len) return;
-    const uint32_t len = min(ce.len - first, static_cast<uint32_t>(kFlatKeys));
-    const uint32_t *__restrict__ src = keys + ce.arena_off + first;
+    if (first >= chunk_len) return;
+    const uint32_t len = min(chunk_len - first, static_cast<uint32_t>(kFlatKeys));
+    const uint32_t *__restrict__ src = m.keys + arena_off + first;
     uint32_t key[N];
     if (len == static_cast<uint32_t>(kFlatKeys)) {
 #pragma unroll
@@ -3931,10 +3996,10 @@ __global__ __launch_bounds__(256) void k_mark_flat(const LayerDev *__restrict__ 
 #pragma unroll
         for (uint32_t j = 0; j < N; ++j) key[j] = src[min(64u * j + lane, len - 1u)];     // (not used past len)
     }
-    const unsigned long long T = state[ce.layer].T;          // (mode kModeFullMap: these layers select something)
+    const unsigned long long T = m.state[layer].T;           // (mode kModeFullMap: these layers select something)
     // K >= T, in two halves: a larger score, or the same at an index that is not higher
     const uint32_t tau = static_cast<uint32_t>(T >> 32), last = ~static_cast<uint32_t>(T);
-    const uint32_t start = ce.start + first;
+    const uint32_t start = chunk_start + first;
     unsigned long long mine = 0;                             // lane j: the ballot of round j
 #pragma unroll
     for (uint32_t j = 0; j < N; ++j) {
@@ -3943,13 +4008,56 @@ __global__ __launch_bounds__(256) void k_mark_flat(const LayerDev *__restrict__ 
         if (lane == j) mine = w;
     }
     // (chunks and layers start at whole pairs of words, and layers are padded to one)
-    if (64u * lane < len) *reinterpret_cast<unsigned long long *>(mask + ((ce.arena_off + first) >> 5) + 2 * lane) = mine;
+    if (64u * lane < len) *reinterpret_cast<unsigned long long *>(m.mask + ((arena_off + first) >> 5) + 2 * lane) = mine;
     uint32_t n = lane < N ? static_cast<uint32_t>(__popcll(mine)) : 0u;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
-    if (lane == 0 && n != 0u) {
-        const CountCtx c = {chunk_cnt, group_cnt, 0, layers[ce.layer].chunk_begin, layers[ce.layer].cgroup_begin, gstride};
-        count_add_chunk(c, ce.start / kChunk, n);
+    if (lane == 0 && n != 0u) count_add_chunk(count_ctx(m.layers[layer], m.chunk_cnt, m.group_cnt, m.gstride), chunk_start / kChunk, n);
+}
+__global__ __launch_bounds__(256) void k_mark_flat(const MarkFlatArgs m) {
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x < m.n_map_chunks) {
+        const ChunkEntry ce = m.map_chunks[blockIdx.x];
+        mark_flat_quarter(m, ce.layer, ce.start, ce.len, ce.arena_off);
+        return;
+    }
+    const uint32_t wg = blockIdx.x - m.n_map_chunks;
+    if (wg < m.n_bucket_wgs) {             // (as in k_mark)
+        const uint32_t l = wg / kListShards, shard = wg % kListShards, lane = tid & 63u;
+        const uint32_t *__restrict__ cnt = m.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
+        const uint32_t c = lane < kListShards ? cnt[lane * kListCntStride] : 0u;
+        const SelState st = m.state[l];
+        const LayerDev &L = m.layers[l];
+        const uint32_t shards = L.list_shards, cap = L.list_cap / shards;
+        if (st.mode != kModeCandidates || st.span == 0u || shard >= shards) return;
+        const CountCtx cctx = count_ctx(L, m.chunk_cnt, m.group_cnt, m.gstride);
+        auto mark = [&](unsigned long long K) {
+            const uint32_t i = ~static_cast<uint32_t>(K);
+            const size_t pos = static_cast<size_t>(L.elem_off) + i;
+            atomicOr(&m.mask[pos >> 5], 1u << (pos & 31));
+            count_add_chunk(cctx, i / kChunk, 1u);
+        };
+        if (__ballot(c > cap) == 0ull) {
+            const uint32_t n = __shfl(c, static_cast<int>(shard), 64);
+            const unsigned long long *__restrict__ part = m.list_ent + L.list_off + static_cast<size_t>(shard) * cap;
+            for (uint32_t i = tid; i < n; i += 256)
+                if (part[i] >= st.T) mark(part[i]);
+        } else {                           // the list overflowed: the bucket's keys are still in the tile slots
+            const unsigned long long bucket_end = (static_cast<unsigned long long>(st.lo) + (1ull << st.span)) << 32;
+            for (uint32_t t = shard; t < L.n_tiles; t += shards) {
+                const uint32_t n = min(m.slot_cnt[L.tile_begin_all + t], L.slot_cap);
+                const unsigned long long *__restrict__ ent = m.slot_ent + L.slot_off + static_cast<size_t>(t) * L.slot_cap;
+                for (uint32_t i = tid; i < n; i += 256)
+                    if (ent[i] >= st.T && ent[i] < bucket_end) mark(ent[i]);
+            }
+        }
+        return;
+    }
+    if (m.flags[0] == 0u) return;
+    const uint32_t before = m.n_map_chunks + m.n_bucket_wgs;
+    for (uint32_t c = blockIdx.x - before; c < m.n_chunks; c += gridDim.x - before) {
+        const ChunkInfo ci = m.chunks[c];
+        if (m.layers[ci.layer].large != 0u && m.state[ci.layer].mode == kModeFullMap) mark_flat_quarter(m, ci.layer, ci.start, ci.len, ci.arena_off);
     }
 }
 
@@ -4468,11 +4576,22 @@ __global__ __launch_bounds__(256) void k_scatter(const LayerDev *__restrict__ la
 // tiles), then every thread takes blocks of the tile: Eqs. 8-10 in double over the p*p slots
 // (zero outside the matrix, divisor p*p), score to the inner score map, 12-bit histogram.
 // Persistent workgroups stride over the tiles; the histogram is flushed on layer change.
+// CAPTURE (plans with a grid on the candidate path): of the grids that have a bound, predicted as in rsdgc_compress (none is ever sampled: without one
+// a grid is ranked on its map), only the blocks that reach it are recorded, per tile, and counted in fine bins: the map is neither written
+// nor read again by the gather and the mark, which have some 500 K keys to go through instead of 15.5 M scores.  VGG-19 at 2 %: this pass 296 /
+// 294 us (it is as fast as it streams), find0 to mark 67 / 34, the call 423.5 -> 377.5; ResNet-18 67.1 -> 53.7, ResNet-50 92.8 -> 78.5, 6000 x 6000
+// with p = 1 at 0.1 % 202 -> 130, 512 x 512 32.5 -> 28.1.  A variant of its own: on grids that stay on the map (300000 x 27) the code for the
+// candidates, unused, took the pass from 63 to 69 us.
 // FEED: tiles come from the launch's work feed (many tiles per workgroup) instead of a
 // fixed strided share.  MOM: Eq. 12's first line on the way in -- u_new = m*u + g (one rounded
 // multiply, one rounded add) takes g's place and goes to the new momentum arena (which, like
 // the residual's, may be the old one).
-template <int P, bool FEED, bool MOM>
+struct BlockCapture {                  // what the candidate path adds: the bounds, and where the blocks that reach them are recorded
+    SelState *state;
+    uint32_t *hist_s, *list_cnt, *slot_cnt;
+    unsigned long long *slot_ent;      // a slot per tile
+};
+template <int P, bool FEED, bool MOM, bool CAPTURE>
 __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ outer,
                                                    const DirEntry *__restrict__ tile_dir,
                                                    uint32_t n_layers, uint32_t n_tiles,
@@ -4482,7 +4601,7 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
                                                    float *__restrict__ score_map,
                                                    uint32_t *__restrict__ hist, double alpha,
                                                    uint32_t *__restrict__ feed_ctr, uint32_t feed_shift,
-                                                   const float *mom_in, float *mom_out, float m) {
+                                                   const float *mom_in, float *mom_out, float m, const BlockCapture cp) {
     constexpr int BCT = block_tile_cols(P);
     constexpr int TR = kBlockTileRows * P, TC = BCT * P;      // tile in elements; TC is a multiple of 4
     constexpr int VEC_PER_ROW = TC / 4;
@@ -4493,6 +4612,7 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
     __shared__ __attribute__((aligned(16))) float tile[TR * TC];
     __shared__ uint32_t lhist[kHistBins];
     __shared__ uint32_t feed_slot[2];
+    __shared__ uint32_t ncand[2];          // candidates of the tile; the other one is being cleared
     const int tid = threadIdx.x;
     const uint32_t stride = gridDim.x;
     WorkFeed feed;
@@ -4505,30 +4625,38 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
         if (first >= n_tiles) return;
     }
     for (int b = tid; b < kHistBins; b += 256) lhist[b] = 0;
+    if (CAPTURE && tid < 2) ncand[tid] = 0;
     __syncthreads();
     const double n = static_cast<double>(P * P);
     const double ca = alpha / n, cb = (1.0 - alpha) / n;
     uint32_t e = dir_lookup(tile_dir, n_layers, first);
-    uint32_t cur_l = 0xffffffffu;
-    bool active = false;
+    uint32_t cur_l = 0xffffffffu, hint_key = 0, recorded = 0, par = 0;
+    bool active = false, capture = false;              // capture: the layer's blocks are held against its bound
     LayerDev O, I;
+    auto flush = [&]() {                               // the finished layer's counts
+        uint32_t *__restrict__ gh = (CAPTURE && capture ? cp.hist_s : hist) + static_cast<size_t>(cur_l) * kHistBins;
+        for (int b = tid; b < (CAPTURE && capture ? kFineBins : kHistBins); b += 256) {
+            const uint32_t c = lhist[b];
+            if (c) { atomicAdd(&gh[b], c); lhist[b] = 0; }
+        }
+        if (CAPTURE && tid == 0 && recorded) atomicAdd(recorded_slot(cp.list_cnt, cur_l, blockIdx.x), recorded);
+        recorded = 0;
+    };
     for (uint32_t t = first; FEED ? t != kNoItem : t < n_tiles;
          t = FEED ? feed.next(feed_slot) : t + stride) {
         e = dir_advance(tile_dir, n_layers, e, t);
         const uint32_t l = tile_dir[e].layer;
         if (l != cur_l) {
-            if (active) {                              // flush the finished layer's counts
-                uint32_t *__restrict__ gh = hist + static_cast<size_t>(cur_l) * kHistBins;
-                for (int b = tid; b < kHistBins; b += 256) {
-                    const uint32_t c = lhist[b];
-                    if (c) { atomicAdd(&gh[b], c); lhist[b] = 0; }
-                }
+            if (active) {
+                flush();
                 __syncthreads();
             }
             cur_l = l;
             O = outer[l];
             I = inner[l];
             active = static_cast<int>(O.p) == P;       // another launch takes the other neighbourhood sides
+            if (CAPTURE) hint_key = cp.state[l].hint_key;
+            capture = CAPTURE && active && I.large != 0u && cp.state[l].mode == kModeCandidates && bound_in_range(hint_key);
         }
         if (!active) {
             if (!FEED) {
@@ -4645,19 +4773,141 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
                 if (P > 1 && d < kCancelFrac * nsq)          // the one-pass variance cancelled (rare)
                     d = __dmul_rn(n, window_ssd<P>(&tile[(br * P) * TC + bc * P], TC, ss / n));
                 const float score = static_cast<float>(nsi_from_var(sa, d, ca, cb));
-                score_map[I.elem_off + static_cast<size_t>(bx) * BC + by] = score;
-                atomicAdd(&lhist[(__float_as_uint(score) & 0x7fffffffu) >> 19], 1u);
+                const uint32_t key = __float_as_uint(score) & 0x7fffffffu;
+                if (!CAPTURE || !capture) {
+                    score_map[I.elem_off + static_cast<size_t>(bx) * BC + by] = score;
+                    atomicAdd(&lhist[key >> kCoarseShift], 1u);
+                } else if (key >= hint_key) {
+                    const uint32_t pos = atomicAdd(&ncand[par], 1u);
+                    if (pos < I.slot_cap) cp.slot_ent[I.slot_off + static_cast<size_t>(local) * I.slot_cap + pos] = composite_key(key, bx * BC + by);
+                    atomicAdd(&lhist[min((key - hint_key) >> kFineShift, static_cast<uint32_t>(kFineBins - 1))], 1u);
+                }
             }
         }
         __syncthreads();                               // the tile is reused by the next item
-    }
-    if (active) {
-        uint32_t *__restrict__ gh = hist + static_cast<size_t>(cur_l) * kHistBins;
-        for (int b = tid; b < kHistBins; b += 256) {
-            const uint32_t c = lhist[b];
-            if (c) atomicAdd(&gh[b], c);
+        if (CAPTURE && capture) {
+            if (tid == 0) {
+                const uint32_t nc = ncand[par];
+                recorded += nc;
+                cp.slot_cnt[I.tile_begin_all + local] = min(nc, I.slot_cap);
+                if (nc > I.slot_cap) cp.state[l].overflow = 1u;
+                ncand[par] = 0u;                       // (used again after the next tile's barrier)
+            }
+            par ^= 1u;
         }
     }
+    if (active) flush();
+}
+
+// A layer whose bound failed, or whose tile overfilled its slot (rare): its blocks' scores once more, for the full map, from v, which the pass
+// above has stored.  Workgroups stride over the chunks of the block grids, a thread per block.  In one launch with k_find0 (up
+// to 256 layers: they look at the layers themselves), or behind it.  Strided reads of v bound it: with every bound failed it takes 380 us on
+// VGG-19 and the call 890, where the map in every call took 424.
+struct BlockRescore {
+    const LayerDev *outer, *inner;
+    const ChunkInfo *chunks;           // of the block grids
+    uint32_t n_chunks;
+    const float *v;
+    float *score_map;
+    uint32_t *hist, *list_cnt;
+    double alpha;
+    bool behind;                       // k_find0 was a launch of its own
+};
+template <int P>
+__device__ __forceinline__ float block_score(const float (&w)[P * P], double alpha) {
+    const double n = static_cast<double>(P * P);
+    double sa = 0.0, ss = 0.0, sq = 0.0;               // (the same sums in the same order as above)
+#pragma unroll
+    for (int i = 0; i < P * P; ++i) {
+        const double e = static_cast<double>(w[i]);
+        sa += fabs(e);
+        ss += e;
+        sq = fma(e, e, sq);
+    }
+    const double nsq = __dmul_rn(n, sq);
+    double d = var_n2_one_pass(ss, nsq);
+    if (P > 1 && d < kCancelFrac * nsq) {
+        const double mean = ss / n;
+        double acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < P * P; ++i) {
+            const double e = static_cast<double>(w[i]) - mean;
+            acc += __dmul_rn(e, e);
+        }
+        d = __dmul_rn(n, acc);
+    }
+    return static_cast<float>(nsi_from_var(sa, d, alpha / n, (1.0 - alpha) / n));
+}
+template <int P>
+__device__ __forceinline__ void rescore_chunk(const BlockRescore &r, const ChunkInfo &ci, const float *__restrict__ v, uint32_t R, uint32_t C, uint32_t BC,
+                                              uint32_t *lhist) {
+    constexpr uint32_t U = P <= 3 ? 4 : P == 5 ? 2 : 1;      // blocks of a thread requested together
+    for (uint32_t e0 = threadIdx.x; e0 < ci.len; e0 += 256 * U) {
+        float w[U][P * P];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t b = ci.start + min(e0 + 256u * u, ci.len - 1u), x0 = b / BC * P, y0 = (b - b / BC * BC) * P;
+#pragma unroll
+            for (uint32_t i = 0; i < P * P; ++i) {
+                const uint32_t x = x0 + i / P, y = y0 + i % P;
+                w[u][i] = x < R && y < C ? v[static_cast<size_t>(x) * C + y] : 0.f;
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            if (e0 + 256u * u >= ci.len) break;
+            const float score = block_score<P>(w[u], r.alpha);
+            r.score_map[ci.arena_off + e0 + 256u * u] = score;
+            atomicAdd(&lhist[(__float_as_uint(score) & 0x7fffffffu) >> kCoarseShift], 1u);
+        }
+    }
+}
+__global__ __launch_bounds__(256) void k_find0_blocks(const Find0Args f, const BlockRescore r) {
+    __shared__ uint32_t lhist[kHistBins];
+    const uint32_t n_layers = static_cast<uint32_t>(f.n_layers), find_wgs = r.behind ? 0u : n_layers;
+    if (blockIdx.x < find_wgs) {
+        find0(f, blockIdx.x);
+        return;
+    }
+    auto failed = [&](uint32_t l) {                    // (without a bound the pass above has written the map)
+        if (r.inner[l].large == 0u || !bound_in_range(f.state[l].hint_key)) return false;
+        return r.behind ? f.state[l].mode == kModeFullMap : layer_falls_back(r.inner, f.state, f.hist_s, r.list_cnt, l);
+    };
+    const uint32_t tid = threadIdx.x;
+    if (r.behind ? f.flags[0] == 0u : !__syncthreads_or(tid < n_layers && failed(tid))) return;
+    for (uint32_t b = tid; b < static_cast<uint32_t>(kHistBins); b += 256) lhist[b] = 0u;
+    __syncthreads();
+    uint32_t cur_l = 0xffffffffu;
+    bool active = false;
+    auto flush = [&]() {
+        uint32_t *__restrict__ gh = r.hist + static_cast<size_t>(cur_l) * kHistBins;
+        for (uint32_t b = tid; b < static_cast<uint32_t>(kHistBins); b += 256) {
+            const uint32_t c = lhist[b];
+            if (c) { atomicAdd(&gh[b], c); lhist[b] = 0u; }
+        }
+    };
+    for (uint32_t c = blockIdx.x - find_wgs; c < r.n_chunks; c += gridDim.x - find_wgs) {
+        const ChunkInfo ci = r.chunks[c];
+        if (ci.layer != cur_l) {
+            __syncthreads();
+            if (active) flush();
+            __syncthreads();
+            cur_l = ci.layer;
+            active = failed(cur_l);
+        }
+        if (!active) continue;
+        const LayerDev &O = r.outer[cur_l];
+        const uint32_t BC = r.inner[cur_l].C, R = O.R, C = O.C;
+        const float *__restrict__ v = r.v + O.elem_off;
+        switch (O.p) {
+            case 1: rescore_chunk<1>(r, ci, v, R, C, BC, lhist); break;
+            case 3: rescore_chunk<3>(r, ci, v, R, C, BC, lhist); break;
+            case 5: rescore_chunk<5>(r, ci, v, R, C, BC, lhist); break;
+            default: rescore_chunk<7>(r, ci, v, R, C, BC, lhist); break;
+        }
+    }
+    __syncthreads();
+    if (active) flush();
 }
 
 // The kept blocks of a chunk, kEmitBlocks at a time: first their places (one division per block, not one per slot), then one
@@ -5598,13 +5848,13 @@ __global__ __launch_bounds__(256) void k_dyn_count(const ChunkInfo *__restrict__
 // the next eager one brings its own preparation.
 int prepare_workspace(rsdgc_plan_s *plan, char *ws, bool sampling, StatesBefore before, hipStream_t stream) {
     const WsLayout &w = plan->ws;
-    const bool block_grid = !plan->k_override.empty();     // always ranked on its full map: no bounds, no centre lists
+    const bool block_grid = !plan->k_override.empty();     // no centre lists
     const size_t n16 = ((block_grid ? w.cmask : w.zero_end) - w.zero_begin) / 16;
     const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n16 + 255) / 256, 4096));
     hipLaunchKernelGGL(k_begin, dim3(blocks + 1), dim3(256), 0, stream,
                        reinterpret_cast<uint4 *>(ws + w.zero_begin), n16,
                        reinterpret_cast<const LayerDev *>(ws + w.layers), reinterpret_cast<SelState *>(ws + w.state),
-                       plan->n_layers, block_grid ? nullptr : reinterpret_cast<PredState *>(ws + w.pred),
+                       plan->n_layers, reinterpret_cast<PredState *>(ws + w.pred),
                        reinterpret_cast<uint32_t *>(ws + w.flags), sampling ? 1 : 0, static_cast<int>(before));
     HIP_TRY(hipGetLastError());
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -5626,7 +5876,7 @@ int upload_tables(rsdgc_plan_s *plan, void *workspace, hipStream_t stream) {
     // Whatever call lays the tables down prepares the rest too: what comes next may be the replay of a graph that was
     // recorded on a prepared workspace.  (A block plan has its tables only; the selection runs on the inner plan's.)
     if (!plan->blocks) {
-        const int rc = prepare_workspace(plan, static_cast<char *>(workspace), plan->any_large, before, stream);
+        const int rc = prepare_workspace(plan, static_cast<char *>(workspace), plan->any_large && plan->k_override.empty(), before, stream);
         if (rc != RSDGC_OK) return rc;
     }
     plan->uploaded_ws = workspace;
@@ -5887,13 +6137,15 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         gl.n_chunks = n_chunks;
         gl.n_map_chunks = static_cast<uint32_t>(plan->map_chunks.size());
         gl.n_cand_groups = n_cand_groups;
-        const bool split = inline_count && n_cand_groups < kSplitGroups;
+        const bool blocks = !plan->k_override.empty(), split = !blocks && inline_count && n_cand_groups < kSplitGroups;
         gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (split ? kSlotParts : 1u), kNumCUs * 8u);
         const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u;
         if (gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs > 0)
         {
             const dim3 grid(gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs);
-            if (split) hipLaunchKernelGGL((k_gather<true, kSlotParts>), grid, dim3(256), 0, stream, a, gl);
+            if (blocks && inline_count) hipLaunchKernelGGL((k_gather<true, 0>), grid, dim3(256), 0, stream, a, gl);
+            else if (blocks) hipLaunchKernelGGL((k_gather<false, 0>), grid, dim3(256), 0, stream, a, gl);
+            else if (split) hipLaunchKernelGGL((k_gather<true, kSlotParts>), grid, dim3(256), 0, stream, a, gl);
             else if (inline_count) hipLaunchKernelGGL((k_gather<true, 1>), grid, dim3(256), 0, stream, a, gl);
             else hipLaunchKernelGGL((k_gather<false, 1>), grid, dim3(256), 0, stream, a, gl);
         }
@@ -5949,11 +6201,27 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         m.slot_cnt = slot_cnt;
         m.slot_ent = slot_ent;
         const uint32_t n_wgs = m.n_bucket_wgs + m.n_list_wgs + n_fb_wgs;
-        if (!plan->k_override.empty()) {                   // a block grid: no candidates, no centre masks
-            const ChunkEntry *chunks = reinterpret_cast<const ChunkEntry *>(ws + w.map_chunks);
-            const uint32_t n = static_cast<uint32_t>(plan->map_chunks.size());
-            if (n != 0u)
-                hipLaunchKernelGGL(k_mark_flat, dim3(n), dim3(256), 0, stream, layers, state, chunks, n, m.keys, mask, m.chunk_cnt, m.group_cnt, gstride);
+        if (!plan->k_override.empty()) {                   // a block grid: no windows, no centre masks
+            MarkFlatArgs b;
+            b.layers = layers;
+            b.state = state;
+            b.map_chunks = reinterpret_cast<const ChunkEntry *>(ws + w.map_chunks);
+            b.chunks = reinterpret_cast<const ChunkInfo *>(ws + w.chunk_info);
+            b.n_map_chunks = static_cast<uint32_t>(plan->map_chunks.size());
+            b.n_bucket_wgs = plan->any_large ? static_cast<uint32_t>(L) * kListShards : 0u;
+            b.n_chunks = n_chunks;
+            b.list_cnt = m.list_cnt;
+            b.slot_cnt = slot_cnt;
+            b.flags = flags;
+            b.keys = m.keys;
+            b.list_ent = m.list_ent;
+            b.slot_ent = slot_ent;
+            b.mask = mask;
+            b.chunk_cnt = m.chunk_cnt;
+            b.group_cnt = m.group_cnt;
+            b.gstride = gstride;
+            const uint32_t n = b.n_map_chunks + b.n_bucket_wgs + (plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u);
+            if (n != 0u) hipLaunchKernelGGL(k_mark_flat, dim3(n), dim3(256), 0, stream, b);
         } else if (n_wgs > 0) {
             if (inline_count) hipLaunchKernelGGL(k_mark<false>, dim3(n_wgs), dim3(256), 0, stream, m);
             else hipLaunchKernelGGL(k_mark<true>, dim3(n_wgs), dim3(256), 0, stream, m);
@@ -6302,7 +6570,10 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     }
     const bool ready = in->ws_ready;       // (false: prepared by the graph that is being recorded)
     in->ws_ready = false;                  // (until all of this call is enqueued)
-    const NextCall nc = next_call(in, ws, inner, state, nullptr, false);
+    PredState *pred = reinterpret_cast<PredState *>(ws + w.pred);
+    const NextCall nc = next_call(in, ws, inner, state, pred, false);
+    const BlockCapture cp = {state, reinterpret_cast<uint32_t *>(ws + w.hist_s), reinterpret_cast<uint32_t *>(ws + w.list_cnt),
+                             reinterpret_cast<uint32_t *>(ws + w.slot_cnt), reinterpret_cast<unsigned long long *>(ws + w.slot_ent)};
     bool have[RSDGC_MAX_P + 1] = {};
     for (int l = 0; l < L; ++l) have[plan->p[l]] = true;
     // the work feed (counters in the inner plan's workspace, cleared above) pays when a
@@ -6315,25 +6586,30 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     for (int pp = 1; pp <= RSDGC_MAX_P; pp += 2) {
         if (!have[pp]) continue;
         switch (pp) {
-#define RSDGC_BLOCK_LAUNCH(PP, FF, MM)                                                           \
+#define RSDGC_BLOCK_LAUNCH(PP, FF, MM, CC)                                                       \
     {                                                                                            \
-        static const uint32_t resident = resident_workgroups(k_block_nsi<PP, FF, MM>);           \
-        hipLaunchKernelGGL((k_block_nsi<PP, FF, MM>), dim3(std::min<uint32_t>(plan->n_tiles_all, resident)), \
+        static const uint32_t resident = resident_workgroups(k_block_nsi<PP, FF, MM, CC>);           \
+        hipLaunchKernelGGL((k_block_nsi<PP, FF, MM, CC>), dim3(std::min<uint32_t>(plan->n_tiles_all, resident)), \
                            dim3(256), 0, stream, outer,                                          \
                            reinterpret_cast<const DirEntry *>(ws_outer + plan->ws.all_tile_dir), \
                            static_cast<uint32_t>(L), plan->n_tiles_all, inner, grad, residual,   \
                            residual_out, score_map, hist, plan->alpha,                           \
                            feed + static_cast<size_t>(PP / 2) * kFeedDomains * kFeedStride,      \
-                           feed_shift, mom.in, mom.out, mom.m);                                  \
+                           feed_shift, mom.in, mom.out, mom.m, cp);                              \
+    }
+#define RSDGC_BLOCK_PICK(PP, FF, MM)                                                             \
+    {                                                                                            \
+        if (in->any_large) RSDGC_BLOCK_LAUNCH(PP, FF, MM, true)                                  \
+        else RSDGC_BLOCK_LAUNCH(PP, FF, MM, false)                                               \
     }
 #define RSDGC_BLOCK_CASE(PP)                                                                     \
     case PP: {                                                                                   \
         if (mom.in) {                                                                            \
-            if (fed) RSDGC_BLOCK_LAUNCH(PP, true, true)                                          \
-            else RSDGC_BLOCK_LAUNCH(PP, false, true)                                             \
+            if (fed) RSDGC_BLOCK_PICK(PP, true, true)                                            \
+            else RSDGC_BLOCK_PICK(PP, false, true)                                               \
         } else {                                                                                 \
-            if (fed) RSDGC_BLOCK_LAUNCH(PP, true, false)                                         \
-            else RSDGC_BLOCK_LAUNCH(PP, false, false)                                            \
+            if (fed) RSDGC_BLOCK_PICK(PP, true, false)                                           \
+            else RSDGC_BLOCK_PICK(PP, false, false)                                              \
         }                                                                                        \
         break;                                                                                   \
     }
@@ -6342,14 +6618,20 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
             RSDGC_BLOCK_CASE(5)
             RSDGC_BLOCK_CASE(7)
 #undef RSDGC_BLOCK_CASE
+#undef RSDGC_BLOCK_PICK
 #undef RSDGC_BLOCK_LAUNCH
         }
     }
     HIP_TRY(hipGetLastError());
-    const Find0Args f = {inner, state, hist, hist, reinterpret_cast<uint32_t *>(ws + w.flags), nullptr,
+    const Find0Args f = {inner, state, hist, cp.hist_s, reinterpret_cast<uint32_t *>(ws + w.flags), pred,
                          reinterpret_cast<uint4 *>(ws + w.chunk_cnt), static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16), L};
-    hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
-    rc = select_mark_count(in, ws, false, marks, nullptr, stream);
+    const bool behind = in->any_large && L > 256;
+    if (!in->any_large || behind) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
+    if (in->any_large) {
+        const BlockRescore r = {outer, inner, inner_chunks, in->n_chunks, residual_out, score_map, hist, cp.list_cnt, plan->alpha, behind};
+        hipLaunchKernelGGL(k_find0_blocks, dim3((behind ? 0 : L) + std::min<uint32_t>(in->n_chunks, kNumCUs * 8u)), dim3(256), 0, stream, f, r);
+    }
+    rc = select_mark_count(in, ws, false, marks, pred, stream);
     if (rc != RSDGC_OK) return rc;
     hipLaunchKernelGGL(k_emit_blocks, dim3(in->n_chunks + 1), dim3(256), 0, stream, outer, inner_chunks, mask,
                        chunk_cnt, group_cnt, inner, residual_out, mom.out, out_block_idx, out_val, out_counts, nc);
