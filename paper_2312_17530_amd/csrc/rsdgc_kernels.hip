@@ -1675,7 +1675,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     else if (b < a.first_wg[3]) nsi_pass<3, kPassCapture, MOM, false>(a.side[1], sh.s3, b - a.first_wg[2], a.first_wg[3] - a.first_wg[2]);
     else capture_flat<MOM, false>(a.side[0], sh.flat, b - a.first_wg[3], a.first_wg[4] - a.first_wg[3]);
 }
-constexpr uint32_t kRideTiles = 256;      // tiles of a side up to which it rides along: one round of workgroups
+constexpr uint32_t kRideTiles = 256;      // tiles of a side up to which it rides along: one round of workgroups ...
+// ... or, up to kRideMost, as many as there are of single elements: two launches one behind the other leave the chip half idle twice (ResNet-50
+// with all its vectors, 2790 and 2950 tiles: 31.4 and 36.4 us, in one launch 61.1; the call 117 -> 105 us, with centre lists 130 -> 120, with momentum 154 -> 139).
+constexpr uint32_t kRideMost = 4096;
 
 // ------------------------------------------------------- ranking digits --
 // The k_l-th largest composite key of a layer (Algorithm 1's ranking, Eq. 11's k_l) is found
@@ -2788,13 +2791,14 @@ struct CountShare {
 };
 // By whole workgroups of NW waves; a wave takes four chunks, 16 lanes and 256 mask words each, four waves a CountGroup.
 template <int NW>
-__device__ __forceinline__ void count_chunks(const CountShare &cs, uint32_t wg, uint32_t *wave_tot /*[NW], LDS*/) {
+__device__ __forceinline__ void count_chunks(const CountShare &cs, uint32_t wg, uint32_t *wave_tot /*[2 NW], LDS*/) {
     static_assert(kCountChunks == 16 && NW % 4 == 0, "four waves of four chunks");
     constexpr int N = kChunk / 32 / 32;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, which = wg * (NW / 4) + wave / 4u;
-    uint32_t n = 0;
+    uint32_t n = 0, group = 0;
     if (which < cs.n_groups) {
         const CountGroup gr = cs.groups[which];
+        group = gr.group;
         const uint32_t chunk = wave % 4u * 4u + lane / 16u, first = chunk * (kChunk / 32);
         uint2 w[N];
 #pragma unroll
@@ -2810,12 +2814,14 @@ __device__ __forceinline__ void count_chunks(const CountShare &cs, uint32_t wg, 
         n += __shfl_xor(n, 16, 64);
         n += __shfl_xor(n, 32, 64);
     }
-    if (lane == 0u) wave_tot[wave] = n;
+    if (lane == 0u) {
+        wave_tot[wave] = n;
+        wave_tot[NW + wave] = group;
+    }
     __syncthreads();
-    const uint32_t mine = wg * (NW / 4) + threadIdx.x;
-    if (threadIdx.x < static_cast<uint32_t>(NW / 4) && mine < cs.n_groups) {
+    if (threadIdx.x < static_cast<uint32_t>(NW / 4)) {
         n = wave_tot[4 * threadIdx.x] + wave_tot[4 * threadIdx.x + 1] + wave_tot[4 * threadIdx.x + 2] + wave_tot[4 * threadIdx.x + 3];
-        if (n != 0u) atomicAdd(&cs.group_cnt[static_cast<size_t>(cs.groups[mine].group) * cs.gstride], n);
+        if (n != 0u) atomicAdd(&cs.group_cnt[static_cast<size_t>(wave_tot[NW + 4 * threadIdx.x]) * cs.gstride], n);
     }
 }
 
@@ -2839,7 +2845,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
     __shared__ unsigned long long rank_key;
     const int l = blockIdx.x, tid = threadIdx.x;
     if (blockIdx.x >= n_layers) {
-        count_chunks<kFinishWaves>(cs, blockIdx.x - n_layers, wave_tot);
+        count_chunks<kFinishWaves>(cs, blockIdx.x - n_layers, lh);
         return;
     }
     if (tid == 0) rank_key = 0ull;
@@ -4067,7 +4073,7 @@ __global__ __launch_bounds__(256) void k_mark_flat(const MarkFlatArgs m) {
 constexpr int kCountThreads = 16 * kCountChunks;
 __global__ __launch_bounds__(kCountThreads) void k_count(const CountGroup *__restrict__ groups, const uint32_t *__restrict__ cmask,
                                                          uint32_t *__restrict__ chunk_ccnt, uint32_t *__restrict__ group_ccnt, uint32_t gstride) {
-    __shared__ uint32_t wave_tot[kCountThreads / 64];
+    __shared__ uint32_t wave_tot[2 * kCountThreads / 64];
     count_chunks<kCountThreads / 64>(CountShare{groups, gridDim.x, cmask, chunk_ccnt, group_ccnt, gstride}, blockIdx.x, wave_tot);
 }
 
@@ -5970,7 +5976,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         a.feed_shift = 7;                  // 128 items per domain and stretch: one per resident workgroup of an XCD
         const uint32_t shares = PASS == kPassCaptureInPlace ? (items + kRun - 1) / kRun : items;       // what the workgroups take at a time
         while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > shares) --a.feed_shift;
-        if (together || (n_flat != 0u && (g.p == 1 || (items <= kRideTiles && !flat_fed && PASS != kPassCaptureInPlace)))) {
+        if (together || (n_flat != 0u && (g.p == 1 || (items <= std::max(kRideTiles, std::min(n_flat, kRideMost)) && !flat_fed && PASS != kPassCaptureInPlace)))) {
             all.side[g.p / 2] = a;
             all_items += items;
             continue;

@@ -1,0 +1,34 @@
+"""Sides of more than a round's tiles that ride along in the main pass of single elements, up to as many as there are of those,
+and one that does not.  Against the CPU oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(a):
+    return np.ascontiguousarray(a, dtype=np.float32).view(np.uint32)
+
+
+@pytest.mark.parametrize("m", [None, 0.9], ids=["plain", "momentum"])
+def test_sides_that_ride_along(m):
+    from paper_2312_17530_amd.session import Session
+    shapes = [(1250, 1024), (1199, 1021), (1040, 1025), (1400, 1030), (1, 700)]      # 313 tiles of single elements; 300, 325, 440
+    ps, ratios = [1, 3, 5, 7, 1], [0.02, 0.02, 0.01, 0.01, 0.05]
+    rng = np.random.default_rng(5)
+    s = Session(shapes, 3, 0.5, ratios, ps, momentum=m)
+    for t in range(5):
+        grads = [(rng.standard_normal(sh) * 1e-2).astype(np.float32) for sh in shapes]
+        resid = s.unpack(s.residual)
+        mom = s.unpack(s.momentum_buf) if m is not None else [np.zeros(sh, np.float32) for sh in shapes]
+        s.set_grad(grads)
+        s.compress()
+        if t not in (0, 4):
+            continue
+        after = s.unpack(s.residual)
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            o, _ = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, ps[l], 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
