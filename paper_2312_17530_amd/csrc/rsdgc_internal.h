@@ -103,7 +103,9 @@ struct LayerDev {
     uint32_t slot_cap;      // entries per tile slot: kSlotCapMax, or what a tile of the layer can hold if that is less; p = 1 in rows of
                             //    whole mask words: what there is room for (usually half of the tile's elements)
     uint32_t cgroup_begin;  // first chunk group (kChunkGroup chunks) of the layer, numbered over all layers
-    uint32_t pad_;
+    uint32_t grid;          // 1: a block grid.  Its bounds lie further below the forecast (twice the margin): a few more keys cost it next to nothing, a
+                            //    bound that fails a third of a call (VGG-19, 200 calls on a carried residual: 9 failed with the margin as it is,
+                            //    none with twice), and none is handed out while the threshold still moves fast
 };
 static_assert(sizeof(LayerDev) == 128, "LayerDev layout");
 

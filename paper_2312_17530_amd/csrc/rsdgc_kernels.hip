@@ -238,8 +238,10 @@ __device__ __forceinline__ bool init_layer_state(const LayerDev *__restrict__ la
             ps.has_forecast = 1;
             // (a threshold that jumps: sampled bounds while there are any; later the trend is
             // taken as far as it is trusted -- a bound that fails costs less than the full map)
-            if (!paused && (fabsf(d) <= kTrendMaxLog2 || !sampling)) {   // (d, not dd: a jump is sampled)
-                const float margin = ps.margin > 0.f ? ps.margin : margin_init_log2(L.k);
+            // (... except of a grid: its map costs it less than a bound that fails)
+            if (!paused && (fabsf(d) <= kTrendMaxLog2 || (!sampling && !L.grid))) {   // (d, not dd: a jump is sampled)
+                float margin = ps.margin > 0.f ? ps.margin : margin_init_log2(L.k);
+                if (L.grid) margin = 2.f * margin + 0.03f;
                 const float bound = exp2f(ps.forecast - margin);
                 const uint32_t key = __float_as_uint(bound);
                 if (key >= kPreF32MinKey && key <= kPreF32MaxKey) {   // (else: no bound, the full map)

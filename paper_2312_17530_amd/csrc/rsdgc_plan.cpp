@@ -95,7 +95,7 @@ int build_tables(rsdgc_plan_s *plan) {
         d.tile_begin_all = tile_begin_all;
         d.group_begin = group_begin;
         d.cgroup_begin = cgroup_begin;
-        d.pad_ = 0;
+        d.grid = plan->k_override.empty() ? 0u : 1u;
         d.n_groups = (d.n_tiles + kSlotGroup - 1) / kSlotGroup;
         d.list_off = list_off;
         // a block grid may be ranked on its full score map whatever its size: its threshold bucket may hold
