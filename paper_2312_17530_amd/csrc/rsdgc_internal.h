@@ -55,7 +55,14 @@ constexpr int kSamplingCalls = 10;             // first calls with a workspace: 
 // Tile of the block-score kernel (block reading): kBlockTileRows block rows by
 // block_tile_cols(p) block columns, i.e. 8p x (8 .. 256)p elements.
 constexpr int kBlockTileRows = 8;
-constexpr uint32_t kBlockSlotMin = 64;       // entries of a tile slot from which a block grid takes the candidate path
+constexpr uint32_t kBlockSlotMin = 64;       // entries of a tile slot from which a block grid takes the candidate path ...
+constexpr int kGridLayers = 256;             // ... in plans of up to so many layers (5000 layers of 48 x 180 to 87 x 711: 1290 us a call, on the map 832)
+// ... from so many blocks on.  The threshold of a smaller grid moves too much from call to call for the bounds below it, and scores over wide
+// blocks lie so close together that a bound with a margin catches half of the grid.  A call on a residual carried through four gradients, all
+// on the map / from 1024 blocks or fewer / from 8192 / 32768 / 131072: p = 3 ResNet-18 77 / 82 / 78 / 76 / 79, ResNet-50 109 / 119 / 104 / 107 / 108,
+// 512 x 512 (29 K blocks) 35 / 30 / 30 / 35 / 35, p = 5 ResNet-50 102 / 124 / 114 / 102 / 102, p = 7 ResNet-50 112 / 138 / 128 / 113 / 113, ResNet-18
+// 96 / 111 / 100 / 94 / 96, VGG-19 403 / 406 / 395 / 388 / 387.
+constexpr int64_t grid_min(int p) { return p <= 3 ? 8192 : p == 5 ? 32768 : 131072; }
 #if defined(__HIPCC__)
 __host__ __device__
 #endif
@@ -105,7 +112,7 @@ struct LayerDev {
     uint32_t cgroup_begin;  // first chunk group (kChunkGroup chunks) of the layer, numbered over all layers
     uint32_t grid;          // 1: a block grid.  Its bounds lie further below the forecast (twice the margin): a few more keys cost it next to nothing, a
                             //    bound that fails a third of a call (VGG-19, 200 calls on a carried residual: 9 failed with the margin as it is,
-                            //    none with twice), and none is handed out while the threshold still moves fast
+                            //    none with twice), and none is handed out while the threshold still moves fast or soon after one that failed
 };
 static_assert(sizeof(LayerDev) == 128, "LayerDev layout");
 

@@ -221,7 +221,7 @@ __device__ __forceinline__ bool init_layer_state(const LayerDev *__restrict__ la
         // after a failed bound the layer goes back to sampled bounds for a few calls -- where there
         // are any: past the calls that sample, the alternative would be the full map, and the
         // widened margin is tried at once
-        const bool paused = ps.cooldown > 0 && sampling;
+        const bool paused = ps.cooldown > 0 && (sampling || L.grid != 0u);
         // the call before failed: its threshold was a jump, not part of a trend -- the forecast
         // is that threshold itself
         const bool just_failed = ps.cooldown == kCooldownCalls;
@@ -1968,7 +1968,7 @@ __device__ __forceinline__ void find0(const Find0Args &f, int l) {
     // state, layer constants and counts are requested together: one round trip to memory
     // instead of three (each costs this one-workgroup-per-layer kernel about 2 us)
     const SelState st = f.state[l];
-    const uint32_t large = f.layers[l].large;
+    const uint32_t large = f.layers[l].large, grid = f.layers[l].grid;
     const bool cand = st.mode == kModeCandidates;                  // uniform
     const uint32_t *__restrict__ h = (cand ? f.hist_s : f.hist) + static_cast<size_t>(l) * kHistBins;
     const int nb = cand ? kFineBins : kHistBins, per = nb >> 8;
@@ -1983,8 +1983,8 @@ __device__ __forceinline__ void find0(const Find0Args &f, int l) {
     }
     if (st.done || st.mode == kModeSkip) return;
     // a large layer that is already on the full map (its sample gave no bound): its histogram
-    // comes with the fallback pass, and the select pass finds its first digit
-    if (st.mode == kModeFullMap && large != 0u) return;
+    // comes with the fallback pass, and the select pass finds its first digit (a block grid's has been counted by the block pass)
+    if (st.mode == kModeFullMap && large != 0u && grid == 0u) return;
     if (tid == 0) res.found = 0;
     const uint32_t incl = block_scan_incl(own, wave_tot);
     const uint32_t excl = incl - own;
@@ -2124,6 +2124,7 @@ struct GatherShared {
 
 struct GatherLists {
     const DirEntry *chunk_dir;       // all chunks by layer (fallback walk)
+    const ChunkInfo *chunks;         // ... each (block grids)
     const ChunkEntry *map_chunks;    // [n_map_chunks]
     const GroupEntry *cand_groups;   // [n_cand_groups]
     uint32_t n_layers, n_chunks, n_map_chunks, n_cand_groups;
@@ -2144,6 +2145,11 @@ struct GatherArgs {
     uint32_t *mask, *cmask;               // kept-element bitmask; selected-centre bitmask (nullable)
     uint32_t *chunk_cnt, *group_cnt;      // kept elements per chunk / chunk group, counted as the bits are set
 };
+
+// Entries of a layer's list.  While a block grid is on the candidate path its tile slots lie in the upper half of it.
+__device__ __forceinline__ uint32_t list_entries(const LayerDev &L, bool candidates) {
+    return L.grid != 0u && candidates ? L.list_cap / 2u - 1u : L.list_cap;
+}
 
 // The list of the layer the workgroup is working on.
 struct GatherList {
@@ -2183,13 +2189,15 @@ __device__ __forceinline__ void gather_stage_key(GatherShared &sh, bool hit, uns
     }
 }
 
-// A chunk of a layer that is always ranked on the full map.  All of a thread's 32 scores are requested before any is looked at, and
+// A chunk of a layer that is ranked on the full map: always, or, a block grid, in this call.  All of a thread's 32 scores are requested before any is looked at, and
 // places in the list are handed out once per chunk: what bounds this is the reading.  (Workgroups that strode over
 // the chunks, a quarter of a chunk and two barriers at a time: 35.9 us for the 62 MB of VGG-19's block scores, now 30.4: an atomic per key on
 // the second digit's counts is most of what is left.)
-__device__ __forceinline__ void gather_map_chunk(const GatherArgs &a, const ChunkEntry ce, GatherShared &sh) {
+constexpr uint32_t kNoDigit = 0xffffffffu;      // the layer's state tells its first digit
+__device__ __forceinline__ void gather_map_chunk(const GatherArgs &a, const ChunkEntry ce, GatherShared &sh, uint32_t digit) {
     constexpr int N = kChunk / 1024;
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // (or places in a chunk are worked out once and kept over a workgroup's chunks, in scratch memory)
     const uint32_t *__restrict__ src = a.keys + ce.arena_off;
     uint4 q[N];
     if (ce.len == static_cast<uint32_t>(kChunk)) {
@@ -2215,7 +2223,8 @@ __device__ __forceinline__ void gather_map_chunk(const GatherArgs &a, const Chun
     if (st.done || st.mode != kModeFullMap) return;                  // uniform
     for (int b = tid; b < kLevel1Bins; b += 256) sh.hist[b] = 0;
     __syncthreads();
-    const uint32_t lo = st.lo, width = 1u << st.span, shift1 = st.span - kLevel1Bits;
+    const uint32_t lo = digit != kNoDigit ? digit << kCoarseShift : st.lo, width = 1u << kCoarseShift;
+    constexpr uint32_t shift1 = kCoarseShift - kLevel1Bits;
     uint32_t hits = 0;                    // a bit per score
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -2416,19 +2425,52 @@ __device__ __forceinline__ void group_write(const GroupGeom &q, GroupMarks<SLOTS
 
 // Held to five waves per SIMD.
 template <bool COUNT, int PARTS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PARTS == 0 ? 4 : 5, 8))) void k_gather(const GatherArgs a, const GatherLists gl) {
     __shared__ GatherShared sh;
     const int tid = threadIdx.x;
-    if (blockIdx.x < gl.n_map_chunks) {
-        gather_map_chunk(a, gl.map_chunks[blockIdx.x], sh);
+    constexpr bool BLOCKS = PARTS == 0;       // block grids: whole groups of slots, and single bits
+    if (BLOCKS ? blockIdx.x - gl.n_map_chunks >= gl.n_slot_wgs : blockIdx.x < gl.n_map_chunks) {
+        uint32_t c = blockIdx.x, stride = 1u, end = c + 1u;           // a listed chunk ...
+        const bool listed = c < gl.n_map_chunks;
+        if (!listed) {                    // ... or those of a grid that has no bound in this call
+            if (a.flags[0] == 0u) return;
+            c -= gl.n_map_chunks + gl.n_slot_wgs;
+            stride = gridDim.x - gl.n_map_chunks - gl.n_slot_wgs;
+            end = gl.n_chunks;
+        }
+        for (; c < end; c += stride) {
+            ChunkEntry ce;
+            uint32_t digit = kNoDigit;
+            if (listed) {
+                ce = gl.map_chunks[c];
+            } else {
+                const ChunkInfo ci = gl.chunks[c];
+                const SelState &st = a.state[ci.layer];
+                if (a.layers[ci.layer].large == 0u || st.mode != kModeFullMap) continue;      // uniform
+                if (st.span == 0u && st.done == 0u) {      // its bound failed: the first digit, from the histogram that the rescoring has counted
+                    const uint32_t k = a.layers[ci.layer].k;
+                    if (tid < 64) {
+                        const WaveBucket wb = wave_find_bucket(a.hist + static_cast<size_t>(ci.layer) * kHistBins, k);
+                        if (tid == 0) sh.n = wb.found && wb.count != k - wb.above ? wb.bucket : kNoDigit;
+                    }
+                    __syncthreads();
+                    digit = sh.n;
+                    __syncthreads();
+                    if (digit == kNoDigit) continue;       // nothing left to rank
+                }
+                ce = ChunkEntry{ci.layer, ci.start, ci.len, 0u, ci.arena_off};
+            }
+            gather_map_chunk(a, ce, sh, digit);
+            if (!BLOCKS) break;
+            __syncthreads();
+        }
         return;
     }
     // role 1: listed slot groups, 2: fallback walk over all chunks
     const uint32_t wg = blockIdx.x - gl.n_map_chunks;
-    const int role = wg < gl.n_slot_wgs ? 1 : 2;
+    const int role = BLOCKS || wg < gl.n_slot_wgs ? 1 : 2;
     const uint32_t first = role == 1 ? wg : wg - gl.n_slot_wgs;
     const uint32_t stride = role == 1 ? gl.n_slot_wgs : gridDim.x - gl.n_map_chunks - gl.n_slot_wgs;
-    constexpr bool BLOCKS = PARTS == 0;       // block grids: whole groups of slots, and single bits
     constexpr int SHARES = BLOCKS ? 1 : PARTS, SLOTS = kSlotGroup / SHARES;
     const uint32_t n_items = role == 1 ? gl.n_cand_groups * SHARES : gl.n_chunks;
     const DirEntry *__restrict__ dir = gl.chunk_dir;
@@ -2508,7 +2550,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             }
             // the workgroup's shard of the layer's list: its own counter (own cache line) and region
             const uint32_t shard = blockIdx.x % L.list_shards;
-            list.cap = L.list_cap / L.list_shards;
+            list.cap = (BLOCKS ? list_entries(L, true) : L.list_cap) / L.list_shards;
             list.cnt = a.list_cnt + (static_cast<size_t>(l) * kListShards + shard) * kListCntStride;
             list.ent = a.list_ent + L.list_off + static_cast<size_t>(shard) * list.cap;
         }
@@ -2676,6 +2718,30 @@ struct FilterLayers {
     uint16_t id[kFilterLayers];
 };
 
+// The keys K of list[0, n) with K - base < 2^top into `stage` (as many as it holds; *nstage counts them all), by workgroup `sub` of nsub.
+__device__ __forceinline__ void filter_keys(const unsigned long long *__restrict__ list, uint32_t n, uint32_t sub, uint32_t nsub, unsigned long long base,
+                                            int top, unsigned long long *stage /*[kList2Cap], LDS*/, uint32_t *nstage /*LDS*/) {
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) *nstage = 0;
+    __syncthreads();
+    constexpr uint32_t U = 4;              // independent loads in flight per thread
+    for (uint32_t i0 = sub * U * kFilterThreads; i0 < n; i0 += nsub * U * kFilterThreads) {
+        unsigned long long K[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = i0 + u * kFilterThreads + tid;
+            K[u] = i < n ? list[i] : 0ull;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (i0 + u * kFilterThreads + tid < n && K[u] >= base && ((K[u] - base) >> top) == 0ull) {
+                const uint32_t pos = atomicAdd(nstage, 1u);
+                if (pos < static_cast<uint32_t>(kList2Cap)) stage[pos] = K[u];
+            }
+    }
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(kFilterThreads) void k_filter(const FilterLayers fl, const LayerDev *__restrict__ layers,
                                                            const SelState *__restrict__ state,
                                                            const uint32_t *__restrict__ hist1,
@@ -2715,24 +2781,7 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter(const FilterLayers fl
     const uint32_t shard = part % shards, sub = part / shards, nsub = (kFilterSplit + shards - 1 - shard) / shards;
     const uint32_t n = __shfl(c, static_cast<int>(shard), 64);
     const unsigned long long *__restrict__ list = list_ent + L.list_off + static_cast<size_t>(shard) * cap;
-    if (tid == 0) nstage = 0;
-    __syncthreads();
-    constexpr uint32_t U = 4;              // independent loads in flight per thread
-    for (uint32_t i0 = sub * U * kFilterThreads; i0 < n; i0 += nsub * U * kFilterThreads) {
-        unsigned long long K[U];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            const uint32_t i = i0 + u * kFilterThreads + tid;
-            K[u] = i < n ? list[i] : 0ull;
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u)
-            if (i0 + u * kFilterThreads + tid < n && K[u] >= base && ((K[u] - base) >> top) == 0ull) {
-                const uint32_t pos = atomicAdd(&nstage, 1u);
-                if (pos < static_cast<uint32_t>(kList2Cap)) stage[pos] = K[u];
-            }
-    }
-    __syncthreads();
+    filter_keys(list, n, sub, nsub, base, top, stage, &nstage);
     const uint32_t m = nstage;
     if (m == 0) return;                    // uniform
     if (tid == 0) base_pos = atomicAdd(&list2_cnt[l], m);        // counts past the capacity too
@@ -2752,6 +2801,15 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter(const FilterLayers fl
 // digit streams the list again; if the list itself overflowed (a huge number of nearly equal
 // scores, e.g. an all-zero layer), each digit streams the layer's keys from the score map or
 // the tile slots.
+// What one workgroup hands to others of the launch goes through these two, past the caches of an XCD, and wait_stores waits until
+// it is out.  (A fence at device scope instead writes back and invalidates the XCD's whole L2, once per wave: a call with a failed
+// bound on 1024 x 1024 took 284 us with fences where it took 106 without.)
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }      // a wave's own stores and adds
+
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishWaves = kFinishThreads / 64;
 
@@ -2827,41 +2885,49 @@ __device__ __forceinline__ void count_chunks(const CountShare &cs, uint32_t wg, 
     }
 }
 
-__global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__restrict__ layers, uint32_t n_layers, const CountShare cs,
-                                                           SelState *__restrict__ state,
-                                                           const uint32_t *__restrict__ hist,
-                                                           const uint32_t *__restrict__ hist1,
-                                                           const uint32_t *__restrict__ list_cnt,
-                                                           const unsigned long long *__restrict__ list_ent,
-                                                           const uint32_t *__restrict__ keys,
-                                                           const uint32_t *__restrict__ slot_cnt,
-                                                           const unsigned long long *__restrict__ slot_ent,
-                                                           const uint32_t *__restrict__ list2_cnt,
-                                                           const unsigned long long *__restrict__ list2_ent,
-                                                           PredState *__restrict__ pred /* nullable */) {
+constexpr int kFinishCtl = 8;      // this word of a layer's last list shard's line: how many of its workgroups have picked their keys
+// GRIDS (block plans that take the candidate path): in a call that ranks a large grid on its map -- it has no bound, or its bound failed -- the
+// bucket's list is as long as those that k_filter is for.  But a launch that nearly every call has nothing to do for costs 4 us, so such a
+// grid has kFilterSplit workgroups here instead: each picks the keys of its `part` of the list, and the last of them to be done with that
+// (nobody waits for another) goes on to rank them.  With one workgroup per grid this kernel took 91 us on VGG-19 without bounds, where
+// k_filter and k_finish took 7 + 9; now 13.
+template <bool GRIDS>
+__device__ __forceinline__ void finish_layer(int l, uint32_t part, const LayerDev *__restrict__ layers,
+    SelState *__restrict__ state, const uint32_t *__restrict__ hist, const uint32_t *__restrict__ hist1, uint32_t *__restrict__ list_cnt,
+    const unsigned long long *__restrict__ list_ent, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ slot_cnt,
+    const unsigned long long *__restrict__ slot_ent, uint32_t *__restrict__ list2_cnt, unsigned long long *__restrict__ list2_ent,
+    PredState *__restrict__ pred /* nullable */) {
     __shared__ uint32_t lh[kLevel1Bins];
     __shared__ unsigned long long sel[kStage];
     __shared__ uint32_t wave_tot[kFinishWaves];
     __shared__ DigitResult res;
-    __shared__ uint32_t nstage;
+    __shared__ uint32_t nstage, ticket;
     __shared__ unsigned long long rank_key;
-    const int l = blockIdx.x, tid = threadIdx.x;
-    if (blockIdx.x >= n_layers) {
-        count_chunks<kFinishWaves>(cs, blockIdx.x - n_layers, lh);
-        return;
-    }
+    const int tid = threadIdx.x;
     if (tid == 0) rank_key = 0ull;
     // lane s of every wave reads shard s's counter (unused shards stay 0); issued with the other loads
-    const uint32_t *__restrict__ cnt = list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
+    const uint32_t *cnt = list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
     const uint32_t c = (tid & 63) < kListShards ? cnt[(tid & 63) * kListCntStride] : 0u;
-    const uint32_t n2 = list2_cnt[l];     // keys that k_filter has already picked from a long list (0: none)
+    uint32_t n2 = GRIDS ? 0u : list2_cnt[l];     // keys that k_filter has already picked from a long list (0: none)
     const SelState st = state[l];
     const LayerDev L = layers[l];
+    // (the state of a grid with several workgroups is written when all of them have read it)
+    const bool several = GRIDS && L.G >= static_cast<uint32_t>(kBigMapLayer) && st.mode == kModeFullMap;
+    if (part != 0u && !several) return;
     for (int b = tid; b < kLevel1Bins; b += kFinishThreads) lh[b] = hist1[static_cast<size_t>(l) * kLevel1Bins + b];
     if (st.done || st.mode == kModeSkip) return;
     __syncthreads();
     uint32_t lo = st.lo, span = st.span, k_rem = st.k_rem;
-    if (st.mode == kModeFullMap && L.large != 0u) {
+    // (a grid's last workgroup goes on; of every other layer its only one)
+    auto is_last = [&]() {
+        if (!several) return true;
+        wait_stores();
+        __syncthreads();
+        if (tid == 0) ticket = atomicAdd(list_cnt + (static_cast<size_t>(l) * kListShards + kListShards - 1) * kListCntStride + kFinishCtl, 1u);
+        __syncthreads();
+        return ticket == static_cast<uint32_t>(kFilterSplit) - 1u;
+    };
+    if (st.mode == kModeFullMap && L.large != 0u && span == 0u) {
         // a large layer that fell back to the full map: its first digit, as the gather pass found it
         __shared__ uint32_t lh0[kHistBins];
         for (int b = tid; b < kHistBins; b += kFinishThreads) lh0[b] = hist[static_cast<size_t>(l) * kHistBins + b];
@@ -2871,7 +2937,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
         span = kCoarseShift;
         k_rem = r0.found ? L.k - r0.above : 0u;
         if (!r0.found || r0.count == k_rem) {      // nothing left to rank
-            if (tid == 0) {
+            if (is_last() && tid == 0) {
                 SelState ns = st;
                 ns.T = static_cast<unsigned long long>(lo) << 32;
                 ns.lo = lo;
@@ -2884,7 +2950,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
             return;
         }
     }
-    const uint32_t shards = L.list_shards, cap = L.list_cap / shards;
+    const uint32_t shards = L.list_shards, cap = (GRIDS ? list_entries(L, st.mode == kModeCandidates) : L.list_cap) / shards;
     const bool use_list = __syncthreads_and(c <= cap) != 0;      // every shard of the list fits
     DigitResult r = block_find_digit<kFinishWaves>(lh, kLevel1Bins, k_rem, wave_tot, &res);
     const uint32_t sh1 = span - kLevel1Bits;                     // score bits still open after this digit
@@ -2895,6 +2961,30 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
         k_rem -= r.above;
         done = r.count == k_rem;           // whole bucket taken: the threshold is its lower edge
     }
+    if constexpr (GRIDS) {
+        uint32_t total = c;
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) total += __shfl_xor(total, d, 64);
+        total = __shfl(total, 0, 64);
+        const bool long_list = several && !done && use_list && total > static_cast<uint32_t>(kStage);
+        if (long_list) {                   // (as in k_filter)
+            const uint32_t shard = part % shards, sub = part / shards, nsub = (kFilterSplit + shards - 1 - shard) / shards;
+            filter_keys(list_ent + L.list_off + static_cast<size_t>(shard) * cap, __shfl(c, static_cast<int>(shard), 64), sub, nsub, T,
+                        32 + static_cast<int>(sh1), sel, &nstage);
+            const uint32_t m = nstage;
+            __syncthreads();
+            if (m != 0u) {                 // uniform
+                if (tid == 0) nstage = atomicAdd(&list2_cnt[l], m);
+                __syncthreads();
+                const uint32_t b0 = nstage;
+                for (uint32_t i = tid; i < min(m, static_cast<uint32_t>(kStage)); i += kFinishThreads)
+                    if (b0 + i < static_cast<uint32_t>(kStage)) agent_store(&list2_ent[static_cast<size_t>(l) * kList2Cap + b0 + i], sel[i]);
+                __syncthreads();           // (nstage is used again)
+            }
+        }
+        if (!is_last()) return;            // uniform
+        if (long_list) n2 = agent_load(&list2_cnt[l]);
+    }
     if (!done) {
         // Keys still in question: K - T < 2^(32 + sh1).  Their remaining bits are ranked as the
         // number rel = K - T, most significant digit first.
@@ -2904,7 +2994,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
         uint32_t nsel = 0xffffffffu;
         if (use_list && n2 != 0u && n2 <= static_cast<uint32_t>(kStage)) {   // already picked by k_filter
             for (uint32_t i = tid; i < n2; i += kFinishThreads)
-                sel[i] = list2_ent[static_cast<size_t>(l) * kList2Cap + i] - base;
+                sel[i] = (GRIDS ? agent_load(&list2_ent[static_cast<size_t>(l) * kList2Cap + i]) : list2_ent[static_cast<size_t>(l) * kList2Cap + i]) - base;
             __syncthreads();
             nsel = n2;
         } else if (use_list) {             // stage the bucket's keys
@@ -2992,6 +3082,36 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__res
         state[l] = ns;
         publish_threshold(pred, l, L.large, L.k, T);
     }
+}
+__global__ __launch_bounds__(kFinishThreads) void k_finish(const LayerDev *__restrict__ layers, uint32_t n_layers, const CountShare cs,
+    SelState *__restrict__ state, const uint32_t *__restrict__ hist, const uint32_t *__restrict__ hist1, uint32_t *__restrict__ list_cnt,
+    const unsigned long long *__restrict__ list_ent, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ slot_cnt,
+    const unsigned long long *__restrict__ slot_ent, uint32_t *__restrict__ list2_cnt, unsigned long long *__restrict__ list2_ent,
+    PredState *__restrict__ pred /* nullable */) {
+    if (blockIdx.x >= n_layers) {
+        __shared__ uint32_t tot[2 * kFinishWaves];
+        count_chunks<kFinishWaves>(cs, blockIdx.x - n_layers, tot);
+        return;
+    }
+    finish_layer<false>(blockIdx.x, 0u, layers, state, hist, hist1, list_cnt, list_ent, keys, slot_cnt, slot_ent, list2_cnt, list2_ent, pred);
+}
+// Workgroups: the layers', those that count, then kFilterSplit - 1 more for each of the listed grids (the large ones).
+__global__ __launch_bounds__(kFinishThreads) void k_finish_grids(const LayerDev *__restrict__ layers, uint32_t n_layers, const CountShare cs,
+    SelState *__restrict__ state, const uint32_t *__restrict__ hist, const uint32_t *__restrict__ hist1, uint32_t *__restrict__ list_cnt,
+    const unsigned long long *__restrict__ list_ent, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ slot_cnt,
+    const unsigned long long *__restrict__ slot_ent, uint32_t *__restrict__ list2_cnt, unsigned long long *__restrict__ list2_ent,
+    PredState *__restrict__ pred /* nullable */,
+    const FilterLayers big, uint32_t n_count_wgs) {
+    const uint32_t b = blockIdx.x, others = n_layers + n_count_wgs;
+    if (b >= n_layers && b < others) {
+        __shared__ uint32_t tot[2 * kFinishWaves];
+        count_chunks<kFinishWaves>(cs, b - n_layers, tot);
+        return;
+    }
+    const uint32_t more = b - others;
+    const bool own = b < n_layers;
+    finish_layer<true>(own ? static_cast<int>(b) : big.id[more / (kFilterSplit - 1)], own ? 0u : 1u + more % (kFilterSplit - 1), layers, state, hist,
+                       hist1, list_cnt, list_ent, keys, slot_cnt, slot_ent, list2_cnt, list2_ent, pred);
 }
 
 // --------------------------------------------------------------- select --
@@ -3198,15 +3318,8 @@ __host__ __device__ constexpr uint32_t select_workgroups(uint32_t n_groups) { re
 static_assert(kHistBins == 4 * kSelectThreads && kChunk == 8 * kSelectThreads && kListShards == kSelectWaves && kTileRows * kTileCols == 4 * kSelectThreads,
               "bins, keys, shards and scores per thread");
 
-// What one workgroup hands to others of the launch goes through these two, past the caches of an XCD; select_shares_done waits until
-// it is out.  (A fence at device scope instead writes back and invalidates the XCD's whole L2, once per wave: a call with a failed
-// bound on 1024 x 1024 took 284 us with fences where it took 106 without.)
-template <typename T>
-__device__ __forceinline__ void agent_store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <typename T>
-__device__ __forceinline__ T agent_load(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void select_shares_done(uint32_t *done, uint32_t n) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // every wave: its own stores and adds
+    wait_stores();
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(done, n);
 }
@@ -4036,7 +4149,7 @@ __global__ __launch_bounds__(256) void k_mark_flat(const MarkFlatArgs m) {
         const uint32_t c = lane < kListShards ? cnt[lane * kListCntStride] : 0u;
         const SelState st = m.state[l];
         const LayerDev &L = m.layers[l];
-        const uint32_t shards = L.list_shards, cap = L.list_cap / shards;
+        const uint32_t shards = L.list_shards, cap = list_entries(L, true) / shards;
         if (st.mode != kModeCandidates || st.span == 0u || shard >= shards) return;
         const CountCtx cctx = count_ctx(L, m.chunk_cnt, m.group_cnt, m.gstride);
         auto mark = [&](unsigned long long K) {
@@ -4588,7 +4701,8 @@ __global__ __launch_bounds__(256) void k_scatter(const LayerDev *__restrict__ la
 // a grid is ranked on its map), only the blocks that reach it are recorded, per tile, and counted in fine bins: the map is neither written
 // nor read again by the gather and the mark, which have some 500 K keys to go through instead of 15.5 M scores.  VGG-19 at 2 %: this pass 296 /
 // 294 us (it is as fast as it streams), find0 to mark 67 / 34, the call 423.5 -> 377.5; ResNet-18 67.1 -> 53.7, ResNet-50 92.8 -> 78.5, 6000 x 6000
-// with p = 1 at 0.1 % 202 -> 130, 512 x 512 32.5 -> 28.1.  A variant of its own: on grids that stay on the map (300000 x 27) the code for the
+// with p = 1 at 0.1 % 202 -> 130, 512 x 512 32.5 -> 28.1.  A call without bounds (the first with a workspace, after new ratios or while the
+// threshold moves fast) takes what it does where no grid is on the candidate path: 398 / 393.  A variant of its own: on grids that stay on the map (300000 x 27) the code for the
 // candidates, unused, took the pass from 63 to 69 us.
 // FEED: tiles come from the launch's work feed (many tiles per workgroup) instead of a
 // fixed strided share.  MOM: Eq. 12's first line on the way in -- u_new = m*u + g (one rounded
@@ -4599,6 +4713,26 @@ struct BlockCapture {                  // what the candidate path adds: the boun
     uint32_t *hist_s, *list_cnt, *slot_cnt;
     unsigned long long *slot_ent;      // a slot per tile
 };
+// The score of the P x P block at `win` (LDS, row pitch `pitch`).  UNROLL: rows of it that are read together.
+template <int P, int UNROLL>
+__device__ __forceinline__ float block_score(const float *win, int pitch, double ca, double cb) {
+    const double n = static_cast<double>(P * P);
+    double sa = 0.0, ss = 0.0, sq = 0.0;
+#pragma unroll UNROLL
+    for (int dx = 0; dx < P; ++dx)
+#pragma unroll
+        for (int dy = 0; dy < P; ++dy) {
+            const double w = static_cast<double>(win[dx * pitch + dy]);
+            sa += fabs(w);
+            ss += w;
+            sq = fma(w, w, sq);
+        }
+    const double nsq = __dmul_rn(n, sq);
+    double d = var_n2_one_pass(ss, nsq);
+    if (P > 1 && d < kCancelFrac * nsq)          // the one-pass variance cancelled (rare)
+        d = __dmul_rn(n, window_ssd<P>(win, pitch, ss / n));
+    return static_cast<float>(nsi_from_var(sa, d, ca, cb));
+}
 template <int P, bool FEED, bool MOM, bool CAPTURE>
 __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ outer,
                                                    const DirEntry *__restrict__ tile_dir,
@@ -4635,8 +4769,7 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
     for (int b = tid; b < kHistBins; b += 256) lhist[b] = 0;
     if (CAPTURE && tid < 2) ncand[tid] = 0;
     __syncthreads();
-    const double n = static_cast<double>(P * P);
-    const double ca = alpha / n, cb = (1.0 - alpha) / n;
+    const double ca = alpha / (P * P), cb = (1.0 - alpha) / (P * P);
     uint32_t e = dir_lookup(tile_dir, n_layers, first);
     uint32_t cur_l = 0xffffffffu, hint_key = 0, recorded = 0, par = 0;
     bool active = false, capture = false;              // capture: the layer's blocks are held against its bound
@@ -4766,21 +4899,7 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
             const uint32_t bx = static_cast<uint32_t>(trow * kBlockTileRows + br);
             const uint32_t by = static_cast<uint32_t>(tcol * BCT + bc);
             if (bx < BR && by < BC) {
-                double sa = 0.0, ss = 0.0, sq = 0.0;
-#pragma unroll
-                for (int dx = 0; dx < P; ++dx)
-#pragma unroll
-                    for (int dy = 0; dy < P; ++dy) {
-                        const double w = static_cast<double>(tile[(br * P + dx) * TC + bc * P + dy]);
-                        sa += fabs(w);
-                        ss += w;
-                        sq = fma(w, w, sq);
-                    }
-                const double nsq = __dmul_rn(n, sq);
-                double d = var_n2_one_pass(ss, nsq);
-                if (P > 1 && d < kCancelFrac * nsq)          // the one-pass variance cancelled (rare)
-                    d = __dmul_rn(n, window_ssd<P>(&tile[(br * P) * TC + bc * P], TC, ss / n));
-                const float score = static_cast<float>(nsi_from_var(sa, d, ca, cb));
+                const float score = block_score<P, P>(&tile[(br * P) * TC + bc * P], TC, ca, cb);
                 const uint32_t key = __float_as_uint(score) & 0x7fffffffu;
                 if (!CAPTURE || !capture) {
                     score_map[I.elem_off + static_cast<size_t>(bx) * BC + by] = score;
@@ -4807,85 +4926,102 @@ __global__ __launch_bounds__(256) void k_block_nsi(const LayerDev *__restrict__ 
     if (active) flush();
 }
 
-// A layer whose bound failed, or whose tile overfilled its slot (rare): its blocks' scores once more, for the full map, from v, which the pass
-// above has stored.  Workgroups stride over the chunks of the block grids, a thread per block.  In one launch with k_find0 (up
-// to 256 layers: they look at the layers themselves), or behind it.  Strided reads of v bound it: with every bound failed it takes 380 us on
-// VGG-19 and the call 890, where the map in every call took 424.
+// A grid whose bound failed, or whose tile overfilled its slot: it is ranked on its full map, and its blocks' scores are formed once more, from v,
+// which the pass above has stored.  Workgroups stride over the tiles; in one launch with k_find0: they look at the layers themselves.
+// P: the largest side of the plan, which sizes the tile in LDS.  VGG-19 with every bound failed: 202 us here (380 where a thread read its block from
+// v, p floats from its neighbour's), the call 614, where a call that ranks them all on their maps takes 424.  (The scores stored by the
+// pass in every call, and only counted here, made that 505 and the calls whose bounds hold 383 instead of 377.)
 struct BlockRescore {
     const LayerDev *outer, *inner;
-    const ChunkInfo *chunks;           // of the block grids
-    uint32_t n_chunks;
+    const DirEntry *tile_dir;
+    uint32_t n_tiles;
     const float *v;
     float *score_map;
     uint32_t *hist, *list_cnt;
     double alpha;
-    bool behind;                       // k_find0 was a launch of its own
 };
+template <int P> constexpr int kBlockTileElems = kBlockTileRows * P * P * block_tile_cols(P);
+static_assert(kBlockTileElems<1> <= kBlockTileElems<3> && kBlockTileElems<3> <= kBlockTileElems<5> && kBlockTileElems<5> <= kBlockTileElems<7>,
+              "the largest side's tile holds any other's");
 template <int P>
-__device__ __forceinline__ float block_score(const float (&w)[P * P], double alpha) {
-    const double n = static_cast<double>(P * P);
-    double sa = 0.0, ss = 0.0, sq = 0.0;               // (the same sums in the same order as above)
+__device__ __forceinline__ void rescore_tile(const BlockRescore &r, const LayerDev &O, const LayerDev &I, uint32_t local, float *tile /*[kBlockTileElems], LDS*/,
+                                             uint32_t *lhist) {
+    constexpr int BCT = block_tile_cols(P), TC = BCT * P, TR = kBlockTileRows * P;
+    const uint32_t tid = threadIdx.x, trow = local / O.tiles_x, tcol = local - trow * O.tiles_x, x0 = trow * TR, y0 = tcol * TC;
+    const double ca = r.alpha / (P * P), cb = (1.0 - r.alpha) / (P * P);
+    const float *__restrict__ v = r.v + O.elem_off;
+    if constexpr (P == 1) {               // (elements in a row: a chunk by the workgroup of the tile of the same number, of which there are more)
+        constexpr uint32_t N = kChunk / 256;
+        if (local >= I.n_chunks) return;
+        const uint32_t start = local * kChunk, len = min(static_cast<uint32_t>(kChunk), I.G - start);
+        float e[N];
 #pragma unroll
-    for (int i = 0; i < P * P; ++i) {
-        const double e = static_cast<double>(w[i]);
-        sa += fabs(e);
-        ss += e;
-        sq = fma(e, e, sq);
-    }
-    const double nsq = __dmul_rn(n, sq);
-    double d = var_n2_one_pass(ss, nsq);
-    if (P > 1 && d < kCancelFrac * nsq) {
-        const double mean = ss / n;
-        double acc = 0.0;
+        for (uint32_t j = 0; j < N; ++j) e[j] = v[start + min(256 * j + tid, len - 1u)];
 #pragma unroll
-        for (int i = 0; i < P * P; ++i) {
-            const double e = static_cast<double>(w[i]) - mean;
-            acc += __dmul_rn(e, e);
-        }
-        d = __dmul_rn(n, acc);
-    }
-    return static_cast<float>(nsi_from_var(sa, d, alpha / n, (1.0 - alpha) / n));
-}
-template <int P>
-__device__ __forceinline__ void rescore_chunk(const BlockRescore &r, const ChunkInfo &ci, const float *__restrict__ v, uint32_t R, uint32_t C, uint32_t BC,
-                                              uint32_t *lhist) {
-    constexpr uint32_t U = P <= 3 ? 4 : P == 5 ? 2 : 1;      // blocks of a thread requested together
-    for (uint32_t e0 = threadIdx.x; e0 < ci.len; e0 += 256 * U) {
-        float w[U][P * P];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            const uint32_t b = ci.start + min(e0 + 256u * u, ci.len - 1u), x0 = b / BC * P, y0 = (b - b / BC * BC) * P;
-#pragma unroll
-            for (uint32_t i = 0; i < P * P; ++i) {
-                const uint32_t x = x0 + i / P, y = y0 + i % P;
-                w[u][i] = x < R && y < C ? v[static_cast<size_t>(x) * C + y] : 0.f;
-            }
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            if (e0 + 256u * u >= ci.len) break;
-            const float score = block_score<P>(w[u], r.alpha);
-            r.score_map[ci.arena_off + e0 + 256u * u] = score;
+        for (uint32_t j = 0; j < N; ++j) {
+            if (256 * j + tid >= len) break;
+            const float score = block_score<1, 1>(&e[j], 1, ca, cb);
+            r.score_map[I.elem_off + start + 256 * j + tid] = score;
             atomicAdd(&lhist[(__float_as_uint(score) & 0x7fffffffu) >> kCoarseShift], 1u);
         }
+        return;
     }
+    if ((O.C & 3u) == 0u) {
+        constexpr uint32_t V = TC / 4, N = (TR * V + 255) / 256;
+        float4 e[N];
+#pragma unroll
+        for (uint32_t j = 0; j < N; ++j) {
+            const uint32_t i = tid + 256 * j, row = i / V, y = y0 + 4 * (i - row * V);
+            e[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (row < TR && x0 + row < O.R && y < O.C) e[j] = *reinterpret_cast<const float4 *>(v + static_cast<size_t>(x0 + row) * O.C + y);
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < N; ++j)
+            if (tid + 256 * j < TR * V) *reinterpret_cast<float4 *>(&tile[4 * (tid + 256 * j)]) = e[j];
+    } else {
+        constexpr uint32_t N = (TC + 63) / 64;         // (whole rows per wave, as in the pass)
+#pragma unroll 1
+        for (uint32_t row = tid >> 6; row < TR; row += 4) {
+            float e[N];
+#pragma unroll
+            for (uint32_t j = 0; j < N; ++j) {
+                const uint32_t y = y0 + tid % 64 + 64 * j;
+                e[j] = x0 + row < O.R && y < O.C ? (v + static_cast<size_t>(x0 + row) * O.C)[y] : 0.f;
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < N; ++j)
+                if (tid % 64 + 64 * j < TC) tile[row * TC + tid % 64 + 64 * j] = e[j];
+        }
+    }
+    __syncthreads();
+    for (uint32_t q = tid; q < kBlockTileRows * BCT; q += 256) {
+        const uint32_t br = q / BCT, bc = q - br * BCT, bx = trow * kBlockTileRows + br, by = tcol * BCT + bc;
+        if (bx >= I.R || by >= I.C) continue;
+        const float score = block_score<P, P <= 3 ? P : 1>(&tile[br * P * TC + bc * P], TC, ca, cb);
+        r.score_map[I.elem_off + static_cast<size_t>(bx) * I.C + by] = score;
+        atomicAdd(&lhist[(__float_as_uint(score) & 0x7fffffffu) >> kCoarseShift], 1u);
+    }
+    __syncthreads();
 }
+template <int P>
 __global__ __launch_bounds__(256) void k_find0_blocks(const Find0Args f, const BlockRescore r) {
     __shared__ uint32_t lhist[kHistBins];
-    const uint32_t n_layers = static_cast<uint32_t>(f.n_layers), find_wgs = r.behind ? 0u : n_layers;
-    if (blockIdx.x < find_wgs) {
+    __shared__ __attribute__((aligned(16))) float tile[kBlockTileElems<P>];
+    const uint32_t n_layers = static_cast<uint32_t>(f.n_layers);
+    if (blockIdx.x < n_layers) {
         find0(f, blockIdx.x);
         return;
     }
     auto failed = [&](uint32_t l) {                    // (without a bound the pass above has written the map)
         if (r.inner[l].large == 0u || !bound_in_range(f.state[l].hint_key)) return false;
-        return r.behind ? f.state[l].mode == kModeFullMap : layer_falls_back(r.inner, f.state, f.hist_s, r.list_cnt, l);
+        return layer_falls_back(r.inner, f.state, f.hist_s, r.list_cnt, l);
     };
     const uint32_t tid = threadIdx.x;
-    if (r.behind ? f.flags[0] == 0u : !__syncthreads_or(tid < n_layers && failed(tid))) return;
+    static_assert(kGridLayers <= 256, "a layer per thread");
+    if (!__syncthreads_or(tid < n_layers && failed(tid))) return;
     for (uint32_t b = tid; b < static_cast<uint32_t>(kHistBins); b += 256) lhist[b] = 0u;
     __syncthreads();
-    uint32_t cur_l = 0xffffffffu;
+    uint32_t e = 0, cur_l = 0xffffffffu;
     bool active = false;
     auto flush = [&]() {
         uint32_t *__restrict__ gh = r.hist + static_cast<size_t>(cur_l) * kHistBins;
@@ -4894,25 +5030,27 @@ __global__ __launch_bounds__(256) void k_find0_blocks(const Find0Args f, const B
             if (c) { atomicAdd(&gh[b], c); lhist[b] = 0u; }
         }
     };
-    for (uint32_t c = blockIdx.x - find_wgs; c < r.n_chunks; c += gridDim.x - find_wgs) {
-        const ChunkInfo ci = r.chunks[c];
-        if (ci.layer != cur_l) {
+    const uint32_t stride = gridDim.x - n_layers;
+    for (uint32_t t = blockIdx.x - n_layers; t < r.n_tiles; t += stride) {
+        e = dir_advance(r.tile_dir, n_layers, e, t);
+        if (r.tile_dir[e].layer != cur_l) {
             __syncthreads();
             if (active) flush();
             __syncthreads();
-            cur_l = ci.layer;
+            cur_l = r.tile_dir[e].layer;
             active = failed(cur_l);
         }
-        if (!active) continue;
-        const LayerDev &O = r.outer[cur_l];
-        const uint32_t BC = r.inner[cur_l].C, R = O.R, C = O.C;
-        const float *__restrict__ v = r.v + O.elem_off;
-        switch (O.p) {
-            case 1: rescore_chunk<1>(r, ci, v, R, C, BC, lhist); break;
-            case 3: rescore_chunk<3>(r, ci, v, R, C, BC, lhist); break;
-            case 5: rescore_chunk<5>(r, ci, v, R, C, BC, lhist); break;
-            default: rescore_chunk<7>(r, ci, v, R, C, BC, lhist); break;
+        if (!active) {                                 // on to this workgroup's first tile of the next layer
+            const uint32_t nb = r.tile_dir[e + 1].begin;
+            t += (nb - t + stride - 1) / stride * stride - stride;
+            continue;
         }
+        const LayerDev &O = r.outer[cur_l], &I = r.inner[cur_l];
+        const uint32_t local = t - r.tile_dir[e].begin;
+        if (P == 7 && O.p == 7u) rescore_tile<7>(r, O, I, local, tile, lhist);
+        else if (P >= 5 && O.p == 5u) rescore_tile<5>(r, O, I, local, tile, lhist);
+        else if (P >= 3 && O.p == 3u) rescore_tile<3>(r, O, I, local, tile, lhist);
+        else rescore_tile<1>(r, O, I, local, tile, lhist);
     }
     __syncthreads();
     if (active) flush();
@@ -6139,6 +6277,7 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         a.group_cnt = inline_count ? reinterpret_cast<uint32_t *>(ws + w.group_cnt) : nullptr;
         GatherLists gl;
         gl.chunk_dir = chunk_dir;
+        gl.chunks = reinterpret_cast<const ChunkInfo *>(ws + w.chunk_info);
         gl.map_chunks = reinterpret_cast<const ChunkEntry *>(ws + w.map_chunks);
         gl.cand_groups = cand_groups;
         gl.n_layers = static_cast<uint32_t>(L);
@@ -6147,7 +6286,7 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         gl.n_cand_groups = n_cand_groups;
         const bool blocks = !plan->k_override.empty(), split = !blocks && inline_count && n_cand_groups < kSplitGroups;
         gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (split ? kSlotParts : 1u), kNumCUs * 8u);
-        const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u;
+        const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * (blocks ? 8u : 2u)) : 0u;
         if (gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs > 0)
         {
             const dim3 grid(gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs);
@@ -6159,11 +6298,12 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         }
         uint32_t *list2_cnt = reinterpret_cast<uint32_t *>(ws + w.list2_cnt);
         unsigned long long *list2_ent = reinterpret_cast<unsigned long long *>(ws + w.list2_ent);
-        if (!plan->big_map_layers.empty()) {   // long threshold-bucket lists: many workgroups pick the keys k_finish needs
-            FilterLayers fl = {};
-            const size_t n_big = plan->big_map_layers.size();
-            fl.listed = n_big <= static_cast<size_t>(kFilterLayers);
-            if (fl.listed) std::copy(plan->big_map_layers.begin(), plan->big_map_layers.end(), fl.id);
+        FilterLayers fl = {};
+        const size_t n_big = plan->big_map_layers.size();
+        fl.listed = n_big <= static_cast<size_t>(kFilterLayers);
+        if (fl.listed) std::copy(plan->big_map_layers.begin(), plan->big_map_layers.end(), fl.id);
+        const bool grids = blocks && plan->any_large;      // (at most kGridLayers of them)
+        if (n_big != 0u && !grids) {           // long threshold-bucket lists: many workgroups pick the keys k_finish needs
             hipLaunchKernelGGL(k_filter, dim3((fl.listed ? static_cast<uint32_t>(n_big) : static_cast<uint32_t>(L)) * kFilterSplit),
                                dim3(kFilterThreads), 0, stream, fl, layers, state, a.hist1, a.list_cnt, a.list_ent, list2_cnt, list2_ent);
         }
@@ -6177,8 +6317,14 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
             cs.gstride = gstride;
         }
         const uint32_t count_wgs = (cs.n_groups * 4u + kFinishWaves - 1u) / kFinishWaves;
-        hipLaunchKernelGGL(k_finish, dim3(L + count_wgs), dim3(kFinishThreads), 0, stream, layers, static_cast<uint32_t>(L), cs, state, hist, a.hist1,
-                           a.list_cnt, a.list_ent, a.keys, slot_cnt, slot_ent, list2_cnt, list2_ent, pred);
+        const unsigned finish_wgs = static_cast<unsigned>(L) + count_wgs;
+        if (grids)
+            hipLaunchKernelGGL(k_finish_grids, dim3(finish_wgs + static_cast<unsigned>(n_big) * (kFilterSplit - 1)), dim3(kFinishThreads), 0, stream,
+                               layers, static_cast<uint32_t>(L), cs, state, hist, a.hist1, a.list_cnt, a.list_ent, a.keys, slot_cnt, slot_ent,
+                               list2_cnt, list2_ent, pred, fl, count_wgs);
+        else
+            hipLaunchKernelGGL(k_finish, dim3(finish_wgs), dim3(kFinishThreads), 0, stream, layers, static_cast<uint32_t>(L), cs, state, hist, a.hist1,
+                               a.list_cnt, a.list_ent, a.keys, slot_cnt, slot_ent, list2_cnt, list2_ent, pred);
     }
     HIP_TRY(hipGetLastError());
     marks.close(4);
@@ -6228,7 +6374,7 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
             b.chunk_cnt = m.chunk_cnt;
             b.group_cnt = m.group_cnt;
             b.gstride = gstride;
-            const uint32_t n = b.n_map_chunks + b.n_bucket_wgs + (plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 2u) : 0u);
+            const uint32_t n = b.n_map_chunks + b.n_bucket_wgs + (plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 8u) : 0u);
             if (n != 0u) hipLaunchKernelGGL(k_mark_flat, dim3(n), dim3(256), 0, stream, b);
         } else if (n_wgs > 0) {
             if (inline_count) hipLaunchKernelGGL(k_mark<false>, dim3(n_wgs), dim3(256), 0, stream, m);
@@ -6633,11 +6779,15 @@ static int compress_blocks_impl(rsdgc_plan_t *plan, const float *grad, const Mom
     HIP_TRY(hipGetLastError());
     const Find0Args f = {inner, state, hist, cp.hist_s, reinterpret_cast<uint32_t *>(ws + w.flags), pred,
                          reinterpret_cast<uint4 *>(ws + w.chunk_cnt), static_cast<uint32_t>((w.list_cnt - w.chunk_cnt) / 16), L};
-    const bool behind = in->any_large && L > 256;
-    if (!in->any_large || behind) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
+    if (!in->any_large) hipLaunchKernelGGL(k_find0, dim3(L), dim3(256), 0, stream, f);
     if (in->any_large) {
-        const BlockRescore r = {outer, inner, inner_chunks, in->n_chunks, residual_out, score_map, hist, cp.list_cnt, plan->alpha, behind};
-        hipLaunchKernelGGL(k_find0_blocks, dim3((behind ? 0 : L) + std::min<uint32_t>(in->n_chunks, kNumCUs * 8u)), dim3(256), 0, stream, f, r);
+        const BlockRescore r = {outer, inner, reinterpret_cast<const DirEntry *>(ws_outer + plan->ws.all_tile_dir), plan->n_tiles_all, residual_out,
+                                score_map, hist, cp.list_cnt, plan->alpha};
+        const dim3 grid(L + std::min<uint32_t>(plan->n_tiles_all, kNumCUs * 8u));
+        if (have[7]) hipLaunchKernelGGL(k_find0_blocks<7>, grid, dim3(256), 0, stream, f, r);
+        else if (have[5]) hipLaunchKernelGGL(k_find0_blocks<5>, grid, dim3(256), 0, stream, f, r);
+        else if (have[3]) hipLaunchKernelGGL(k_find0_blocks<3>, grid, dim3(256), 0, stream, f, r);
+        else hipLaunchKernelGGL(k_find0_blocks<1>, grid, dim3(256), 0, stream, f, r);
     }
     rc = select_mark_count(in, ws, false, marks, pred, stream);
     if (rc != RSDGC_OK) return rc;
@@ -6876,7 +7026,10 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
 }
 
 int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, void *stream_) {
-    if (!plan || plan->blocks || !workspace || !paths) return RSDGC_EINVAL;
+    if (!plan || !workspace || !paths) return RSDGC_EINVAL;
+    const char *states = static_cast<const char *>(workspace) + plan->ws.state;
+    if (plan->blocks)                  // (the grids' states, in the inner plan's workspace)
+        states = static_cast<const char *>(workspace) + plan->ws.table_bytes + plan->inner->ws.state;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     std::vector<SelState> host;
     try {
@@ -6885,8 +7038,7 @@ int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, 
         return RSDGC_ENOMEM;
     }
     HIP_TRY(hipStreamSynchronize(stream));
-    HIP_TRY(hipMemcpy(host.data(), static_cast<const char *>(workspace) + plan->ws.state,
-                      sizeof(SelState) * plan->n_layers, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(host.data(), states, sizeof(SelState) * plan->n_layers, hipMemcpyDeviceToHost));
     for (int l = 0; l < plan->n_layers; ++l)
         paths[l] = static_cast<int32_t>(host[l].predicted >> kLastPathShift);
     return RSDGC_OK;

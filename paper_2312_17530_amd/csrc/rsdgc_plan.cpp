@@ -145,17 +145,16 @@ int build_tables(rsdgc_plan_s *plan) {
             if (plan->allow_candidates && k > 0 && per_tile <= double(d.slot_cap)) d.large = 1u;
         }
         if (grid) {
-            // A block grid's slots lie in its part of the score map, which is free while it is on the candidate path: half of a tile's
-            // blocks.  Grids whose tiles are mostly empty (narrow ones) have too little room for the hottest of them and stay on the map.
+            // A block grid's slots lie in the upper half of its list (the keys of a candidates' bucket are few): half of a tile's
+            // blocks.  Grids whose tiles are mostly empty (narrow ones) have too little room for the hottest of them and stay on the map; so do
+            // small ones, and those of a plan of very many layers.
             // The score map written, gathered from and marked from / candidates: VGG-19 at 2 % 424 / 378 us a call.
-            const uint64_t in_map = static_cast<uint64_t>(G) / 2 / d.n_tiles;
-            slots_in_map[l] = true;
-            d.slot_cap = static_cast<uint32_t>(std::min<uint64_t>(in_map, 0xfffe) & ~uint64_t(1));
-            d.large = plan->allow_candidates && k > 0 && d.slot_cap >= kBlockSlotMin && per_tile <= double(d.slot_cap) ? 1u : 0u;
+            d.slot_cap = static_cast<uint32_t>(std::min<uint64_t>(static_cast<uint64_t>(G) / 2 / d.n_tiles, 0xfffe) & ~uint64_t(1));
+            d.large = plan->allow_candidates && L <= kGridLayers && k > 0 && G >= grid_min(plan->block_p[l]) && d.slot_cap >= kBlockSlotMin && per_tile <= double(d.slot_cap) ? 1u : 0u;
         }
         d.hint_target = d.large ? static_cast<uint32_t>(std::ceil(want + 4.0 * std::sqrt(want) + 8.0)) : 0u;
         plan->any_large = plan->any_large || d.large;
-        if (!d.large && k > 0 && G >= kBigMapLayer) plan->big_map_layers.push_back(static_cast<uint16_t>(l));   // (l < 65536)
+        if ((!d.large || grid) && k > 0 && G >= kBigMapLayer) plan->big_map_layers.push_back(static_cast<uint16_t>(l));   // (l < 65536)
 
         plan->chunk_dir.push_back(DirEntry{chunk_begin, static_cast<uint32_t>(l)});
         plan->all_tile_dir.push_back(DirEntry{tile_begin_all, static_cast<uint32_t>(l)});
@@ -307,7 +306,7 @@ int build_tables(rsdgc_plan_s *plan) {
     w.cmask = off;        off = align_up(off + sizeof(uint32_t) * words, A);
     w.zero_end = off;
     w.slot_cnt = off;     off = align_up(off + sizeof(uint32_t) * sized_tiles, A);
-    // (a block grid's tile slots lie in its score map)
+    // (a block grid's tile slots lie in its list)
     w.slot_ent = off;     off = align_up(off + (plan->k_override.empty() ? sizeof(uint64_t) * size_t(plan->slot_entries) : 0), A);
     w.list_ent = off;     off = align_up(off + sizeof(uint64_t) * static_cast<size_t>(list_off), A);
     w.list2_ent = off;    off = align_up(off + sizeof(uint64_t) * 2048 * size_t(L), A);
@@ -319,6 +318,11 @@ int build_tables(rsdgc_plan_s *plan) {
     w.apply_starts = off; off = align_up(off + sizeof(uint32_t) * 2 * RSDGC_MAX_MSGS * static_cast<size_t>(plan->n_chunks), A);
     w.total = off;
 
+    for (LayerDev &d : plan->layers) {
+        if (d.grid == 0u) continue;
+        const uint64_t upper = d.list_off + d.list_cap / 2;        // (slots start at an even entry, from slot_ent on)
+        d.slot_off = (w.list_ent - w.slot_ent) / sizeof(uint64_t) + upper - (upper & 1u);
+    }
     for (int l = 0; l < L; ++l)                // (both sections start at a multiple of 256 bytes, a layer at one of 64 elements)
         if (slots_in_map[l]) plan->layers[l].slot_off = (w.nsi - w.slot_ent) / sizeof(uint64_t) + static_cast<uint64_t>(plan->layers[l].elem_off) / 2;
     for (GroupEntry &e : plan->cand_groups) {
