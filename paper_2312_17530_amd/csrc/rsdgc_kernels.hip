@@ -458,7 +458,6 @@ struct TileSeams {
     __device__ __forceinline__ TileSeams(const RunTile &rt, int R, int C)
         : top(rt.trow > 0 && !rt.above), bottom(rt.trow * kTileRows + kTileRows - H < R && !rt.below), left(rt.tcol > 0),
           right((rt.tcol + 1) * kTileCols < C) {}
-    __device__ __forceinline__ bool on_row(int row) const { return (row < H && top) || (row >= kTileRows - H && bottom); }
     __device__ __forceinline__ bool on_column(int col) const { return (col < H && left) || (col >= kTileCols - H && right); }
 };
 
@@ -1248,7 +1247,8 @@ void k_nsi(const NsiArgs a) {
 // nothing but the candidates' counts: bins for one layer, that of the launch's middle tile, a list for the others (a
 // few hundred candidates a workgroup in all).  They go to memory at the end: an atomic that is on its way holds up the next
 // run's loads (59.6 us where each of the others' candidates was added at once, of which a quarter of the elements had
-// them).
+// them).  Nothing is counted of a layer whose slots are overfilled: after a gradient four times as large, when every window reaches the
+// bounds, the adds to one bin of each layer took 9.2 ms.
 template <int P>
 struct SeamWave {
     static constexpr int kH = (P - 1) / 2, kRows = 6 * kH, kRunRows = kRun * kTileRows;      // rows around the edges, the upper one's first
@@ -1299,7 +1299,8 @@ __global__ __launch_bounds__(256) void k_seams(const NsiArgs a) {
             l = at.layer;
             L = a.layers[l];
             hint_key = a.state[l].hint_key;
-            active = a.state[l].mode == kModeCandidates && bound_in_range(hint_key);
+            // (with a tile overfilled the layer is ranked on its map, and what is added here would only be counted, at worst for every window)
+            active = __builtin_amdgcn_readfirstlane(a.state[l].mode == kModeCandidates && bound_in_range(hint_key) && a.state[l].overflow == 0u ? 1u : 0u) != 0u;
         }
         const RunTile rt(L, at.local_tile, t);
         const int R = static_cast<int>(L.R), C = static_cast<int>(L.C), tcol = rt.tcol;
@@ -1461,13 +1462,14 @@ __global__ __launch_bounds__(256) void k_seams(const NsiArgs a) {
             if (key >= key0) {
                 const bool second = row >= kTileRows;
                 const uint32_t cp = (second ? had1 : had0) + atomicAdd(&sh.ncand[second ? 1 : 0], 1u);
-                if (cp < cap)
-                    dst[(second ? static_cast<size_t>(tiles_x) * cap : 0u) + cp] = composite_key(key, static_cast<uint32_t>(me.x0 + row) * C32 + static_cast<uint32_t>(me.y0 + col));
+                if (cp >= cap) continue;       // (overfilled: as above)
+                dst[(second ? static_cast<size_t>(tiles_x) * cap : 0u) + cp] = composite_key(key, static_cast<uint32_t>(me.x0 + row) * C32 + static_cast<uint32_t>(me.y0 + col));
                 const uint32_t bin = min((key - key0) >> kFineShift, static_cast<uint32_t>(kFineBins - 1));
                 if (ml == hist_l) {
                     atomicAdd(&shared.lhist[bin], 1u);
                 } else {
-                    const uint32_t at = ml < (1u << 22) ? atomicAdd(&shared.n_others, 1u) : shared.kOthers;
+                    static_assert(kFineBins == 1 << 10, "a list entry's lower bits, under a layer's number (< 65536)");
+                    const uint32_t at = atomicAdd(&shared.n_others, 1u);
                     if (at < shared.kOthers) shared.others[at] = ml << 10 | bin;
                     else atomicAdd(&a.hist_s[static_cast<size_t>(ml) * kHistBins + bin], 1u);
                 }
@@ -1490,7 +1492,6 @@ __global__ __launch_bounds__(256) void k_seams(const NsiArgs a) {
         const uint32_t n = shared.lhist[b];
         if (n) atomicAdd(&gh[b], n);
     }
-    static_assert(kFineBins == 1 << 10, "a list entry's lower bits");
     for (uint32_t i = threadIdx.x; i < min(shared.n_others, shared.kOthers); i += 256)
         atomicAdd(&a.hist_s[static_cast<size_t>(shared.others[i] >> 10) * kHistBins + (shared.others[i] & (kFineBins - 1))], 1u);
 }
