@@ -29,6 +29,18 @@ constexpr int kListShards = 16;      // a layer's threshold-bucket list is fille
 constexpr int kGroupCntStride = 32;   // words between two chunk-group counters where many workgroups add to one: a cache line each
 constexpr int kGroupCntStrideLarge = 8;   // ... in plans of more than kInlineCountChunks chunks: few adds, but an emit that reads hundreds of them per chunk
 constexpr uint32_t kInlineCountChunks = 4096;   // plans up to this many chunks (33 M elements) count their kept elements where the bits are set
+// Where a plan's kept elements are counted.
+enum CountHow : int {
+    kCountMarked,     // as the gather and the mark set their bits (small plans)
+    kCountBeside,     // what the gather has marked beside the ranking, the rest as the mark sets the bits (large plans of few layers, most
+                      // of whose tiles are on the candidate path; block grids)
+    kCountAfter,      // in a launch of their own (k_count)
+};
+constexpr int group_cnt_stride(CountHow how) { return how == kCountMarked ? kGroupCntStride : how == kCountBeside ? kGroupCntStrideLarge : 1; }
+// Layers up to which a large plan's are counted beside the ranking, and as long as few of its tiles are marked from the map.  The call counted in a launch of
+// its own / beside: 19 layers (VGG-19) 415 / 411 us, 64 of 1024 x 1024 218 / 223, 128 of 768 x 768 252 / 261, 256 of 512 x 512 235 / 250, 5000 of
+// 48 x 180 to 87 x 711 1100 / 1400; VGG-19 all on the map 846 / 856, 20 % kept 1140 / 1150.
+constexpr int kBesideLayers = 32;
 constexpr int kListCntStride = 32;   // uint32 between two of them (one 128-byte line each)
 constexpr uint32_t kSelectTiles = 1024;  // a plan goes through k_select while its largest layer has at most so many tiles ...
 // ... and selects at most so many centres.  One layer, k_select / the launches it replaces: 512 x 512 with 13108 centres 30.7 / 32.3 us,
@@ -304,6 +316,7 @@ struct rsdgc_plan_s {
     uint64_t slot_entries = 0;          // composite keys in all tile slots together
     uint32_t n_slot_groups = 0;
     bool any_large = false;
+    rsdgc::CountHow count_how = rsdgc::kCountMarked;
     bool one_select = false;            // every layer that selects something is on the candidate path and small enough for k_select
     bool v_in_place = false;            // one arena: the main pass puts v in the residual's place (plans that do not go through k_select)
     std::vector<uint16_t> big_map_layers;   // layers of a million elements or more that are ranked on the full map

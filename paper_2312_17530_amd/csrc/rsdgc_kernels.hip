@@ -30,8 +30,8 @@
 //              (Section III-C: whole neighbourhoods are kept); full-map layers: every centre
 //              (small plans with every layer on the candidate path: find0 to mark are one launch, k_select)
 //   count      kept elements per chunk and per group of chunks (no scan kernel: each consumer
-//              adds up its own prefix from those): small plans count as they mark, large ones beside the
-//              ranking; a launch of its own for the centres only, where their lists are wanted
+//              adds up its own prefix from those): small plans count as they mark, large ones of few layers beside
+//              the ranking, the others in a launch of its own, as all do with the centres, where their lists are wanted
 //   emit       ordered (index, value) pairs and the residual update (Eq. 12): either only the
 //              kept elements are touched (v is stored already; by workgroups or, on large plans, by
 //              waves), or g and r are streamed again (one arena, smaller plans)
@@ -206,6 +206,8 @@ __device__ __forceinline__ bool init_layer_state(const LayerDev *__restrict__ la
                                                  uint32_t last_path) {
     SelState s;
     const LayerDev L = layers[l];
+    PredState ps = {};
+    if (pred) ps = pred[l];              // (beside the layer's constants: with thousands of layers this chain is what the last kernel waits for)
     bool fallback_work = false;
     s.T = L.k == 0 ? ~0ull : 0ull;   // no key reaches ~0: nothing is selected when k = 0
     s.k_rem = L.k;
@@ -217,7 +219,6 @@ __device__ __forceinline__ bool init_layer_state(const LayerDev *__restrict__ la
     s.span = 0;
     s.predicted = last_path << kLastPathShift;
     if (pred && s.mode == kModeCandidates) {
-        PredState ps = pred[l];
         // after a failed bound the layer goes back to sampled bounds for a few calls -- where there
         // are any: past the calls that sample, the alternative would be the full map, and the
         // widened margin is tried at once
@@ -1762,9 +1763,9 @@ __device__ __forceinline__ void publish_threshold(PredState *__restrict__ pred, 
 // and per group of kChunkGroup chunks, which the emit turns into output positions -- and the
 // pass over the mask is not needed.  A call on a
 // small plan is a chain of launches of a few microseconds each; on a large one the extra atomics of the gather
-// cost more than a pass (measured: VGG-19 +12 us, ResNet-18 -7 us), so there the gather counts nothing, k_finish's launch counts what it
-// has marked (CountShare), and only k_mark, which sets few bits, counts as it goes.  A mask word lies in one chunk: chunks
-// are 256 words long and a layer starts at a word boundary.
+// cost more than a pass (measured: VGG-19 +12 us, ResNet-18 -7 us), so there the gather counts nothing: in a plan of few layers k_finish's launch counts
+// what it has marked (CountShare), and only k_mark, which sets few bits, counts as it goes; in the others k_count goes over the finished mask
+// (CountHow).  A mask word lies in one chunk: chunks are 256 words long and a layer starts at a word boundary.
 struct CountCtx {
     uint32_t *chunk_cnt, *group_cnt;   // cleared by the find0 launch, or by the main pass where k_select follows; null: nothing is counted
     size_t word0;                      // the layer's first mask word
@@ -1829,7 +1830,8 @@ struct WindowGeom {
     int R, C, h;
 };
 constexpr uint32_t kMarkGroups = 512;      // (2^28 elements)
-template <bool LARGE>
+enum MarkCount : int { kMarkOnly, kMarkCounts, kMarkCountsShared };       // no counts, counts, the groups' in LDS first
+template <MarkCount HOW>
 __device__ __forceinline__ void mark_window(const WindowGeom &g, const CountCtx &c, uint32_t *groups /*[kMarkGroups], LDS*/, uint32_t i,
                                             uint32_t *__restrict__ mask, uint32_t *__restrict__ cmask) {
     const int xc = static_cast<int>(i / static_cast<uint32_t>(g.C));
@@ -1858,11 +1860,11 @@ __device__ __forceinline__ void mark_window(const WindowGeom &g, const CountCtx 
         if (n == 0u) return;
         const uint32_t cl = static_cast<uint32_t>((w - c.word0) >> 8), gl = cl / kChunkGroup;
         count_add_chunk_only(c, cl, n);
-        if (LARGE && gl < kMarkGroups) atomicAdd(&groups[gl], n);
+        if (HOW == kMarkCountsShared && gl < kMarkGroups) atomicAdd(&groups[gl], n);
         else count_add_group(c, gl, n);
     };
 #pragma unroll
-    for (int d = 0; d < RSDGC_MAX_P; ++d) {
+    for (int d = 0; d < RSDGC_MAX_P && HOW != kMarkOnly; ++d) {
         count(word[d], __popc(lo[d] & ~old_lo[d]));
         count(word[d] + 1, __popc(hi[d] & ~old_hi[d]));
     }
@@ -2839,10 +2841,11 @@ __device__ __forceinline__ void for_each_list_key(const unsigned long long *__re
     }
 }
 
-// The plans that do not count as they gather (CountCtx): the kept elements that the gather has marked, counted by workgroups of this launch
+// kCountBeside: the kept elements that the gather has marked, counted by workgroups of this launch
 // beside the ranking, which leaves most of the chip idle; k_mark adds the few that the threshold buckets contribute.  Ranking, marks and
 // a counting launch behind them / ranking with counts and marks that count: VGG-19 6.4 + 4.5 + 9.3 / 12.1 + 6.2 us, in one arena, where
-// more keys lie in the buckets, 9.8 + 6.4 + 9.1 / 10.8 + 8.2, 25088 x 4096 with p = 5 the call 250.9 -> 247.5.
+// more keys lie in the buckets, 9.8 + 6.4 + 9.1 / 10.8 + 8.2, 25088 x 4096 with p = 5 the call 250.9 -> 247.5.  Not with more layers, which the
+// ranking and the marks have workgroups enough for already, nor where most tiles are marked from the map (the rule: kBesideLayers).
 struct CountShare {
     const CountGroup *groups;      // null: nothing is counted here
     uint32_t n_groups;
@@ -2855,7 +2858,7 @@ template <int NW>
 __device__ __forceinline__ void count_chunks(const CountShare &cs, uint32_t wg, uint32_t *wave_tot /*[2 NW], LDS*/) {
     static_assert(kCountChunks == 16 && NW % 4 == 0, "four waves of four chunks");
     constexpr int N = kChunk / 32 / 32;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, which = wg * (NW / 4) + wave / 4u;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), which = wg * (NW / 4) + wave / 4u;
     uint32_t n = 0, group = 0;
     if (which < cs.n_groups) {
         const CountGroup gr = cs.groups[which];
@@ -3832,7 +3835,7 @@ __device__ __forceinline__ void or_bits_shared(uint32_t *__restrict__ mask, size
 // walk all tiles and take those of such layers.
 // Large plans: several workgroups per shard, a key per thread (a window's marks are two round trips to memory: in one arena on
 // VGG-19 12.2 us with one, 8.2 with four).
-constexpr uint32_t mark_parts(bool large) { return large ? 4u : 1u; }
+constexpr uint32_t mark_parts(MarkCount how) { return how == kMarkCountsShared ? 4u : 1u; }
 constexpr int kMarkCountSlots = 64;   // chunks a tile counts for in LDS (more only for rows beyond 32 K elements: directly)
 
 struct MarkArgs {
@@ -3856,14 +3859,15 @@ struct MarkArgs {
     float *resid;
 };
 
-template <bool LARGE>
+template <MarkCount HOW>
 __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
+    constexpr bool COUNT = HOW != kMarkOnly, SHARED = HOW == kMarkCountsShared;
     constexpr int MAXH = (RSDGC_MAX_P - 1) / 2;
     constexpr int NSEG = kTileCols / 64;       // 64-column segments of a tile row
     static_assert(kTileRows * NSEG == 64, "one lane of wave 0 per row segment");
     __shared__ unsigned long long bits[kTileRows + 2 * MAXH][NSEG + 2];   // [row][left, segments, right]
     __shared__ uint32_t ccnt[kMarkCountSlots];      // bits set by the tile, per chunk from the tile's first one on
-    __shared__ uint32_t groups[LARGE ? kMarkGroups : 1];      // bits set by the bucket keys, per chunk group
+    __shared__ uint32_t groups[SHARED ? kMarkGroups : 1];      // bits set by the bucket keys, per chunk group
     const LayerDev *__restrict__ layers = m.layers;
     const DirEntry *__restrict__ dir = m.dir;
     const SampleEntry *__restrict__ map_tiles = m.map_tiles;
@@ -3874,7 +3878,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     const uint32_t n_layers = m.n_layers;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x < m.n_bucket_wgs) {
-        constexpr uint32_t PARTS = mark_parts(LARGE);
+        constexpr uint32_t PARTS = mark_parts(HOW);
         const uint32_t l = blockIdx.x / (kListShards * PARTS), shard = blockIdx.x % kListShards, part = blockIdx.x / kListShards % PARTS;
         const uint32_t *__restrict__ cnt = m.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
         const uint32_t c = static_cast<uint32_t>(lane) < kListShards ? cnt[lane * kListCntStride] : 0u;
@@ -3886,7 +3890,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
                                  (static_cast<int>(Lc.p) - 1) / 2};
         const uint32_t shards = Lc.list_shards, cap = Lc.list_cap / shards;
         if (shard >= shards) return;
-        if (LARGE) {
+        if (SHARED) {
             for (uint32_t b = tid; b < kMarkGroups; b += 256) groups[b] = 0u;
             __syncthreads();
         }
@@ -3896,7 +3900,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
             const unsigned long long *__restrict__ keys = m.list_ent + Lc.list_off + static_cast<size_t>(shard) * cap;
             for (uint32_t i = part * 256u + tid; i < n; i += 256u * PARTS) {
                 const unsigned long long K = keys[i];
-                if (K >= Tc) mark_window<LARGE>(geom, cctx, groups, ~static_cast<uint32_t>(K), mask, cmask);
+                if (K >= Tc) mark_window<HOW>(geom, cctx, groups, ~static_cast<uint32_t>(K), mask, cmask);
             }
         } else {                               // the list overflowed: the bucket's keys are still in the tile slots
             const unsigned long long bucket_end = (static_cast<unsigned long long>(st.lo) + (1ull << st.span)) << 32;
@@ -3905,11 +3909,11 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
                 const unsigned long long *__restrict__ ent = m.slot_ent + Lc.slot_off + static_cast<size_t>(t) * Lc.slot_cap;
                 for (uint32_t i = tid; i < n; i += 256) {
                     const unsigned long long K = ent[i];
-                    if (K >= Tc && K < bucket_end) mark_window<LARGE>(geom, cctx, groups, ~static_cast<uint32_t>(K), mask, cmask);
+                    if (K >= Tc && K < bucket_end) mark_window<HOW>(geom, cctx, groups, ~static_cast<uint32_t>(K), mask, cmask);
                 }
             }
         }
-        if (LARGE) {
+        if (SHARED) {
             __syncthreads();
             for (uint32_t b = tid; b < min(kMarkGroups, (Lc.n_chunks + kChunkGroup - 1) / kChunkGroup); b += 256)
                 if (groups[b]) count_add_group(cctx, b, groups[b]);
@@ -3923,7 +3927,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
     const uint32_t n_items = listed ? m.n_map_tiles : m.n_tiles;
     if (first >= n_items) return;
     if (!listed && m.flags[0] == 0u) return;
-    if (tid < kMarkCountSlots) ccnt[tid] = 0u;       // (the tile loop's barriers come before the first use)
+    if (COUNT && tid < kMarkCountSlots) ccnt[tid] = 0u;       // (the tile loop's barriers come before the first use)
     uint32_t e = listed ? 0u : dir_lookup(dir, n_layers, first);
     uint32_t cur_l = 0xffffffffu;
     bool active = false, form_v = false;
@@ -4034,13 +4038,16 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
                 // its bits, per chunk (the two words may lie in different chunks)
 #pragma unroll
                 for (int part = 0; part < 2; ++part) {
-                    const uint32_t n = __popc(static_cast<uint32_t>(acc >> (32 * part)));
+                    const uint32_t n = COUNT ? __popc(static_cast<uint32_t>(acc >> (32 * part))) : 0u;
                     if (n) {
                         const uint32_t slot = static_cast<uint32_t>((w + part - cctx.word0) >> 8) - cl0;
                         if (slot < static_cast<uint32_t>(kMarkCountSlots)) atomicAdd(&ccnt[slot], n);
                         else count_add_chunk(cctx, cl0 + slot, n);
                     }
                 }
+            } else if (!COUNT) {
+                or_bits_shared(mask, pos, acc);
+                if (cmask) or_bits_shared(cmask, pos, own);
             } else {                                 // shared words: an OR tells which bits were new
                 const size_t w = pos >> 5;
                 const uint32_t b = static_cast<uint32_t>(pos & 31);
@@ -4076,7 +4083,7 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
         }
         __syncthreads();                        // the ballot words are reused by the next tile
         static_assert(kMarkCountSlots == 64, "one lane of the first wave per counted chunk");
-        if (tid < 64) {
+        if (COUNT && tid < 64) {
             count_flush_wave0(cctx, cl0, ccnt[tid]);
             ccnt[tid] = 0u;
         }
@@ -4086,9 +4093,9 @@ __global__ __launch_bounds__(256) void k_mark(const MarkArgs m) {
 // The mark of block grids (neighbourhoods of one "element").  Layers ranked on the full map: the mask is the comparison itself, so
 // there is no tile and no halo.  One wave per kFlatKeys consecutive scores -- a ballot over 64 of them is two mask words --, no
 // barrier, few registers: all waves of a plan as large as VGG-19 (62 MB of scores) are on their way at once.  28.5 us by tiles
-// in k_mark, 16.0 us so.  Layers on the candidate path: the keys of the threshold bucket's list that reach the threshold, a bit
+// in k_mark, 16.0 us so, 14 since a workgroup adds its chunk's count at once.  Layers on the candidate path: the keys of the threshold bucket's list that reach the threshold, a bit
 // each.  Counts as it marks, as k_mark does.  Workgroups, as there: the listed chunks, a layer's list shards, and those that walk all
-// chunks if some layer fell back.
+// chunks if some layer is on its map in this call.
 constexpr int kFlatKeys = 2048;
 struct MarkFlatArgs {
     const LayerDev *layers;
@@ -4101,13 +4108,15 @@ struct MarkFlatArgs {
     uint32_t *mask, *chunk_cnt, *group_cnt;
     uint32_t gstride;
 };
-// A quarter of a chunk, by one wave.
-__device__ __forceinline__ void mark_flat_quarter(const MarkFlatArgs &m, uint32_t layer, uint32_t chunk_start, uint32_t chunk_len, uint64_t arena_off) {
+// A quarter of a chunk, by one wave: the blocks it marked.
+__device__ __forceinline__ uint32_t mark_flat_quarter(const MarkFlatArgs &m, uint32_t layer, uint32_t chunk_start, uint32_t chunk_len, uint64_t arena_off) {
     constexpr uint32_t N = kFlatKeys / 64, PER = kChunk / kFlatKeys;
     static_assert(PER == 4 && N == 32, "four waves, a workgroup, per chunk");
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t lane = threadIdx.x & 63u;
+    asm volatile("" : "+v"(lane));        // (as in gather_map_chunk)
     const uint32_t first = wave * kFlatKeys;                 // inside the chunk
-    if (first >= chunk_len) return;
+    if (first >= chunk_len) return 0u;
     const uint32_t len = min(chunk_len - first, static_cast<uint32_t>(kFlatKeys));
     const uint32_t *__restrict__ src = m.keys + arena_off + first;
     uint32_t key[N];
@@ -4134,17 +4143,27 @@ __device__ __forceinline__ void mark_flat_quarter(const MarkFlatArgs &m, uint32_
     uint32_t n = lane < N ? static_cast<uint32_t>(__popcll(mine)) : 0u;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
-    if (lane == 0 && n != 0u) count_add_chunk(count_ctx(m.layers[layer], m.chunk_cnt, m.group_cnt, m.gstride), chunk_start / kChunk, n);
+    return n;
 }
-__global__ __launch_bounds__(256) void k_mark_flat(const MarkFlatArgs m) {
-    const uint32_t tid = threadIdx.x;
-    if (blockIdx.x < m.n_map_chunks) {
-        const ChunkEntry ce = m.map_chunks[blockIdx.x];
-        mark_flat_quarter(m, ce.layer, ce.start, ce.len, ce.arena_off);
+// A chunk, by a workgroup.
+__device__ __forceinline__ void mark_flat_chunk(const MarkFlatArgs &m, uint32_t layer, uint32_t start, uint32_t len, uint64_t arena_off, uint32_t *tot /*[4], LDS*/) {
+    const uint32_t n = mark_flat_quarter(m, layer, start, len, arena_off);
+    const CountCtx cctx = count_ctx(m.layers[layer], m.chunk_cnt, m.group_cnt, m.gstride);
+    if (len < static_cast<uint32_t>(kChunk)) {       // uniform (a short chunk, of which most plans have few: its waves need not meet)
+        if ((threadIdx.x & 63u) == 0u && n != 0u) count_add_chunk(cctx, start / kChunk, n);
         return;
     }
-    const uint32_t wg = blockIdx.x - m.n_map_chunks;
-    if (wg < m.n_bucket_wgs) {             // (as in k_mark)
+    if ((threadIdx.x & 63u) == 0u) tot[threadIdx.x >> 6] = n;
+    __syncthreads();
+    const uint32_t all = tot[0] + tot[1] + tot[2] + tot[3];
+    if (threadIdx.x == 0 && all != 0u) count_add_chunk(cctx, start / kChunk, all);
+    __syncthreads();
+}
+__global__ __launch_bounds__(256) void k_mark_flat(const MarkFlatArgs m) {
+    __shared__ uint32_t tot[4];
+    const uint32_t tid = threadIdx.x, wg = blockIdx.x - m.n_map_chunks;
+    const bool listed = blockIdx.x < m.n_map_chunks;
+    if (!listed && wg < m.n_bucket_wgs) {  // (as in k_mark)
         const uint32_t l = wg / kListShards, shard = wg % kListShards, lane = tid & 63u;
         const uint32_t *__restrict__ cnt = m.list_cnt + static_cast<size_t>(l) * kListShards * kListCntStride;
         const uint32_t c = lane < kListShards ? cnt[lane * kListCntStride] : 0u;
@@ -4175,22 +4194,90 @@ __global__ __launch_bounds__(256) void k_mark_flat(const MarkFlatArgs m) {
         }
         return;
     }
-    if (m.flags[0] == 0u) return;
-    const uint32_t before = m.n_map_chunks + m.n_bucket_wgs;
-    for (uint32_t c = blockIdx.x - before; c < m.n_chunks; c += gridDim.x - before) {
-        const ChunkInfo ci = m.chunks[c];
-        if (m.layers[ci.layer].large != 0u && m.state[ci.layer].mode == kModeFullMap) mark_flat_quarter(m, ci.layer, ci.start, ci.len, ci.arena_off);
+    if (!listed && m.flags[0] == 0u) return;
+    const uint32_t stride = gridDim.x - m.n_map_chunks - m.n_bucket_wgs, end = listed ? blockIdx.x + 1u : m.n_chunks;
+    for (uint32_t c = listed ? blockIdx.x : wg - m.n_bucket_wgs; c < end; c += listed ? 1u : stride) {
+        ChunkEntry ce;
+        if (listed) {
+            ce = m.map_chunks[c];
+        } else {
+            const ChunkInfo ci = m.chunks[c];
+            if (m.layers[ci.layer].large == 0u || m.state[ci.layer].mode != kModeFullMap) continue;      // uniform
+            ce = ChunkEntry{ci.layer, ci.start, ci.len, 0u, ci.arena_off};
+        }
+        mark_flat_chunk(m, ce.layer, ce.start, ce.len, ce.arena_off, tot);
     }
 }
 
 // ---------------------------------------------------------------- count --
-// Selected centres per chunk and per group of kChunkGroup chunks, from the finished mask, where their lists are wanted.  (Kept
-// elements: CountCtx, CountShare.)  One workgroup per kCountChunks = 16 chunks, four per wave.
+// Kept elements of the plans that count them here (kCountAfter; else `mask` is null), and selected centres where their lists are wanted, per
+// chunk and per group of kChunkGroup chunks, from the finished masks.  One workgroup per kCountChunks = 16 chunks; 16 adjacent threads read the 256 mask words of one
+// chunk (16 consecutive words each, as independent 8-byte loads) and add their popcounts with
+// four shuffles.  A workgroup adds its total to its chunk group's with one atomic -- four per
+// group (one atomic per chunk put 17 k of them on 9 cache lines and cost 18 us).
 constexpr int kCountThreads = 16 * kCountChunks;
-__global__ __launch_bounds__(kCountThreads) void k_count(const CountGroup *__restrict__ groups, const uint32_t *__restrict__ cmask,
-                                                         uint32_t *__restrict__ chunk_ccnt, uint32_t *__restrict__ group_ccnt, uint32_t gstride) {
-    __shared__ uint32_t wave_tot[2 * kCountThreads / 64];
-    count_chunks<kCountThreads / 64>(CountShare{groups, gridDim.x, cmask, chunk_ccnt, group_ccnt, gstride}, blockIdx.x, wave_tot);
+
+__global__ __launch_bounds__(kCountThreads) void k_count(const CountGroup *__restrict__ groups,
+                                                         const uint32_t *__restrict__ mask,
+                                                         const uint32_t *__restrict__ cmask,
+                                                         uint32_t *__restrict__ chunk_cnt,
+                                                         uint32_t *__restrict__ chunk_ccnt,
+                                                         uint32_t *__restrict__ group_cnt,
+                                                         uint32_t *__restrict__ group_ccnt, uint32_t gstride) {
+    constexpr int kPerThread = kChunk / 32 / 16;    // 16 words
+    static_assert(kCountChunks <= 64, "one lane of the first wave per chunk");
+    __shared__ uint32_t lcnt[2][kCountChunks];
+    const int tid = threadIdx.x;
+    const CountGroup gr = groups[blockIdx.x];
+    const uint32_t i0 = static_cast<uint32_t>(tid) * kPerThread;
+    // (a layer starts at a multiple of 64 elements, so word0 and i0 are even: 8-byte loads)
+    uint2 wa[kPerThread / 2], wb[kPerThread / 2];
+#pragma unroll
+    for (int j = 0; j < kPerThread / 2; ++j) {
+        const uint32_t i = i0 + 2 * j;
+        wa[j] = make_uint2(0u, 0u);
+        wb[j] = make_uint2(0u, 0u);
+        if (i + 1 < gr.n_words) {
+            if (mask) wa[j] = *reinterpret_cast<const uint2 *>(mask + gr.word0 + i);
+            if (cmask) wb[j] = *reinterpret_cast<const uint2 *>(cmask + gr.word0 + i);
+        } else if (i < gr.n_words) {
+            if (mask) wa[j].x = mask[gr.word0 + i];
+            if (cmask) wb[j].x = cmask[gr.word0 + i];
+        }
+    }
+    uint32_t a = 0, b = 0;
+#pragma unroll
+    for (int j = 0; j < kPerThread / 2; ++j) {
+        a += __popc(wa[j].x) + __popc(wa[j].y);
+        b += __popc(wb[j].x) + __popc(wb[j].y);
+    }
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) {
+        a += __shfl_xor(a, d, 64);
+        b += __shfl_xor(b, d, 64);
+    }
+    if ((tid & 15) == 0) {
+        lcnt[0][tid >> 4] = a;
+        lcnt[1][tid >> 4] = b;
+    }
+    __syncthreads();
+    if (tid < 64) {                        // the first wave: one lane per chunk
+        a = tid < kCountChunks ? lcnt[0][tid] : 0u;
+        b = tid < kCountChunks ? lcnt[1][tid] : 0u;
+        if (static_cast<uint32_t>(tid) < gr.n_chunks) {
+            if (mask) chunk_cnt[gr.first_chunk + tid] = a;
+            if (cmask) chunk_ccnt[gr.first_chunk + tid] = b;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            a += __shfl_xor(a, d, 64);
+            b += __shfl_xor(b, d, 64);
+        }
+        if (tid == 0) {                    // (the group totals are cleared by the find0 launch)
+            if (mask && a) atomicAdd(&group_cnt[static_cast<size_t>(gr.group) * gstride], a);
+            if (cmask && b) atomicAdd(&group_ccnt[static_cast<size_t>(gr.group) * gstride], b);
+        }
+    }
 }
 
 // The chunk's prefix -- kept elements of its layer before it -- is the sum of the totals of
@@ -6235,6 +6322,17 @@ extern "C" {
 
 const char *rsdgc_last_hip_error(void) { return g_hip_error; }
 
+// The counts from finished masks: the kept elements' (nullable), the centres' (nullable), or both in one launch.
+static void launch_count(const rsdgc_plan_s *plan, char *ws, const uint32_t *mask, const uint32_t *cmask, hipStream_t stream) {
+    if (!mask && !cmask) return;
+    const WsLayout &w = plan->ws;
+    const CountGroup *groups = reinterpret_cast<const CountGroup *>(ws + w.count_groups);
+    hipLaunchKernelGGL(k_count, dim3(plan->n_count_groups), dim3(kCountThreads), 0, stream, groups, mask, cmask,
+                       reinterpret_cast<uint32_t *>(ws + w.chunk_cnt), reinterpret_cast<uint32_t *>(ws + w.chunk_ccnt),
+                       reinterpret_cast<uint32_t *>(ws + w.group_cnt), reinterpret_cast<uint32_t *>(ws + w.group_ccnt),
+                       static_cast<uint32_t>(group_cnt_stride(plan->count_how)));
+}
+
 // The part of a compress call between the NSI passes and the emit: radix select of every
 // layer's threshold, marking of the kept elements, kept counts per chunk and chunk group.
 static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, StageMarks &marks,
@@ -6252,8 +6350,8 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
     uint32_t *mask = reinterpret_cast<uint32_t *>(ws + w.mask);
     uint32_t *cmask = want_centres ? reinterpret_cast<uint32_t *>(ws + w.cmask) : nullptr;
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
-    const bool inline_count = n_chunks <= kInlineCountChunks;    // small plan: the gather counts as it sets the bits
-    const uint32_t gstride = inline_count ? kGroupCntStride : kGroupCntStrideLarge;
+    const bool inline_count = plan->count_how == kCountMarked;
+    const uint32_t gstride = group_cnt_stride(plan->count_how);
     const GroupEntry *cand_groups = reinterpret_cast<const GroupEntry *>(ws + w.cand_groups);
     const uint32_t n_cand_groups = static_cast<uint32_t>(plan->cand_groups.size());
     const uint32_t *slot_cnt = reinterpret_cast<const uint32_t *>(ws + w.slot_cnt);
@@ -6285,9 +6383,9 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         gl.n_chunks = n_chunks;
         gl.n_map_chunks = static_cast<uint32_t>(plan->map_chunks.size());
         gl.n_cand_groups = n_cand_groups;
-        const bool blocks = !plan->k_override.empty(), split = !blocks && inline_count && n_cand_groups < kSplitGroups;
+        const bool blocks = !plan->k_override.empty() && plan->any_large, split = !blocks && inline_count && n_cand_groups < kSplitGroups;
         gl.n_slot_wgs = std::min<uint32_t>(n_cand_groups * (split ? kSlotParts : 1u), kNumCUs * 8u);
-        const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * (blocks ? 8u : 2u)) : 0u;
+        const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * (blocks ? 32u : 2u)) : 0u;
         if (gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs > 0)
         {
             const dim3 grid(gl.n_map_chunks + gl.n_slot_wgs + n_fb_wgs);
@@ -6303,13 +6401,12 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         const size_t n_big = plan->big_map_layers.size();
         fl.listed = n_big <= static_cast<size_t>(kFilterLayers);
         if (fl.listed) std::copy(plan->big_map_layers.begin(), plan->big_map_layers.end(), fl.id);
-        const bool grids = blocks && plan->any_large;      // (at most kGridLayers of them)
-        if (n_big != 0u && !grids) {           // long threshold-bucket lists: many workgroups pick the keys k_finish needs
+        if (n_big != 0u && !blocks) {           // long threshold-bucket lists: many workgroups pick the keys k_finish needs
             hipLaunchKernelGGL(k_filter, dim3((fl.listed ? static_cast<uint32_t>(n_big) : static_cast<uint32_t>(L)) * kFilterSplit),
                                dim3(kFilterThreads), 0, stream, fl, layers, state, a.hist1, a.list_cnt, a.list_ent, list2_cnt, list2_ent);
         }
         CountShare cs = {};
-        if (!inline_count && plan->any_large) {
+        if (plan->count_how == kCountBeside && plan->any_large) {
             cs.groups = reinterpret_cast<const CountGroup *>(ws + w.count_groups);
             cs.n_groups = plan->n_count_groups;
             cs.mask = mask;
@@ -6319,7 +6416,7 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         }
         const uint32_t count_wgs = (cs.n_groups * 4u + kFinishWaves - 1u) / kFinishWaves;
         const unsigned finish_wgs = static_cast<unsigned>(L) + count_wgs;
-        if (grids)
+        if (blocks)                            // (at most kGridLayers of them)
             hipLaunchKernelGGL(k_finish_grids, dim3(finish_wgs + static_cast<unsigned>(n_big) * (kFilterSplit - 1)), dim3(kFinishThreads), 0, stream,
                                layers, static_cast<uint32_t>(L), cs, state, hist, a.hist1, a.list_cnt, a.list_ent, a.keys, slot_cnt, slot_ent,
                                list2_cnt, list2_ent, pred, fl, count_wgs);
@@ -6350,7 +6447,8 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
         m.group_cnt = reinterpret_cast<uint32_t *>(ws + w.group_cnt);
         m.gstride = gstride;
         const uint32_t n_fb_wgs = plan->any_large ? std::min<uint32_t>(plan->n_tiles_all, kNumCUs * 4u) : 0u;
-        m.n_bucket_wgs = plan->any_large ? static_cast<uint32_t>(L) * kListShards * mark_parts(!inline_count) : 0u;
+        const MarkCount how = inline_count ? kMarkCounts : plan->count_how == kCountBeside ? kMarkCountsShared : kMarkOnly;
+        m.n_bucket_wgs = plan->any_large ? static_cast<uint32_t>(L) * kListShards * mark_parts(how) : 0u;
         m.list_cnt = reinterpret_cast<const uint32_t *>(ws + w.list_cnt);
         m.list_ent = reinterpret_cast<const unsigned long long *>(ws + w.list_ent);
         m.slot_cnt = slot_cnt;
@@ -6375,19 +6473,16 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
             b.chunk_cnt = m.chunk_cnt;
             b.group_cnt = m.group_cnt;
             b.gstride = gstride;
-            const uint32_t n = b.n_map_chunks + b.n_bucket_wgs + (plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 8u) : 0u);
+            const uint32_t n = b.n_map_chunks + b.n_bucket_wgs + (plan->any_large ? std::min<uint32_t>(n_chunks, kNumCUs * 32u) : 0u);
             if (n != 0u) hipLaunchKernelGGL(k_mark_flat, dim3(n), dim3(256), 0, stream, b);
         } else if (n_wgs > 0) {
-            if (inline_count) hipLaunchKernelGGL(k_mark<false>, dim3(n_wgs), dim3(256), 0, stream, m);
-            else hipLaunchKernelGGL(k_mark<true>, dim3(n_wgs), dim3(256), 0, stream, m);
+            if (how == kMarkOnly) hipLaunchKernelGGL(k_mark<kMarkOnly>, dim3(n_wgs), dim3(256), 0, stream, m);
+            else if (how == kMarkCounts) hipLaunchKernelGGL(k_mark<kMarkCounts>, dim3(n_wgs), dim3(256), 0, stream, m);
+            else hipLaunchKernelGGL(k_mark<kMarkCountsShared>, dim3(n_wgs), dim3(256), 0, stream, m);
         }
     }
     marks.close(5);
-    // the selected centres, when their lists are wanted, are counted from their mask
-    if (cmask)
-        hipLaunchKernelGGL(k_count, dim3(plan->n_count_groups), dim3(kCountThreads), 0, stream,
-                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), cmask, chunk_ccnt,
-                           reinterpret_cast<uint32_t *>(ws + w.group_ccnt), gstride);
+    launch_count(plan, ws, plan->count_how == kCountAfter && plan->k_override.empty() ? mask : nullptr, cmask, stream);
     marks.close(6);
     return RSDGC_OK;
 }
@@ -6428,11 +6523,7 @@ static int launch_select(rsdgc_plan_s *plan, char *ws, const float *grad, const 
     hipLaunchKernelGGL(k_select, dim3(n_wgs), dim3(kSelectThreads), 0, stream, a);
     marks.close(4);
     marks.close(5);
-    if (want_centres)
-        hipLaunchKernelGGL(k_count, dim3(plan->n_count_groups), dim3(kCountThreads), 0, stream,
-                           reinterpret_cast<const CountGroup *>(ws + w.count_groups), a.cmask,
-                           reinterpret_cast<uint32_t *>(ws + w.chunk_ccnt), reinterpret_cast<uint32_t *>(ws + w.group_ccnt),
-                           static_cast<uint32_t>(kGroupCntStride));
+    launch_count(plan, ws, nullptr, a.cmask, stream);
     HIP_TRY(hipGetLastError());
     marks.close(6);
     return RSDGC_OK;

@@ -208,6 +208,9 @@ int build_tables(rsdgc_plan_s *plan) {
     }
 
     plan->n_map_tiles = static_cast<uint32_t>(plan->map_tiles.size());
+    plan->count_how = plan->n_chunks <= kInlineCountChunks ? kCountMarked
+                      : !plan->k_override.empty() || (plan->any_large && L <= kBesideLayers && plan->n_map_tiles <= plan->n_tiles_all / 16) ? kCountBeside
+                                                                                                                                          : kCountAfter;
     plan->one_select = plan->any_large && plan->map_chunks.empty() && plan->n_chunks <= kInlineCountChunks;
     for (const LayerDev &d : plan->layers)
         plan->one_select = plan->one_select && d.n_tiles <= kSelectTiles && d.k <= kSelectMaxK;
@@ -373,7 +376,7 @@ int build_tables(rsdgc_plan_s *plan) {
                                                   first_group + c / kChunkGroup,
                                                   d.chunk_begin + c / kChunkGroup * kChunkGroup, first_group,
                                                   c + 1 == d.n_chunks ? 1u : 0u,
-                                                  uint32_t(plan->n_chunks <= kInlineCountChunks ? kGroupCntStride : kGroupCntStrideLarge), 0u};
+                                                  static_cast<uint32_t>(group_cnt_stride(plan->count_how)), 0u};
             }
             first_group += (d.n_chunks + kChunkGroup - 1) / kChunkGroup;
         }
