@@ -53,8 +53,8 @@ def stage_algorithmic_bytes(stage: str, n_elems: int, n_pairs: int, n_cand_elems
                             in_place: bool, momentum: bool = False) -> float:
     """Bytes a stage has to move by its own contract (float32 data).  With two residual
     arenas the NSI passes also store v = r + g (4 more bytes per element) and the emit only
-    touches the kept elements; so they do in place on large plans (p <= 5, from 2^25 elements on: there v
-    takes the residual's place).  On others the emit streams g and r again and rewrites r (`in_place`)."""
+    touches the kept elements; so they do in place where v takes the residual's place
+    (rsdgc_replaces_residual).  In other plans the emit streams g and r again and rewrites r (`in_place`)."""
     v_store = 0.0 if in_place else 4.0
     if momentum:              # Eq. 12 in full: read u as well, write the new u beside v
         v_store += 8.0
@@ -379,7 +379,7 @@ def main() -> int:
         variant = ("in_place" if args.in_place else "momentum" if args.momentum is not None else
                    "full_map" if args.full_map else "centres" if args.centres else "two_arenas")
         traffic, traffic_src = measured_traffic(w.name, variant, dom)
-        streamed_again = args.in_place and (G < 1 << 25 or args.full_map)
+        streamed_again = args.in_place and not sess.plan.replaces_residual
         alg = stage_algorithmic_bytes(dom, G, n_pairs, n_cand, streamed_again, args.momentum is not None)
         per_elem = 20.0 if args.momentum is not None else 12.0     # whole path: read g, (u,) r; write (u,) r
         achieved = alg / dur_s / 1e9

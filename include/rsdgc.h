@@ -132,6 +132,10 @@ int64_t rsdgc_out_capacity(const rsdgc_plan_t *plan);            /* sum_l min(k_
 int64_t rsdgc_centre_offset(const rsdgc_plan_t *plan, int32_t l);/* start of layer l's centres  */
 int64_t rsdgc_centre_capacity(const rsdgc_plan_t *plan);         /* sum_l k_l                   */
 size_t  rsdgc_workspace_bytes(const rsdgc_plan_t *plan);
+/* How rsdgc_compress with residual_out == residual updates the arena with this plan (and its
+ * ratios, path and work feed as they are): 1 v takes the residual's place as it is formed, 0 g and r
+ * are streamed once more behind the selection.  A block plan: 1.  NULL: -1.                    */
+int32_t rsdgc_replaces_residual(const rsdgc_plan_t *plan);
 
 /* ------------------------------------------------------------- compress --
  * One iteration of the sparsifier for all layers (Eq. 2's Sparse, Algorithm 1
@@ -146,9 +150,11 @@ size_t  rsdgc_workspace_bytes(const rsdgc_plan_t *plan);
  *             pointers between iterations; v is stored while the scores are
  *             computed and only the kept elements are touched afterwards:
  *             12 bytes of HBM traffic per element), or residual_out == residual
- *             for an update in place (large plans with p <= 5: v takes the
- *             residual's place as it is formed, 13 bytes per element; others:
- *             one more streaming pass over g and r, 20 bytes per element).
+ *             for an update in place (v takes the residual's place as it is
+ *             formed, 13 bytes per element, or one more streaming pass over g
+ *             and r, 20 bytes per element; the first where it is faster, about
+ *             from 2^25 elements on, with p <= 5 and most layers on the candidate
+ *             path, or p = 1: rsdgc_replaces_residual tells).
  *             Any other overlap is RSDGC_EINVAL.
  *   out_idx   [device] uint32, rsdgc_out_capacity entries.  Layer l's pairs
  *   out_val   [device] float32, same length.     start at rsdgc_out_offset(l);

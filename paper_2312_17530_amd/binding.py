@@ -22,7 +22,7 @@ EXPORTS = [
     "rsdgc_plan", "rsdgc_plan_set_ratios", "rsdgc_plan_set_path", "rsdgc_plan_set_work_feed", "rsdgc_plan_forget_workspace", "rsdgc_plan_destroy", "rsdgc_n_layers",
     "rsdgc_total_elems", "rsdgc_layer_offset", "rsdgc_layer_elems", "rsdgc_layer_k",
     "rsdgc_out_offset", "rsdgc_out_capacity", "rsdgc_centre_offset", "rsdgc_centre_capacity",
-    "rsdgc_workspace_bytes", "rsdgc_compress", "rsdgc_compress_static", "rsdgc_compress_momentum", "rsdgc_dynamic_ratios", "rsdgc_apply", "rsdgc_apply_blocks", "rsdgc_plan_blocks", "rsdgc_compress_blocks", "rsdgc_compress_blocks_momentum",
+    "rsdgc_workspace_bytes", "rsdgc_replaces_residual", "rsdgc_compress", "rsdgc_compress_static", "rsdgc_compress_momentum", "rsdgc_dynamic_ratios", "rsdgc_apply", "rsdgc_apply_blocks", "rsdgc_plan_blocks", "rsdgc_compress_blocks", "rsdgc_compress_blocks_momentum",
     "rsdgc_decompress_blocks", "rsdgc_nsi", "rsdgc_decompress",
     "rsdgc_last_paths", "rsdgc_profile_begin", "rsdgc_profile_end", "rsdgc_stage_name",
     "rsdgc_strerror", "rsdgc_last_hip_error",
@@ -87,6 +87,8 @@ def load() -> ctypes.CDLL:
         getattr(lib, name).restype = i64
     lib.rsdgc_workspace_bytes.argtypes = [vp]
     lib.rsdgc_workspace_bytes.restype = ctypes.c_size_t
+    lib.rsdgc_replaces_residual.argtypes = [vp]
+    lib.rsdgc_replaces_residual.restype = i32
     lib.rsdgc_compress.argtypes = [vp] * 11
     lib.rsdgc_compress.restype = ctypes.c_int
     lib.rsdgc_compress_static.argtypes = [vp] * 10
@@ -184,6 +186,11 @@ class Plan:
     @property
     def workspace_bytes(self) -> int:
         return load().rsdgc_workspace_bytes(self._h)
+
+    @property
+    def replaces_residual(self) -> bool:
+        """Whether an update in place stores v as it is formed (else g and r are streamed once more)."""
+        return load().rsdgc_replaces_residual(self._h) == 1
 
     def layer_offset(self, l: int) -> int:
         return load().rsdgc_layer_offset(self._h, l)

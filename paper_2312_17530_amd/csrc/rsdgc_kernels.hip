@@ -6346,7 +6346,6 @@ static int select_mark_count(rsdgc_plan_s *plan, char *ws, bool want_centres, St
     const uint32_t *hist = reinterpret_cast<const uint32_t *>(ws + w.hist);
     uint32_t *flags = reinterpret_cast<uint32_t *>(ws + w.flags);
     uint32_t *chunk_cnt = reinterpret_cast<uint32_t *>(ws + w.chunk_cnt);
-    uint32_t *chunk_ccnt = reinterpret_cast<uint32_t *>(ws + w.chunk_ccnt);
     uint32_t *mask = reinterpret_cast<uint32_t *>(ws + w.mask);
     uint32_t *cmask = want_centres ? reinterpret_cast<uint32_t *>(ws + w.cmask) : nullptr;
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
@@ -6547,6 +6546,19 @@ static NextCall next_call(const rsdgc_plan_s *plan, char *ws, const LayerDev *la
     return nc;
 }
 
+// Plans whose layers' candidates a workgroup can read through: everything up to the emit in one launch.
+static bool selects_in_one_launch(const rsdgc_plan_s *plan) {
+    bool one = plan->one_select && plan->work_feed != RSDGC_FEED_ON;
+    for (const PGroup &g : plan->groups) one = one && g.n_large_tiles < kFeedTiles;      // (no feed for the main pass)
+    return one;
+}
+// One arena: whether the main pass puts v in the residual's place as it goes (as a test asks for with the work feed).
+static bool replaces_residual(const rsdgc_plan_s *plan) {
+    return plan->any_large && !selects_in_one_launch(plan) && (plan->v_in_place || plan->work_feed == RSDGC_FEED_ON);
+}
+
+int32_t rsdgc_replaces_residual(const rsdgc_plan_t *plan) { return !plan ? -1 : plan->blocks || replaces_residual(plan) ? 1 : 0; }
+
 static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &mom,
                          const float *residual, float *residual_out, uint32_t *out_idx,
                          float *out_val, int32_t *out_counts, uint32_t *out_centre_idx,
@@ -6589,11 +6601,8 @@ static int compress_impl(rsdgc_plan_t *plan, const float *grad, const Momentum &
     uint32_t *cmask = want_centres ? reinterpret_cast<uint32_t *>(ws + w.cmask) : nullptr;
     float *nsi = reinterpret_cast<float *>(ws + w.nsi);
 
-    // plans whose layers' candidates a workgroup can read through: everything up to the emit in one launch
-    bool one_select = plan->one_select && plan->work_feed != RSDGC_FEED_ON;
-    for (const PGroup &g : plan->groups) one_select = one_select && g.n_large_tiles < kFeedTiles;      // (no feed for the main pass)
-    // one arena: the main pass puts v in the residual's place as it goes (as a test asks for with the work feed)
-    const bool v_in_place = in_place && plan->any_large && !one_select && (plan->v_in_place || plan->work_feed == RSDGC_FEED_ON);
+    const bool one_select = selects_in_one_launch(plan);
+    const bool v_in_place = in_place && replaces_residual(plan);
 
     StageMarks marks(plan, stream);
     if (!plan->ws_ready) {                 // the call before failed half way

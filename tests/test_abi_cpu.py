@@ -115,6 +115,24 @@ def test_work_feed_mode_is_validated():
     assert binding.load().rsdgc_plan_forget_workspace(None) == binding.RSDGC_EINVAL
 
 
+def test_form_of_the_update_in_place():
+    """v takes the residual's place in large plans with most layers on the candidate path: both sides of each line of the rule."""
+    def form(shapes, p, ratios, full_map=False, blocks=False):
+        plan = binding.rsdgc_plan(shapes, 3, 0.5, ratios, p, blocks=blocks)
+        if full_map:
+            binding.rsdgc_plan_set_path(plan, binding.RSDGC_PATH_FULL_MAP)
+        return plan.replaces_residual
+    m = (4096, 2048)
+    assert form([m] * 4, [3] * 4, [0.02] * 4) and not form([m] * 3, [3] * 3, [0.02] * 3)                # 2^25 elements
+    assert form([m] * 8, [5] * 8, [0.01] * 8) and not form([m] * 7, [5] * 7, [0.01] * 7)                # p = 5 counts half
+    assert form([m] * 16, [3] * 15 + [7], [0.01] * 16) and not form([m] * 16, [3] * 14 + [7] * 2, [0.01] * 16)
+    for p in (1, 3):                                                                                    # ranked on their maps
+        assert form([m] * 8, [p] * 8, [0.02] * 6 + [0.2] * 2) and not form([m] * 8, [p] * 8, [0.02] * 5 + [0.2] * 3)
+    assert not form([m] * 8, [3] * 8, [0.02] * 8, full_map=True)
+    assert form([m], [1], [0.02]) and not form([(512, 512)], [1], [0.02])                                # (selects in one launch)
+    assert form([m], [3], [0.02], blocks=True)
+
+
 def test_per_layer_neighbourhood_side():
     plan = binding.rsdgc_plan([(90, 90), (90, 90), (90, 90)], 3, 0.5, [0.1, 0.1, 0.1], [1, 3, 5])
     assert [plan.layer_k(l) for l in range(3)] == [810, 90, 33]
