@@ -133,7 +133,7 @@ int64_t rsdgc_centre_offset(const rsdgc_plan_t *plan, int32_t l);/* start of lay
 int64_t rsdgc_centre_capacity(const rsdgc_plan_t *plan);         /* sum_l k_l                   */
 size_t  rsdgc_workspace_bytes(const rsdgc_plan_t *plan);
 /* How rsdgc_compress with residual_out == residual updates the arena with this plan (and its
- * ratios, path and work feed as they are): 1 v takes the residual's place as it is formed, 0 g and r
+ * ratios and path as they are): 1 v takes the residual's place as it is formed, 0 g and r
  * are streamed once more behind the selection.  A block plan: 1.  NULL: -1.                    */
 int32_t rsdgc_replaces_residual(const rsdgc_plan_t *plan);
 

@@ -6552,10 +6552,8 @@ static bool selects_in_one_launch(const rsdgc_plan_s *plan) {
     for (const PGroup &g : plan->groups) one = one && g.n_large_tiles < kFeedTiles;      // (no feed for the main pass)
     return one;
 }
-// One arena: whether the main pass puts v in the residual's place as it goes (as a test asks for with the work feed).
-static bool replaces_residual(const rsdgc_plan_s *plan) {
-    return plan->any_large && !selects_in_one_launch(plan) && (plan->v_in_place || plan->work_feed == RSDGC_FEED_ON);
-}
+// One arena: whether the main pass puts v in the residual's place as it goes.
+static bool replaces_residual(const rsdgc_plan_s *plan) { return plan->any_large && plan->v_in_place && !selects_in_one_launch(plan); }
 
 int32_t rsdgc_replaces_residual(const rsdgc_plan_t *plan) { return !plan ? -1 : plan->blocks || replaces_residual(plan) ? 1 : 0; }
 

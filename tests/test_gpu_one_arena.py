@@ -21,8 +21,8 @@ def test_one_arena(sides, more, feed):
     wide, rows of odd length; a layer always ranked on the full map (whose v is formed when it is marked), one without
     anything to keep, frozen ones (no bound), few values (ties), a tile that overfills its slot; then a gradient that jumps, so that
     bounds fail after v has replaced the residual.  Calls without history, on predicted bounds and around the jump.  Plans that v replaces the
-    residual in because the work feed is asked for, because of their size (more < 0: a large layer without anything to keep) or their
-    single elements, by both forms of the emit; and two that it does not."""
+    residual in because of their size (more < 0: a large layer without anything to keep) or their single elements, by both forms of the
+    emit; the others, with and without the work feed, that it does not."""
     from paper_2312_17530_amd.session import Session
     shapes = [(40, 40), (33, 512), (16, 256), (17, 257), (48, 768), (18, 259), (35, 1030), (15, 511), (64, 27), (1, 700), (3, 2100),
               (130, 131), (49, 1028), (32, 513), (50, 64), (34, 300), (64, 520)]
@@ -56,3 +56,42 @@ def test_one_arena(sides, more, feed):
             assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
             assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
     assert more > 0 or len(failed) >= 10
+
+
+@pytest.mark.parametrize("sides", [[1, 1, 3], [3], [5], [7], [1, 3, 5, 7]], ids=["p1", "p3", "p5", "p7", "mixed"])
+@pytest.mark.parametrize("feed", [0, 2], ids=["shares", "fed"])
+def test_beside_a_large_layer(sides, feed):
+    """Small layers of every side whose v replaces the residual because of a large layer in the plan (one without anything to keep, so that the
+    oracle has little to do): with the tiles in fixed shares and from the work feed, which does not decide the form."""
+    from paper_2312_17530_amd.session import Session
+    shapes = [(40, 40), (33, 512), (16, 256), (17, 257), (48, 768), (18, 259), (35, 1030), (15, 511), (64, 27), (1, 700), (3, 2100),
+              (130, 131), (49, 1028), (32, 513), (50, 64), (34, 300), (64, 520), (4096, 8200)]
+    ratios = [0.9, 0.02, 0.02, 0.05, 0.03, 0.05, 0.02, 0.05, 0.03, 0.02, 0.02, 0.04, 0.01, 0.05, 0.0, 0.02, 0.02, 0.0]
+    frozen, tied, hot, big = {13}, {15}, 16, 17
+    ps = [sides[l % len(sides)] for l in range(big)] + [3]
+    rng = np.random.default_rng(170 + sides[0] + len(sides))
+    s = Session(shapes, 3, 0.5, ratios, ps, in_place=True, work_feed=feed)
+    assert s.plan.replaces_residual
+    small = Session(shapes[:big], 3, 0.5, ratios[:big], [3] * big, in_place=True, work_feed=feed)
+    assert not small.plan.replaces_residual
+    paths = []
+    for t in range(5):
+        scale = 10.0 if t == 4 else 1e-2
+        grads = [np.zeros(sh, np.float32) if l in frozen else (rng.integers(-1, 2, sh) * scale).astype(np.float32) if l in tied else
+                 (rng.standard_normal(sh, np.float32) * np.float32(scale)) for l, sh in enumerate(shapes)]
+        grads[hot][16:32, :256] *= np.float32(30.0)
+        resid = s.unpack(s.residual)
+        s.set_grad(grads)
+        s.compress()
+        paths.append(binding.rsdgc_last_paths(s.plan, s.workspace))
+        if t in (1, 2):
+            continue
+        after = s.unpack(s.residual)
+        for l, (idx, val, centres, _) in enumerate(s.results()):
+            if l == big:
+                assert len(idx) == 0 and np.array_equal(_bits(after[l]), _bits(resid[l] + grads[l])), t
+                continue
+            o = oracle.compress_layer(grads[l], resid[l], ps[l], 0.5, ratios[l])
+            assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
+            assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
+    assert paths[0].count(0) >= 10 and paths[4].count(1) > paths[3].count(1), paths
