@@ -290,6 +290,7 @@ struct PGroup {           // layers sharing one neighbourhood side: one launch p
     uint32_t large_dir_begin = 0;   // index of the first DirEntry in large_dir
     uint32_t large_dir_count = 0;   // entries excluding the sentinel
     uint32_t n_large_tiles = 0;
+    uint32_t most_large_tiles = 0;  // of one layer
     uint32_t large_list_begin = 0;  // index of their first SampleEntry in map_tiles (behind the map layers' tiles)
 };
 

@@ -1509,8 +1509,8 @@ struct NsiAllArgs {
 // and no test in front of the score.  A workgroup takes tiles as in nsi_pass; what reaches the bound goes straight to the tile's
 // slot.  FEED: the tiles come from the launch's work feed, under the rule of the other sides (fixed shares / by the feed: 134 M
 // elements 415 / 399 us a call, VGG-19 434 / 412, 72 M 233 / 238, 34 M 126 / 139).
-// What bounds it is the streaming of g, r and v.  Small groups of layers with other neighbourhoods (up to kRideTiles tiles
-// a side) ride along as workgroups of the same launch: alone, a side's launch takes 8 to 15 us however few its tiles are.
+// What bounds it is the streaming of g, r and v.  Groups of layers with other neighbourhoods that are not too large (kRideTiles,
+// kRideMost) ride along as workgroups of the same launch: alone, a side's launch takes 8 to 15 us however few its tiles are.
 // ResNet-50 with all its vectors, p after the kernels' sides: four launches of 24.1, 23.4, 34.4 and 14.6 us before, now two of 30.3 and 37.2;
 // the call, whose magnitudes no longer need the score map, 191.7 -> 138.0 us.  2048 x 1024 at 2 % 60.0 -> 38.9 us, 8192 x 4096 232.7 -> 136.8.
 struct FlatShared {
@@ -1680,9 +1680,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     else capture_flat<MOM, false>(a.side[0], sh.flat, b - a.first_wg[3], a.first_wg[4] - a.first_wg[3]);
 }
 constexpr uint32_t kRideTiles = 256;      // tiles of a side up to which it rides along: one round of workgroups ...
-// ... or, up to kRideMost, as many as there are of single elements: two launches one behind the other leave the chip half idle twice (ResNet-50
-// with all its vectors, 2790 and 2950 tiles: 31.4 and 36.4 us, in one launch 61.1; the call 117 -> 105 us, with centre lists 130 -> 120, with momentum 154 -> 139).
-constexpr uint32_t kRideMost = 4096;
+// ... or, up to kRideMost for all sides together and as many as there are of single elements, where none of the side's layers has more than
+// kRideLayer of them: two launches one behind the other leave the chip half idle twice, but more workgroups add more counts to the one
+// row of a large layer, and with more tiles the launch of all sides, at three waves per SIMD, takes longer than theirs.  The call in two launches / one,
+// so many tiles of p = 3 beside about as many of single elements: 1024 in one layer 81 / 73 us, 1536 90.5 / 89.4, 2048 106 / 107, 2816 131 / 147,
+// in two 131 / 123, in four 129 / 115, 3072 in 16 127 / 125, 3584 in 16 131 / 137; p = 5 1536 in one 91 / 87, 2816 130 / 137, in two 128 / 118, 3072
+// in 16 125 / 123, 3584 135 / 138; p = 7 94 / 90, 133 / 140, 132 / 122, 131 / 126, 141 / 140; with momentum p = 3 1024 in one 93 / 85, 2816 in two
+// 169 / 153, p = 7 2048 in one 131 / 139, 2816 in two 164 / 160.  ResNet-50 with all its vectors (2790 beside 2950) 230 / 214, with
+// momentum 258 / 243.
+constexpr uint32_t kRideMost = 3072, kRideLayer = 1536;
 
 // ------------------------------------------------------- ranking digits --
 // The k_l-th largest composite key of a layer (Algorithm 1's ranking, Eq. 11's k_l) is found
@@ -6179,7 +6185,7 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
     // the registers of the largest, which the main pass would feel)
     const bool together = PASS == kPassFullMap && find0_args && plan->groups.size() > 1 && plan->n_tiles_all < kFeedTiles;
     NsiAllArgs all = {};
-    uint32_t all_items = 0;
+    uint32_t all_items = 0, ridden = 0;
     // the main pass of single elements has a kernel of its own, which takes small groups of other sides along
     uint32_t n_flat = 0;
     for (const PGroup &g : plan->groups)
@@ -6204,7 +6210,9 @@ int launch_nsi(const rsdgc_plan_s *plan, char *ws, const float *grad, const floa
         a.feed_shift = 7;                  // 128 items per domain and stretch: one per resident workgroup of an XCD
         const uint32_t shares = PASS == kPassCaptureInPlace ? (items + kRun - 1) / kRun : items;       // what the workgroups take at a time
         while (a.feed_shift > 0 && (static_cast<uint32_t>(kFeedDomains) << a.feed_shift) > shares) --a.feed_shift;
-        if (together || (n_flat != 0u && (g.p == 1 || (items <= std::max(kRideTiles, std::min(n_flat, kRideMost)) && !flat_fed && PASS != kPassCaptureInPlace)))) {
+        const bool rides = items <= kRideTiles || (ridden + items <= std::min(n_flat, kRideMost) && g.most_large_tiles <= kRideLayer);
+        if (together || (n_flat != 0u && (g.p == 1 || (rides && !flat_fed && PASS != kPassCaptureInPlace)))) {
+            if (g.p != 1) ridden += items;
             all.side[g.p / 2] = a;
             all_items += items;
             continue;

@@ -251,6 +251,7 @@ int build_tables(rsdgc_plan_s *plan) {
             if (d.large) {
                 plan->large_dir.push_back(DirEntry{g.n_large_tiles, static_cast<uint32_t>(l)});
                 g.n_large_tiles += d.n_tiles;
+                g.most_large_tiles = std::max(g.most_large_tiles, d.n_tiles);
                 ++g.large_dir_count;
                 for (uint32_t t = 0; t < d.n_tiles; ++t) plan->map_tiles.push_back(SampleEntry{static_cast<uint32_t>(l), t});
             }
