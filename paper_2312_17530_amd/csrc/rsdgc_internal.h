@@ -67,8 +67,7 @@ constexpr int kSamplingCalls = 10;             // first calls with a workspace: 
 // Tile of the block-score kernel (block reading): kBlockTileRows block rows by
 // block_tile_cols(p) block columns, i.e. 8p x (8 .. 256)p elements.
 constexpr int kBlockTileRows = 8;
-constexpr uint32_t kBlockSlotMin = 64;       // entries of a tile slot from which a block grid takes the candidate path ...
-constexpr int kGridLayers = 256;             // ... in plans of up to so many layers (5000 layers of 48 x 180 to 87 x 711: 1290 us a call, on the map 832)
+constexpr int kGridLayers = 256;             // layers of a plan up to which its block grids take the candidate path (5000 layers of 48 x 180 to 87 x 711: 1290 us a call, on the map 832)
 // ... from so many blocks on.  The threshold of a smaller grid moves too much from call to call for the bounds below it, and scores over wide
 // blocks lie so close together that a bound with a margin catches half of the grid.  A call on a residual carried through four gradients, all
 // on the map / from 1024 blocks or fewer / from 8192 / 32768 / 131072: p = 3 ResNet-18 77 / 82 / 78 / 76 / 79, ResNet-50 109 / 119 / 104 / 107 / 108,

@@ -146,11 +146,13 @@ int build_tables(rsdgc_plan_s *plan) {
         }
         if (grid) {
             // A block grid's slots lie in the upper half of its list (the keys of a candidates' bucket are few): half of a tile's
-            // blocks.  Grids whose tiles are mostly empty (narrow ones) have too little room for the hottest of them and stay on the map; so do
-            // small ones, and those of a plan of very many layers.
+            // blocks.  Grids whose tiles are less than half filled (narrow ones) have too little room for the hottest of them, and a pass that
+            // is bound by their many tiles, and stay on the map (20 layers of 1639 x 10 to 67695 x 10 with p = 1: 208 us a call, as candidates
+            // 236); so do small ones, and those of a plan of very many layers.
             // The score map written, gathered from and marked from / candidates: VGG-19 at 2 % 424 / 378 us a call.
             d.slot_cap = static_cast<uint32_t>(std::min<uint64_t>(static_cast<uint64_t>(G) / 2 / d.n_tiles, 0xfffe) & ~uint64_t(1));
-            d.large = plan->allow_candidates && L <= kGridLayers && k > 0 && G >= grid_min(plan->block_p[l]) && d.slot_cap >= kBlockSlotMin && per_tile <= double(d.slot_cap) ? 1u : 0u;
+            const bool filled = 2 * G >= static_cast<int64_t>(d.n_tiles) * kBlockTileRows * block_tile_cols(plan->block_p[l]);
+            d.large = plan->allow_candidates && L <= kGridLayers && k > 0 && G >= grid_min(plan->block_p[l]) && filled && per_tile <= double(d.slot_cap) ? 1u : 0u;
         }
         d.hint_target = d.large ? static_cast<uint32_t>(std::ceil(want + 4.0 * std::sqrt(want) + 8.0)) : 0u;
         plan->any_large = plan->any_large || d.large;

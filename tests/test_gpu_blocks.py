@@ -68,7 +68,7 @@ def _against_oracle(s, grads, resid, mom, m, ps, ratios, tag):
 
 
 # grids of block rows by block columns that are large enough for the candidate path: they end on, before and after a tile of 8 by 256, 64 or 32
-_GRIDS = {1: [(32, 256), (33, 257), (40, 255), (8, 1025), (129, 70)], 3: [(128, 64), (129, 65), (127, 66), (8, 1030), (64, 130)],
+_GRIDS = {1: [(32, 256), (33, 513), (40, 255), (8, 1025), (72, 129)], 3: [(128, 64), (129, 70), (127, 66), (8, 1030), (64, 130)],
           5: [(256, 128), (257, 129), (255, 130)], 7: [(512, 256), (513, 257)]}
 
 
