@@ -228,9 +228,11 @@ int build_tables(rsdgc_plan_s *plan) {
         const int64_t all = of_side[1] + of_side[3] + of_side[5] + of_side[7];
         // Layers that are always ranked on their map gain nothing by it -- the mark forms their v, which is read once more where the emit
         // would form it -- and lose where they keep much: VGG-19 with the mapped layers' ratio 20 %, the others' 2 %: none of them mapped
-        // 570 / 460, 12 % of the elements 669 / 578, 14 % 669 / 581, 72 % 1044 / 1182, all 1150 / 1383; p = 1, half of 67 M 496 / 509.
+        // 570 / 460, 12 % of the elements 669 / 578, 14 % 669 / 581, 72 % 1044 / 1182, all 1150 / 1383; single elements, of which the others gain less the
+        // more is kept, half of 67 M with 2 and 20 % 496 / 509, a quarter of VGG-19 with 5 to 33 % 767 / 840.
         int64_t mapped = 0;
-        for (const LayerDev &d : plan->layers) mapped += d.large == 0u && d.k > 0u ? d.G : 0;
+        for (const LayerDev &d : plan->layers)
+            if (d.large == 0u && d.k > 0u) mapped += d.p == 1u ? 2 * static_cast<int64_t>(d.G) : d.G;
         plan->v_in_place = mapped <= all / 4 && (all == of_side[1] || (of_side[7] <= all / 16 && of_side[1] + of_side[3] + of_side[5] / 2 >= kInPlaceElems));
     }
 

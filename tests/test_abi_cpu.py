@@ -126,8 +126,8 @@ def test_form_of_the_update_in_place():
     assert form([m] * 4, [3] * 4, [0.02] * 4) and not form([m] * 3, [3] * 3, [0.02] * 3)                # 2^25 elements
     assert form([m] * 8, [5] * 8, [0.01] * 8) and not form([m] * 7, [5] * 7, [0.01] * 7)                # p = 5 counts half
     assert form([m] * 16, [3] * 15 + [7], [0.01] * 16) and not form([m] * 16, [3] * 14 + [7] * 2, [0.01] * 16)
-    for p in (1, 3):                                                                                    # ranked on their maps
-        assert form([m] * 8, [p] * 8, [0.02] * 6 + [0.2] * 2) and not form([m] * 8, [p] * 8, [0.02] * 5 + [0.2] * 3)
+    for p, n in ((1, 1), (3, 2)):                                                                       # ranked on their maps
+        assert form([m] * 8, [p] * 8, [0.02] * (8 - n) + [0.2] * n) and not form([m] * 8, [p] * 8, [0.02] * (7 - n) + [0.2] * (n + 1))
     assert not form([m] * 8, [3] * 8, [0.02] * 8, full_map=True)
     assert form([m], [1], [0.02]) and not form([(512, 512)], [1], [0.02])                                # (selects in one launch)
     assert form([m], [3], [0.02], blocks=True)
