@@ -18,7 +18,9 @@
  *     Padding elements between layers are never read or written.
  *   - Pointers marked [device] must be device memory of the current HIP
  *     device; [host] is ordinary host memory.  The caller owns every buffer;
- *     the library never allocates, frees or synchronises device memory.
+ *     the library never allocates, frees or synchronises device memory.  (A
+ *     plan that rsdgc_dynamic_ratios was called with owns a small block of
+ *     pinned host memory, see there.)
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All device work is enqueued on it and the call returns without waiting.
  *   - Every function returning int returns RSDGC_OK (0) or a negative
@@ -97,7 +99,12 @@ int rsdgc_plan_set_ratios(rsdgc_plan_t *plan, const double *keep_ratio);
  *                        and so is a layer whose bound would lie outside 2^-40 .. 2^40
  *                        (scores of the order of 1e-12 or 1e12).
  *   RSDGC_PATH_FULL_MAP  every layer writes its full score map and ranks it with
- *                        histogram passes over all elements.                       */
+ *                        histogram passes over all elements.
+ * A block plan takes the setting too: with RSDGC_PATH_AUTO its large block grids (from
+ * 8192 blocks on for p <= 3, 32768 for p = 5, 131072 for p = 7, with up to about 6 %
+ * kept, in plans of up to 256 layers) record only the blocks whose score reaches a bound
+ * predicted from the two calls before, and are ranked on their map in a call without one
+ * or whose bound fails.                                                            */
 #define RSDGC_PATH_AUTO      0
 #define RSDGC_PATH_FULL_MAP  1
 int rsdgc_plan_set_path(rsdgc_plan_t *plan, int32_t path);
@@ -119,6 +126,11 @@ int rsdgc_plan_set_work_feed(rsdgc_plan_t *plan, int32_t mode);
  * prepares it afresh.  Host side only; no GPU work.                          */
 int rsdgc_plan_forget_workspace(rsdgc_plan_t *plan);
 
+/* Frees the plan; NULL is allowed.  No call with the plan may still be running
+ * on the host.  Host only, with two exceptions: a plan whose profiling was begun
+ * and not ended waits for the recorded events (rsdgc_profile_end), and one that
+ * rsdgc_dynamic_ratios was called with frees its pinned host memory, which may
+ * wait for the device.                                                       */
 void rsdgc_plan_destroy(rsdgc_plan_t *plan);
 
 /* Host queries; l in [0, n_layers).  Invalid arguments give -1 (0 for size_t). */
@@ -239,11 +251,19 @@ int rsdgc_compress_momentum(rsdgc_plan_t *plan, const float *grad, const float *
  *   ratios_out  [host] double[n_layers]; feed it to rsdgc_plan_set_ratios.
  * Runs on `stream` and waits (a per-epoch step, not part of the per-iteration
  * path): one streaming pass from 2^20 weights on (and up to 4096 layers), four
- * more where a sample of the weights misled it; otherwise four.  Uses the
- * workspace's scratch only, so it must not overlap a compress call that uses the
- * same workspace.                                                            */
+ * more where a sample of the weights misled it; otherwise four
+ * (rsdgc_ratio_passes tells).  Uses the workspace's scratch, so it must not overlap
+ * a compress call that uses the same workspace, and, for the one pass, 8 bytes per
+ * layer of pinned host memory that the counts are written to.  The plan owns that
+ * block: its first such call allocates it (hipHostMalloc, so that call must not be
+ * made while a stream capture in global mode is under way; without it the four
+ * passes are made), rsdgc_plan_destroy frees it.                              */
 int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global_ratio,
                          double *ratios_out, void *workspace, void *stream);
+
+/* Streaming passes over the weights that the plan's last rsdgc_dynamic_ratios made:
+ * 1, 4 or 5 (see there); 0 before the first, -1 for NULL.                     */
+int32_t rsdgc_ratio_passes(const rsdgc_plan_t *plan);
 
 /* NSI map only (Eqs. 8-10 at every element of every layer), for inspection:
  *   residual [device, nullable] NULL means an all-zero residual.

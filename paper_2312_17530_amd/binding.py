@@ -22,7 +22,7 @@ EXPORTS = [
     "rsdgc_plan", "rsdgc_plan_set_ratios", "rsdgc_plan_set_path", "rsdgc_plan_set_work_feed", "rsdgc_plan_forget_workspace", "rsdgc_plan_destroy", "rsdgc_n_layers",
     "rsdgc_total_elems", "rsdgc_layer_offset", "rsdgc_layer_elems", "rsdgc_layer_k",
     "rsdgc_out_offset", "rsdgc_out_capacity", "rsdgc_centre_offset", "rsdgc_centre_capacity",
-    "rsdgc_workspace_bytes", "rsdgc_replaces_residual", "rsdgc_compress", "rsdgc_compress_static", "rsdgc_compress_momentum", "rsdgc_dynamic_ratios", "rsdgc_apply", "rsdgc_apply_blocks", "rsdgc_plan_blocks", "rsdgc_compress_blocks", "rsdgc_compress_blocks_momentum",
+    "rsdgc_workspace_bytes", "rsdgc_replaces_residual", "rsdgc_compress", "rsdgc_compress_static", "rsdgc_compress_momentum", "rsdgc_dynamic_ratios", "rsdgc_ratio_passes", "rsdgc_apply", "rsdgc_apply_blocks", "rsdgc_plan_blocks", "rsdgc_compress_blocks", "rsdgc_compress_blocks_momentum",
     "rsdgc_decompress_blocks", "rsdgc_nsi", "rsdgc_decompress",
     "rsdgc_last_paths", "rsdgc_profile_begin", "rsdgc_profile_end", "rsdgc_stage_name",
     "rsdgc_strerror", "rsdgc_last_hip_error",
@@ -97,6 +97,8 @@ def load() -> ctypes.CDLL:
     lib.rsdgc_compress_momentum.restype = ctypes.c_int
     lib.rsdgc_dynamic_ratios.argtypes = [vp, vp, f64, ctypes.POINTER(f64), vp, vp]
     lib.rsdgc_dynamic_ratios.restype = ctypes.c_int
+    lib.rsdgc_ratio_passes.argtypes = [vp]
+    lib.rsdgc_ratio_passes.restype = i32
     lib.rsdgc_apply.argtypes = [vp, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(vp), vp,
                                 ctypes.c_float, vp, vp]
     lib.rsdgc_apply.restype = ctypes.c_int
@@ -313,6 +315,11 @@ def rsdgc_dynamic_ratios(plan: Plan, weights, global_ratio: float, workspace, st
     return [float(x) for x in out]
 
 
+def rsdgc_ratio_passes(plan: Plan) -> int:
+    """Streaming passes of the last rsdgc_dynamic_ratios call: 1, or 4 or 5 on the general path."""
+    return load().rsdgc_ratio_passes(plan.handle)
+
+
 def rsdgc_apply(plan: Plan, messages, weights, eta: float, workspace, stream=None) -> None:
     """Eq. 12, third line: weights -= eta * (sum of the messages, in order).
     messages: sequence of (idx, val, counts) device tensors as written by rsdgc_compress."""
@@ -363,7 +370,8 @@ def rsdgc_profile_end(plan: Plan):
 
 
 def rsdgc_last_paths(plan: Plan, workspace, stream=None):
-    """Ranking path per layer of the last compress call (0 candidates, 1 full map, 2 none)."""
+    """Ranking path per layer of the last compress call (0 candidates above a sampled bound, 3 above a predicted
+    one, 1 full map, 2 none); of a block plan, of the last rsdgc_compress_blocks call."""
     out = (ctypes.c_int32 * plan.n_layers)()
     _check(load().rsdgc_last_paths(plan.handle, _ptr(workspace), out, _stream(stream)),
            "rsdgc_last_paths")

@@ -341,6 +341,7 @@ struct rsdgc_plan_s {
     uint32_t *dyn_out = nullptr;
     void (*dyn_free)(void *) = nullptr;
     bool dyn_clear = false;
+    int32_t dyn_passes = 0;             // streaming passes of the last call
     // block reading (non-overlapping p x p neighbourhoods): this plan describes the element
     // matrices; `inner` describes the block grids as layers with p = 1 and the same k_l, and
     // the selection machinery runs on it.  The workspace is this plan's tables followed by

@@ -7071,6 +7071,7 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
     // One pass, where it is the better one: from a million weights on (below, both forms are a chain of launches), and with a
     // counter per layer in LDS.  Its lists lie where a compress call keeps its score map.
     bool counted = false;
+    plan->dyn_passes = 0;
     if (n_real >= static_cast<double>(kDynSplitMin) && L <= kDynMaxLayers && pinned_counts(plan)) {
         DynSplitArgs a;
         a.out = plan->dyn_out;
@@ -7099,8 +7100,10 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
         std::copy(a.out, a.out + host.size(), host.begin());
         counted = host[0] != 0xffffffffu;                 // (no layer has that many weights: rows * cols < 2^32)
         plan->dyn_clear = counted;                        // (the general path counts in the same place)
+        plan->dyn_passes = 1;
     }
     if (!counted) {
+        plan->dyn_passes += 4;
         plan->dyn_clear = false;
         hipLaunchKernelGGL(k_dyn_init, dim3(1), dim3(256), 0, stream, state, hist, cnt,
                            static_cast<uint32_t>(2 * L), K);

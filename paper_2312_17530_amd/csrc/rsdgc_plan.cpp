@@ -1,6 +1,6 @@
 // Host side of the C ABI: plan construction, validation, queries.
-// No HIP call is made from this file (destroying a plan that still holds profiling
-// events releases them through rsdgc_profile_end).
+// No HIP call is made from this file (destroying a plan releases profiling events that it still holds through
+// rsdgc_profile_end, and the counts' host memory of rsdgc_dynamic_ratios through a function that this left with it).
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -559,6 +559,7 @@ int64_t rsdgc_out_capacity(const rsdgc_plan_t *plan) { return plan ? plan->out_c
 int64_t rsdgc_centre_offset(const rsdgc_plan_t *plan, int32_t l) {
     return layer_ok(plan, l) ? plan->layers[l].centre_off : -1;
 }
+int32_t rsdgc_ratio_passes(const rsdgc_plan_t *plan) { return plan ? plan->dyn_passes : -1; }
 int64_t rsdgc_centre_capacity(const rsdgc_plan_t *plan) {
     return plan ? plan->centre_capacity : -1;
 }

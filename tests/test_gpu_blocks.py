@@ -19,8 +19,8 @@ def _bits(a):
 def test_blocks_call_after_call(sides, m, in_place, feed, more):
     """Grids that end on, before and after a tile of 8 by 32, 64 or 256 blocks, one tile and several, rows of odd length and grids cut by the
     matrix's edges; narrow grids and ratios beyond the candidate path's (full map), one without anything to keep, frozen ones (no bound), few
-    values (ties), a tile that overfills its slot, a gradient that jumps; more than 256 layers.  Calls without history, on
-    predicted bounds, around the jump and after it."""
+    values (ties), a tile that holds much of what is kept, a gradient that jumps; more than 256 layers.  Most of them are too small for the
+    candidate path (test_bounds_that_hold_and_that_fail has those that are not).  Calls without history, around the jump and after it."""
     from paper_2312_17530_amd.session import BlockSession
     p0 = max(sides)
     shapes = [(8 * p0, 64 * p0), (16 * p0 + 1, 130 * p0 + 2), (24 * p0 - 1, 257 * p0), (9 * p0, 33 * p0 + 1), (40, 40), (300, 5), (17 * p0, 70 * p0),

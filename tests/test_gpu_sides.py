@@ -1,5 +1,5 @@
 """Sides of more than a round's tiles that ride along in the main pass of single elements, up to as many as there are of those,
-and one that does not.  Against the CPU oracle."""
+and two that do not.  Against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -29,6 +29,8 @@ def test_sides_that_ride_along(m):
             continue
         after = s.unpack(s.residual)
         for l, (idx, val, centres, _) in enumerate(s.results()):
-            o, _ = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, ps[l], 0.5, ratios[l])
+            o, u_new = oracle.compress_layer_momentum(grads[l], mom[l], resid[l], m or 0.0, ps[l], 0.5, ratios[l])
+            if m is not None:
+                assert np.array_equal(_bits(s.unpack(s.momentum_buf)[l]), _bits(u_new)), (t, l)
             assert np.array_equal(idx, o.idx) and np.array_equal(centres, o.centres), (t, l)
             assert np.array_equal(_bits(val), _bits(o.val)) and np.array_equal(_bits(after[l]), _bits(o.r_new)), (t, l)
