@@ -385,7 +385,7 @@ int rsdgc_profile_begin(rsdgc_plan_t *plan, int32_t max_calls);
 int rsdgc_profile_end(rsdgc_plan_t *plan, double *stage_ms, int32_t *n_calls);
 const char *rsdgc_stage_name(int32_t stage);
 
-/* Which ranking path each layer took in the last rsdgc_compress(_blocks) that used `workspace`:
+/* Which ranking path each layer took in the last rsdgc_compress that used `workspace`:
  * paths[l] [host, n_layers] = 0 candidates above a bound taken from a sample of the layer,
  * 1 full score map, 2 nothing to select (k_l = 0), 3 candidates above a bound predicted
  * from the layer's earlier thresholds.  Waits for `stream`, then copies from the device.
@@ -396,11 +396,12 @@ const char *rsdgc_stage_name(int32_t stage);
  *     the first ten calls with a workspace the next four bounds are sampled ones; later
  *     the next bound is set below this call's threshold, without a trend;
  *   - the workspace is past those ten calls, the only ones that sample tiles, and one
- *     of the layer's last two thresholds is zero or subnormal (nothing to predict from).
- * A block plan's grids take 1, 2 or 3: none of their bounds is sampled, a grid has none while its
- * threshold moves by more than a tenth from call to call or in the four calls after a failed one,
- * and small grids never have one.                                                              */
+ *     of the layer's last two thresholds is zero or subnormal (nothing to predict from). */
 int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, void *stream);
+/* The same of a block plan's grids in the last rsdgc_compress_blocks(_momentum): 1, 2 or 3.  None of
+ * their bounds is sampled, a grid has none while its threshold moves by more than a tenth from call
+ * to call or in the four calls after a failed one, and small grids never have one.               */
+int rsdgc_last_paths_blocks(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, void *stream);
 
 /* ----------------------------------------------------------- diagnostics */
 const char *rsdgc_strerror(int code);

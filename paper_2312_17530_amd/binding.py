@@ -24,7 +24,7 @@ EXPORTS = [
     "rsdgc_out_offset", "rsdgc_out_capacity", "rsdgc_centre_offset", "rsdgc_centre_capacity",
     "rsdgc_workspace_bytes", "rsdgc_replaces_residual", "rsdgc_compress", "rsdgc_compress_static", "rsdgc_compress_momentum", "rsdgc_dynamic_ratios", "rsdgc_ratio_passes", "rsdgc_apply", "rsdgc_apply_blocks", "rsdgc_plan_blocks", "rsdgc_compress_blocks", "rsdgc_compress_blocks_momentum",
     "rsdgc_decompress_blocks", "rsdgc_nsi", "rsdgc_decompress",
-    "rsdgc_last_paths", "rsdgc_profile_begin", "rsdgc_profile_end", "rsdgc_stage_name",
+    "rsdgc_last_paths", "rsdgc_last_paths_blocks", "rsdgc_profile_begin", "rsdgc_profile_end", "rsdgc_stage_name",
     "rsdgc_strerror", "rsdgc_last_hip_error",
 ]
 RSDGC_N_STAGES = 9
@@ -119,6 +119,8 @@ def load() -> ctypes.CDLL:
     lib.rsdgc_decompress.restype = ctypes.c_int
     lib.rsdgc_last_paths.argtypes = [vp, vp, ctypes.POINTER(i32), vp]
     lib.rsdgc_last_paths.restype = ctypes.c_int
+    lib.rsdgc_last_paths_blocks.argtypes = [vp, vp, ctypes.POINTER(i32), vp]
+    lib.rsdgc_last_paths_blocks.restype = ctypes.c_int
     lib.rsdgc_profile_begin.argtypes = [vp, i32]
     lib.rsdgc_profile_begin.restype = ctypes.c_int
     lib.rsdgc_profile_end.argtypes = [vp, ctypes.POINTER(f64), ctypes.POINTER(i32)]
@@ -371,8 +373,16 @@ def rsdgc_profile_end(plan: Plan):
 
 def rsdgc_last_paths(plan: Plan, workspace, stream=None):
     """Ranking path per layer of the last compress call (0 candidates above a sampled bound, 3 above a predicted
-    one, 1 full map, 2 none); of a block plan, of the last rsdgc_compress_blocks call."""
+    one, 1 full map, 2 none)."""
     out = (ctypes.c_int32 * plan.n_layers)()
     _check(load().rsdgc_last_paths(plan.handle, _ptr(workspace), out, _stream(stream)),
            "rsdgc_last_paths")
+    return list(out)
+
+
+def rsdgc_last_paths_blocks(plan: Plan, workspace, stream=None):
+    """The same of a block plan's grids in the last rsdgc_compress_blocks(_momentum) call."""
+    out = (ctypes.c_int32 * plan.n_layers)()
+    _check(load().rsdgc_last_paths_blocks(plan.handle, _ptr(workspace), out, _stream(stream)),
+           "rsdgc_last_paths_blocks")
     return list(out)

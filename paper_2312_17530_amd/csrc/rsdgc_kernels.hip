@@ -7135,11 +7135,7 @@ int rsdgc_dynamic_ratios(rsdgc_plan_t *plan, const float *weights, double global
     return RSDGC_OK;
 }
 
-int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, void *stream_) {
-    if (!plan || !workspace || !paths) return RSDGC_EINVAL;
-    const char *states = static_cast<const char *>(workspace) + plan->ws.state;
-    if (plan->blocks)                  // (the grids' states, in the inner plan's workspace)
-        states = static_cast<const char *>(workspace) + plan->ws.table_bytes + plan->inner->ws.state;
+static int last_paths(const rsdgc_plan_s *plan, const char *states, int32_t *paths, void *stream_) {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     std::vector<SelState> host;
     try {
@@ -7152,6 +7148,17 @@ int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, 
     for (int l = 0; l < plan->n_layers; ++l)
         paths[l] = static_cast<int32_t>(host[l].predicted >> kLastPathShift);
     return RSDGC_OK;
+}
+
+int rsdgc_last_paths(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, void *stream) {
+    if (!plan || plan->blocks || !workspace || !paths) return RSDGC_EINVAL;
+    return last_paths(plan, static_cast<const char *>(workspace) + plan->ws.state, paths, stream);
+}
+
+int rsdgc_last_paths_blocks(rsdgc_plan_t *plan, const void *workspace, int32_t *paths, void *stream) {
+    if (!plan || !plan->blocks || !workspace || !paths) return RSDGC_EINVAL;
+    // (the grids' states, in the inner plan's workspace)
+    return last_paths(plan, static_cast<const char *>(workspace) + plan->ws.table_bytes + plan->inner->ws.state, paths, stream);
 }
 
 static void destroy_events(rsdgc_plan_s *plan) {

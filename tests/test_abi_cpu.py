@@ -133,6 +133,15 @@ def test_form_of_the_update_in_place():
     assert form([m], [3], [0.02], blocks=True)
 
 
+def test_paths_are_asked_by_the_plans_kind():
+    lib, room, paths = binding.load(), (ctypes.c_char * 64)(), (ctypes.c_int32 * 1)()
+    of = [(lib.rsdgc_last_paths, binding.rsdgc_plan([(64, 64)], 3, 0.5, [0.1], blocks=True)),
+          (lib.rsdgc_last_paths_blocks, binding.rsdgc_plan([(64, 64)], 3, 0.5, [0.1]))]
+    for query, other in of:                     # (refused before the workspace is looked at)
+        assert query(other.handle, room, paths, None) == binding.RSDGC_EINVAL
+        assert query(None, room, paths, None) == binding.RSDGC_EINVAL
+
+
 def test_per_layer_neighbourhood_side():
     plan = binding.rsdgc_plan([(90, 90), (90, 90), (90, 90)], 3, 0.5, [0.1, 0.1, 0.1], [1, 3, 5])
     assert [plan.layer_k(l) for l in range(3)] == [810, 90, 33]

@@ -109,7 +109,7 @@ def test_bounds_that_hold_and_that_fail(sides, m, in_place, feed):
         if m is not None:
             s.set_momentum(u_in)
         s.compress()
-        paths = binding.rsdgc_last_paths(s.plan, s.workspace)
+        paths = binding.rsdgc_last_paths_blocks(s.plan, s.workspace)
         if t in want:
             assert paths[:len(large)] == [want[t]] * len(large), t
         assert paths[frozen] == 1 and paths[hot + 1] == 1 and paths[hot + 2] == 1 and paths[none] == 2, t
@@ -132,7 +132,7 @@ def test_more_than_4096_chunks():
         s.set_grad(grads)
         s.set_residual(zero)
         s.compress()
-        paths = binding.rsdgc_last_paths(s.plan, s.workspace)
+        paths = binding.rsdgc_last_paths_blocks(s.plan, s.workspace)
         assert paths[:4] == [3 if t in (2, 3) else 1] * 2 + [1, 1], t
         if t in (1, 3, 4):
             _against_oracle(s, grads, zero, zero, None, [1] * 5, ratios, t)
